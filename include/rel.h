@@ -117,8 +117,8 @@ rel_status rel_filter_compact_noalloc(rel_ctx* ctx, const int32_t* col, int64_t 
  * on the high-bandwidth GPU. Here a predicate is either compiled, as a kernel
  * generated for it and built at run time with hipRTC (literals and column
  * types fixed in the code, each column read with 16-byte loads), or
- * interpreted by one fixed kernel that walks the term list for every row. Both
- * produce the stable selection vector of rel_filter_compact.
+ * interpreted by one fixed kernel that walks the term list once for every 2048
+ * rows of a wave. Both produce the stable selection vector of rel_filter_compact.
  */
 typedef enum rel_dtype {
   REL_DT_I8 = 0, REL_DT_I16 = 1, REL_DT_I32 = 2, REL_DT_I64 = 3, REL_DT_F32 = 4, REL_DT_F64 = 5
