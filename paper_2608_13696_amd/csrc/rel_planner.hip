@@ -7,6 +7,7 @@
 // largest rho = 1 + leading zeros of the remaining 58 bits (59 if all zero).
 // The hash of an int32 key is the first SplitMix64 output (Steele, Lea and
 // Flood 2014) with the key as the state.
+#include <algorithm>
 #include <cmath>
 
 #include "rel_device.h"
@@ -256,133 +257,256 @@ __global__ __launch_bounds__(256) void k_sketch_features(SketchArgs a) {
 
 // ---- MLP ----------------------------------------------------------------------------------------------------------------
 
-constexpr int kSPB = 16;  // samples per workgroup
+// The network's kernels are bound by latency, not by arithmetic (a training
+// step of 256 samples is 14 MFLOP): what counts is how few dependent steps a
+// workgroup takes. A workgroup of four waves stages the parameters into LDS
+// and takes 16 samples at a time; lane j of wave q holds hidden unit j of the
+// samples 4 q .. 4 q + 3, so a weight is read from LDS once for four samples
+// and the samples' inputs, stored unit by unit, come as one broadcast 16-byte
+// read. At 256 samples: forward 6.5 us, backward 11.3 us and the reduction 3.1
+// us; one wave per workgroup and one sample at a time took 29.6, 61.9 and 5.5.
+constexpr int kSPB = 16;           // samples of a workgroup's step
+constexpr int kMlpBlock = 256;
+constexpr int kSPT = 4;            // samples per thread
+constexpr int kSRow = kSPB + 4;    // row of a [unit][sample] array: lanes' 16-byte accesses spread over the banks
+constexpr int kW2Row = kH + 1;     // W2's rows, padded so that a lane may also walk its own row
+constexpr int kMaxGradParts = 256; // workgroups (and partial gradients) of a backward pass
 
-// The parameters into LDS, 16 loads per thread in flight at a time (one
-// after another they cost a round trip each, which dominated a single-sample
-// forward pass).
-__device__ __forceinline__ void load_params(float* lp, const float* __restrict__ p) {
-  constexpr int kBurst = 16;
-  for (int base = 0; base < kParams; base += kBurst * (int)blockDim.x) {
-    float v[kBurst];
+struct alignas(16) MlpLds {
+  float w1[kIn * kH], w2[kH * kW2Row], w3[kH * kOut], b1[kH], b2[kH], b3[kOut];
+  alignas(16) float x[kIn * kSRow];
+  alignas(16) float h1[kH * kSRow];
+  alignas(16) float h2[kH * kSRow];
+  float y[kSPB * kOut];
+
+  __device__ __forceinline__ float* param(int i) {
+    if (i < kB1) return &w1[i];
+    if (i < kW2) return &b1[i - kB1];
+    if (i < kB2) return &w2[(i - kW2) / kH * kW2Row + (i - kW2) % kH];
+    if (i < kW3) return &b2[i - kB2];
+    if (i < kB3) return &w3[i - kW3];
+    return &b3[i - kB3];
+  }
+  // All loads of a thread in flight before the first is stored.
+  __device__ __forceinline__ void load_params(const float* __restrict__ p) {
+    constexpr int kN = (kParams + kMlpBlock - 1) / kMlpBlock;
+    float v[kN];
 #pragma unroll
-    for (int k = 0; k < kBurst; ++k) {
-      const int i = base + k * (int)blockDim.x + (int)threadIdx.x;
+    for (int k = 0; k < kN; ++k) {
+      const int i = k * kMlpBlock + (int)threadIdx.x;
       v[k] = i < kParams ? p[i] : 0.f;
     }
 #pragma unroll
-    for (int k = 0; k < kBurst; ++k) {
-      const int i = base + k * (int)blockDim.x + (int)threadIdx.x;
-      if (i < kParams) lp[i] = v[k];
+    for (int k = 0; k < kN; ++k) {
+      const int i = k * kMlpBlock + (int)threadIdx.x;
+      if (i < kParams) *param(i) = v[k];
     }
   }
-}
+  // The samples s0 .. s0 + 15 (those past B as zeros).
+  __device__ __forceinline__ void load_x(const float* __restrict__ xg, int s0, int B) {
+    for (int e = threadIdx.x; e < kSPB * kIn; e += kMlpBlock) {
+      const int s = e / kIn, i = e % kIn;
+      x[i * kSRow + s] = s0 + s < B ? xg[(size_t)(s0 + s) * kIn + i] : 0.f;
+    }
+  }
+  // One hidden layer for the thread's four samples: out[j] = relu(b[j] + sum_i in[i] w[i][j]),
+  // summed in the order of i; the units of samples past B are zero.
+  template <int N, int ROW>
+  __device__ __forceinline__ void layer(const float* in, const float* w, const float* b, float* out, int valid) {
+    const int j = threadIdx.x & (kWave - 1), q = threadIdx.x / kWave;
+    const float bj = b[j];
+    float z[kSPT] = {bj, bj, bj, bj};
+#pragma unroll 8
+    for (int i = 0; i < N; ++i) {
+      const float wi = w[i * ROW + j];
+      const float4 v = *reinterpret_cast<const float4*>(in + i * kSRow + kSPT * q);
+      z[0] += v.x * wi;
+      z[1] += v.y * wi;
+      z[2] += v.z * wi;
+      z[3] += v.w * wi;
+    }
+#pragma unroll
+    for (int k = 0; k < kSPT; ++k) z[k] = z[k] > 0.f && kSPT * q + k < valid ? z[k] : 0.f;
+    *reinterpret_cast<float4*>(out + j * kSRow + kSPT * q) = make_float4(z[0], z[1], z[2], z[3]);
+  }
+  // Both hidden layers and the outputs of a step of `valid` samples; ends with a barrier.
+  __device__ __forceinline__ void forward(int valid) {
+    layer<kIn, kH>(x, w1, b1, h1, valid);
+    __syncthreads();
+    layer<kH, kW2Row>(h1, w2, b2, h2, valid);
+    __syncthreads();
+    if (threadIdx.x < kSPB * kOut) {
+      const int s = threadIdx.x / kOut, o = threadIdx.x % kOut;
+      float v = b3[o];
+#pragma unroll 8
+      for (int i = 0; i < kH; ++i) v += h2[i * kSRow + s] * w3[i * kOut + o];
+      y[threadIdx.x] = v;
+    }
+    __syncthreads();
+  }
+};
 
-// 64 threads: thread j computes hidden unit j; threads 0 and 1 the outputs.
-__global__ __launch_bounds__(64) void k_mlp_forward(const float* __restrict__ params, const float* __restrict__ x, int32_t B,
-                                                    float* __restrict__ y) {
-  __shared__ float P[kParams];
-  __shared__ float xs[kIn], h1[kH], h2[kH];
-  load_params(P, params);
-  const int j = threadIdx.x;
-  for (int s = blockIdx.x * kSPB; s < B && s < (int)(blockIdx.x + 1) * kSPB; ++s) {
-    __syncthreads();
-    if (j < kIn) xs[j] = x[(size_t)s * kIn + j];
-    __syncthreads();
-    float z = P[kB1 + j];
-    for (int i = 0; i < kIn; ++i) z += xs[i] * P[kW1 + i * kH + j];
-    h1[j] = z > 0.f ? z : 0.f;
-    __syncthreads();
-    z = P[kB2 + j];
-    for (int i = 0; i < kH; ++i) z += h1[i] * P[kW2 + i * kH + j];
-    h2[j] = z > 0.f ? z : 0.f;
-    __syncthreads();
-    if (j < kOut) {
-      float o = P[kB3 + j];
-      for (int i = 0; i < kH; ++i) o += h2[i] * P[kW3 + i * kOut + j];
-      y[(size_t)s * kOut + j] = o;
-    }
-  }
-}
-
-// Per-workgroup partial gradients; thread j owns column j of W1 and W2, row j
-// of W3 and entry j of b1, b2 (thread 0 also b3), so no two threads write the
-// same entry and nothing needs an atomic.
-__global__ __launch_bounds__(64) void k_mlp_backward(const float* __restrict__ params, const float* __restrict__ x,
-                                                     const float* __restrict__ tgt, int32_t B, float* __restrict__ partial,
-                                                     float* __restrict__ partial_loss) {
-  __shared__ float P[kParams];
-  __shared__ float G[kParams];
-  __shared__ float xs[kIn], z1[kH], h1[kH], z2[kH], h2[kH], dz2[kH], dy[kOut];
-  __shared__ float yv[kOut];
-  load_params(P, params);
-  for (int i = threadIdx.x; i < kParams; i += blockDim.x) G[i] = 0.f;
-  const int j = threadIdx.x;
-  const float invB = 1.0f / (float)B;
-  float loss = 0.f;
-  for (int s = blockIdx.x * kSPB; s < B && s < (int)(blockIdx.x + 1) * kSPB; ++s) {
-    __syncthreads();
-    if (j < kIn) xs[j] = x[(size_t)s * kIn + j];
-    __syncthreads();
-    float z = P[kB1 + j];
-    for (int i = 0; i < kIn; ++i) z += xs[i] * P[kW1 + i * kH + j];
-    z1[j] = z;
-    h1[j] = z > 0.f ? z : 0.f;
-    __syncthreads();
-    z = P[kB2 + j];
-    for (int i = 0; i < kH; ++i) z += h1[i] * P[kW2 + i * kH + j];
-    z2[j] = z;
-    h2[j] = z > 0.f ? z : 0.f;
-    __syncthreads();
-    if (j < kOut) {
-      float o = P[kB3 + j];
-      for (int i = 0; i < kH; ++i) o += h2[i] * P[kW3 + i * kOut + j];
-      yv[j] = o;
-      const float d = o - tgt[(size_t)s * kOut + j];
-      dy[j] = d * invB;
-    }
-    __syncthreads();
-    if (j == 0) loss += (yv[0] - tgt[(size_t)s * kOut]) * (yv[0] - tgt[(size_t)s * kOut]) +
-                        (yv[1] - tgt[(size_t)s * kOut + 1]) * (yv[1] - tgt[(size_t)s * kOut + 1]);
-    // output layer
-    G[kW3 + j * kOut + 0] += h2[j] * dy[0];
-    G[kW3 + j * kOut + 1] += h2[j] * dy[1];
-    if (j == 0) {
-      G[kB3 + 0] += dy[0];
-      G[kB3 + 1] += dy[1];
-    }
-    const float dh2 = dy[0] * P[kW3 + j * kOut] + dy[1] * P[kW3 + j * kOut + 1];
-    dz2[j] = z2[j] > 0.f ? dh2 : 0.f;
-    __syncthreads();
-    // second layer: column j of W2
-    for (int i = 0; i < kH; ++i) G[kW2 + i * kH + j] += h1[i] * dz2[j];
-    G[kB2 + j] += dz2[j];
-    float dh1 = 0.f;
-    for (int c = 0; c < kH; ++c) dh1 += dz2[c] * P[kW2 + j * kH + c];
-    const float dz1 = z1[j] > 0.f ? dh1 : 0.f;
-    // first layer: column j of W1
-    for (int i = 0; i < kIn; ++i) G[kW1 + i * kH + j] += xs[i] * dz1;
-    G[kB1 + j] += dz1;
-  }
+__global__ __launch_bounds__(kMlpBlock) void k_mlp_forward(const float* __restrict__ params, const float* __restrict__ x,
+                                                           int32_t B, float* __restrict__ y) {
+  __shared__ MlpLds m;
+  const int s0 = blockIdx.x * kSPB, valid = min(kSPB, B - s0);
+  m.load_x(x, s0, B);
+  m.load_params(params);
   __syncthreads();
-  for (int i = threadIdx.x; i < kParams; i += blockDim.x) partial[(size_t)blockIdx.x * kParams + i] = G[i];
-  if (j == 0) partial_loss[blockIdx.x] = loss;
+  m.forward(valid);
+  if ((int)threadIdx.x < valid * kOut) y[(size_t)s0 * kOut + threadIdx.x] = m.y[threadIdx.x];
 }
 
-// Sum the per-workgroup partials in workgroup order (deterministic).
+// sum_s a[s] b[s] over a step's samples, added to `acc` in the order of s.
+__device__ __forceinline__ float dot_samples(const float* a, const float (&b)[kSPB], float acc) {
+#pragma unroll
+  for (int k = 0; k < kSPB / 4; ++k) {
+    const float4 v = *reinterpret_cast<const float4*>(a + 4 * k);
+    acc += v.x * b[4 * k];
+    acc += v.y * b[4 * k + 1];
+    acc += v.z * b[4 * k + 2];
+    acc += v.w * b[4 * k + 3];
+  }
+  return acc;
+}
+
+__device__ __forceinline__ void read_samples(const float* a, float (&b)[kSPB]) {
+#pragma unroll
+  for (int k = 0; k < kSPB / 4; ++k) {
+    const float4 v = *reinterpret_cast<const float4*>(a + 4 * k);
+    b[4 * k] = v.x;
+    b[4 * k + 1] = v.y;
+    b[4 * k + 2] = v.z;
+    b[4 * k + 3] = v.w;
+  }
+}
+
+// Per-workgroup partial gradients over steps blockIdx.x, blockIdx.x + G, ...
+// Lane j of wave q owns rows 10 q .. 10 q + 9 of W1's column j and rows 16 q ..
+// 16 q + 15 of W2's; waves 0 and 1 also W3, the biases and the loss. Every
+// entry has one owner, which keeps it in a register over all steps, so
+// nothing needs an atomic and the sums have a fixed order.
+__global__ __launch_bounds__(kMlpBlock) void k_mlp_backward(const float* __restrict__ params, const float* __restrict__ x,
+                                                            const float* __restrict__ tgt, int32_t B,
+                                                            float* __restrict__ partial, float* __restrict__ partial_loss) {
+  __shared__ MlpLds m;
+  __shared__ alignas(16) float dz1[kH * kSRow];
+  __shared__ alignas(16) float dz2[kH * kSRow];
+  __shared__ float dy[kSPB * kOut];
+  __shared__ float s_loss[kSPB * kOut];
+  const int t = threadIdx.x, j = t & (kWave - 1), q = t / kWave;
+  constexpr int kR1 = kIn / 4, kR2 = kH / 4;
+  float g1[kR1] = {}, g2[kR2] = {}, g3 = 0.f, gb1 = 0.f, gb2 = 0.f, gb3 = 0.f, loss = 0.f;
+  const float invB = 1.0f / (float)B;
+  m.load_params(params);
+  for (int s0 = blockIdx.x * kSPB; s0 < B; s0 += gridDim.x * kSPB) {
+    const int valid = min(kSPB, B - s0);
+    m.load_x(x, s0, B);
+    __syncthreads();
+    m.forward(valid);
+    if (t < kSPB * kOut) {
+      const float d = t < valid * kOut ? m.y[t] - tgt[(size_t)s0 * kOut + t] : 0.f;
+      dy[t] = d * invB;
+      s_loss[t] = d * d;
+    }
+    __syncthreads();
+    // output layer: W3 and b3 (entry t), and the second layer's deltas
+    float4 d2;
+    {
+      const float wa = m.w3[j * kOut], wb = m.w3[j * kOut + 1];
+      const float4 h = *reinterpret_cast<const float4*>(m.h2 + j * kSRow + kSPT * q);
+      const float* e = dy + kSPT * q * kOut;
+      d2.x = h.x > 0.f ? e[0] * wa + e[1] * wb : 0.f;
+      d2.y = h.y > 0.f ? e[2] * wa + e[3] * wb : 0.f;
+      d2.z = h.z > 0.f ? e[4] * wa + e[5] * wb : 0.f;
+      d2.w = h.w > 0.f ? e[6] * wa + e[7] * wb : 0.f;
+      *reinterpret_cast<float4*>(dz2 + j * kSRow + kSPT * q) = d2;
+    }
+    if (t < kH * kOut) {
+      const int i = t / kOut, o = t % kOut;
+      for (int s = 0; s < kSPB; ++s) g3 += m.h2[i * kSRow + s] * dy[s * kOut + o];
+    } else if (t < kH * kOut + kOut) {
+      for (int s = 0; s < kSPB; ++s) gb3 += dy[s * kOut + (t - kH * kOut)];
+    } else if (t == kMlpBlock - 1) {
+      for (int s = 0; s < kSPB; ++s) loss += s_loss[s * kOut] + s_loss[s * kOut + 1];
+    }
+    __syncthreads();
+    // second layer: W2's column j, and the first layer's deltas (unit j)
+    float d[kSPB];
+    read_samples(dz2 + j * kSRow, d);
+#pragma unroll
+    for (int r = 0; r < kR2; ++r) g2[r] = dot_samples(m.h1 + (kR2 * q + r) * kSRow, d, g2[r]);
+    if (q == 1) {
+#pragma unroll
+      for (int s = 0; s < kSPB; ++s) gb2 += d[s];
+    }
+    float e[kSPT] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int c = 0; c < kH; ++c) {
+      const float w = m.w2[j * kW2Row + c];
+      const float4 v = *reinterpret_cast<const float4*>(dz2 + c * kSRow + kSPT * q);
+      e[0] += v.x * w;
+      e[1] += v.y * w;
+      e[2] += v.z * w;
+      e[3] += v.w * w;
+    }
+    const float4 h = *reinterpret_cast<const float4*>(m.h1 + j * kSRow + kSPT * q);
+    *reinterpret_cast<float4*>(dz1 + j * kSRow + kSPT * q) =
+        make_float4(h.x > 0.f ? e[0] : 0.f, h.y > 0.f ? e[1] : 0.f, h.z > 0.f ? e[2] : 0.f, h.w > 0.f ? e[3] : 0.f);
+    __syncthreads();
+    // first layer: W1's column j
+    read_samples(dz1 + j * kSRow, d);
+#pragma unroll
+    for (int r = 0; r < kR1; ++r) g1[r] = dot_samples(m.x + (kR1 * q + r) * kSRow, d, g1[r]);
+    if (q == 0) {
+#pragma unroll
+      for (int s = 0; s < kSPB; ++s) gb1 += d[s];
+    }
+    __syncthreads();  // the next step writes x
+  }
+  float* out = partial + (size_t)blockIdx.x * kParams;
+#pragma unroll
+  for (int r = 0; r < kR1; ++r) out[kW1 + (kR1 * q + r) * kH + j] = g1[r];
+#pragma unroll
+  for (int r = 0; r < kR2; ++r) out[kW2 + (kR2 * q + r) * kH + j] = g2[r];
+  if (q == 0) out[kB1 + j] = gb1;
+  if (q == 1) out[kB2 + j] = gb2;
+  if (t < kH * kOut) out[kW3 + t] = g3;
+  else if (t < kH * kOut + kOut) out[kB3 + t - kH * kOut] = gb3;
+  if (t == kMlpBlock - 1) partial_loss[blockIdx.x] = loss;
+}
+
+// Sum the per-workgroup partials: a thread adds every fourth one, in order,
+// and the four sums are added in order (deterministic).
+constexpr int kReduceCols = 64;
+constexpr int kReduceBurst = 8;
 __global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ partial, const float* __restrict__ partial_loss,
                                                     int32_t nparts, int32_t B, float* __restrict__ grad,
                                                     float* __restrict__ loss) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ float s_part[4][kReduceCols];
+  const int c = threadIdx.x % kReduceCols, g = threadIdx.x / kReduceCols;
+  const int i = blockIdx.x * kReduceCols + c;
+  float s = 0.f;
   if (i < kParams) {
-    float s = 0.f;
-    for (int b = 0; b < nparts; ++b) s += partial[(size_t)b * kParams + i];
-    grad[i] = s;
+    for (int b0 = g; b0 < nparts; b0 += 4 * kReduceBurst) {
+      float v[kReduceBurst];
+#pragma unroll
+      for (int k = 0; k < kReduceBurst; ++k) {
+        const int b = b0 + 4 * k;
+        v[k] = b < nparts ? partial[(size_t)b * kParams + i] : 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < kReduceBurst; ++k) s += v[k];
+    }
   }
-  if (i == 0 && loss) {
-    float s = 0.f;
-    for (int b = 0; b < nparts; ++b) s += partial_loss[b];
-    *loss = s / (2.0f * (float)B);
+  s_part[g][c] = s;
+  __syncthreads();
+  if (g == 0 && i < kParams) grad[i] = s_part[0][c] + s_part[1][c] + s_part[2][c] + s_part[3][c];
+  if (blockIdx.x == 0 && g == 1 && loss) {
+    float l = 0.f;
+    for (int b = c; b < nparts; b += kWave) l += partial_loss[b];
+    l = wave_sum(l);
+    if (c == 0) *loss = l / (2.0f * (float)B);
   }
 }
 
@@ -508,7 +632,7 @@ rel_status rel_mlp_forward(rel_ctx* ctx, const float* d_params, const float* d_x
   if (!ctx || !d_params || !d_x || !d_y || B < 0) return relh::fail(ctx, REL_INVALID_ARG, "rel_mlp_forward: bad argument");
   if (B == 0) return REL_OK;
   relh::KernelTimer kt(ctx, "mlp_forward");
-  hipLaunchKernelGGL(k_mlp_forward, dim3((B + kSPB - 1) / kSPB), dim3(64), 0, ctx->stream, d_params, d_x, B, d_y);
+  hipLaunchKernelGGL(k_mlp_forward, dim3((B + kSPB - 1) / kSPB), dim3(kMlpBlock), 0, ctx->stream, d_params, d_x, B, d_y);
   REL_LAUNCH_CHECK(ctx, "mlp_forward");
   return REL_OK;
 }
@@ -517,13 +641,13 @@ rel_status rel_mlp_backward(rel_ctx* ctx, const float* d_params, const float* d_
                             float* d_grad, float* d_loss) {
   if (!ctx || !d_params || !d_x || !d_t || !d_grad || B < 1)
     return relh::fail(ctx, REL_INVALID_ARG, "rel_mlp_backward: bad argument");
-  const int32_t nb = (B + kSPB - 1) / kSPB;
+  const int32_t nb = std::min((B + kSPB - 1) / kSPB, kMaxGradParts);
   void* part;
   TRY(relh::scratch(ctx, SCR_MLP, ((size_t)nb * kParams + nb) * sizeof(float), &part));
   float* pl = (float*)part + (size_t)nb * kParams;
   relh::KernelTimer kt(ctx, "mlp_backward");
-  hipLaunchKernelGGL(k_mlp_backward, dim3(nb), dim3(64), 0, ctx->stream, d_params, d_x, d_t, B, (float*)part, pl);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + 255) / 256), dim3(256), 0, ctx->stream, (const float*)part,
+  hipLaunchKernelGGL(k_mlp_backward, dim3(nb), dim3(kMlpBlock), 0, ctx->stream, d_params, d_x, d_t, B, (float*)part, pl);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + kReduceCols - 1) / kReduceCols), dim3(256), 0, ctx->stream, (const float*)part,
                      (const float*)pl, nb, B, d_grad, d_loss);
   REL_LAUNCH_CHECK(ctx, "mlp_backward");
   return REL_OK;
