@@ -245,7 +245,14 @@ rel_status rel_ctx_destroy(rel_ctx* ctx) {
     (void)hipEventDestroy(ctx->ev_join);
   }
   if (ctx->d_status_words) (void)hipFree(ctx->d_status_words);
-  delete ctx;
+  bool tables_left;
+  {
+    std::lock_guard<std::mutex> lock(ctx->table_mu);
+    if (ctx->spare.ptr) (void)hipFree(ctx->spare.ptr);
+    ctx->closed = true;
+    tables_left = ctx->tables > 0;  // their destroy calls still look at this struct
+  }
+  if (!tables_left) delete ctx;
   return REL_OK;
 }
 

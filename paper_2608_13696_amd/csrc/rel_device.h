@@ -206,7 +206,7 @@ __device__ __forceinline__ bool join_finish(const JoinView& t, int32_t key, uint
 // host round trip is needed. An entry is 0 (no key) or, with an int8 payload,
 // the 16-bit 0x100 | payload byte (half the bytes, so that more of the array
 // stays in the L2 caches while fact rows probe it); otherwise the 32-bit dim
-// row j + 1. Entries are written with plain stores, so a repeated key is
+// row j + 1, or (a stand-alone table with payloads) the 64-bit 2^32 | payload. Entries are written with plain stores, so a repeated key is
 // detected by counting: m distinct keys fill exactly m entries, a repeated key
 // fewer (dense_count_entries).
 struct JoinIndex {
@@ -217,6 +217,7 @@ struct JoinIndex {
   const void* payload;  // the dim payload column (int32 or int8), or null for row ids
   int32_t pkind;        // relh::PayloadKind
   int32_t narrow;       // 16-bit entries (int8 payload)
+  int32_t wide;         // 64-bit entries that hold an int32 payload (stand-alone tables, which do not keep the column)
   int64_t m;            // build rows
 };
 
@@ -242,7 +243,7 @@ __device__ __forceinline__ DenseRange dense_range(const JoinIndex& x) { return d
 // entries that the clearing kernel zeroes too).
 __device__ __forceinline__ int64_t dense_words(const JoinIndex& x, const DenseRange& r) {
   if (r.range <= 0) return 0;
-  return (r.range * (x.narrow ? 2 : 4) + 15) / 16;
+  return (r.range * (x.narrow ? 2 : x.wide ? 8 : 4) + 15) / 16;
 }
 
 // The dense entry of a key: 0 when the key is outside the range or absent.
@@ -254,12 +255,14 @@ __device__ __forceinline__ uint32_t dense_entry(const JoinIndex& x, const DenseR
 
 // The entry dim row j stores.
 __device__ __forceinline__ uint32_t dense_encode(const JoinIndex& x, int64_t j) {
+  if (x.wide) return (uint32_t)((const int32_t*)x.payload)[j];  // the payload; dense_store adds the mark
   if (x.narrow) return 0x100u | (uint32_t)(uint8_t)((const int8_t*)x.payload)[j];
   return (uint32_t)(j + 1);
 }
 
 __device__ __forceinline__ void dense_store(const JoinIndex& x, int64_t off, uint32_t e) {
-  if (x.narrow) ((uint16_t*)x.dense)[off] = (uint16_t)e;
+  if (x.wide) ((uint64_t*)x.dense)[off] = 1ull << 32 | e;
+  else if (x.narrow) ((uint16_t*)x.dense)[off] = (uint16_t)e;
   else ((uint32_t*)x.dense)[off] = e;
 }
 
@@ -278,14 +281,23 @@ template <int NT>
 __device__ __forceinline__ uint64_t dense_count_entries(const JoinIndex& x, int64_t w0, int64_t w1) {
   typedef uint32_t v4u __attribute__((ext_vector_type(4)));
   const v4u* w = reinterpret_cast<const v4u*>(x.dense);
+  constexpr int kInFlight = 4;
   uint64_t c = 0;
-  for (int64_t i = w0 + threadIdx.x; i < w1; i += NT) {
-    const v4u v = w[i];
-    if (x.narrow) {
-      c += ((v.x & 0xFFFFu) != 0) + ((v.x >> 16) != 0) + ((v.y & 0xFFFFu) != 0) + ((v.y >> 16) != 0) +
-           ((v.z & 0xFFFFu) != 0) + ((v.z >> 16) != 0) + ((v.w & 0xFFFFu) != 0) + ((v.w >> 16) != 0);
-    } else {
-      c += (v.x != 0) + (v.y != 0) + (v.z != 0) + (v.w != 0);
+  for (int64_t i0 = w0 + threadIdx.x; i0 < w1; i0 += kInFlight * NT) {
+    v4u in[kInFlight];
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) in[u] = i0 + u * NT < w1 ? w[i0 + u * NT] : v4u{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) {
+      const v4u v = in[u];
+      if (x.narrow) {
+        c += ((v.x & 0xFFFFu) != 0) + ((v.x >> 16) != 0) + ((v.y & 0xFFFFu) != 0) + ((v.y >> 16) != 0) +
+             ((v.z & 0xFFFFu) != 0) + ((v.z >> 16) != 0) + ((v.w & 0xFFFFu) != 0) + ((v.w >> 16) != 0);
+      } else if (x.wide) {  // the high word of an entry is 1
+        c += v.y + v.w;
+      } else {
+        c += (v.x != 0) + (v.y != 0) + (v.z != 0) + (v.w != 0);
+      }
     }
   }
   return c;

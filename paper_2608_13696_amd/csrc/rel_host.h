@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -84,13 +85,28 @@ struct rel_ctx {
   // run beside the caller's stream, with the fork / join events; made on first use.
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  // Under table_mu (a table may be destroyed by another thread than the one
+  // that uses the context): memory of the last destroyed join table, for the
+  // next one of its size, with the one stream it was used on; and the number
+  // of join tables alive. A context destroyed before its tables keeps this
+  // struct (all else freed) until the last of them is gone.
+  std::mutex table_mu;
+  ScratchBuf spare;
+  hipStream_t spare_stream = nullptr;
+  int tables = 0;
+  bool closed = false;
 };
 
 struct rel_join_table {
   rel_ctx* ctx = nullptr;
   uint64_t* slots = nullptr;
+  size_t bytes = 0;
   uint32_t log2cap = 0;
   int64_t m = 0;
+  bool may_be_dense = false;  // dense or hash by the keys' range, known on the device only
+  bool wide = false;          // built with a payload column
+  hipStream_t stream = nullptr;       // the stream it was built on
+  mutable bool many_streams = false;  // and probed on another one
 };
 
 namespace relh {

@@ -1,6 +1,10 @@
 // Hash join: build (insert_if_n analogue) and probe (count + retrieve
 // analogue, fused into one pass because a PK-FK probe emits at most one pair
 // per probe row, so no counting pass is needed to size the output).
+#include <algorithm>
+#include <mutex>
+#include <utility>
+
 #include "rel_device.h"
 #include "rel_host.h"
 #include "rel_ops.h"
@@ -203,30 +207,80 @@ __global__ __launch_bounds__(kVerifyBlock) void k_index_verify(JoinIndex x, uint
   if (threadIdx.x == 0 && c != (uint64_t)x.m) set_status(status, kDevDupKey);
 }
 
+// The same check by many workgroups, for a stand-alone table, whose build
+// must report a repeated key itself: every workgroup adds its entries to
+// tail[0], and the last one to arrive (tail[1]) compares the sum with m.
+__global__ __launch_bounds__(kVerifyBlock) void k_index_count(JoinIndex x, uint64_t* __restrict__ tail,
+                                                              uint32_t* __restrict__ status) {
+  __shared__ uint64_t s_red[kVerifyBlock / kWave];
+  const DenseRange r = dense_range(x);
+  if (!r.dense) return;
+  const int64_t words = dense_words(x, r), per = (words + gridDim.x - 1) / gridDim.x;
+  const int64_t w0 = (int64_t)blockIdx.x * per;
+  const uint64_t c = block_sum_u64<kVerifyBlock>(dense_count_entries<kVerifyBlock>(x, w0, min(words, w0 + per)), s_red);
+  if (threadIdx.x != 0) return;
+  __hip_atomic_fetch_add(&tail[0], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__hip_atomic_fetch_add(&tail[1], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+  if (__hip_atomic_load(&tail[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint64_t)x.m)
+    set_status(status, kDevDupKey);
+}
+
 // Probe: a wave takes 8 x 64 consecutive probe rows per step, one row of each
-// 64 per lane. Every lane issues the first-slot loads of its eight rows
-// together (the random table reads are the cost, so eight are in flight per
-// lane instead of one), then finishes each probe. A wave runs kProbeGroup
-// steps, keeping each row's match in registers, and then reserves output
-// space for all of them with one atomic: the count is one word, and atomics
-// on one cache line serialise on this chip at about 12 ns each, so one per
-// step (512 rows) bounded the kernel. Matches are compacted with one ballot
-// per row group. Output order is therefore unspecified.
-// On 28.15M probes into a 15M-key table: 0.78 ms with eight rows per lane and
-// one atomic per step, 1.40 ms with four, 5.31 ms with one; sixteen spill the
-// ballot masks.
+// 64 per lane. Every lane issues the first reads of its eight rows (the dense
+// entry, or the first hash slot) together (the random table reads are the
+// cost, so eight are in flight per lane instead of one), then finishes each
+// probe. A wave runs kProbeGroup steps, keeping each row's match in
+// registers, and then the workgroup reserves output space for all of them
+// with one atomic: the count is one word, and atomics on one cache line
+// serialise on this chip at about 12 ns each, so one per step (512 rows)
+// bounded the kernel. Matches are compacted with one ballot per row group. Output order is therefore
+// unspecified.
+// On 28.15M probes into a 15M-key hash table, with one atomic per wave and
+// step: 0.78 ms with eight rows per lane, 1.40 ms with four, 5.31 ms with one;
+// sixteen spill the ballot masks. 28.15M probes of Zipf(0.8) keys into a dense
+// table of 15M keys (60 MB): 0.37 ms with one atomic per workgroup, 0.46 ms
+// with one per wave; the table's lines, fetched at 7 TB/s, then bound it (two
+// steps or one per reservation, and larger workgroups, measured the same).
+constexpr int kProbeBlock = 256;
 constexpr int kProbeRows = 8;
 constexpr int kProbeGroup = 4;
 
-__global__ __launch_bounds__(256) void k_join_probe(JoinView t, const int32_t* __restrict__ fk,
-                                                    const int32_t* __restrict__ sel, int64_t n,
-                                                    int32_t* __restrict__ out_fact, int32_t* __restrict__ out_payload,
-                                                    int64_t* __restrict__ d_count) {
+enum ProbeKind { PROBE_HASH = 0, PROBE_ROW_ID, PROBE_WIDE };
+
+// Output positions for a workgroup's matches, `total` of them in this wave
+// (the same on every lane): one atomic per workgroup, then the waves' shares in
+// order. Synchronises the workgroup.
+template <int NT>
+__device__ __forceinline__ int64_t reserve_output(uint32_t total, int64_t* __restrict__ d_count) {
+  __shared__ uint32_t s_total[NT / kWave];
+  __shared__ int64_t s_off;
+  const uint32_t wave = threadIdx.x / kWave;
+  __syncthreads();  // (the last reservation has been read)
+  if (lane_id() == 0) s_total[wave] = total;
+  __syncthreads();
+  uint32_t before = 0, sum = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < NT / kWave; ++w) {
+    const uint32_t t = s_total[w];
+    before += w < wave ? t : 0u;
+    sum += t;
+  }
+  if (threadIdx.x == 0 && sum != 0)
+    s_off = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)d_count, (unsigned long long)sum);
+  __syncthreads();
+  return s_off + before;
+}
+
+template <int KIND>
+__device__ __forceinline__ void probe_rows(const JoinIndex& x, const DenseRange& r, const int32_t* __restrict__ fk,
+                                           const int32_t* __restrict__ sel, int64_t n, int32_t* __restrict__ out_fact,
+                                           int32_t* __restrict__ out_payload, int64_t* __restrict__ d_count) {
   constexpr int64_t kStep = (int64_t)kWave * kProbeRows;
-  const int64_t wave_global = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
-  const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) / kWave;
+  const JoinView& t = x.hash;
+  constexpr int64_t kBlockRows = kStep * kProbeGroup * (kProbeBlock / kWave);
   const uint32_t lane = lane_id();
-  for (int64_t base0 = wave_global * kStep * kProbeGroup; base0 < n; base0 += n_waves * kStep * kProbeGroup) {
+  for (int64_t block0 = blockIdx.x * kBlockRows; block0 < n; block0 += gridDim.x * kBlockRows) {
+    const int64_t base0 = block0 + (int64_t)(threadIdx.x / kWave) * kStep * kProbeGroup;
     int32_t hrow[kProbeGroup][kProbeRows];  // the matching fact row, or -1
     int32_t hpl[kProbeGroup][kProbeRows];
     uint32_t total = 0;
@@ -238,24 +292,36 @@ __global__ __launch_bounds__(256) void k_join_probe(JoinView t, const int32_t* _
 #pragma unroll
       for (int k = 0; k < kProbeRows; ++k) {
         const int64_t i = base + k * kWave + lane;
-        row[k] = i < n ? (sel ? sel[i] : (int32_t)i) : -1;
+        row[k] = i < n ? (sel ? ld_once(sel + i) : (int32_t)i) : -1;
       }
 #pragma unroll
-      for (int k = 0; k < kProbeRows; ++k) key[k] = row[k] >= 0 ? fk[row[k]] : 0;
+      for (int k = 0; k < kProbeRows; ++k) key[k] = row[k] >= 0 ? ld_once(fk + row[k]) : 0;
 #pragma unroll
-      for (int k = 0; k < kProbeRows; ++k) first[k] = row[k] >= 0 ? t.slots[join_first_index(t, key[k])] : kJoinEmpty;
+      for (int k = 0; k < kProbeRows; ++k) {
+        if (KIND == PROBE_HASH) {
+          first[k] = row[k] >= 0 ? t.slots[join_first_index(t, key[k])] : kJoinEmpty;
+        } else {
+          const uint32_t off = (uint32_t)key[k] - (uint32_t)r.kmin;
+          const bool in = row[k] >= 0 && (int64_t)off < r.range;
+          if (KIND == PROBE_WIDE) first[k] = in ? ((const uint64_t*)x.dense)[off] : 0ull;
+          else first[k] = in ? ((const uint32_t*)x.dense)[off] : 0u;
+        }
+      }
 #pragma unroll
       for (int k = 0; k < kProbeRows; ++k) {
         hpl[g][k] = 0;
-        const bool hit = row[k] >= 0 && join_finish(t, key[k], first[k], &hpl[g][k]);
+        bool hit;
+        if (KIND == PROBE_HASH) {
+          hit = row[k] >= 0 && join_finish(t, key[k], first[k], &hpl[g][k]);
+        } else {
+          hit = first[k] != 0;
+          hpl[g][k] = KIND == PROBE_WIDE ? (int32_t)(uint32_t)first[k] : (int32_t)((uint32_t)first[k] - 1u);
+        }
         hrow[g][k] = hit ? row[k] : -1;
         total += (uint32_t)__popcll(wave_ballot(hit));
       }
     }
-    if (total == 0) continue;
-    int64_t off = 0;
-    if (lane == 0) off = dev_add_ret<unsigned long long>((unsigned long long*)d_count, (unsigned long long)total);
-    off = __shfl(off, 0, kWave);
+    int64_t off = reserve_output<kProbeBlock>(total, d_count);
 #pragma unroll
     for (int g = 0; g < kProbeGroup; ++g) {
 #pragma unroll
@@ -272,33 +338,54 @@ __global__ __launch_bounds__(256) void k_join_probe(JoinView t, const int32_t* _
   }
 }
 
+__global__ __launch_bounds__(kProbeBlock) void k_join_probe(JoinIndex x, const int32_t* __restrict__ fk,
+                                                    const int32_t* __restrict__ sel, int64_t n,
+                                                    int32_t* __restrict__ out_fact, int32_t* __restrict__ out_payload,
+                                                    int64_t* __restrict__ d_count) {
+  probe_rows<PROBE_HASH>(x, DenseRange{}, fk, sel, n, out_fact, out_payload, d_count);
+}
+
+// A table that may be dense: the keys' range on the device says whether it is.
+template <bool WIDE>
+__global__ __launch_bounds__(kProbeBlock) void k_join_probe_index(JoinIndex x, const int32_t* __restrict__ fk,
+                                                                  const int32_t* __restrict__ sel, int64_t n,
+                                                                  int32_t* __restrict__ out_fact,
+                                                                  int32_t* __restrict__ out_payload,
+                                                                  int64_t* __restrict__ d_count) {
+  const DenseRange r = dense_range(x);
+  if (r.dense) probe_rows<WIDE ? PROBE_WIDE : PROBE_ROW_ID>(x, r, fk, sel, n, out_fact, out_payload, d_count);
+  else probe_rows<PROBE_HASH>(x, r, fk, sel, n, out_fact, out_payload, d_count);
+}
+
 }  // namespace
 
 namespace relh {
 
-rel_status join_build_into(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
-                           uint64_t* slots, uint32_t log2cap) {
-  const uint64_t cap = 1ull << log2cap;
-  rel_status s;
+// The index's kernels up to its entries: the keys' range, the clearing of what
+// the range selects (dense words or `hash_words` slots) and the entries.
+static rel_status index_fill(rel_ctx* ctx, const int32_t* pk, int payload_kind, uint32_t* part, int64_t hash_words,
+                             const ZeroSpans& zero, const rel::JoinIndex& x) {
+  const int64_t m = x.m;
+  const int32_t parts = key_minmax_partials(ctx, pk, m, part);
   {
     KernelTimer kt(ctx, "join_table_init");
-    s = fill_u64(ctx, slots, cap + 1, rel::kJoinEmpty);
+    const int64_t most = x.dense_cap > hash_words ? x.dense_cap : hash_words;
+    hipLaunchKernelGGL(k_index_clear, dim3(grid_for(ctx, most, kIdxBlock * 8, 4)), dim3(kIdxBlock), 0, ctx->stream, x,
+                       hash_words, (const uint32_t*)part, parts, zero);
   }
-  if (s != REL_OK) return s;
+  REL_LAUNCH_CHECK(ctx, "join index clear");
   if (m == 0) return REL_OK;
-  const unsigned grid = grid_for(ctx, m, 256 * 4, 8);
-  const uint32_t mask = (uint32_t)(cap - 1), shift = 32u - log2cap;
-  KernelTimer kt(ctx, "join_build");
-  if (payload_kind == PAY_I32)
-    hipLaunchKernelGGL(k_join_build<PAY_I32>, dim3(grid), dim3(256), 0, ctx->stream, pk, payload, m, slots, mask, shift,
-                       ctx->d_status);
-  else if (payload_kind == PAY_I8)
-    hipLaunchKernelGGL(k_join_build<PAY_I8>, dim3(grid), dim3(256), 0, ctx->stream, pk, payload, m, slots, mask, shift,
-                       ctx->d_status);
-  else
-    hipLaunchKernelGGL(k_join_build<PAY_ROW_ID>, dim3(grid), dim3(256), 0, ctx->stream, pk, payload, m, slots, mask,
-                       shift, ctx->d_status);
-  REL_LAUNCH_CHECK(ctx, "join_build");
+  const unsigned grid = grid_for(ctx, m, kIdxBlock * 4, 8);
+  {
+    KernelTimer kt(ctx, "join_build");
+    if (payload_kind == PAY_I32)
+      hipLaunchKernelGGL(k_index_build<PAY_I32>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
+    else if (payload_kind == PAY_I8)
+      hipLaunchKernelGGL(k_index_build<PAY_I8>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
+    else
+      hipLaunchKernelGGL(k_index_build<PAY_ROW_ID>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
+  }
+  REL_LAUNCH_CHECK(ctx, "join index build");
   return REL_OK;
 }
 
@@ -321,34 +408,7 @@ rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload
   x.pkind = payload_kind;
   x.narrow = payload_kind == PAY_I8;
   x.m = m;
-  int64_t gm = (m + kMinMaxBlock * 16 - 1) / (kMinMaxBlock * 16);
-  if (gm > kMinMaxGrid) gm = kMinMaxGrid;
-  {
-    KernelTimer kt(ctx, "key_minmax");
-    if (m > 0)
-      hipLaunchKernelGGL(k_key_minmax, dim3((unsigned)gm), dim3(kMinMaxBlock), 0, ctx->stream, pk, m, (uint32_t*)part);
-  }
-  {
-    KernelTimer kt(ctx, "join_table_init");
-    const int64_t words = (int64_t)(1ull << jl) + 1;
-    const int64_t most = dcap > words ? dcap : words;
-    hipLaunchKernelGGL(k_index_clear, dim3(grid_for(ctx, most, kIdxBlock * 8, 4)), dim3(kIdxBlock), 0, ctx->stream, x, words,
-                       (const uint32_t*)part, (int32_t)gm, zero);
-  }
-  REL_LAUNCH_CHECK(ctx, "join index clear");
-  if (m > 0) {
-    const unsigned grid = grid_for(ctx, m, kIdxBlock * 4, 8);
-    {
-      KernelTimer kt(ctx, "join_build");
-      if (payload_kind == PAY_I32)
-        hipLaunchKernelGGL(k_index_build<PAY_I32>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
-      else if (payload_kind == PAY_I8)
-        hipLaunchKernelGGL(k_index_build<PAY_I8>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
-      else
-        hipLaunchKernelGGL(k_index_build<PAY_ROW_ID>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
-    }
-    REL_LAUNCH_CHECK(ctx, "join index build");
-  }
+  if ((s = index_fill(ctx, pk, payload_kind, (uint32_t*)part, (int64_t)(1ull << jl) + 1, zero, x)) != REL_OK) return s;
   *out = x;
   return REL_OK;
 }
@@ -383,6 +443,115 @@ uint32_t join_log2cap(int64_t m, const rel_table_opts* opts) {
 
 }  // namespace relh
 
+namespace {
+
+// A stand-alone table's memory: 2^log2cap + 1 slots, of which a dense array
+// uses as much as its range needs, then the tail: the keys' order-encoded
+// minimum and maximum, the entry count and the count's arrivals.
+constexpr size_t kTailBytes = 32;
+// From this many keys a table may be dense. Below it the hash table (at most
+// 2 MB) stays in L2 and the two kernels more cost as much as they save.
+constexpr int64_t kDenseMinKeys = 1 << 16;
+
+uint64_t* table_tail(const rel_join_table* t) { return (uint64_t*)((char*)t->slots + t->bytes - kTailBytes); }
+
+rel::JoinIndex table_index(const rel_join_table* t, const int32_t* payload) {
+  rel::JoinIndex x{};
+  x.hash = rel::JoinView{t->slots, (uint32_t)((1ull << t->log2cap) - 1), 32u - t->log2cap};
+  x.dense = t->slots;
+  x.mm = (const uint32_t*)table_tail(t);
+  // at most twice the keys, and what the slots hold
+  x.dense_cap = std::min<int64_t>(2 * t->m, (int64_t)1 << (t->log2cap + (t->wide ? 0 : 1)));
+  x.payload = payload;
+  x.pkind = t->wide ? PAY_I32 : PAY_ROW_ID;
+  x.wide = t->wide;
+  x.m = t->m;
+  return x;
+}
+
+// Table memory: a context keeps the last table's memory that was given back
+// (one buffer, freed with the context, when another one takes its place or
+// when an allocation fails), because allocating and freeing the 256 MB of a
+// 15M-key table for each query took 0.3 ms, as long as building and probing
+// it. A table that only ever saw one stream is kept, for a table on the same
+// stream, whose kernels follow the old ones'; any other goes back through
+// hipFree, which waits for the device. Under capture nothing is kept or
+// reused, so that no graph holds memory that another table gets.
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+rel_status take_table(rel_ctx* ctx, size_t bytes, uint64_t** out) {
+  if (!capturing(ctx->stream)) {
+    std::lock_guard<std::mutex> lock(ctx->table_mu);
+    ScratchBuf& b = ctx->spare;
+    if (b.ptr && b.bytes == bytes && ctx->spare_stream == ctx->stream) {
+      *out = (uint64_t*)b.ptr;
+      b = ScratchBuf{};
+      return REL_OK;
+    }
+  }
+  void* p = nullptr;
+  hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    std::lock_guard<std::mutex> lock(ctx->table_mu);
+    if (ctx->spare.ptr) {
+      (void)hipGetLastError();
+      (void)hipFree(ctx->spare.ptr);
+      ctx->spare = ScratchBuf{};
+      e = hipMalloc(&p, bytes);
+    }
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return relh::fail(ctx, REL_OOM, "rel_join_build: table allocation failed");
+  }
+  *out = (uint64_t*)p;
+  return REL_OK;
+}
+
+// A kernel of the context's stream is about to use the table.
+void note_stream(const rel_join_table* t) {
+  if (t->stream != t->ctx->stream) t->many_streams = true;
+}
+
+rel_status build_table(rel_ctx* ctx, const int32_t* pk, const int32_t* payload, const rel_join_table* t) {
+  const int64_t m = t->m;
+  const int64_t words = (int64_t)(1ull << t->log2cap) + 1;
+  const rel::JoinIndex x = table_index(t, payload);
+  const int kind = payload ? PAY_I32 : PAY_ROW_ID;
+  rel_status s;
+  if (!t->may_be_dense) {
+    {
+      relh::KernelTimer kt(ctx, "join_table_init");
+      s = relh::fill_u64(ctx, t->slots, (size_t)words, rel::kJoinEmpty);
+    }
+    if (s != REL_OK || m == 0) return s;
+    relh::KernelTimer kt(ctx, "join_build");
+    auto* kernel = kind == PAY_I32 ? &k_join_build<PAY_I32> : &k_join_build<PAY_ROW_ID>;
+    hipLaunchKernelGGL(kernel, dim3(relh::grid_for(ctx, m, 256 * 4, 8)), dim3(256), 0, ctx->stream, pk,
+                       (const void*)payload, m, t->slots, x.hash.mask, x.hash.shift, ctx->d_status);
+    REL_LAUNCH_CHECK(ctx, "join_build");
+    return REL_OK;
+  }
+  void* part;
+  if ((s = relh::scratch(ctx, SCR_MINMAX, (size_t)kMinMaxGrid * 8, &part)) != REL_OK) return s;
+  uint64_t* tail = table_tail(t);
+  const relh::ZeroSpans zero{{tail + 1, nullptr}, {2, 0}};
+  if ((s = relh::index_fill(ctx, pk, kind, (uint32_t*)part, words, zero, x)) != REL_OK) return s;
+  relh::KernelTimer kt(ctx, "join_index_verify");
+  hipLaunchKernelGGL(k_index_count, dim3((unsigned)ctx->num_cus), dim3(kVerifyBlock), 0, ctx->stream, x, tail + 1, ctx->d_status);
+  REL_LAUNCH_CHECK(ctx, "join_index_verify");
+  return REL_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 rel_status rel_join_build(rel_ctx* ctx, const int32_t* pk, const int32_t* payload, int64_t m,
@@ -397,17 +566,23 @@ rel_status rel_join_build(rel_ctx* ctx, const int32_t* pk, const int32_t* payloa
   t->ctx = ctx;
   t->log2cap = l;
   t->m = m;
-  hipError_t e = hipMalloc(&t->slots, (sizeof(uint64_t) << l) + sizeof(uint64_t));
-  if (e != hipSuccess) {
-    delete t;
-    (void)hipGetLastError();
-    return relh::fail(ctx, REL_OOM, "rel_join_build: table allocation failed");
+  t->may_be_dense = m >= kDenseMinKeys && relh::aligned16(pk);  // (the range is found by 16-byte loads)
+  t->stream = ctx->stream;
+  t->wide = payload != nullptr;
+  const size_t bytes = ((size_t)8 << l) + 8;
+  t->bytes = (bytes + 15) / 16 * 16 + kTailBytes;
+  rel_status s = take_table(ctx, t->bytes, &t->slots);
+  if (s == REL_OK) {
+    s = build_table(ctx, pk, payload, t);
+    if (s != REL_OK) (void)hipFree(t->slots);
   }
-  rel_status s = relh::join_build_into(ctx, pk, payload, payload ? relh::PAY_I32 : relh::PAY_ROW_ID, m, t->slots, l);
   if (s != REL_OK) {
-    (void)hipFree(t->slots);
     delete t;
     return s;
+  }
+  {
+    std::lock_guard<std::mutex> lock(ctx->table_mu);
+    ++ctx->tables;
   }
   *out = t;
   return REL_OK;
@@ -415,8 +590,20 @@ rel_status rel_join_build(rel_ctx* ctx, const int32_t* pk, const int32_t* payloa
 
 rel_status rel_join_table_destroy(rel_join_table* t) {
   if (!t) return REL_INVALID_ARG;
-  if (t->ctx) (void)hipStreamSynchronize(t->ctx->stream);
-  if (t->slots) (void)hipFree(t->slots);
+  rel_ctx* ctx = t->ctx;
+  void* give = t->slots;
+  bool last = false;
+  {
+    std::lock_guard<std::mutex> lock(ctx->table_mu);
+    if (!ctx->closed && !t->many_streams && !capturing(t->stream)) {
+      std::swap(give, ctx->spare.ptr);
+      ctx->spare.bytes = t->bytes;
+      ctx->spare_stream = t->stream;
+    }
+    last = --ctx->tables == 0 && ctx->closed;
+  }
+  if (give) (void)hipFree(give);
+  if (last) delete ctx;
   delete t;
   return REL_OK;
 }
@@ -430,10 +617,12 @@ rel_status rel_join_probe(rel_ctx* ctx, const rel_join_table* t, const int32_t* 
   if (out_cap < n) return relh::fail(ctx, REL_CAPACITY, "rel_join_probe: out_cap %lld < n %lld", (long long)out_cap, (long long)n);
   rel_status s = relh::fill_u64(ctx, d_out_count, 1, 0);
   if (s != REL_OK || n == 0) return s;
-  rel::JoinView v{t->slots, (uint32_t)((1ull << t->log2cap) - 1), 32u - t->log2cap};
-  const unsigned grid = relh::grid_for(ctx, n, 256 * kProbeRows, 8);
+  const rel::JoinIndex x = table_index(t, nullptr);
+  note_stream(t);
+  const unsigned grid = relh::grid_for(ctx, n, kProbeBlock * kProbeRows, 8);
   relh::KernelTimer kt(ctx, "join_probe");
-  hipLaunchKernelGGL(k_join_probe, dim3(grid), dim3(256), 0, ctx->stream, v, fk, sel, n, out_fact_idx, out_payload,
+  auto* kernel = !t->may_be_dense ? &k_join_probe : t->wide ? &k_join_probe_index<true> : &k_join_probe_index<false>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kProbeBlock), 0, ctx->stream, x, fk, sel, n, out_fact_idx, out_payload,
                      d_out_count);
   REL_LAUNCH_CHECK(ctx, "join_probe");
   return REL_OK;
