@@ -38,22 +38,20 @@ struct GatherArgs {
   GCol cols[kGMaxCols];
 };
 
+// `c.side` 0: fact rows come in ascending runs, so their elements stream and
+// are not worth keeping; dim rows come in any order.
 template <class T>
 __device__ __forceinline__ T gather_one(const GCol& c, int32_t row, uint32_t* status) {
   if ((uint64_t)(uint32_t)row >= (uint64_t)c.src_rows) {
     set_status(status, kDevBadArg);
     return T(0);
   }
-  return static_cast<const T*>(c.src)[row];
+  return c.side ? static_cast<const T*>(c.src)[row] : ld_once(static_cast<const T*>(c.src) + row);
 }
 
-// Four pairs starting at i0 (all in range): element reads first, then one store.
+// Four consecutive results at element i0 (a multiple of four).
 template <class T>
-__device__ __forceinline__ void gather_quad(const GCol& c, const int4& idx, int64_t i0, uint32_t* status) {
-  const T v0 = gather_one<T>(c, idx.x, status);
-  const T v1 = gather_one<T>(c, idx.y, status);
-  const T v2 = gather_one<T>(c, idx.z, status);
-  const T v3 = gather_one<T>(c, idx.w, status);
+__device__ __forceinline__ void store_quad(const GCol& c, int64_t i0, T v0, T v1, T v2, T v3) {
   T* d = static_cast<T*>(c.dst) + i0;
   if constexpr (sizeof(T) == 1) {
     *reinterpret_cast<uint32_t*>(d) = (uint32_t)(uint8_t)v0 | (uint32_t)(uint8_t)v1 << 8 |
@@ -67,6 +65,16 @@ __device__ __forceinline__ void gather_quad(const GCol& c, const int4& idx, int6
     *reinterpret_cast<ulonglong2*>(d) = make_ulonglong2((unsigned long long)v0, (unsigned long long)v1);
     *reinterpret_cast<ulonglong2*>(d + 2) = make_ulonglong2((unsigned long long)v2, (unsigned long long)v3);
   }
+}
+
+// Four pairs starting at i0 (all in range): element reads first, then one store.
+template <class T>
+__device__ __forceinline__ void gather_quad(const GCol& c, const int4& idx, int64_t i0, uint32_t* status) {
+  const T v0 = gather_one<T>(c, idx.x, status);
+  const T v1 = gather_one<T>(c, idx.y, status);
+  const T v2 = gather_one<T>(c, idx.z, status);
+  const T v3 = gather_one<T>(c, idx.w, status);
+  store_quad<T>(c, i0, v0, v1, v2, v3);
 }
 
 template <class T>
@@ -83,6 +91,7 @@ __global__ __launch_bounds__(kGBlock) void k_join_gather(GatherArgs a) {
     n = a.max_pairs;
   }
   if (n < 0) n = 0;
+  if (a.ncols == 0) return;
   const int64_t quads = n / 4;
   const int64_t stride = (int64_t)gridDim.x * kGBlock;
   bool need_f = false, need_d = false;
@@ -92,8 +101,8 @@ __global__ __launch_bounds__(kGBlock) void k_join_gather(GatherArgs a) {
   }
   for (int64_t q = blockIdx.x * (int64_t)kGBlock + threadIdx.x; q < quads; q += stride) {
     const int64_t i0 = 4 * q;
-    const int4 f = need_f ? *reinterpret_cast<const int4*>(a.fidx + i0) : make_int4(0, 0, 0, 0);
-    const int4 d = need_d ? *reinterpret_cast<const int4*>(a.didx + i0) : make_int4(0, 0, 0, 0);
+    const int4 f = need_f ? ld_once(reinterpret_cast<const int4*>(a.fidx + i0)) : make_int4(0, 0, 0, 0);
+    const int4 d = need_d ? ld_once(reinterpret_cast<const int4*>(a.didx + i0)) : make_int4(0, 0, 0, 0);
     for (int c = 0; c < a.ncols; ++c) {
       const GCol& col = a.cols[c];
       const int4& idx = col.side ? d : f;
@@ -121,6 +130,62 @@ __global__ __launch_bounds__(kGBlock) void k_join_gather(GatherArgs a) {
   }
 }
 
+// A dim column larger than an XCD's L2, read by slices (sliced_read): a thread
+// takes four quads of pairs.
+constexpr int kSliceQuads = kSliceReads / 4;
+
+template <class T>
+__global__ __launch_bounds__(kGBlock, 8) void k_join_gather_sliced(GCol c, const int32_t* __restrict__ idx,
+                                                                   const int64_t* __restrict__ d_n, int64_t max_pairs,
+                                                                   uint32_t* __restrict__ status) {
+  const int64_t n = max(min(*d_n, max_pairs), (int64_t)0);
+  const int64_t quads = n / 4;
+  const int64_t b0 = (int64_t)blockIdx.x * kGBlock * kSliceQuads;
+  if (b0 > quads) return;
+  const int64_t q0 = b0 + threadIdx.x;
+  const uint32_t rows = (uint32_t)c.src_rows, bytes = rows * (uint32_t)sizeof(T);
+  uint32_t o[kSliceReads];
+  typename SliceReg<T>::type v[kSliceReads];
+#pragma unroll
+  for (int u = 0; u < kSliceQuads; ++u) {
+    const int64_t q = q0 + u * kGBlock;
+    const int4 t = q < quads ? ld_once(reinterpret_cast<const int4*>(idx) + q) : make_int4(0, 0, 0, 0);
+    o[4 * u] = t.x;
+    o[4 * u + 1] = t.y;
+    o[4 * u + 2] = t.z;
+    o[4 * u + 3] = t.w;
+  }
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < kSliceReads; ++k) {
+    v[k] = 0;
+    bad |= o[k] >= rows;
+    o[k] = o[k] < rows ? o[k] * (uint32_t)sizeof(T) : ~0u;
+  }
+  if (bad) set_status(status, kDevBadArg);
+  sliced_read<T>(c.src, bytes, o, v);
+#pragma unroll
+  for (int u = 0; u < kSliceQuads; ++u) {
+    const int64_t q = q0 + u * kGBlock;
+    if (q < quads) store_quad<T>(c, 4 * q, (T)v[4 * u], (T)v[4 * u + 1], (T)v[4 * u + 2], (T)v[4 * u + 3]);
+  }
+  // the last n mod 4 pairs
+  if (blockIdx.x == 0 && threadIdx.x < n - 4 * quads) gather_tail<T>(c, nullptr, idx, 4 * quads + threadIdx.x, status);
+}
+
+// Fact rows come in ascending runs, which need no slices.
+bool take_sliced(const GCol& c, int64_t max_pairs) {
+  return c.side == REL_SIDE_DIM && sliced_size(c.src_rows * c.eb) && max_pairs >= kSliceMinReads;
+}
+
+template <class T>
+void launch_sliced(rel_ctx* ctx, const GCol& c, const int32_t* idx, const int64_t* d_n, int64_t max_pairs) {
+  const int64_t per = (int64_t)kGBlock * kSliceQuads;
+  const unsigned grid = (unsigned)((max_pairs / 4 + per - 1) / per + (max_pairs < 4));
+  hipLaunchKernelGGL(k_join_gather_sliced<T>, dim3(grid), dim3(kGBlock), 0, ctx->stream, c, idx, d_n, max_pairs,
+                     ctx->d_status);
+}
+
 }  // namespace
 
 extern "C" {
@@ -131,6 +196,8 @@ rel_status rel_join_gather(rel_ctx* ctx, const int32_t* fact_idx, const int32_t*
     return relh::fail(ctx, REL_INVALID_ARG, "rel_join_gather: bad argument");
   if (max_pairs >= (1ll << 31)) return relh::fail(ctx, REL_UNSUPPORTED, "rel_join_gather: max_pairs >= 2^31");
   GatherArgs a{};
+  GCol sliced[kGMaxCols];
+  int n_sliced = 0;
   bool need_f = false, need_d = false;
   for (int32_t c = 0; c < n_cols; ++c) {
     const rel_gather_col& g = cols[c];
@@ -140,7 +207,9 @@ rel_status rel_join_gather(rel_ctx* ctx, const int32_t* fact_idx, const int32_t*
       return relh::fail(ctx, REL_INVALID_ARG, "rel_join_gather: column %d invalid", c);
     if (((uintptr_t)g.src % (uintptr_t)eb) != 0 || !relh::aligned16(g.dst))
       return relh::fail(ctx, REL_INVALID_ARG, "rel_join_gather: column %d misaligned (src to its element, dst to 16 B)", c);
-    a.cols[c] = GCol{g.src, g.dst, g.src_rows, eb, g.side};
+    const GCol col{g.src, g.dst, g.src_rows, eb, g.side};
+    if (take_sliced(col, max_pairs)) sliced[n_sliced++] = col;
+    else a.cols[a.ncols++] = col;
     need_f |= g.side == REL_SIDE_FACT;
     need_d |= g.side == REL_SIDE_DIM;
   }
@@ -152,10 +221,19 @@ rel_status rel_join_gather(rel_ctx* ctx, const int32_t* fact_idx, const int32_t*
   a.d_n = d_n_pairs;
   a.max_pairs = max_pairs;
   a.status = ctx->d_status;
-  a.ncols = n_cols;
   const unsigned grid = relh::grid_for(ctx, (max_pairs + 3) / 4, kGBlock, 8);
   relh::KernelTimer kt(ctx, "join_gather");
-  hipLaunchKernelGGL(k_join_gather, dim3(grid), dim3(kGBlock), 0, ctx->stream, a);
+  // (also with no column left: it checks the count)
+  hipLaunchKernelGGL(k_join_gather, dim3(a.ncols ? grid : 1), dim3(kGBlock), 0, ctx->stream, a);
+  for (int c = 0; c < n_sliced; ++c) {
+    const GCol& col = sliced[c];
+    switch (col.eb) {
+      case 1: launch_sliced<uint8_t>(ctx, col, dim_idx, d_n_pairs, max_pairs); break;
+      case 2: launch_sliced<uint16_t>(ctx, col, dim_idx, d_n_pairs, max_pairs); break;
+      case 4: launch_sliced<uint32_t>(ctx, col, dim_idx, d_n_pairs, max_pairs); break;
+      default: launch_sliced<uint64_t>(ctx, col, dim_idx, d_n_pairs, max_pairs); break;
+    }
+  }
   REL_LAUNCH_CHECK(ctx, "join_gather");
   return REL_OK;
 }

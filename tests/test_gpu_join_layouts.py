@@ -1,5 +1,6 @@
 """GPU parity of stand-alone join tables around the choice between the dense
-array and the hash table; table memory that passes from one table to the next."""
+array and the hash table, and of gathers around the sizes that are read by
+slices; table memory that passes from one table to the next."""
 import ctypes
 
 import numpy as np
@@ -105,3 +106,26 @@ def test_memory_of_closed_tables_is_reused_safely():
     t.h = None
     ctx.close()  # a table may outlive its context as far as being destroyed
     assert rel.lib().rel_join_table_destroy(raw) == rel.OK
+
+
+@pytest.mark.parametrize("dt", [torch.int8, torch.int16, torch.int32, torch.int64])
+@pytest.mark.parametrize("mb", [4.0, 4.000001, 11.3, 41.0, 64.0, 64.000001])  # slices are 4 MB, at most 16 of them
+def test_gather_by_slices(ctx, dt, mb):
+    es = torch.empty(0, dtype=dt).element_size()
+    rows = int(mb * (1 << 20)) // es + (mb != int(mb) and es > 1)
+    n = (2 << 20) + 3
+    g = torch.Generator(device="cuda:0").manual_seed(rows)
+    src = torch.randint(-100, 100, (rows,), generator=g, device="cuda:0", dtype=torch.int32).to(dt)
+    idx = torch.randint(0, rows, (n,), generator=g, device="cuda:0", dtype=torch.int32)
+    idx[:4] = torch.tensor([0, rows - 1, rows // 2, 0], dtype=torch.int32)
+    for count in (n, n - 2, 3, 0):
+        cnt = torch.tensor([count], device="cuda:0")
+        out, = ctx.join_gather(None, idx, cnt, [(src, "dim")])
+        assert torch.equal(out[:count], src[idx[:count].long()])
+    assert ctx.sync() == 0
+    idx[5], idx[n - 1] = rows, -1  # out of range: zero, and the status bit
+    out, = ctx.join_gather(None, idx, torch.tensor([n], device="cuda:0"), [(src, "dim")])
+    assert int(out[5]) == 0 and int(out[n - 1]) == 0 and ctx.sync() == rel.DEV_BADARG
+    ok = torch.ones(n, dtype=torch.bool, device="cuda:0")
+    ok[5] = ok[n - 1] = False
+    assert torch.equal(out[:n][ok], src[idx[ok].long()])
