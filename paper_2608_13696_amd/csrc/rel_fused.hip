@@ -107,7 +107,8 @@ __device__ __forceinline__ void load_fused(const FusedArgs& a, int64_t r0, Fused
 // workgroups adding into the same few device slots at the kernel's end, and
 // atomics on one cache line serialise (about 12 ns each on this chip).
 template <int NT>
-__device__ void stage_or_flush(LdsGroups<kLdsSlots>& lds, const FusedArgs& a, uint64_t dev_rows) {
+__device__ void stage_or_flush(LdsGroups<kLdsSlots>& lds, const GroupView& groups, GroupSlot* stage, uint32_t* touched,
+                               uint64_t dev_rows) {
   static_assert(NT == kLdsSlots, "one LDS slot per thread");
   __shared__ uint32_t s_wcnt[NT / kWave];
   __shared__ uint64_t s_red[NT / kWave];
@@ -124,15 +125,15 @@ __device__ void stage_or_flush(LdsGroups<kLdsSlots>& lds, const FusedArgs& a, ui
     before += w < wave ? c : 0u;
     total += c;
   }
-  GroupSlot* st = a.stage + (int64_t)blockIdx.x * kStageMax;
+  GroupSlot* st = stage + (int64_t)blockIdx.x * kStageMax;
   if (total <= (uint32_t)kStageMax) {
     if (occ) st[before + mask_rank(ball)] = GroupSlot{lds.key[t], lds.sum_price[t], lds.sum_qty[t], lds.count[t]};
     if (t >= (int)total && t < kStageMax) st[t] = GroupSlot{kGroupEmpty, 0, 0, 0};
   } else {
-    if (occ) group_add(a.groups, lds.key[t], lds.sum_price[t], lds.sum_qty[t], lds.count[t]);
+    if (occ) group_add(groups, lds.key[t], lds.sum_price[t], lds.sum_qty[t], lds.count[t]);
     if (t < kStageMax) st[t] = GroupSlot{kGroupEmpty, 0, 0, 0};
   }
-  if (t == 0 && (dev_rows != 0 || total > (uint32_t)kStageMax)) *a.touched = 1u;
+  if (t == 0 && (dev_rows != 0 || total > (uint32_t)kStageMax)) *touched = 1u;
 }
 
 // Persistent: each workgroup walks tiles with a grid stride and loads its next
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(NT) void k_fused(FusedArgs a) {
   }
   if constexpr (GP == G_LDS) {
     __syncthreads();
-    stage_or_flush<NT>(lds, a, dev_rows);
+    stage_or_flush<NT>(lds, a.groups, a.stage, a.touched, dev_rows);
   }
   // the totals go out with plain stores, one triple per workgroup; the merge
   // or finalize kernel adds them up
@@ -239,13 +240,14 @@ constexpr int kMergeUnroll = 8;
 
 struct MergeArgs {
   const GroupSlot* stage;  // n_wg * kStageMax
-  const uint32_t* touched;
+  uint32_t* touched;
   int64_t n_wg;
-  const uint64_t* wg_counts;
+  const uint64_t* wg_counts;  // (null: none)
   int64_t* counters;
   GroupView groups;
   uint32_t* done;
   JoinIndex join;  // for the dense index's entry count
+  const uint32_t* few;  // clear: the stages were not written (null: they were)
 };
 
 // The per-workgroup counts summed by NT threads (valid in thread 0): rows
@@ -274,31 +276,65 @@ __device__ void sum_wg_counts(const uint64_t* wg, int64_t n_wg, const JoinIndex&
 struct OutArgs;
 __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs o);
 
-// Standalone group-by over key[row], row = sel ? sel[k] : k.
-template <int GP>
-__global__ __launch_bounds__(kBlock) void k_groupby(const int64_t* __restrict__ key, const int64_t* __restrict__ price,
-                                                    const int32_t* __restrict__ qty, const int32_t* __restrict__ sel,
-                                                    int64_t n, GroupView g) {
-  __shared__ LdsGroups<GP == G_LDS ? kLdsSlots : 1> lds;
-  if (GP == G_LDS) {
-    lds.init(threadIdx.x, kBlock);
-    __syncthreads();
+// Stand-alone group-by over key[row], row = sel ? sel[k] : k, straight into the
+// device table.
+__device__ __forceinline__ void groupby_device(const relh::GroupRows& in, const GroupView& g) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < in.n; k += stride) {
+    const int64_t row = in.sel ? (int64_t)in.sel[k] : k;
+    group_add(g, in.key[row], (uint64_t)in.price[row], (uint64_t)(int64_t)in.qty[row], 1ull);
   }
-  int64_t k = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (; k < n; k += stride) {
-    const int64_t row = sel ? (int64_t)sel[k] : k;
-    const int64_t kv = key[row];
-    const uint64_t sp = (uint64_t)price[row], sq = (uint64_t)(int64_t)qty[row];
-    int s = -1;
-    if (GP == G_LDS && kv != kGroupEmpty) s = lds.find(kv, kLdsProbe);
-    if (s >= 0) lds.add(s, sp, sq, 1ull);
-    else group_add(g, kv, sp, sq, 1ull);
+}
+
+__global__ __launch_bounds__(kBlock) void k_groupby_global(relh::GroupRows in, GroupView g) { groupby_device(in, g); }
+
+// The same through an LDS table per workgroup, with the device table behind
+// it; groups leave as in the fused kernel's LDS variant (stage_or_flush).
+// kGbAhead rows per thread are loaded before any is added: 4.2M selected rows
+// of 15 groups take 26 us (125 us with one row at a time in 256-thread
+// workgroups that each flushed to the device table).
+constexpr int kGbAhead = 4;
+__global__ __launch_bounds__(kLdsBlock) void k_groupby_lds(relh::GroupRows in, const uint32_t* __restrict__ few, GroupView g,
+                                                           int32_t probe, bool device_if_many,
+                                                           GroupSlot* __restrict__ stage, uint32_t* __restrict__ touched) {
+  __shared__ LdsGroups<kLdsSlots> lds;
+  if (*few == 0) {
+    if (device_if_many) groupby_device(in, g);
+    return;
   }
-  if (GP == G_LDS) {
-    __syncthreads();
-    lds.flush(g, threadIdx.x, kBlock);
+  lds.init(threadIdx.x, kLdsBlock);
+  __syncthreads();
+  uint64_t dev_rows = 0;
+  const int64_t step = (int64_t)gridDim.x * kLdsBlock;
+  for (int64_t k0 = blockIdx.x * (int64_t)kLdsBlock + threadIdx.x; k0 < in.n; k0 += kGbAhead * step) {
+    int64_t row[kGbAhead], key[kGbAhead];
+    uint64_t sp[kGbAhead], sq[kGbAhead];
+#pragma unroll
+    for (int u = 0; u < kGbAhead; ++u) {
+      const int64_t k = k0 + u * step;
+      row[u] = k < in.n ? (in.sel ? (int64_t)in.sel[k] : k) : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kGbAhead; ++u) {
+      const int64_t r = row[u] >= 0 ? row[u] : 0;
+      key[u] = in.key[r];
+      sp[u] = (uint64_t)in.price[r];
+      sq[u] = (uint64_t)(int64_t)in.qty[r];
+    }
+#pragma unroll
+    for (int u = 0; u < kGbAhead; ++u) {
+      if (row[u] < 0) continue;
+      const int s = key[u] != kGroupEmpty ? lds.find(key[u], probe) : -1;
+      if (s >= 0) {
+        lds.add(s, sp[u], sq[u], 1ull);
+      } else {
+        group_add(g, key[u], sp[u], sq[u], 1ull);
+        ++dev_rows;
+      }
+    }
   }
+  __syncthreads();
+  stage_or_flush<kLdsBlock>(lds, g, stage, touched, dev_rows);
 }
 
 __global__ void k_init_groups(GroupSlot* __restrict__ slots, int64_t nslots) {
@@ -329,6 +365,9 @@ struct OutArgs {
   int64_t* counters;
   const uint32_t* done;  // set: the merge kernel wrote the output (may be null)
   JoinIndex join;        // for the dense index's entry count (mm null: none)
+  const uint64_t* base;  // groups that were written before this kernel's, which follow them (may be null)
+  const uint32_t* touched;  // with base: clear when the table holds no group
+  int64_t limit;            // with base: more groups than this overflow the table that the caller sized
 };
 
 __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs o) {
@@ -336,6 +375,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   __shared__ uint32_t s_lost;  // a group went to the device table here
   __shared__ uint32_t s_wcnt[kLdsBlock / kWave];
   const int t = threadIdx.x;
+  if (m.few != nullptr && *m.few == 0) return;
   lds.init(t, kLdsBlock);
   if (t == 0) s_lost = 0;
   __syncthreads();
@@ -362,9 +402,11 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   }
   // the streaming kernel's per-workgroup counts (the barriers inside also end
   // the merge)
-  sum_wg_counts<kLdsBlock>(m.wg_counts, m.n_wg, m.join, m.counters, o.status);
+  if (m.wg_counts) sum_wg_counts<kLdsBlock>(m.wg_counts, m.n_wg, m.join, m.counters, o.status);
+  else __syncthreads();
   const bool occ = lds.count[t] != 0;
   if (*m.touched != 0 || s_lost != 0) {
+    if (t == 0) *m.touched = 1u;
     if (occ) group_add(m.groups, lds.key[t], lds.sum_price[t], lds.sum_qty[t], lds.count[t]);
     return;
   }
@@ -450,6 +492,14 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Src src, int64_t nitems, Ou
   __shared__ uint64_t s_excl;
   __shared__ uint64_t s_wave[kBlock / kWave];
   if (o.done != nullptr && *o.done != 0) return;
+  const uint64_t base = o.base != nullptr ? *o.base : 0ull;
+  if (o.base != nullptr && *o.touched == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *o.d_n = (int64_t)base;
+      if ((int64_t)base > o.limit) set_status(o.status, kDevOverflow);
+    }
+    return;
+  }
   if (threadIdx.x == 0) s_group = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)ticket, 1ull);
   __syncthreads();
   const int64_t group = s_group;
@@ -490,8 +540,11 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Src src, int64_t nitems, Ou
   if (wave == 0) {
     const uint64_t excl = lookback_prefix(state, group, group_total);
     if (threadIdx.x == 0) {
-      s_excl = excl;
-      if (group == ngroups - 1) *o.d_n = (int64_t)(excl + group_total);
+      s_excl = base + excl;
+      if (group == ngroups - 1) {
+        *o.d_n = (int64_t)(base + excl + group_total);
+        if (o.base != nullptr && *o.d_n > o.limit) set_status(o.status, kDevOverflow);
+      }
     }
   }
   __syncthreads();
@@ -502,10 +555,10 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Src src, int64_t nitems, Ou
     int64_t pos = (int64_t)s_excl + before + (int64_t)((my_off >> (16 * g)) & 0xFFFFu);
     for (int k = 0; k < kFinIPT; ++k) {
       if (!(bits[g] & (1u << k))) continue;
+      int64_t key;
+      uint64_t sp, sq, cnt;
+      src.get(i0 + (int64_t)k * kBlock, &key, &sp, &sq, &cnt);  // (also empties the slot of a group past cap)
       if (pos < o.cap) {
-        int64_t key;
-        uint64_t sp, sq, cnt;
-        src.get(i0 + (int64_t)k * kBlock, &key, &sp, &sq, &cnt);
         o.key[pos] = key;
         o.sum_price[pos] = (int64_t)sp;
         o.sum_qty[pos] = (int64_t)sq;
@@ -570,7 +623,7 @@ bool out_ok(const rel_groups_out* out) {
 
 OutArgs out_args(rel_ctx* ctx, const rel_groups_out* out) {
   return OutArgs{out->key, out->sum_price, out->sum_qty, out->count, out->cap, out->d_n_groups, ctx->d_status,
-                 nullptr, 0, nullptr, nullptr, JoinIndex{}};
+                 nullptr, 0, nullptr, nullptr, JoinIndex{}, nullptr, nullptr, 0};
 }
 
 // Group-table capacity (power of two) for `expected` distinct keys at load `load`.
@@ -607,6 +660,13 @@ constexpr int64_t kPartitionMinRows = 1 << 20;
 // are dense, 16 MB at this size) stays in the caches.
 constexpr int64_t kPartitionMinDim = 1 << 22;
 
+// A stand-alone group-by of many groups partitions its rows from this many on
+// (twice as many when a sample has to say whether there are many groups).
+// Measured, partitioned against the device table: 32K rows 37 and 37 us, 64K 39
+// and 41, 128K 41 and 51, 1M 65 and 205, 4M 178 and 611; with the sample, 64K
+// rows 56 and 47 us, 128K 59 and 62.
+constexpr int64_t kGroupbyPartitionRows = 1 << 16;
+
 rel_status sync_stats(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim, const rel_query* q, const rel_plan* plan,
                       rel_groups_out* out, rel_stats* stats, int64_t* cnt, int64_t join_cap, int64_t group_cap,
                       int join_place, int group_place);
@@ -621,28 +681,68 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
     return relh::fail(ctx, REL_INVALID_ARG, "rel_groupby_agg: bad argument");
   if (n >= (1ll << 31)) return relh::fail(ctx, REL_UNSUPPORTED, "rel_groupby_agg: n >= 2^31");
   const double load = (opts && opts->max_load > 0.f) ? (opts->max_load > 0.9f ? 0.9 : opts->max_load) : 0.5;
-  int64_t expected = (opts && opts->capacity_hint > 0) ? opts->capacity_hint : (n < (1ll << 30) ? n : (1ll << 30));
-  int placement = opts ? opts->placement : REL_PLACE_AUTO;
+  const bool hinted = opts && opts->capacity_hint > 0;
+  const int64_t expected = hinted ? opts->capacity_hint : (n < (1ll << 30) ? n : (1ll << 30));
+  const int placement = opts ? opts->placement : REL_PLACE_AUTO;
   if (placement == REL_PLACE_PARTITIONED) return relh::fail(ctx, REL_UNSUPPORTED, "rel_groupby_agg: partitioned placement");
-  if (placement == REL_PLACE_AUTO) placement = expected <= kLdsSlots / 2 ? REL_PLACE_LDS : REL_PLACE_GLOBAL;
   const uint32_t l = group_log2cap(expected, load);
   if (l > 31) return relh::fail(ctx, REL_UNSUPPORTED, "rel_groupby_agg: capacity above 2^31");
+  if (n == 0) return relh::fill_u64(ctx, out->d_n_groups, 1, 0);
+  // Which way: LDS tables over the rows as they come when the caller expects
+  // few groups; partitioned for many groups of many rows, the device table for
+  // many groups of fewer rows; for an unknown number of groups a sample of the
+  // keys decides between few and many on the device.
+  const bool few_expected = expected <= kLdsSlots / 2;
+  const bool lds = placement == REL_PLACE_LDS || (placement == REL_PLACE_AUTO && (few_expected || !hinted));
+  const bool many = placement == REL_PLACE_GLOBAL || (placement == REL_PLACE_AUTO && !few_expected);
+  const bool partition = placement == REL_PLACE_AUTO && many && n >= (hinted ? kGroupbyPartitionRows : 2 * kGroupbyPartitionRows);
+  // the table is left empty by the finalize kernel, so only its first use (or a larger one) clears it
   const int64_t nslots = (1ll << l) + 1;
+  const size_t gbytes = (size_t)nslots * sizeof(GroupSlot);
   void* tbl;
-  TRY(relh::scratch(ctx, SCR_GROUP_TABLE, (size_t)nslots * sizeof(GroupSlot), &tbl));
-  TRY(init_groups(ctx, (GroupSlot*)tbl, nslots));
-  const uint32_t probe = (opts && opts->capacity_hint > 0) ? kPlannedProbe : (uint32_t)(1ull << l);
-  GroupView g{(GroupSlot*)tbl, (uint32_t)((1ull << l) - 1), 32u - l, ctx->d_status, probe};
-  if (n > 0) {
-    const unsigned grid = relh::grid_for(ctx, n, kBlock * 4, placement == REL_PLACE_LDS ? 2 : 8);
+  TRY(relh::scratch(ctx, SCR_GROUP_CLEAN, gbytes, &tbl));
+  ScratchBuf& sb = ctx->scratch[SCR_GROUP_CLEAN];
+  const size_t clean_after = sb.clean > gbytes ? sb.clean : gbytes;
+  if (sb.clean < gbytes) TRY(init_groups(ctx, (GroupSlot*)tbl, nslots));
+  sb.clean = 0;  // until this call's finalize kernel is enqueued
+  const uint32_t probe = hinted ? kPlannedProbe : (uint32_t)(1ull << l);
+  const GroupView g{(GroupSlot*)tbl, (uint32_t)((1ull << l) - 1), 32u - l, ctx->d_status, probe};
+  const relh::GroupRows in{key, price, qty, sel, n};
+  TRY(relh::ensure_counters(ctx));
+  int64_t* cnt = relh::counters(ctx);
+  uint32_t* flags = (uint32_t*)(cnt + CNT_AUX1);  // [0] touched, [1] done
+  uint32_t* few = (uint32_t*)(cnt + CNT_AUX2);
+  uint64_t* state;
+  TRY(finalize_state(ctx, nslots, &state));
+  const int mode = !many ? relh::GB_FEW : !lds ? relh::GB_MANY : relh::GB_SAMPLE;
+  TRY(relh::groupby_begin(ctx, in, mode, few, (uint64_t*)cnt, CNT_AUX2, state, finalize_tiles(nslots)));
+  OutArgs oa = out_args(ctx, out);
+  if (lds) {
+    const unsigned grid = relh::grid_for(ctx, n, partition || !many ? kLdsBlock * kGbAhead : kLdsBlock, 1);
+    void* stage;
+    TRY(relh::scratch(ctx, SCR_STAGE, (size_t)grid * kStageMax * sizeof(GroupSlot), &stage));
     relh::KernelTimer kt(ctx, "groupby");
-    if (placement == REL_PLACE_LDS)
-      hipLaunchKernelGGL(k_groupby<G_LDS>, dim3(grid), dim3(kBlock), 0, ctx->stream, key, price, qty, sel, n, g);
-    else
-      hipLaunchKernelGGL(k_groupby<G_GLOBAL>, dim3(grid), dim3(kBlock), 0, ctx->stream, key, price, qty, sel, n, g);
+    hipLaunchKernelGGL(k_groupby_lds, dim3(grid), dim3(kLdsBlock), 0, ctx->stream, in, (const uint32_t*)few, g,
+                       few_expected || placement == REL_PLACE_LDS ? kLdsProbe : kLdsCacheProbe, !partition, (GroupSlot*)stage, flags);
+    MergeArgs mg{(const GroupSlot*)stage, flags, (int64_t)grid, nullptr, cnt, g, flags + 1, JoinIndex{}, few};
+    hipLaunchKernelGGL(k_group_merge, dim3(1), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
+    oa.done = flags + 1;
+    REL_LAUNCH_CHECK(ctx, "groupby");
+  } else if (!partition) {
+    relh::KernelTimer kt(ctx, "groupby");
+    hipLaunchKernelGGL(k_groupby_global, dim3(relh::grid_for(ctx, n, kBlock * 4, 8)), dim3(kBlock), 0, ctx->stream, in, g);
     REL_LAUNCH_CHECK(ctx, "groupby");
   }
-  return finalize(ctx, SlotSource{(GroupSlot*)tbl, nslots - 1, false}, nslots, out_args(ctx, out));
+  if (partition) {
+    const relh::DirectOut direct{out->key, out->sum_price, out->sum_qty, out->count, out->cap, (uint64_t*)(cnt + CNT_GROUPS), flags};
+    TRY(relh::groupby_partitioned(ctx, in, expected, few, g, direct));
+    oa.base = direct.n_direct;
+    oa.touched = flags;
+    oa.limit = hinted ? nslots : INT64_MAX;
+  }
+  TRY(finalize(ctx, SlotSource{(GroupSlot*)tbl, nslots - 1, true}, nslots, oa, true));
+  ctx->scratch[SCR_GROUP_CLEAN].clean = clean_after;
+  return REL_OK;
 }
 
 rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim, const rel_query* q,
@@ -795,7 +895,7 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     else if (gb == REL_GROUP_FK) TRY(launch_fused<M_FK>(ctx, gp, a, grid));
     else TRY(launch_fused<M_DIM_GRP>(ctx, gp, a, grid));
     if (gp == G_LDS) {
-      MergeArgs mg{a.stage, flags, (int64_t)grid, a.wg_counts, cnt, a.groups, flags + 1, jx};
+      MergeArgs mg{a.stage, flags, (int64_t)grid, a.wg_counts, cnt, a.groups, flags + 1, jx, nullptr};
       oa.n_wg = 0;  // the merge kernel sums the counts
       oa.done = flags + 1;
       relh::KernelTimer kt(ctx, "group_merge");

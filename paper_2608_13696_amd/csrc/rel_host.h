@@ -38,6 +38,7 @@ enum ScratchId : int {
   SCR_STAGE,           // per-workgroup staged groups for the merge kernel
   SCR_MINMAX,          // per-workgroup key minimum and maximum of the join index build
   SCR_SELECT,          // row bits and tile counts of a selection
+  SCR_GROUPBY,         // partitioned rows of a stand-alone group-by
   SCR_COUNT
 };
 

@@ -52,4 +52,35 @@ rel_status partitioned_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_di
                                 void* group_slots, uint32_t group_log2cap, uint32_t max_probe, int32_t lds_probe,
                                 bool eager, int64_t* counters);
 
+// Rows of a stand-alone group-by: row = sel ? sel[k] : k for k in [0, n).
+struct GroupRows {
+  const int64_t* key;
+  const int64_t* price;
+  const int32_t* qty;
+  const int32_t* sel;
+  int64_t n;
+};
+
+// Where units of the partitioned group-by write finished groups.
+struct DirectOut {
+  int64_t* key;
+  int64_t* sum_price;
+  int64_t* sum_qty;
+  int64_t* count;
+  int64_t cap;
+  uint64_t* n_direct;  // groups written so far (may exceed cap)
+  uint32_t* touched;   // set when a group went to the device table instead
+};
+
+// How a group-by decides between LDS tables over its rows as they come (few
+// groups) and partitioning them.
+enum GroupbyMode : int { GB_FEW = 0, GB_MANY, GB_SAMPLE };
+// Writes the decision (1: few groups) to *few and clears words[0, n_words) and state[0, n_state).
+rel_status groupby_begin(rel_ctx* ctx, const GroupRows& in, int mode, uint32_t* few, uint64_t* words, int32_t n_words,
+                         uint64_t* state, int64_t n_state);
+// Groups of the rows, unless *few: straight to `o`, or to the device table g
+// (set *o.touched), about `expected` of them.
+rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expected, const uint32_t* few,
+                               const rel::GroupView& g, const DirectOut& o);
+
 }  // namespace relh
