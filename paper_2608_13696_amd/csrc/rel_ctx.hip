@@ -56,6 +56,10 @@ rel_status scratch(rel_ctx* ctx, int id, size_t bytes, void** out) {
     b.bytes = want;
     b.clean = 0;
   }
+  if (b.dirty) {
+    b.clean = 0;
+    b.dirty = false;
+  }
   *out = b.ptr;
   return REL_OK;
 }

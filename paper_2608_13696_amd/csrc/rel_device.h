@@ -277,6 +277,7 @@ struct JoinIndex {
   JoinView hash;
   void* dense;         // dense_cap entries (16-byte aligned, padded to whole 16-byte words)
   const uint32_t* mm;  // {max of ~(key ^ 2^31), max of (key ^ 2^31)}: the keys' min and max, order-encoded
+                       // (null: a hash table)
   int64_t dense_cap;
   const void* payload;  // the dim payload column (int32 or int8), or null for row ids
   int32_t pkind;        // relh::PayloadKind
@@ -301,7 +302,9 @@ __device__ __forceinline__ DenseRange dense_range_of(const JoinIndex& x, uint32_
   return r;
 }
 
-__device__ __forceinline__ DenseRange dense_range(const JoinIndex& x) { return dense_range_of(x, x.mm[0], x.mm[1]); }
+__device__ __forceinline__ DenseRange dense_range(const JoinIndex& x) {
+  return x.mm ? dense_range_of(x, x.mm[0], x.mm[1]) : DenseRange{0, 0, false};
+}
 
 // 16-byte words that hold the range's entries (the last one padded with
 // entries that the clearing kernel zeroes too).
@@ -365,6 +368,21 @@ __device__ __forceinline__ uint64_t dense_count_entries(const JoinIndex& x, int6
     }
   }
   return c;
+}
+
+// Empties an index again: the dense words in use or the whole hash table, by
+// the threads tid, tid + stride, ...
+__device__ __forceinline__ void join_index_wipe(const JoinIndex& x, int64_t tid, int64_t stride) {
+  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+  const DenseRange r = dense_range(x);
+  if (r.dense) {
+    const int64_t words = dense_words(x, r);
+    for (int64_t i = tid; i < words; i += stride) reinterpret_cast<v4u*>(x.dense)[i] = v4u{0u, 0u, 0u, 0u};
+  } else {
+    uint64_t* slots = const_cast<uint64_t*>(x.hash.slots);
+    const int64_t words = (int64_t)x.hash.mask + 2;
+    for (int64_t i = tid; i < words; i += stride) slots[i] = kJoinEmpty;
+  }
 }
 
 // Insert (key, payload) into a join table with one 64-bit CAS per attempted

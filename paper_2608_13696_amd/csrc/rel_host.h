@@ -16,7 +16,8 @@
 struct ScratchBuf {
   void* ptr = nullptr;
   size_t bytes = 0;
-  size_t clean = 0;  // leading bytes known to hold an empty group table (SCR_GROUP_CLEAN)
+  size_t clean = 0;    // leading bytes known to be empty between calls (tables that their last kernel empties)
+  bool dirty = false;  // a call that was to leave them empty has not said so
 };
 
 // Scratch slots a context keeps between calls (each grows on demand, never shrinks).
@@ -35,6 +36,7 @@ enum ScratchId : int {
   SCR_DENSE,           // dense join index entries
   SCR_WG_COUNTS,       // per-workgroup counts of a streaming kernel
   SCR_GROUP_CLEAN,     // plain path's group table, left empty by its finalize
+  SCR_ROW_AGG,         // plain path's per-dim-row aggregates, left zero by its finalize
   SCR_STAGE,           // per-workgroup staged groups for the merge kernel
   SCR_MINMAX,          // per-workgroup key minimum and maximum of the join index build
   SCR_SELECT,          // row bits and tile counts of a selection

@@ -18,11 +18,20 @@ using relh::PAY_ROW_ID;
 
 // Insert (pk[j], payload) with one 64-bit CAS per attempted slot. Consecutive
 // threads take consecutive rows, so the key and payload reads are coalesced
-// and each thread keeps its CAS independent of the others.
+// and each thread keeps its CAS independent of the others. Also zeroes the
+// caller's spans of words.
+__device__ __forceinline__ void zero_spans(const relh::ZeroSpans& z) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < z.n[k]; i += stride) z.p[k][i] = 0;
+}
+
 template <int PK>
 __global__ __launch_bounds__(256) void k_join_build(const int32_t* __restrict__ pk, const void* __restrict__ payload,
                                                     int64_t m, uint64_t* __restrict__ slots, uint32_t mask,
-                                                    uint32_t shift, uint32_t* __restrict__ status) {
+                                                    uint32_t shift, uint32_t* __restrict__ status, relh::ZeroSpans z) {
+  zero_spans(z);
   int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; j < m; j += stride) {
@@ -50,7 +59,9 @@ __device__ __forceinline__ void minmax_add(int32_t k, uint32_t& lo, uint32_t& hi
   hi = max(hi, o);
 }
 
-__global__ __launch_bounds__(kMinMaxBlock) void k_key_minmax(const int32_t* __restrict__ pk, int64_t m, uint32_t* part) {
+__global__ __launch_bounds__(kMinMaxBlock) void k_key_minmax(const int32_t* __restrict__ pk, int64_t m, uint32_t* part,
+                                                             relh::ZeroSpans z) {
+  zero_spans(z);
   __shared__ uint32_t s_lo[kMinMaxBlock / kWave], s_hi[kMinMaxBlock / kWave];
   uint32_t lo = 0, hi = 0;  // max of ~(key ^ 2^31), max of (key ^ 2^31)
   const int64_t nq = m / 4;  // whole 16-byte quads (pk is 16-byte aligned)
@@ -90,14 +101,10 @@ __global__ __launch_bounds__(kMinMaxBlock) void k_key_minmax(const int32_t* __re
   }
 }
 
-// Combines the min/max pairs of k_key_minmax (every workgroup for itself;
-// workgroup 0 also stores the result in x.mm for the kernels that follow),
-// then clears whichever structure the keys' range selects: the 16-byte words
-// that hold the dense entries in use, or the whole hash table; and zeroes the
-// caller's spans of 64-bit words.
-__global__ __launch_bounds__(kIdxBlock) void k_index_clear(JoinIndex x, int64_t hash_words, const uint32_t* __restrict__ part,
-                                                           int32_t nparts, relh::ZeroSpans z) {
-  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+// The keys' range from the min/max pairs of k_key_minmax, which every workgroup
+// combines for itself; workgroup 0 also stores it in x.mm for the kernels that
+// follow. Synchronises the workgroup.
+__device__ __forceinline__ DenseRange combine_minmax(const JoinIndex& x, const uint32_t* __restrict__ part, int32_t nparts) {
   __shared__ uint32_t s_mm[2];
   if (threadIdx.x < kWave) {
     uint32_t lo = 0, hi = 0;
@@ -121,19 +128,26 @@ __global__ __launch_bounds__(kIdxBlock) void k_index_clear(JoinIndex x, int64_t 
     }
   }
   __syncthreads();
-  const DenseRange r = dense_range_of(x, s_mm[0], s_mm[1]);
+  return dense_range_of(x, s_mm[0], s_mm[1]);
+}
+
+// Clears whichever structure the keys' range selects: the 16-byte words that
+// hold the dense entries in use, or the whole hash table; and zeroes the
+// caller's spans of 64-bit words. (Stand-alone tables; the fused path's index
+// is emptied by the kernel after the one that probes it.)
+__global__ __launch_bounds__(kIdxBlock) void k_index_clear(JoinIndex x, const uint32_t* __restrict__ part, int32_t nparts,
+                                                           relh::ZeroSpans z) {
+  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+  const DenseRange r = combine_minmax(x, part, nparts);
   const int64_t stride = (int64_t)gridDim.x * kIdxBlock;
-  const int64_t tid = blockIdx.x * (int64_t)kIdxBlock + threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-    for (int64_t i = tid; i < z.n[k]; i += stride) z.p[k][i] = 0;
-  int64_t i = tid;
+  int64_t i = blockIdx.x * (int64_t)kIdxBlock + threadIdx.x;
+  zero_spans(z);
   if (r.dense) {
     const int64_t words = dense_words(x, r);
     for (; i < words; i += stride) reinterpret_cast<v4u*>(x.dense)[i] = v4u{0u, 0u, 0u, 0u};
   } else {
     uint64_t* slots = const_cast<uint64_t*>(x.hash.slots);
-    for (; i < hash_words; i += stride) slots[i] = kJoinEmpty;
+    for (; i < (int64_t)x.hash.mask + 2; i += stride) slots[i] = kJoinEmpty;
   }
 }
 
@@ -148,8 +162,9 @@ constexpr int kBuildQuads = 4;
 
 template <int PK>
 __global__ __launch_bounds__(kIdxBlock) void k_index_build(const int32_t* __restrict__ pk, int64_t m, JoinIndex x,
+                                                           const uint32_t* __restrict__ part, int32_t nparts,
                                                            uint32_t* __restrict__ status) {
-  const DenseRange r = dense_range(x);
+  const DenseRange r = nparts > 0 ? combine_minmax(x, part, nparts) : dense_range(x);
   if (r.dense) {
     const int64_t nq = (m + 3) / 4;
     const int4* q = reinterpret_cast<const int4*>(pk);
@@ -361,66 +376,98 @@ __global__ __launch_bounds__(kProbeBlock) void k_join_probe_index(JoinIndex x, c
 
 namespace relh {
 
-// The index's kernels up to its entries: the keys' range, the clearing of what
-// the range selects (dense words or `hash_words` slots) and the entries.
-static rel_status index_fill(rel_ctx* ctx, const int32_t* pk, int payload_kind, uint32_t* part, int64_t hash_words,
-                             const ZeroSpans& zero, const rel::JoinIndex& x) {
-  const int64_t m = x.m;
-  const int32_t parts = key_minmax_partials(ctx, pk, m, part);
-  {
-    KernelTimer kt(ctx, "join_table_init");
-    const int64_t most = x.dense_cap > hash_words ? x.dense_cap : hash_words;
-    hipLaunchKernelGGL(k_index_clear, dim3(grid_for(ctx, most, kIdxBlock * 8, 4)), dim3(kIdxBlock), 0, ctx->stream, x,
-                       hash_words, (const uint32_t*)part, parts, zero);
-  }
-  REL_LAUNCH_CHECK(ctx, "join index clear");
-  if (m == 0) return REL_OK;
-  const unsigned grid = grid_for(ctx, m, kIdxBlock * 4, 8);
-  {
-    KernelTimer kt(ctx, "join_build");
-    if (payload_kind == PAY_I32)
-      hipLaunchKernelGGL(k_index_build<PAY_I32>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
-    else if (payload_kind == PAY_I8)
-      hipLaunchKernelGGL(k_index_build<PAY_I8>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
-    else
-      hipLaunchKernelGGL(k_index_build<PAY_ROW_ID>, dim3(grid), dim3(kIdxBlock), 0, ctx->stream, pk, m, x, ctx->d_status);
-  }
+// The entries of an index that is empty. nparts > 0: the keys' range is still
+// to be combined from `part`.
+static rel_status index_entries(rel_ctx* ctx, const int32_t* pk, int payload_kind, const rel::JoinIndex& x,
+                                const uint32_t* part, int32_t nparts) {
+  if (x.m == 0) return REL_OK;
+  KernelTimer kt(ctx, "join_build");
+  auto* kernel = payload_kind == PAY_I32  ? &k_index_build<PAY_I32>
+                 : payload_kind == PAY_I8 ? &k_index_build<PAY_I8>
+                                          : &k_index_build<PAY_ROW_ID>;
+  hipLaunchKernelGGL(kernel, dim3(grid_for(ctx, x.m, kIdxBlock * 4, 8)), dim3(kIdxBlock), 0, ctx->stream, pk, x.m, x, part,
+                     nparts, ctx->d_status);
   REL_LAUNCH_CHECK(ctx, "join index build");
   return REL_OK;
 }
 
-rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
-                            uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out) {
-  const uint32_t jl = join_log2cap(m, nullptr);
-  void *jt, *dt;
-  rel_status s;
-  if ((s = scratch(ctx, SCR_JOIN_TABLE, ((size_t)8 << jl) + 8, &jt)) != REL_OK) return s;
-  const int64_t dcap = 2 * (m > 8 ? m : 8);
-  if ((s = scratch(ctx, SCR_DENSE, (size_t)dcap * 4 + 16, &dt)) != REL_OK) return s;
-  void* part;
-  if ((s = scratch(ctx, SCR_MINMAX, (size_t)kMinMaxGrid * 8, &part)) != REL_OK) return s;
-  rel::JoinIndex x{};
-  x.hash = rel::JoinView{(const uint64_t*)jt, (uint32_t)((1ull << jl) - 1), 32u - jl};
-  x.dense = dt;
-  x.mm = mm;
-  x.dense_cap = dcap;
-  x.payload = payload;
-  x.pkind = payload_kind;
-  x.narrow = payload_kind == PAY_I8;
-  x.m = m;
-  if ((s = index_fill(ctx, pk, payload_kind, (uint32_t*)part, (int64_t)(1ull << jl) + 1, zero, x)) != REL_OK) return s;
-  *out = x;
-  return REL_OK;
-}
-
-int32_t key_minmax_partials(rel_ctx* ctx, const int32_t* pk, int64_t m, uint32_t* part) {
+static int32_t key_minmax(rel_ctx* ctx, const int32_t* pk, int64_t m, uint32_t* part, const ZeroSpans& zero) {
   int64_t gm = (m + kMinMaxBlock * 16 - 1) / (kMinMaxBlock * 16);
   if (gm > kMinMaxGrid) gm = kMinMaxGrid;
   if (m > 0) {
     KernelTimer kt(ctx, "key_minmax");
-    hipLaunchKernelGGL(k_key_minmax, dim3((unsigned)gm), dim3(kMinMaxBlock), 0, ctx->stream, pk, m, part);
+    hipLaunchKernelGGL(k_key_minmax, dim3((unsigned)gm), dim3(kMinMaxBlock), 0, ctx->stream, pk, m, part, zero);
   }
   return (int32_t)gm;
+}
+
+int32_t key_minmax_partials(rel_ctx* ctx, const int32_t* pk, int64_t m, uint32_t* part) {
+  return key_minmax(ctx, pk, m, part, ZeroSpans{});
+}
+
+static rel_status hash_entries(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
+                               const rel::JoinView& v, const ZeroSpans& zero) {
+  KernelTimer kt(ctx, "join_build");
+  auto* kernel = payload_kind == PAY_I32  ? &k_join_build<PAY_I32>
+                 : payload_kind == PAY_I8 ? &k_join_build<PAY_I8>
+                                          : &k_join_build<PAY_ROW_ID>;
+  hipLaunchKernelGGL(kernel, dim3(grid_for(ctx, m, 256, 8)), dim3(256), 0, ctx->stream, pk, payload, m,
+                     const_cast<uint64_t*>(v.slots), v.mask, v.shift, ctx->d_status, zero);
+  REL_LAUNCH_CHECK(ctx, "join_build");
+  return REL_OK;
+}
+
+// Up to this many keys the fused path's index is a hash table whatever their
+// range: its 2 MB stay in L2, and one launch builds it, where a dense array
+// takes two (the keys' range first). 15K keys: one launch of 3.5 us where the
+// range, the clearing and the dense entries took three of 9.8 us together.
+constexpr int64_t kHashMaxKeys = 1 << 16;
+
+rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
+                            uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out) {
+  const uint32_t jl = join_log2cap(m, nullptr);
+  const size_t hash_bytes = ((size_t)8 << jl) + 8;
+  rel_status s;
+  // both structures are empty between calls (join_index_wipe), so only their
+  // first use, or a larger one, fills them
+  auto empty = [&](int id, size_t bytes, uint64_t word, void** p) {
+    rel_status r = scratch(ctx, id, bytes, p);
+    ScratchBuf& sb = ctx->scratch[id];
+    if (r == REL_OK && sb.clean < bytes) {
+      r = fill_u64(ctx, *p, (bytes + 7) / 8, word);
+      if (r == REL_OK) sb.clean = bytes;
+    }
+    return r;
+  };
+  void *jt, *dt = nullptr, *part = nullptr;
+  if ((s = empty(SCR_JOIN_TABLE, hash_bytes, rel::kJoinEmpty, &jt)) != REL_OK) return s;
+  rel::JoinIndex x{};
+  x.hash = rel::JoinView{(const uint64_t*)jt, (uint32_t)((1ull << jl) - 1), 32u - jl};
+  x.payload = payload;
+  x.pkind = payload_kind;
+  x.narrow = payload_kind == PAY_I8;
+  x.m = m;
+  if (m <= kHashMaxKeys) {
+    s = hash_entries(ctx, pk, payload, payload_kind, m, x.hash, zero);
+  } else {
+    x.dense_cap = 2 * m;
+    x.mm = mm;
+    if ((s = empty(SCR_DENSE, (size_t)x.dense_cap * 4 + 16, 0, &dt)) != REL_OK) return s;
+    x.dense = dt;
+    if ((s = scratch(ctx, SCR_MINMAX, (size_t)kMinMaxGrid * 8, &part)) != REL_OK) return s;
+    const int32_t parts = key_minmax(ctx, pk, m, (uint32_t*)part, zero);
+    s = index_entries(ctx, pk, payload_kind, x, (const uint32_t*)part, parts);
+  }
+  // until join_index_wiped: whatever happens to the call, the next one does not trust the memory
+  ctx->scratch[SCR_JOIN_TABLE].dirty = true;
+  ctx->scratch[SCR_DENSE].dirty = true;
+  *out = x;
+  return s;
+}
+
+void join_index_wiped(rel_ctx* ctx) {
+  ctx->scratch[SCR_JOIN_TABLE].dirty = false;
+  ctx->scratch[SCR_DENSE].dirty = false;
 }
 
 rel_status join_index_verify(rel_ctx* ctx, const rel::JoinIndex& x) {
@@ -532,18 +579,20 @@ rel_status build_table(rel_ctx* ctx, const int32_t* pk, const int32_t* payload, 
       s = relh::fill_u64(ctx, t->slots, (size_t)words, rel::kJoinEmpty);
     }
     if (s != REL_OK || m == 0) return s;
-    relh::KernelTimer kt(ctx, "join_build");
-    auto* kernel = kind == PAY_I32 ? &k_join_build<PAY_I32> : &k_join_build<PAY_ROW_ID>;
-    hipLaunchKernelGGL(kernel, dim3(relh::grid_for(ctx, m, 256 * 4, 8)), dim3(256), 0, ctx->stream, pk,
-                       (const void*)payload, m, t->slots, x.hash.mask, x.hash.shift, ctx->d_status);
-    REL_LAUNCH_CHECK(ctx, "join_build");
-    return REL_OK;
+    return relh::hash_entries(ctx, pk, payload, kind, m, x.hash, relh::ZeroSpans{});
   }
   void* part;
   if ((s = relh::scratch(ctx, SCR_MINMAX, (size_t)kMinMaxGrid * 8, &part)) != REL_OK) return s;
   uint64_t* tail = table_tail(t);
   const relh::ZeroSpans zero{{tail + 1, nullptr}, {2, 0}};
-  if ((s = relh::index_fill(ctx, pk, kind, (uint32_t*)part, words, zero, x)) != REL_OK) return s;
+  const int32_t parts = relh::key_minmax(ctx, pk, m, (uint32_t*)part, relh::ZeroSpans{});
+  {
+    relh::KernelTimer kt(ctx, "join_table_init");
+    hipLaunchKernelGGL(k_index_clear, dim3(relh::grid_for(ctx, std::max(x.dense_cap, words), kIdxBlock * 8, 4)), dim3(kIdxBlock), 0,
+                       ctx->stream, x, (const uint32_t*)part, parts, zero);
+    REL_LAUNCH_CHECK(ctx, "join index clear");
+  }
+  if ((s = relh::index_entries(ctx, pk, kind, x, nullptr, 0)) != REL_OK) return s;
   relh::KernelTimer kt(ctx, "join_index_verify");
   hipLaunchKernelGGL(k_index_count, dim3((unsigned)ctx->num_cus), dim3(kVerifyBlock), 0, ctx->stream, x, tail + 1, ctx->d_status);
   REL_LAUNCH_CHECK(ctx, "join_index_verify");

@@ -15,19 +15,23 @@ constexpr int64_t kLdsGroupCap = 512;
 
 // log2 of the join-table capacity for m keys under opts (plain: 2m rounded up).
 uint32_t join_log2cap(int64_t m, const rel_table_opts* opts);
-// The join index over pk[0..m) (dense array when the keys' range is at most
-// 2m wide, else the plain-sized hash table; decided on the device), in the
-// context's scratch. mm: two device words that receive the keys'
-// order-encoded minimum and maximum. The index's clearing kernel also zeroes
-// `zero`'s spans (words later kernels of the call start from). A dense index is not yet checked
-// for repeated keys: the kernel that probes it counts its entries
-// (dense_count_entries, compared with m), or the caller runs join_index_verify.
+// The join index over pk[0..m) in the context's scratch: for few keys a hash
+// table, else a dense array when the keys' range is at most 2m wide, or the
+// plain-sized hash table (decided on the device). mm: two device words that
+// receive the keys' order-encoded minimum and maximum. The first kernel also
+// zeroes `zero`'s spans (words later kernels of the call start from). A dense
+// index is not yet checked for repeated keys: the kernel that probes it counts
+// its entries (dense_count_entries, compared with m), or the caller runs
+// join_index_verify. The memory is taken to be empty and has to be left empty:
+// a kernel after the probing one runs join_index_wipe, and once that is
+// enqueued the caller says so with join_index_wiped.
 struct ZeroSpans {
   uint64_t* p[2];
   int64_t n[2];
 };
 rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
                             uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out);
+void join_index_wiped(rel_ctx* ctx);
 rel_status join_index_verify(rel_ctx* ctx, const rel::JoinIndex& x);
 // Order-encoded minimum and maximum of pk[0..m) per workgroup: pair i is
 // {max of ~(key ^ 2^31), max of (key ^ 2^31)} over workgroup i's keys, so the
