@@ -220,9 +220,16 @@ rel_status rel_ctx_create(int device, void* hip_stream, rel_ctx** out) {
     return REL_OOM;
   }
   ctx->d_status = ctx->d_status_words;
+  if (hipHostMalloc((void**)&ctx->report, relh::kReportWords * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(ctx->d_status_words);
+    delete ctx;
+    return REL_OOM;
+  }
   if (relh::fill_u32(ctx, ctx->d_status_words, 64, 0) != REL_OK || relh::ensure_counters(ctx) != REL_OK ||
       relh::noalloc_scratch_init(ctx, device) != REL_OK || hipStreamSynchronize(ctx->stream) != hipSuccess) {
     (void)hipFree(ctx->d_status_words);
+    (void)hipHostFree(ctx->report);
     delete ctx;
     return REL_HIP;
   }
@@ -249,6 +256,7 @@ rel_status rel_ctx_destroy(rel_ctx* ctx) {
     (void)hipEventDestroy(ctx->ev_join);
   }
   if (ctx->d_status_words) (void)hipFree(ctx->d_status_words);
+  if (ctx->report) (void)hipHostFree(ctx->report);
   bool tables_left;
   {
     std::lock_guard<std::mutex> lock(ctx->table_mu);

@@ -902,7 +902,8 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   } scope{ctx, ctx->d_status};
   if (stats != nullptr || (planned && plan->allow_fallback)) {
     ctx->d_status = ctx->d_status_words + 1;
-    TRY(relh::fill_u32(ctx, ctx->d_status, 1, 0));
+    if (ctx->sync_word_dirty) TRY(relh::fill_u32(ctx, ctx->d_status, 1, 0));
+    ctx->sync_word_dirty = true;  // until k_report of this call has cleared it again
   } else {
     ctx->d_status = ctx->d_status_words;  // also inside a synchronising call's fallback run
   }
@@ -1056,6 +1057,14 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
 
 namespace {
 
+__global__ void k_report(const int64_t* cnt, const int64_t* n_groups, uint32_t* status, int64_t* report) {
+  report[0] = cnt[0];
+  report[1] = cnt[1];
+  report[2] = *n_groups;
+  report[3] = (int64_t)*status;
+  *status = 0;
+}
+
 // Common tail of the fused pipeline: when the caller wants statistics or a
 // planned table may need the fallback, synchronise, read the counters and the
 // status word, and rerun with plain sizing if a planned table overflowed.
@@ -1066,13 +1075,16 @@ rel_status sync_stats(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim, co
   const bool planned = plan && plan->group_capacity > 0;
   const bool want_sync = stats != nullptr || (planned && plan->allow_fallback);
   if (!want_sync) return REL_OK;
+  // One kernel writes all that the host needs to pinned memory, and clears this
+  // call's status word for the next one: three copies back cost a round trip each.
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(1), 0, ctx->stream, (const int64_t*)cnt, (const int64_t*)out->d_n_groups,
+                     ctx->d_status, ctx->report);
+  REL_LAUNCH_CHECK(ctx, "report");
   REL_HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
-  int64_t hc[2] = {0, 0}, ng = 0;
-  uint32_t bits = 0;
-  REL_HIP_CHECK(ctx, hipMemcpy(hc, cnt, sizeof hc, hipMemcpyDeviceToHost));
-  REL_HIP_CHECK(ctx, hipMemcpy(&ng, out->d_n_groups, sizeof ng, hipMemcpyDeviceToHost));
-  // this call's own word (cleared at its start)
-  REL_HIP_CHECK(ctx, hipMemcpy(&bits, ctx->d_status, sizeof bits, hipMemcpyDeviceToHost));
+  ctx->sync_word_dirty = false;
+  const volatile int64_t* rep = ctx->report;
+  const int64_t hc[2] = {rep[0], rep[1]}, ng = rep[2];
+  const uint32_t bits = (uint32_t)rep[3];
   if (bits & kDevDupKey) return relh::fail(ctx, REL_DUPLICATE_KEY, "rel_filter_join_agg: duplicate pk");
   const bool overflow = (bits & kDevOverflow) != 0;
   if (overflow && ng > out->cap) return relh::fail(ctx, REL_CAPACITY, "rel_filter_join_agg: %lld groups > cap", (long long)ng);

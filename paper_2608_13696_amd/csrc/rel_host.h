@@ -79,6 +79,10 @@ struct rel_ctx {
   // kernels launched now report to.
   uint32_t* d_status_words = nullptr;
   uint32_t* d_status = nullptr;
+  // Pinned host words that a kernel at the end of a synchronising call writes
+  // (kReportWords of them), and whether such a call may have left word 1 set.
+  int64_t* report = nullptr;
+  bool sync_word_dirty = false;
   std::string err;
   ScratchBuf scratch[SCR_COUNT];
   bool timing = false;
@@ -113,6 +117,8 @@ struct rel_join_table {
 };
 
 namespace relh {
+
+constexpr int kReportWords = 8;
 
 rel_status fail(rel_ctx* ctx, rel_status s, const char* fmt, ...);
 rel_status hip_fail(rel_ctx* ctx, hipError_t e, const char* what);

@@ -554,12 +554,11 @@ class Groups:
 
 
 def _alloc_groups(cap: int, device) -> Groups:
+    # one allocation for the four columns and the count (which every successful call writes)
     cap = max(int(cap), 1)
-    t = torch.empty((4, cap), dtype=torch.int64, device=device)
-    ng = torch.empty(1, dtype=torch.int64, device=device)  # every successful call writes it
-    g = Groups(t[0], t[1], t[2], t[3], ng, None)
-    g.c = GroupsOut(_ptr(t[0]), _ptr(t[1]), _ptr(t[2]), _ptr(t[3]), cap, _ptr(ng))
-    return g
+    t = torch.empty(4 * cap + 1, dtype=torch.int64, device=device)
+    p, step = t.data_ptr(), 8 * cap
+    return Groups(*t.split((cap, cap, cap, cap, 1)), GroupsOut(p, p + step, p + 2 * step, p + 3 * step, cap, p + 4 * step))
 
 
 def sorted_groups(h: dict) -> dict:
