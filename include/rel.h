@@ -320,14 +320,15 @@ typedef struct rel_batch_item {
 } rel_batch_item;
 
 /* One size bucket of the tuning table: instances with fact rows
- * n < 2^log2_rows_below use this configuration. Entries ascend; the last one
- * also takes every larger instance. */
+ * n < 2^log2_rows_below use this configuration where they go by tables in device
+ * memory (the others a workgroup takes whole, with nothing to tune). Entries
+ * ascend; the last one also takes every larger instance. */
 typedef struct rel_batch_tuning {
   int32_t log2_rows_below;
   int32_t items_per_thread; /* fact rows per thread per step: 1, 2, 4 or 8 */
   int32_t block;            /* workgroup size: 64, 128, 256 or 512 */
   int32_t lds_groups_max;   /* LDS group table when the instance's group bound is at most this (<= 512); 0 = never */
-  int32_t rows_per_item;    /* fact rows per work item (multiple of block * items_per_thread) */
+  int32_t rows_per_item;    /* fact rows per work item (multiple of block * items_per_thread); fewer in small batches */
   int32_t lds_join_max;     /* LDS join table (built per work item from the dim columns) when the instance's dim
                                has at most this many keys (<= 1024); 0 = never: the device-memory table */
 } rel_batch_tuning;

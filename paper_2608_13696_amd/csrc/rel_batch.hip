@@ -2,13 +2,15 @@
 //
 // A small query alone cannot fill 256 CUs (the paper's undersaturation
 // finding, Section 6.1); thousands of them issued one by one pay a launch and
-// a dependency gap per kernel. Here every instance's build, probe/aggregate
-// and finalize become work items of three persistent kernels (one per phase
-// and size bucket), workgroups pull items largest-first from a ticket
-// counter, and the whole sequence is captured once into a HIP graph so that a
-// run is one graph launch.
+// a dependency gap per kernel. Here one persistent kernel takes whole instances,
+// a workgroup each (k_batch_whole), and the instances that are too large for one
+// workgroup, or too sparse for its arrays, become work items of three more
+// kernels that share tables in device memory: build, probe/aggregate, finalize
+// (one per phase and size bucket). Workgroups pull instances and items
+// largest-first from ticket counters, and the whole sequence is captured once
+// into a HIP graph so that a run is one graph launch.
 //
-// Per-bucket configuration (rows per thread, workgroup size, LDS or
+// Per-bucket configuration of the shared tables (rows per thread, workgroup size, LDS or
 // device-memory group table, LDS or device-memory join table, rows per work
 // item) comes from a tuning table that the autotuner measures.
 #include <algorithm>
@@ -69,6 +71,17 @@ struct BItem {
   int64_t lo, hi;
 };
 
+// How much of a list the kernels of the shared-table path work through: its
+// first `n` entries belong to instances that only they take, the others, up to
+// `all`, to instances that one workgroup may take whole. Those count only when
+// some of them were left, and are then skipped where they are done.
+struct BList {
+  int64_t n, all;
+  const uint32_t* left;
+  const uint32_t* done;
+  __device__ __forceinline__ int64_t size() const { return n < all && *left != 0 ? all : n; }
+};
+
 // The join payload of dim row j (the group attribute, or the row id for GROUP BY fk).
 __device__ __forceinline__ int32_t batch_payload(const BInst& I, int64_t j) {
   return I.group_by == REL_GROUP_PRIO_FLAG ? (int32_t)I.prio[j] : I.group_by == REL_GROUP_DIM_GRP ? I.grp[j] : (int32_t)j;
@@ -80,9 +93,11 @@ __global__ void k_batch_zero_outputs(const BInst* __restrict__ inst, int32_t k) 
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_batch_build(const BInst* __restrict__ inst, const BItem* __restrict__ items,
-                                                       int64_t n_items, int64_t* __restrict__ ticket,
-                                                       uint32_t* __restrict__ status) {
+                                                       int64_t* __restrict__ ticket,
+                                                       uint32_t* __restrict__ status, BList list) {
   __shared__ int64_t s_item;
+  const int64_t n_items = list.size();
+  if (n_items == 0) return;
   for (;;) {
     if (threadIdx.x == 0) s_item = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)ticket, 1ull);
     __syncthreads();
@@ -90,6 +105,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_build(const BInst* __restrict__
     __syncthreads();
     if (it >= n_items) break;
     const BItem w = items[it];
+    if (list.done[w.inst] != 0) continue;
     const BInst& I = inst[w.inst];
     for (int64_t j = w.lo + threadIdx.x; j < w.hi; j += BLOCK) {
       join_insert(I.jslots, I.jmask, I.jshift, I.pk[j], batch_payload(I, j), status);
@@ -160,17 +176,23 @@ struct LdsJoinStore<false> {};
 
 template <int BLOCK, int IPT, bool LJ>
 __global__ __launch_bounds__(BLOCK) void k_batch_probe(const BInst* __restrict__ inst, const BItem* __restrict__ items,
-                                                       int64_t n_items, int64_t* __restrict__ ticket,
-                                                       uint32_t* __restrict__ status) {
+                                                       int64_t* __restrict__ ticket,
+                                                       uint32_t* __restrict__ status, BList list) {
   __shared__ LdsGroups<kBLdsSlots> lds;
   __shared__ LdsJoinStore<LJ> ljs;
   __shared__ int64_t s_item;
+  const int64_t n_items = list.size();
+  if (n_items == 0) return;
   for (;;) {
     if (threadIdx.x == 0) s_item = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)ticket, 1ull);
     __syncthreads();
     const int64_t it = s_item;
     if (it >= n_items) break;
     const BItem w = items[it];
+    if (list.done[w.inst] != 0) {
+      __syncthreads();  // (every thread has read s_item)
+      continue;
+    }
     const BInst& I = inst[w.inst];
     const int lds_probe = I.lds != 0 ? kBLdsProbe : kBLdsCacheProbe;
     const JoinView jv{I.jslots, I.jmask, I.jshift};
@@ -233,9 +255,11 @@ __global__ __launch_bounds__(BLOCK) void k_batch_probe(const BInst* __restrict__
 // Emit the occupied group slots of each instance: one atomic per wave on the
 // instance's own output counter (instances are small, so it is not contended).
 __global__ __launch_bounds__(256) void k_batch_finalize(const BInst* __restrict__ inst, const BItem* __restrict__ items,
-                                                        int64_t n_items, int64_t* __restrict__ ticket,
-                                                        uint32_t* __restrict__ status) {
+                                                        int64_t* __restrict__ ticket,
+                                                        uint32_t* __restrict__ status, BList list) {
   __shared__ int64_t s_item;
+  const int64_t n_items = list.size();
+  if (n_items == 0) return;
   for (;;) {
     if (threadIdx.x == 0) s_item = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)ticket, 1ull);
     __syncthreads();
@@ -243,6 +267,7 @@ __global__ __launch_bounds__(256) void k_batch_finalize(const BInst* __restrict_
     __syncthreads();
     if (it >= n_items) break;
     const BItem w = items[it];
+    if (list.done[w.inst] != 0) continue;
     const BInst& I = inst[w.inst];
     const int64_t side = (int64_t)I.gmask + 1;
     // wave-uniform trip count, so ballots see every lane
@@ -276,7 +301,8 @@ __global__ __launch_bounds__(256) void k_batch_finalize(const BInst* __restrict_
   }
 }
 
-__global__ void k_batch_init_groups(GroupSlot* __restrict__ slots, int64_t nslots) {
+__global__ void k_batch_init_groups(GroupSlot* __restrict__ slots, BList list) {
+  const int64_t nslots = list.size();
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < nslots; i += stride) {
@@ -289,10 +315,543 @@ __global__ void k_batch_init_groups(GroupSlot* __restrict__ slots, int64_t nslot
   }
 }
 
-__global__ void k_batch_fill(uint64_t* __restrict__ p, int64_t n, uint64_t v) {
+__global__ void k_batch_fill(uint64_t* __restrict__ p, uint64_t v, BList list) {
+  const int64_t n = list.size();
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) p[i] = v;
+}
+
+// ---- whole instances -------------------------------------------------------------------------------------------------
+//
+// The kernels above pay for device memory: a compare-and-swap per dim row and
+// up to four atomics per joined row, at about 27 G/s for the whole chip. When
+// there are enough instances to keep every CU busy, one workgroup takes a whole
+// instance instead and nothing is shared with another workgroup: no atomics on
+// device memory, no group table, no merge.
+//
+//   1. the dim keys' and group attributes' minima and maxima;
+//   2. the join table, an array over the keys' range of as few bits per entry as
+//      hold 0 or the dim row's group attribute relative to the smallest, plus 1
+//      (1, 2, 4, 8 or 16), filled in LDS slice by slice and streamed to memory, or
+//      left in LDS when it fits beside the groups;
+//   3. the fact rows: filter, lookup, and adds into LDS arrays of sums indexed
+//      by the group's number;
+//   4. the groups that have rows, written out in order.
+//
+// With more groups than the LDS arrays hold, step 3 sorts each tile's joined
+// rows by chunk of groups into memory of the workgroup's own, and the chunks are
+// then summed one after another. Where few dim rows have attributes of a wide
+// range, the attributes that occur are numbered first, so that one chunk holds
+// them. Instances whose keys or attributes are too sparse for arrays are left to
+// the kernels above (`BWhole::left`).
+//
+// 4096 instances of 1K to 1M rows (585M rows, 12.9 GB of columns): 19.99 ms by
+// the shared tables, 4.09 ms here. What bounds it is the fabric: of the large
+// instances, most lookups miss the XCD's L2 and fetch a 128-byte line, as many
+// bytes again as the columns. With 16-bit entries throughout it was 5.97 ms
+// (31 GB fetched; 22 GB with entries of as few bits as will do), without the
+// next tile's loads in flight 6.65, with two workgroups of 512 threads per CU
+// 9.90 ms (half the LDS each: twice the chunks). The steps hand their values on
+// in LDS (`WPlan`): in registers over the whole instance they spilled inside the
+// loop over the rows (11.5 ms). A one-tile instance takes about 10 us.
+constexpr int kWBlock = 1024;
+constexpr int kWRows = 4;                                  // rows per thread and tile
+constexpr int kWTile = kWBlock * kWRows;
+constexpr int kWPool = 152 * 1024;                         // bytes of LDS for tables, sums and sorted tiles
+constexpr int kWGroupBytes = 20;                           // price and quantity sums, count
+constexpr int kWCap = 7168;                                // groups of one chunk
+constexpr int kWMaxChunks = 128;
+constexpr int kWSortBytes = kWTile * 16;                   // a sorted tile
+constexpr int kWRankRows = 5120;                           // at most so many dim rows have their attributes numbered
+constexpr int kWRankBytes = 65536 / 8 + 65536 / 16 + kWRankRows * 2;
+constexpr int64_t kWMaxRange = (int64_t)kWCap * kWMaxChunks;  // group numbers
+constexpr size_t kWMaxSpill = 8ull << 30;                  // bytes of spill memory of a batch
+static_assert(kWCap * kWGroupBytes <= kWPool && kWSortBytes + 64 * 1024 <= kWPool, "LDS pool");
+static_assert(kWRankRows <= kWCap && kWRankRows * (kWGroupBytes + 4) + 64 + kWRankBytes <= kWPool, "LDS pool");
+
+struct BWhole {
+  const BInst* inst;
+  const int32_t* order;   // instances to take, largest first
+  int32_t n;              // their number
+  int64_t* ticket;
+  uint32_t* status;
+  uint32_t* done;         // per instance: finished here
+  uint32_t* left;         // instances of `order` that were not
+  uint64_t* spill;        // per workgroup: spill_rows words of {group, quantity}, then as many prices
+  uint32_t* spill_off;    // per workgroup: [tiles][kWMaxChunks + 1]
+  int64_t spill_rows;     // 0: no instance may need more than one chunk
+};
+
+__device__ __forceinline__ int32_t w_attr(const BInst& I, int64_t j) {
+  return I.group_by == REL_GROUP_PRIO_FLAG ? (int32_t)I.prio[j] : I.group_by == REL_GROUP_DIM_GRP ? I.grp[j] : 0;
+}
+
+// Entries of 2^lb bits, packed in words (one lookup is one word read).
+struct WBits {
+  uint32_t lb;
+  static __device__ __forceinline__ WBits of(int64_t most) { return WBits{most <= 1 ? 0u : most <= 3 ? 1u : most <= 15 ? 2u : most <= 255 ? 3u : 4u}; }
+  __device__ __forceinline__ uint32_t word(uint32_t off) const { return off >> (5 - lb); }
+  __device__ __forceinline__ uint32_t shift(uint32_t off) const { return (off & ((32u >> lb) - 1u)) << lb; }
+  __device__ __forceinline__ uint32_t get(uint32_t w, uint32_t off) const { return (w >> shift(off)) & ((1u << (1u << lb)) - 1u); }
+  __device__ __forceinline__ uint32_t words(uint64_t entries) const { return (uint32_t)((entries + (32 >> lb) - 1) >> (5 - lb)); }
+  __device__ __forceinline__ uint32_t used(uint32_t w) const {  // entries of a word that are not 0
+    for (uint32_t d = (1u << lb) >> 1; d != 0; d >>= 1) w |= w >> d;
+    const uint32_t low = lb == 0 ? ~0u : lb == 1 ? 0x55555555u : lb == 2 ? 0x11111111u : lb == 3 ? 0x01010101u : 0x00010001u;
+    return (uint32_t)__popc(w & low);
+  }
+};
+
+// Adds one joined row to the sums of group number g.
+struct WSums {
+  uint64_t* price;
+  uint64_t* qty;
+  uint32_t* count;
+  __device__ __forceinline__ void add(uint32_t g, int64_t p, int32_t q) const {
+    atomicAdd((unsigned long long*)&price[g], (unsigned long long)p);
+    atomicAdd((unsigned long long*)&qty[g], (unsigned long long)(int64_t)q);
+    atomicAdd(&count[g], 1u);
+  }
+  __device__ __forceinline__ void clear(uint32_t groups) const {
+    for (uint32_t g = threadIdx.x; g < groups; g += kWBlock) {
+      price[g] = 0;
+      qty[g] = 0;
+      count[g] = 0;
+    }
+  }
+};
+
+// Groups with rows among the sums' first `groups` to the output from row *out
+// on: key0 + the group's number (or, where it is given, key0 + attr[number]).
+// Every thread calls it; each wave takes a run of groups, counts first and then
+// writes. `scr` is not in use by another wave.
+__device__ void w_emit(const BInst& I, const WSums& s, uint32_t groups, int64_t key0, const uint16_t* attr, uint32_t* scr,
+                       int64_t* out, uint32_t* status) {
+  const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+  const uint32_t run = (groups + kWBlock - 1) / kWBlock * kWave, lo = wave * run, hi = min(lo + run, groups);
+  uint32_t n = 0;
+  for (uint32_t b = lo; b < hi; b += kWave) n += (uint32_t)__popcll(__ballot(b + lane < hi && s.count[b + lane] != 0));
+  if (lane == 0) scr[wave] = n;
+  __syncthreads();
+  int64_t at = *out;
+#pragma unroll
+  for (uint32_t w = 0; w < kWBlock / kWave; ++w) {
+    at += w < wave ? scr[w] : 0u;
+    *out += scr[w];
+  }
+  for (uint32_t b = lo; b < hi; b += kWave) {
+    const uint32_t g = b + lane;
+    const bool has = g < hi && s.count[g] != 0;
+    const uint64_t all = __ballot(has);
+    const int64_t o = at + __popcll(all & ((1ull << lane) - 1));
+    at += __popcll(all);
+    if (!has) continue;
+    if (o < I.out_cap) {
+      I.out_key[o] = key0 + (attr ? (int64_t)attr[g] : (int64_t)g);
+      I.out_sp[o] = (int64_t)s.price[g];
+      I.out_sq[o] = (int64_t)s.qty[g];
+      I.out_cnt[o] = (int64_t)s.count[g];
+    } else {
+      set_status(status, kDevOverflow);
+    }
+  }
+}
+
+// The attributes of few dim rows over a wide range, numbered in order: which
+// occur, how many do before each word of 32, and the number's attribute.
+struct WRanks {
+  uint32_t* bits;
+  uint16_t* before;
+  uint16_t* attr;
+  __device__ __forceinline__ uint32_t of(uint32_t a) const { return before[a >> 5] + (uint32_t)__popc(bits[a >> 5] & ((1u << (a & 31)) - 1u)); }
+};
+
+// What the steps of an instance share, in LDS (each step reads what it needs:
+// kept in registers over all of them, these values spill).
+struct WPlan {
+  int32_t inst, kmin, amin;
+  uint32_t range, arange;  // of the keys and of the attributes
+  uint32_t groups;         // group numbers
+  uint32_t chunks;
+  uint32_t ranked, in_lds;
+  uint32_t front;          // bytes of LDS in front of the join table
+  uint32_t lb;             // log2 of a table entry's bits
+};
+
+struct WShared {
+  uint64_t pool[kWPool / 8];
+  uint32_t cnt[kWMaxChunks + 1];
+  uint32_t scr[kWBlock / kWave];
+  uint64_t red[3][kWBlock / kWave];  // rows passed, join matches, table entries
+  int32_t mn[2][kWBlock / kWave], mx[2][kWBlock / kWave];
+  WPlan p;
+  int64_t item;
+
+  __device__ __forceinline__ char* bytes() { return reinterpret_cast<char*>(pool); }
+  __device__ __forceinline__ WSums sums(uint32_t groups) {
+    return WSums{pool, pool + groups, reinterpret_cast<uint32_t*>(pool + 2 * (size_t)groups)};
+  }
+  __device__ __forceinline__ WRanks ranks() {
+    uint32_t* const bits = reinterpret_cast<uint32_t*>(bytes() + kWPool - kWRankBytes);
+    uint16_t* const before = reinterpret_cast<uint16_t*>(bits + 65536 / 32);
+    return WRanks{bits, before, before + 65536 / 32};
+  }
+};
+
+__device__ __forceinline__ uint32_t w_uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ int32_t w_uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Step 1: the ranges, and from them the plan. False: the instance is not one for arrays.
+__device__ __forceinline__ bool w_plan(const BWhole& a, const BInst& I, WShared& s) {
+  const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+  const int32_t m = (int32_t)I.m;
+  int32_t kmin = INT32_MAX, kmax = INT32_MIN, amin = INT32_MAX, amax = INT32_MIN;
+  for (int32_t b = 0; b < m; b += kWTile) {
+    int32_t key[kWRows], at[kWRows];
+#pragma unroll
+    for (int k = 0; k < kWRows; ++k) {
+      const int32_t j = min(b + (int32_t)t + k * kWBlock, m - 1);
+      key[k] = I.pk[j];
+      at[k] = w_attr(I, j);
+    }
+#pragma unroll
+    for (int k = 0; k < kWRows; ++k) {
+      kmin = min(kmin, key[k]);
+      kmax = max(kmax, key[k]);
+      amin = min(amin, at[k]);
+      amax = max(amax, at[k]);
+    }
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    kmin = min(kmin, __shfl_xor(kmin, d, kWave));
+    kmax = max(kmax, __shfl_xor(kmax, d, kWave));
+    amin = min(amin, __shfl_xor(amin, d, kWave));
+    amax = max(amax, __shfl_xor(amax, d, kWave));
+  }
+  if (lane == 0) {
+    s.mn[0][wave] = kmin;
+    s.mx[0][wave] = kmax;
+    s.mn[1][wave] = amin;
+    s.mx[1][wave] = amax;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWBlock / kWave; ++w) {
+    kmin = min(kmin, s.mn[0][w]);
+    kmax = max(kmax, s.mx[0][w]);
+    amin = min(amin, s.mn[1][w]);
+    amax = max(amax, s.mx[1][w]);
+  }
+  const int64_t range = m > 0 ? (int64_t)kmax - kmin + 1 : 0;
+  const int64_t arange = m > 0 ? (int64_t)amax - amin + 1 : 0;  // 1 for GROUP BY fk
+  const bool by_fk = I.group_by == REL_GROUP_FK, by_flag = I.group_by == REL_GROUP_PRIO_FLAG;
+  // (numbered attributes: the sums of a chunk hold them all)
+  const bool ranked = !by_fk && !by_flag && arange > kWCap && arange <= 65535 && m <= kWRankRows;
+  uint32_t distinct = 0;
+  if (ranked) {
+    const WRanks r = s.ranks();
+    static_assert(65536 / 32 == 2 * kWBlock, "two words per thread");
+    r.bits[2 * t] = 0;
+    r.bits[2 * t + 1] = 0;
+    __syncthreads();
+    for (int32_t j = (int32_t)t; j < m; j += kWBlock) {
+      const uint32_t at = (uint32_t)(I.grp[j] - amin);
+      atomicOr(&r.bits[at >> 5], 1u << (at & 31));
+    }
+    __syncthreads();
+    const uint32_t w0 = r.bits[2 * t], w1 = r.bits[2 * t + 1];
+    uint32_t n = block_excl_scan<kWBlock>((uint32_t)(__popc(w0) + __popc(w1)), s.scr, &distinct);
+    r.before[2 * t] = (uint16_t)n;
+    r.before[2 * t + 1] = (uint16_t)(n + (uint32_t)__popc(w0));
+    for (uint32_t w = w0; w != 0; w &= w - 1) r.attr[n++] = (uint16_t)(64 * t + (uint32_t)__ffs((int)w) - 1u);
+    for (uint32_t w = w1; w != 0; w &= w - 1) r.attr[n++] = (uint16_t)(64 * t + 32 + (uint32_t)__ffs((int)w) - 1u);
+  }
+  const int64_t groups = by_fk ? range : by_flag ? arange * 256 : ranked ? (int64_t)distinct : arange;
+  const int64_t chunks = (groups + kWCap - 1) / kWCap;
+  // (the table takes the place of the instance's hash table, of at least 2 m 8-byte slots)
+  const bool fits = range <= 2 * (int64_t)m + 16 && arange <= 65535 && groups <= kWMaxRange && (chunks <= 1 || I.n <= a.spill_rows);
+  if (t == 0 && fits) {
+    // LDS: the sums of a chunk or a sorted tile, and behind them the join table
+    // when there is room (the tile and the sums are not in use at the same time)
+    const uint32_t sums_bytes = ((uint32_t)(chunks <= 1 ? groups : kWCap) * kWGroupBytes + 15) / 16 * 16;
+    s.p.kmin = kmin;
+    s.p.amin = amin;
+    s.p.range = (uint32_t)range;
+    s.p.arange = (uint32_t)arange;
+    s.p.groups = (uint32_t)groups;
+    s.p.chunks = (uint32_t)chunks;
+    s.p.ranked = ranked;
+    s.p.front = chunks <= 1 ? sums_bytes : max(sums_bytes, (uint32_t)kWSortBytes);
+    const WBits bits = WBits::of(by_fk ? 1 : ranked ? groups : arange);
+    s.p.lb = bits.lb;
+    s.p.in_lds = (int64_t)s.p.front + (int64_t)bits.words((uint64_t)range) * 4 <= (ranked ? kWPool - kWRankBytes : kWPool);
+  }
+  __syncthreads();
+  return fits;
+}
+
+// Step 2: the join table, a slice of the range at a time.
+__device__ __forceinline__ void w_build(const BWhole& a, const BInst& I, WShared& s) {
+  const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+  const int32_t m = (int32_t)I.m;
+  const uint32_t range = w_uni(s.p.range), kmin = (uint32_t)w_uni(s.p.kmin);
+  const int32_t amin = w_uni(s.p.amin);
+  const bool in_lds = w_uni(s.p.in_lds) != 0, ranked = w_uni(s.p.ranked) != 0;
+  const WBits bits{w_uni(s.p.lb)};
+  const WRanks ranks = s.ranks();
+  uint32_t* const lds_table = reinterpret_cast<uint32_t*>(s.bytes() + (in_lds ? w_uni(s.p.front) : 0u));
+  uint32_t* const mem_table = reinterpret_cast<uint32_t*>(I.jslots);
+  const uint32_t slice = in_lds ? range : (uint32_t)((ranked ? kWPool - kWRankBytes : kWPool) / 4) << (5 - bits.lb);
+  uint32_t entries = 0;
+  // (a range below 2^32 and slices of at most 2^21 entries: `lo` may pass the range's end once, so it has 64 bits)
+  for (uint64_t lo = 0; lo < range; lo += slice) {
+    const uint32_t len = (uint32_t)min((uint64_t)slice, range - lo), words = bits.words(len);
+    for (uint32_t i = t; i < words; i += kWBlock) lds_table[i] = 0;
+    __syncthreads();
+    for (int32_t b = 0; b < m; b += kWTile) {
+      int32_t key[kWRows], at[kWRows];
+#pragma unroll
+      for (int k = 0; k < kWRows; ++k) {
+        const int32_t j = min(b + (int32_t)t + k * kWBlock, m - 1);
+        key[k] = I.pk[j];
+        at[k] = w_attr(I, j);
+      }
+#pragma unroll
+      for (int k = 0; k < kWRows; ++k) {
+        const uint32_t off = (uint32_t)key[k] - kmin - (uint32_t)lo;
+        if (b + (int32_t)t + k * kWBlock < m && off < len) {
+          const uint32_t v = (uint32_t)at[k] - (uint32_t)amin;
+          atomicOr(&lds_table[bits.word(off)], ((ranked ? ranks.of(v) : v) + 1u) << bits.shift(off));
+        }
+      }
+    }
+    __syncthreads();
+    for (uint32_t i = t; i < words; i += kWBlock) {
+      const uint32_t w = lds_table[i];
+      entries += bits.used(w);
+      if (!in_lds) mem_table[bits.word((uint32_t)lo) + i] = w;
+    }
+    if (!in_lds) __syncthreads();
+  }
+  const uint64_t all = wave_sum_u64(entries);
+  if (lane == 0) s.red[2][wave] = all;
+  const uint32_t groups = w_uni(s.p.groups);
+  if (w_uni(s.p.chunks) <= 1) s.sums(groups).clear(groups);
+  for (uint32_t c = t; c <= (uint32_t)kWMaxChunks; c += kWBlock) s.cnt[c] = 0;
+  __syncthreads();
+  if (t == 0) {
+    uint64_t e = 0;
+    for (int w = 0; w < kWBlock / kWave; ++w) e += s.red[2][w];
+    if (e != (uint64_t)m) set_status(a.status, kDevDupKey);
+  }
+}
+
+// One thread's rows of a tile, all loads in flight together.
+struct WRows {
+  int32_t d[kWRows], f[kWRows], q[kWRows];
+  int64_t p[kWRows];
+  uint32_t fl[kWRows];
+};
+__device__ __forceinline__ void w_load(const BInst& I, int32_t base, int32_t n, bool by_flag, WRows& r) {
+  const int32_t* const day = I.day + base;
+  const int32_t* const fk = I.fk + base;
+  const int32_t* const qty = I.qty + base;
+  const long long* const price = (const long long*)I.price + base;
+#pragma unroll
+  for (int k = 0; k < kWRows; ++k) {
+    const uint32_t i = threadIdx.x + k * kWBlock;
+    const bool ok = (int32_t)i < n - base;
+    r.d[k] = INT32_MAX;  // (a row past the end fails any day < day_lt)
+    if (ok) {
+      r.d[k] = ld_once(day + i);
+      r.f[k] = ld_once(fk + i);
+      r.q[k] = ld_once(qty + i);
+      r.p[k] = ld_once(price + i);
+    }
+  }
+  if (by_flag) {
+    const int8_t* const flag = I.flag + base;
+#pragma unroll
+    for (int k = 0; k < kWRows; ++k) {
+      const uint32_t i = threadIdx.x + k * kWBlock;
+      r.fl[k] = (int32_t)i < n - base ? (uint32_t)(uint8_t)flag[i] : 0u;
+    }
+  }
+}
+
+// The workgroup's spill memory.
+struct WSpill {
+  uint64_t* gq;   // group in its chunk, quantity << 32
+  int64_t* price;
+  uint32_t* off;  // [tiles][kWMaxChunks + 1]
+  __device__ __forceinline__ explicit WSpill(const BWhole& a)
+      : gq(a.spill + (size_t)blockIdx.x * 2 * (size_t)a.spill_rows),
+        price(reinterpret_cast<int64_t*>(gq + a.spill_rows)),
+        off(a.spill_off + (size_t)blockIdx.x * (size_t)((a.spill_rows + kWTile - 1) / kWTile) * (kWMaxChunks + 1)) {}
+};
+
+// Step 3: the fact rows, into the sums (kSpill: sorted by chunk into the spill memory).
+template <bool kSpill>
+__device__ __forceinline__ void w_rows(const BWhole& a, const BInst& I, WShared& s) {
+  const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+  const int32_t n = (int32_t)I.n, day_lt = I.day_lt;
+  const bool by_fk = I.group_by == REL_GROUP_FK, by_flag = I.group_by == REL_GROUP_PRIO_FLAG;
+  const uint32_t range = w_uni(s.p.range), kmin = (uint32_t)w_uni(s.p.kmin);
+  const bool in_lds = w_uni(s.p.in_lds) != 0;
+  const WBits bits{w_uni(s.p.lb)};
+  const uint32_t* const lds_table = reinterpret_cast<const uint32_t*>(s.bytes() + (in_lds ? w_uni(s.p.front) : 0u));
+  const uint32_t* const mem_table = reinterpret_cast<const uint32_t*>(I.jslots);
+  const WSums sums = s.sums(w_uni(s.p.groups));
+  const WSpill spill(a);
+  uint32_t passed = 0, matched = 0, spilled = 0;
+  WRows cur, nxt;
+  if (n > 0) w_load(I, 0, n, by_flag, cur);
+  // (fewer than 2^31 rows: `base` passes the end by less than a tile)
+  for (uint32_t base = 0; base < (uint32_t)n; base += kWTile) {
+    if (base + kWTile < (uint32_t)n) w_load(I, (int32_t)(base + kWTile), n, by_flag, nxt);
+    uint32_t e[kWRows], g[kWRows];
+#pragma unroll
+    for (int k = 0; k < kWRows; ++k) {
+      const bool pass = cur.d[k] < day_lt && base + t + k * kWBlock < (uint32_t)n;
+      passed += pass;
+      g[k] = (uint32_t)cur.f[k] - kmin;  // (a key below the smallest wraps to past the range)
+      e[k] = 0;
+      if (pass && g[k] < range) e[k] = in_lds ? lds_table[bits.word(g[k])] : mem_table[bits.word(g[k])];
+    }
+#pragma unroll
+    for (int k = 0; k < kWRows; ++k) {
+      e[k] = bits.get(e[k], g[k]);
+      matched += e[k] != 0;
+      if (!by_fk) g[k] = by_flag ? (e[k] - 1u) * 256u + cur.fl[k] : e[k] - 1u;
+    }
+    if constexpr (!kSpill) {
+#pragma unroll
+      for (int k = 0; k < kWRows; ++k)
+        if (e[k] != 0) sums.add(g[k], cur.p[k], cur.q[k]);
+    } else {
+      // the tile's joined rows, sorted by chunk
+      uint32_t rank[kWRows];
+#pragma unroll
+      for (int k = 0; k < kWRows; ++k) rank[k] = e[k] != 0 ? atomicAdd(&s.cnt[g[k] / kWCap], 1u) : 0u;
+      __syncthreads();
+      const uint32_t c = t < (uint32_t)kWMaxChunks ? s.cnt[t] : 0u;
+      uint32_t total;
+      const uint32_t first = block_excl_scan<kWBlock>(c, s.scr, &total);
+      uint32_t* const off = spill.off + (size_t)(base / kWTile) * (kWMaxChunks + 1);
+      if (t < (uint32_t)kWMaxChunks) {
+        s.cnt[t] = first;
+        off[t] = spilled + first;
+      }
+      if (t == 0) off[kWMaxChunks] = spilled + total;
+      __syncthreads();
+      uint64_t* const sort_gq = s.pool;
+      int64_t* const sort_p = reinterpret_cast<int64_t*>(s.pool) + kWTile;
+#pragma unroll
+      for (int k = 0; k < kWRows; ++k)
+        if (e[k] != 0) {
+          const uint32_t at = s.cnt[g[k] / kWCap] + rank[k];
+          sort_gq[at] = (uint64_t)(g[k] % kWCap) | (uint64_t)(uint32_t)cur.q[k] << 32;
+          sort_p[at] = cur.p[k];
+        }
+      __syncthreads();
+      for (uint32_t i = t; i < total; i += kWBlock) {
+        spill.gq[spilled + i] = sort_gq[i];
+        spill.price[spilled + i] = sort_p[i];
+      }
+      if (t < (uint32_t)kWMaxChunks) s.cnt[t] = 0;
+      spilled += total;
+      __syncthreads();
+    }
+    cur = nxt;
+  }
+  const uint64_t p = wave_sum_u64(passed), q = wave_sum_u64(matched);
+  if (lane == 0) {
+    s.red[0][wave] = p;
+    s.red[1][wave] = q;
+  }
+  __syncthreads();
+}
+
+// Step 4: the groups, to the output. Returns their number.
+__device__ __forceinline__ int64_t w_groups(const BWhole& a, const BInst& I, WShared& s) {
+  const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+  const uint32_t groups = w_uni(s.p.groups), chunks = w_uni(s.p.chunks);
+  // (keys: dim.grp, fk, or prio * 256 + flag, all counted from their smallest)
+  const int64_t key0 = I.group_by == REL_GROUP_FK          ? (int64_t)w_uni(s.p.kmin)
+                       : I.group_by == REL_GROUP_PRIO_FLAG ? (int64_t)w_uni(s.p.amin) * 256
+                                                           : (int64_t)w_uni(s.p.amin);
+  int64_t out = 0;
+  if (chunks <= 1) {
+    w_emit(I, s.sums(groups), groups, key0, w_uni(s.p.ranked) != 0 ? s.ranks().attr : nullptr, s.scr, &out, a.status);
+    return out;
+  }
+  const WSpill spill(a);
+  const uint32_t tiles = ((uint32_t)I.n + kWTile - 1) / kWTile;
+  for (uint32_t c = 0; c < chunks; ++c) {
+    const uint32_t here = min((uint32_t)kWCap, groups - c * kWCap);
+    const WSums sums = s.sums(here);
+    sums.clear(here);
+    __syncthreads();
+    // a wave takes the chunk's run of every 16th tile
+    for (uint32_t tile = wave; tile < tiles; tile += kWBlock / kWave) {
+      const uint32_t lo = spill.off[(size_t)tile * (kWMaxChunks + 1) + c], hi = spill.off[(size_t)tile * (kWMaxChunks + 1) + c + 1];
+      for (uint32_t i0 = lo + lane; i0 - lane < hi; i0 += kWave * kWRows) {
+        uint64_t gq[kWRows];
+        int64_t p[kWRows];
+#pragma unroll
+        for (int k = 0; k < kWRows; ++k) {
+          const uint32_t i = min(i0 + k * kWave, hi - 1);
+          gq[k] = spill.gq[i];
+          p[k] = spill.price[i];
+        }
+#pragma unroll
+        for (int k = 0; k < kWRows; ++k)
+          if (i0 + k * kWave < hi) sums.add((uint32_t)gq[k], p[k], (int32_t)(uint32_t)(gq[k] >> 32));
+      }
+    }
+    __syncthreads();
+    w_emit(I, sums, here, key0 + (int64_t)c * kWCap, nullptr, s.scr, &out, a.status);
+    __syncthreads();
+  }
+  return out;
+}
+
+__global__ __launch_bounds__(kWBlock) void k_batch_whole(BWhole a) {
+  __shared__ WShared s;
+  const uint32_t t = threadIdx.x;
+  // (at most n + 1 tickets per workgroup, whatever the ticket holds)
+  for (int32_t turn = 0; turn <= a.n; ++turn) {
+    if (t == 0) s.item = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)a.ticket, 1ull);
+    __syncthreads();
+    const int64_t item = s.item;
+    if (item < 0 || item >= a.n) break;
+    const int32_t inst = w_uni(a.order[item]);  // (the same on every lane: scalar loads)
+    const BInst& I = a.inst[inst];
+    if (!w_plan(a, I, s)) {
+      if (t == 0) dev_add<uint32_t>(a.left, 1u);
+      __syncthreads();
+      continue;
+    }
+    w_build(a, I, s);
+    if (w_uni(s.p.chunks) <= 1) w_rows<false>(a, I, s);
+    else w_rows<true>(a, I, s);
+    const int64_t out = w_groups(a, I, s);
+    if (t == 0) {
+      uint64_t p = 0, q = 0;
+      for (int w = 0; w < kWBlock / kWave; ++w) {
+        p += s.red[0][w];
+        q += s.red[1][w];
+      }
+      I.stats[0] = (int64_t)p;
+      I.stats[1] = (int64_t)q;
+      I.stats[2] = out;
+      *I.d_n = out;
+      a.done[inst] = 1u;
+      if (out > (int64_t)I.gmask + 2) set_status(a.status, kDevOverflow);  // more groups than the table sized for them has slots
+    }
+    __syncthreads();
+  }
 }
 
 const rel_batch_tuning kDefaultTuning[] = {
@@ -314,8 +873,8 @@ bool tuning_ok(const rel_batch_tuning& t) {
 
 struct BucketPlan {
   rel_batch_tuning t;
-  int64_t build_lo = 0, build_n = 0;  // item ranges inside the item arrays
-  int64_t probe_lo = 0, probe_n = 0;
+  int64_t build_lo = 0, probe_lo = 0;  // where the item lists begin
+  BList build{}, probe{};
 };
 
 struct rel_batch {
@@ -329,11 +888,13 @@ struct rel_batch {
   int64_t* d_stats = nullptr;
   uint32_t* d_status = nullptr;  // this batch's status word, cleared at the start of every run
   uint64_t* d_join = nullptr;
-  size_t join_words = 0;
   GroupSlot* d_groups = nullptr;
-  size_t group_slots = 0;
-  int64_t fin_lo = 0, fin_n = 0;
-  size_t zero_words = 0;  // tickets + stats + status word
+  int64_t fin_lo = 0;
+  BList fin{};
+  size_t zero_words = 0;  // tickets + stats + status word + whole-instance words
+  BWhole whole{};         // the instances that one workgroup takes each
+  unsigned whole_grid = 0;
+  void* spill = nullptr;
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -342,41 +903,41 @@ struct rel_batch {
 namespace {
 
 template <int BLOCK, bool LJ>
-void launch_probe(hipStream_t s, unsigned grid, int ipt, const BInst* inst, const BItem* items, int64_t n,
-                  int64_t* ticket, uint32_t* status) {
+void launch_probe(hipStream_t s, unsigned grid, int ipt, const BInst* inst, const BItem* items,
+                  int64_t* ticket, uint32_t* status, BList list) {
   switch (ipt) {
-    case 1: hipLaunchKernelGGL((k_batch_probe<BLOCK, 1, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, n, ticket, status); break;
-    case 2: hipLaunchKernelGGL((k_batch_probe<BLOCK, 2, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, n, ticket, status); break;
-    case 4: hipLaunchKernelGGL((k_batch_probe<BLOCK, 4, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, n, ticket, status); break;
-    default: hipLaunchKernelGGL((k_batch_probe<BLOCK, 8, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, n, ticket, status); break;
+    case 1: hipLaunchKernelGGL((k_batch_probe<BLOCK, 1, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, ticket, status, list); break;
+    case 2: hipLaunchKernelGGL((k_batch_probe<BLOCK, 2, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, ticket, status, list); break;
+    case 4: hipLaunchKernelGGL((k_batch_probe<BLOCK, 4, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, ticket, status, list); break;
+    default: hipLaunchKernelGGL((k_batch_probe<BLOCK, 8, LJ>), dim3(grid), dim3(BLOCK), 0, s, inst, items, ticket, status, list); break;
   }
 }
 
-void launch_build(hipStream_t s, unsigned grid, int block, const BInst* inst, const BItem* items, int64_t n,
-                  int64_t* ticket, uint32_t* status) {
+void launch_build(hipStream_t s, unsigned grid, int block, const BInst* inst, const BItem* items,
+                  int64_t* ticket, uint32_t* status, BList list) {
   switch (block) {
-    case 64: hipLaunchKernelGGL(k_batch_build<64>, dim3(grid), dim3(64), 0, s, inst, items, n, ticket, status); break;
-    case 128: hipLaunchKernelGGL(k_batch_build<128>, dim3(grid), dim3(128), 0, s, inst, items, n, ticket, status); break;
-    case 256: hipLaunchKernelGGL(k_batch_build<256>, dim3(grid), dim3(256), 0, s, inst, items, n, ticket, status); break;
-    default: hipLaunchKernelGGL(k_batch_build<512>, dim3(grid), dim3(512), 0, s, inst, items, n, ticket, status); break;
+    case 64: hipLaunchKernelGGL(k_batch_build<64>, dim3(grid), dim3(64), 0, s, inst, items, ticket, status, list); break;
+    case 128: hipLaunchKernelGGL(k_batch_build<128>, dim3(grid), dim3(128), 0, s, inst, items, ticket, status, list); break;
+    case 256: hipLaunchKernelGGL(k_batch_build<256>, dim3(grid), dim3(256), 0, s, inst, items, ticket, status, list); break;
+    default: hipLaunchKernelGGL(k_batch_build<512>, dim3(grid), dim3(512), 0, s, inst, items, ticket, status, list); break;
   }
 }
 
 template <bool LJ>
 void launch_probe_blk(hipStream_t s, unsigned grid, int block, int ipt, const BInst* inst, const BItem* items,
-                      int64_t n, int64_t* ticket, uint32_t* status) {
+                      int64_t* ticket, uint32_t* status, BList list) {
   switch (block) {
-    case 64: launch_probe<64, LJ>(s, grid, ipt, inst, items, n, ticket, status); break;
-    case 128: launch_probe<128, LJ>(s, grid, ipt, inst, items, n, ticket, status); break;
-    case 256: launch_probe<256, LJ>(s, grid, ipt, inst, items, n, ticket, status); break;
-    default: launch_probe<512, LJ>(s, grid, ipt, inst, items, n, ticket, status); break;
+    case 64: launch_probe<64, LJ>(s, grid, ipt, inst, items, ticket, status, list); break;
+    case 128: launch_probe<128, LJ>(s, grid, ipt, inst, items, ticket, status, list); break;
+    case 256: launch_probe<256, LJ>(s, grid, ipt, inst, items, ticket, status, list); break;
+    default: launch_probe<512, LJ>(s, grid, ipt, inst, items, ticket, status, list); break;
   }
 }
 
 void launch_probe_any(hipStream_t s, unsigned grid, int block, int ipt, bool lj, const BInst* inst,
-                      const BItem* items, int64_t n, int64_t* ticket, uint32_t* status) {
-  if (lj) launch_probe_blk<true>(s, grid, block, ipt, inst, items, n, ticket, status);
-  else launch_probe_blk<false>(s, grid, block, ipt, inst, items, n, ticket, status);
+                      const BItem* items, int64_t* ticket, uint32_t* status, BList list) {
+  if (lj) launch_probe_blk<true>(s, grid, block, ipt, inst, items, ticket, status, list);
+  else launch_probe_blk<false>(s, grid, block, ipt, inst, items, ticket, status, list);
 }
 
 // Workgroups for a persistent kernel: enough to fill the chip, never more than the items.
@@ -387,12 +948,52 @@ unsigned persistent_grid(const rel_ctx* ctx, int64_t items, int block) {
   return (unsigned)(g < 1 ? 1 : g);
 }
 
+// Items that there should be for each CU: with the tuning's rows per item (up to
+// 65536, found on batches of thousands) a batch of 8 instances of up to 1M rows
+// kept 20 workgroups busy and took 606 us; with items of an even share 230 us.
+constexpr int64_t kItemsPerCu = 4;
+
+// How many of a batch's instances, largest first (`rows`: their fact rows), go
+// the shared-table way, so that the estimated times of both ways, which follow
+// one another, add up to the least. A workgroup takes 1.7 ns per row of an
+// instance of its own and 10 us besides, while all CUs have one; the shared
+// tables take 35 ps per row over the whole chip and 60 us besides. Measured,
+// all instances by the shared tables / all whole / as chosen, in us:
+//   8 of up to 32K rows         88 /   81 /   81
+//   8 of up to 1M              230 /  890 /  232
+//   128 of up to 32K           175 /  113 /  113
+//   128 of up to 250K          461 /  483 /  460
+//   128 of up to 1M           1346 / 1877 / 1349
+//   512 of up to 250K         1179 /  612 /  611
+//   512 of up to 1M           3480 / 2515 / 2521
+//   2048 of up to 1M         10251 / 3004 / 3003
+constexpr double kWholeNs = 10000, kWholeRowNs = 1.7, kSharedNs = 60000, kSharedRowNs = 0.035;
+int32_t whole_from(const std::vector<int64_t>& rows, int cus) {
+  const int32_t k = (int32_t)rows.size();
+  double after = 0, before = 0, best = 0;
+  for (int64_t n : rows) after += kWholeNs + kWholeRowNs * (double)n;
+  int32_t at = 0;
+  for (int32_t c = 0; c <= k; ++c) {
+    const double whole = c < k ? std::max(kWholeNs + kWholeRowNs * (double)rows[c], after / cus) : 0;
+    const double t = whole + (c > 0 ? kSharedNs + kSharedRowNs * before : 0);
+    if (c == 0 || t < best) {
+      best = t;
+      at = c;
+    }
+    if (c == k) break;
+    after -= kWholeNs + kWholeRowNs * (double)rows[c];
+    before += (double)rows[c];
+  }
+  return at;
+}
+
 void free_batch(rel_batch* b) {
   if (!b) return;
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   if (b->mem) (void)hipFree(b->mem);
+  if (b->spill) (void)hipFree(b->spill);
   delete b;
 }
 
@@ -436,11 +1037,42 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
     return (int)tun.size() - 1;
   };
 
+  // largest instance first; from `order[n_shared]` on they are taken whole
+  std::vector<int32_t> order(k);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return items[x].fact.n > items[y].fact.n; });
+  std::vector<int64_t> sorted_rows(k);
+  for (int32_t i = 0; i < k; ++i) sorted_rows[i] = items[order[i]].fact.n;
+  const int32_t n_shared = whole_from(sorted_rows, ctx->num_cus), n_whole = k - n_shared;
+  b->whole_grid = (unsigned)std::min<int32_t>(n_whole, ctx->num_cus);
+  int64_t shared_rows = 0, spill_rows = 0;
+  for (int32_t p = 0; p < k; ++p) {
+    const rel_batch_item& it = items[order[p]];
+    if (p < n_shared) {
+      shared_rows += it.fact.n;
+      continue;
+    }
+    const int64_t groups = it.q.group_by == REL_GROUP_FK         ? 2 * it.dim.m
+                           : it.q.group_by == REL_GROUP_PRIO_FLAG ? 0
+                           : it.group_capacity > 0                ? it.group_capacity
+                                                                  : it.dim.m;
+    if (groups > kWCap) spill_rows = std::max<int64_t>(spill_rows, it.fact.n);
+  }
+  const size_t spill_tiles = (size_t)((spill_rows + kWTile - 1) / kWTile);
+  const size_t spill_bytes = (size_t)b->whole_grid * ((size_t)spill_rows * 16 + spill_tiles * (kWMaxChunks + 1) * 4);
+  if (spill_rows > 0 && (spill_bytes > kWMaxSpill || hipMalloc(&b->spill, spill_bytes) != hipSuccess)) {
+    (void)hipGetLastError();
+    b->spill = nullptr;
+    spill_rows = 0;  // instances with more groups than one chunk go the other way
+  }
+
   // table sizes and offsets
   std::vector<BInst> hinst(k);
   std::vector<size_t> joff(k), goff(k);
   size_t jw = 0, gs = 0;
-  for (int32_t i = 0; i < k; ++i) {
+  size_t jw_shared = 0, gs_shared = 0;
+  for (int32_t p = 0; p < k; ++p) {
+    const int32_t i = order[p];
     const rel_batch_item& it = items[i];
     const int64_t n = it.fact.n, m = it.dim.m;
     const uint32_t jl = relh::join_log2cap(m, nullptr);
@@ -480,47 +1112,53 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
     jw += (1ull << jl) + 1;
     goff[i] = gs;
     gs += (1ull << gl) + 1;
+    if (p < n_shared) {
+      jw_shared = jw;
+      gs_shared = gs;
+    }
   }
 
-  // work items, largest instance first inside each bucket
-  std::vector<int32_t> order(k);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return items[x].fact.n > items[y].fact.n; });
+  // work items, largest instance first inside each bucket; fewer rows per item
+  // where the tuning's would leave workgroups without one
   std::vector<BItem> hitems;
+  // bucket t's instances (t < 0: all), `count` elements each, in items of `step`
+  auto add_items = [&](int t, auto&& count, auto&& step) {
+    BList l{};
+    for (int32_t p = 0; p < k; ++p) {
+      const int32_t i = order[p];
+      if (t >= 0 && bucket_of(items[i].fact.n) != t) continue;
+      const int64_t n = count(i), rows = step(p);
+      for (int64_t lo = 0; lo < n; lo += rows) hitems.push_back(BItem{i, 0, lo, std::min(n, lo + rows)});
+      l.all += (n + rows - 1) / rows;
+      if (p < n_shared) l.n = l.all;
+    }
+    return l;
+  };
   b->buckets.resize(tun.size());
   for (size_t t = 0; t < tun.size(); ++t) {
     BucketPlan& bp = b->buckets[t];
     bp.t = tun[t];
+    const int64_t unit = (int64_t)tun[t].block * tun[t].items_per_thread, even = shared_rows / (ctx->num_cus * kItemsPerCu);
+    const int64_t few = std::min<int64_t>(std::max<int64_t>(even / unit, 1) * unit, tun[t].rows_per_item);
+    auto rows = [&](int32_t p) { return p < n_shared ? few : (int64_t)tun[t].rows_per_item; };
     bp.build_lo = (int64_t)hitems.size();
-    for (int32_t i : order) {
-      if (bucket_of(items[i].fact.n) != (int)t) continue;
-      const int64_t m = items[i].dim.m, step = std::max<int64_t>(tun[t].rows_per_item / 4, 256);
-      for (int64_t lo = 0; lo < m; lo += step) hitems.push_back(BItem{i, 0, lo, std::min(m, lo + step)});
-    }
-    bp.build_n = (int64_t)hitems.size() - bp.build_lo;
+    bp.build = add_items((int)t, [&](int32_t i) { return items[i].dim.m; }, [&](int32_t p) { return std::max<int64_t>(rows(p) / 4, 256); });
     bp.probe_lo = (int64_t)hitems.size();
-    for (int32_t i : order) {
-      if (bucket_of(items[i].fact.n) != (int)t) continue;
-      const int64_t n = items[i].fact.n, step = tun[t].rows_per_item;
-      for (int64_t lo = 0; lo < n; lo += step) hitems.push_back(BItem{i, 0, lo, std::min(n, lo + step)});
-    }
-    bp.probe_n = (int64_t)hitems.size() - bp.probe_lo;
+    bp.probe = add_items((int)t, [&](int32_t i) { return items[i].fact.n; }, rows);
   }
   b->fin_lo = (int64_t)hitems.size();
-  for (int32_t i : order) {
-    const int64_t ns = (int64_t)(hinst[i].gmask) + 2;
-    for (int64_t lo = 0; lo < ns; lo += kFinItemSlots) hitems.push_back(BItem{i, 0, lo, std::min(ns, lo + kFinItemSlots)});
-  }
-  b->fin_n = (int64_t)hitems.size() - b->fin_lo;
+  b->fin = add_items(-1, [&](int32_t i) { return (int64_t)hinst[i].gmask + 2; }, [](int32_t) { return kFinItemSlots; });
 
   // one device allocation: instances, items, tickets + stats, join tables, group tables
-  const size_t n_tickets = 2 * tun.size() + 1;
+  const size_t n_tickets = 2 * tun.size() + 2;
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t o_inst = 0;
-  const size_t o_items = al(o_inst + sizeof(BInst) * (size_t)std::max(k, 1));
+  const size_t o_order = al(o_inst + sizeof(BInst) * (size_t)std::max(k, 1));
+  const size_t o_items = al(o_order + sizeof(int32_t) * (size_t)std::max(n_whole, 1));
   const size_t o_zero = al(o_items + sizeof(BItem) * std::max<size_t>(hitems.size(), 1));
-  // tickets, per-instance stats, and the batch's own status word (all cleared at the start of every run)
-  b->zero_words = n_tickets + 3 * (size_t)k + 1;
+  // tickets, per-instance stats, the batch's own status word, the number of
+  // instances left and the finished ones' marks (all cleared at the start of every run)
+  b->zero_words = n_tickets + 3 * (size_t)k + 2 + ((size_t)k + 1) / 2;
   const size_t o_join = al(o_zero + 8 * b->zero_words);
   const size_t o_groups = al(o_join + 8 * jw);
   const size_t total = al(o_groups + sizeof(GroupSlot) * gs);
@@ -537,9 +1175,7 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
   b->d_stats = b->d_tickets + n_tickets;
   b->d_status = (uint32_t*)(b->d_stats + 3 * (size_t)k);
   b->d_join = (uint64_t*)(base + o_join);
-  b->join_words = jw;
   b->d_groups = (GroupSlot*)(base + o_groups);
-  b->group_slots = gs;
   for (int32_t i = 0; i < k; ++i) {
     hinst[i].jslots = b->d_join + joff[i];
     hinst[i].gslots = b->d_groups + goff[i];
@@ -550,6 +1186,12 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
     if (x != hipSuccess && st == REL_OK) st = relh::hip_fail(ctx, x, what);
   };
   if (k > 0) hip(hipMemcpy(b->d_inst, hinst.data(), sizeof(BInst) * k, hipMemcpyHostToDevice), "copy instances");
+  b->whole = BWhole{b->d_inst, (const int32_t*)(base + o_order), n_whole, b->d_tickets + n_tickets - 1, b->d_status,
+                    (uint32_t*)(b->d_stats + 3 * (size_t)k + 2), (uint32_t*)(b->d_stats + 3 * (size_t)k + 1),
+                    (uint64_t*)b->spill, (uint32_t*)((char*)b->spill + (size_t)b->whole_grid * (size_t)spill_rows * 16), spill_rows};
+  auto list = [&](int64_t shared, int64_t all) { return BList{shared, all, b->whole.left, b->whole.done}; };
+  if (n_whole > 0)
+    hip(hipMemcpy((void*)b->whole.order, order.data() + n_shared, sizeof(int32_t) * n_whole, hipMemcpyHostToDevice), "copy order");
   if (!hitems.empty()) hip(hipMemcpy(b->d_items, hitems.data(), sizeof(BItem) * hitems.size(), hipMemcpyHostToDevice), "copy items");
   hip(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking), "capture stream");
   if (st != REL_OK) {
@@ -562,26 +1204,28 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
   if (st == REL_OK) {
     hipStream_t s = b->cap;
     const unsigned fg = (unsigned)ctx->num_cus * 4;
-    hipLaunchKernelGGL(k_batch_fill, dim3(fg), dim3(256), 0, s, (uint64_t*)b->d_tickets, (int64_t)b->zero_words, 0ull);
-    if (jw) hipLaunchKernelGGL(k_batch_fill, dim3(fg), dim3(256), 0, s, b->d_join, (int64_t)jw, kJoinEmpty);
-    if (gs) hipLaunchKernelGGL(k_batch_init_groups, dim3(fg), dim3(256), 0, s, b->d_groups, (int64_t)gs);
+    hipLaunchKernelGGL(k_batch_fill, dim3(fg), dim3(256), 0, s, (uint64_t*)b->d_tickets, 0ull,
+                       list((int64_t)b->zero_words, (int64_t)b->zero_words));
     if (k) hipLaunchKernelGGL(k_batch_zero_outputs, dim3((k + 255) / 256), dim3(256), 0, s, (const BInst*)b->d_inst, k);
+    if (b->whole_grid) hipLaunchKernelGGL(k_batch_whole, dim3(b->whole_grid), dim3(kWBlock), 0, s, b->whole);
+    if (jw) hipLaunchKernelGGL(k_batch_fill, dim3(fg), dim3(256), 0, s, b->d_join, kJoinEmpty, list((int64_t)jw_shared, (int64_t)jw));
+    if (gs) hipLaunchKernelGGL(k_batch_init_groups, dim3(fg), dim3(256), 0, s, b->d_groups, list((int64_t)gs_shared, (int64_t)gs));
     for (size_t t = 0; t < b->buckets.size(); ++t) {
       const BucketPlan& bp = b->buckets[t];
-      if (bp.build_n)
-        launch_build(s, persistent_grid(ctx, bp.build_n, bp.t.block), bp.t.block, b->d_inst, b->d_items + bp.build_lo,
-                     bp.build_n, b->d_tickets + 2 * t, b->d_status);
+      if (bp.build.all)
+        launch_build(s, persistent_grid(ctx, bp.build.all, bp.t.block), bp.t.block, b->d_inst, b->d_items + bp.build_lo,
+                     b->d_tickets + 2 * t, b->d_status, list(bp.build.n, bp.build.all));
     }
     for (size_t t = 0; t < b->buckets.size(); ++t) {
       const BucketPlan& bp = b->buckets[t];
-      if (bp.probe_n)
-        launch_probe_any(s, persistent_grid(ctx, bp.probe_n, bp.t.block), bp.t.block, bp.t.items_per_thread,
-                         bp.t.lds_join_max > 0, b->d_inst, b->d_items + bp.probe_lo, bp.probe_n,
-                         b->d_tickets + 2 * t + 1, b->d_status);
+      if (bp.probe.all)
+        launch_probe_any(s, persistent_grid(ctx, bp.probe.all, bp.t.block), bp.t.block, bp.t.items_per_thread,
+                         bp.t.lds_join_max > 0, b->d_inst, b->d_items + bp.probe_lo, b->d_tickets + 2 * t + 1, b->d_status,
+                         list(bp.probe.n, bp.probe.all));
     }
-    if (b->fin_n)
-      hipLaunchKernelGGL(k_batch_finalize, dim3(persistent_grid(ctx, b->fin_n, 256)), dim3(256), 0, s, b->d_inst,
-                         b->d_items + b->fin_lo, b->fin_n, b->d_tickets + 2 * tun.size(), b->d_status);
+    if (b->fin.all)
+      hipLaunchKernelGGL(k_batch_finalize, dim3(persistent_grid(ctx, b->fin.all, 256)), dim3(256), 0, s, b->d_inst,
+                         b->d_items + b->fin_lo, b->d_tickets + 2 * tun.size(), b->d_status, list(b->fin.n, b->fin.all));
     hip(hipGetLastError(), "batch kernels");
     hipGraph_t g = nullptr;
     hipError_t ee = hipStreamEndCapture(s, &g);
