@@ -4,7 +4,7 @@
 // Updating a table in device memory costs three or four atomics per row, and
 // those run at about 27 G/s for the whole chip: 20M rows into 2M groups took
 // 2.7 ms. Partitioning reads and writes every row once more, but in runs, and
-// then all updates are LDS operations: GROUPBY_FIGURES.
+// then all updates are LDS operations: 0.43 ms (6M rows of 15 groups: 147 -> 41 us).
 //
 //   k_gb_hist     rows per (tile, bin), one tile per workgroup
 //   k_gb_colsum   those summed over chunks of tiles, per bin

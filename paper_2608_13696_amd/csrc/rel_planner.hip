@@ -25,51 +25,113 @@ constexpr int kParams = kB3 + kOut;
 static_assert(kParams == REL_MLP_PARAMS, "parameter layout");
 constexpr int kMaxSample = 256;
 
+// The sketch reads every key of both columns once (300 MB at 60M fact and 15M dim
+// rows, 59 us at the rate of a copy); the hash's 64-bit products cost as much
+// again where they do not overlap with the loads, since 32-bit multiplies run at
+// a quarter of the rate and a 64-bit product is three of them. So only the hash's
+// high word is computed, where it decides the row, and the first product's part
+// of the constant high word is picked, not multiplied: five multiplies per key.
+// One launch for both columns takes 80 us, two with the whole hash took 109;
+// without the lookups of the registers in LDS it would be 65, but a hot key
+// passes any common threshold (88).
+constexpr uint64_t kHllAdd = 0x9E3779B97F4A7C15ull, kHllMul1 = 0xBF58476D1CE4E5B9ull, kHllMul2 = 0x94D049BB133111EBull;
+
 __device__ __forceinline__ uint64_t hll_hash(int32_t v) {
-  uint64_t z = (uint64_t)(uint32_t)v + 0x9E3779B97F4A7C15ull;
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  uint64_t z = (uint64_t)(uint32_t)v + kHllAdd;
+  z = (z ^ (z >> 30)) * kHllMul1;
+  z = (z ^ (z >> 27)) * kHllMul2;
   return z ^ (z >> 31);
 }
 
-__device__ __forceinline__ void hll_add(uint32_t* regs, int32_t v) {
-  const uint64_t h = hll_hash(v);
-  const uint32_t idx = (uint32_t)(h >> 58);
-  const uint64_t w = h << 6;
-  const uint32_t rho = w ? (uint32_t)__clzll((long long)w) + 1u : 59u;
-  if (rho > regs[idx]) atomicMax(&regs[idx], rho);  // the read skips most atomics once registers settle
+// The high word of hll_hash(v).
+__device__ __forceinline__ uint32_t hll_hash_high(int32_t v) {
+  constexpr uint32_t kHi0 = (uint32_t)(kHllAdd >> 32), kHi1 = kHi0 + 1;  // the sum's high word, without and with a carry
+  constexpr uint32_t kX0 = kHi0 ^ (kHi0 >> 30), kX1 = kHi1 ^ (kHi1 >> 30);
+  const uint32_t lo = (uint32_t)v + (uint32_t)kHllAdd;
+  const bool carry = lo < (uint32_t)kHllAdd;
+  const uint32_t x = lo ^ __builtin_amdgcn_alignbit(carry ? kHi1 : kHi0, lo, 30);
+  const uint64_t p0 = (uint64_t)x * (uint32_t)kHllMul1;
+  const uint32_t pl = (uint32_t)p0;
+  const uint32_t ph = (uint32_t)(p0 >> 32) + x * (uint32_t)(kHllMul1 >> 32) + (carry ? kX1 * (uint32_t)kHllMul1 : kX0 * (uint32_t)kHllMul1);
+  const uint32_t yl = pl ^ __builtin_amdgcn_alignbit(ph, pl, 27), yh = ph ^ (ph >> 27);
+  const uint32_t q = __umulhi(yl, (uint32_t)kHllMul2) + yl * (uint32_t)(kHllMul2 >> 32) + yh * (uint32_t)kHllMul2;
+  return q ^ (q >> 31);
 }
 
-// Registers of one column over all rows; regs (device, 64 words) must start at zero.
-__global__ __launch_bounds__(256) void k_hll(const int32_t* __restrict__ keys, int64_t n, uint32_t* __restrict__ regs) {
+__device__ __forceinline__ void hll_add(uint32_t* regs, int32_t v) {
+  const uint64_t h = hll_hash(v), w = h << 6;
+  atomicMax(&regs[h >> 58], w ? (uint32_t)__clzll((long long)w) + 1u : 59u);
+}
+
+// Four keys. Reading the registers first skips most atomics once they settle; a
+// row past the hash's high word (27 and more) always takes the long way.
+__device__ __forceinline__ void hll_add4(uint32_t* regs, int4 v) {
+  const int32_t k[4] = {v.x, v.y, v.z, v.w};
+  bool more = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t h = hll_hash_high(k[i]);
+    more = more || (uint32_t)__clz((int)(h << 6 | 32u)) >= min(regs[h >> 26], 26u);
+  }
+  if (more) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) hll_add(regs, k[i]);
+  }
+}
+
+constexpr int kHllLoads = 2;  // 16-byte loads in flight per thread
+
+constexpr int kHllBlock = 1024;  // two workgroups per CU: few registers to settle
+constexpr int kHllCopies = 16;   // of the device's registers: atomics on one line take turns
+
+// Registers of two columns over all rows, each with its share of the
+// workgroups; regs (device, kHllCopies x 2 x 64 words) must start at zero.
+
+__global__ __launch_bounds__(kHllBlock) void k_hll(const int32_t* __restrict__ keys0, int64_t n0, uint32_t grid0,
+                                             const int32_t* __restrict__ keys1, int64_t n1, uint32_t* __restrict__ regs) {
   __shared__ uint32_t r[64];
   if (threadIdx.x < 64) r[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t n4 = n / 4;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n4; i += stride) {
-    const int4 v = reinterpret_cast<const int4*>(keys)[i];
-    hll_add(r, v.x);
-    hll_add(r, v.y);
-    hll_add(r, v.z);
-    hll_add(r, v.w);
+  const bool second = blockIdx.x >= grid0;
+  const int32_t* const keys = second ? keys1 : keys0;
+  const int64_t n = second ? n1 : n0, n4 = n / 4;
+  const int64_t at = (second ? blockIdx.x - grid0 : blockIdx.x) * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t stride = (int64_t)(second ? gridDim.x - grid0 : grid0) * blockDim.x;
+  const int4* const k4 = reinterpret_cast<const int4*>(keys);
+  uint32_t* const mine = regs + blockIdx.x % kHllCopies * 128 + (second ? 64 : 0);
+  // A register that has seen few keys is raised often. The first keys of all
+  // workgroups are therefore shared (n4 is the same for all of a column's).
+  if (n4 > stride) {
+    if (at < n4) hll_add4(r, k4[at]);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      uint32_t best = r[threadIdx.x];
+      __hip_atomic_fetch_max(&mine[threadIdx.x], best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int c = 0; c < kHllCopies; ++c)
+        best = max(best, __hip_atomic_load(&regs[c * 128 + (second ? 64 : 0) + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      r[threadIdx.x] = best;
+    }
+    __syncthreads();
   }
-  for (int64_t i = 4 * n4 + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += stride) hll_add(r, keys[i]);
+  const int64_t start = at + (n4 > stride ? stride : 0);
+  int4 v[kHllLoads], next[kHllLoads];
+  auto load = [&](int64_t i, int4 (&to)[kHllLoads]) {  // (a key twice changes nothing)
+#pragma unroll
+    for (int k = 0; k < kHllLoads; ++k) to[k] = k4[min(i + k * stride, n4 - 1)];
+  };
+  if (start < n4) load(start, v);
+  for (int64_t i = start; i < n4; i += stride * kHllLoads) {
+    if (i + stride * kHllLoads < n4) load(i + stride * kHllLoads, next);
+#pragma unroll
+    for (int k = 0; k < kHllLoads; ++k) hll_add4(r, v[k]);
+#pragma unroll
+    for (int k = 0; k < kHllLoads; ++k) v[k] = next[k];
+  }
+  for (int64_t i = 4 * n4 + at; i < n; i += stride) hll_add(r, keys[i]);
   __syncthreads();
-  if (threadIdx.x < 64 && r[threadIdx.x]) __hip_atomic_fetch_max(&regs[threadIdx.x], r[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ double hll_estimate(const uint32_t* regs, int* zeros_out) {
-  double z = 0.0;
-  int zeros = 0;
-  for (int r = 0; r < 64; ++r) {
-    z += ldexp(1.0, -(int)regs[r]);
-    zeros += regs[r] == 0;
-  }
-  double e = 0.709 * 64.0 * 64.0 / z;
-  if (e <= 2.5 * 64.0 && zeros > 0) e = 64.0 * log(64.0 / (double)zeros);
-  *zeros_out = zeros;
-  return e;
+  if (threadIdx.x < 64 && r[threadIdx.x])
+    __hip_atomic_fetch_max(&mine[threadIdx.x], r[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 struct SketchArgs {
@@ -82,73 +144,109 @@ struct SketchArgs {
   const int64_t* fsample;
   const int64_t* dsample;
   int32_t k;
-  const uint32_t* regs;  // 128: fk then grp
+  const uint32_t* regs;  // kHllCopies x (fk, then grp)
   float* features;
   uint8_t* hll_out;
 };
 
-// Deterministic tree sum over the 256 threads of the block.
-__device__ double block_sum_d(double v, double* buf) {
-  buf[threadIdx.x] = v;
+// One workgroup computes the features, so its chain of dependent steps is all
+// that counts: sums and extremes go over LDS only across the waves and by
+// shuffles inside one, counts of conditions are ballots, several values share
+// one pass over LDS, the registers' sums take a wave, a register per lane, and
+// the logarithms a lane each: 17 us, where thread 0 and trees of barriers took 40.
+
+// Sums over the 256 threads, always in the same order (thread t's with t + 128's,
+// then t + 64's, ... t + 1's). Every thread calls it and gets the sums.
+template <int N>
+__device__ void block_sum_d(double (&v)[N], double (*buf)[256]) {
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < N; ++i) buf[i][t] = v[i];
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) buf[threadIdx.x] += buf[threadIdx.x + s];
-    __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int l = t & 63;
+    double x = (buf[i][l] + buf[i][l + 128]) + (buf[i][l + 64] + buf[i][l + 192]);
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) x += __shfl_down(x, s, kWave);
+    v[i] = __shfl(x, 0, kWave);
   }
-  const double r = buf[0];
   __syncthreads();
-  return r;
 }
 
-// Per sampled value: its count among the k samples, whether it is the first
-// occurrence, then distinct / singleton / doubleton counts and the maximum.
-struct FreqStats {
-  double distinct, singles, doubles, maxfreq;
-};
-
-__device__ FreqStats freq_stats(const int32_t* vals, int k, double* dbuf) {
-  int c = 0;
-  bool first = true;
-  const int t = threadIdx.x;
-  if (t < k) {
-    const int32_t v = vals[t];
-    for (int j = 0; j < k; ++j) {
-      c += vals[j] == v;
-      first = first && !(j < t && vals[j] == v);
-    }
+// Threads of the 256 for which each of N conditions holds.
+template <int N>
+__device__ void block_counts(const bool (&c)[N], int (&n)[N], int (*buf)[4]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const uint64_t b = __ballot(c[i]);
+    if ((threadIdx.x & 63) == 0) buf[i][threadIdx.x / kWave] = __popcll(b);
   }
-  const bool in = t < k;
-  FreqStats f;
-  f.distinct = block_sum_d(in && first ? 1.0 : 0.0, dbuf);
-  f.singles = block_sum_d(in && c == 1 ? 1.0 : 0.0, dbuf);
-  f.doubles = block_sum_d(in && first && c == 2 ? 1.0 : 0.0, dbuf);
-  // maximum through the same tree with max
-  dbuf[t] = in ? (double)c : 0.0;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) dbuf[t] = fmax(dbuf[t], dbuf[t + s]);
-    __syncthreads();
-  }
-  f.maxfreq = dbuf[0];
+#pragma unroll
+  for (int i = 0; i < N; ++i) n[i] = buf[i][0] + buf[i][1] + buf[i][2] + buf[i][3];
   __syncthreads();
-  return f;
 }
 
-__device__ void block_minmax(const int32_t* vals, int k, int32_t* mn, int32_t* mx, int32_t* buf_lo, int32_t* buf_hi) {
-  const int t = threadIdx.x;
-  buf_lo[t] = t < k ? vals[t] : INT32_MAX;
-  buf_hi[t] = t < k ? vals[t] : INT32_MIN;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) {
-      buf_lo[t] = min(buf_lo[t], buf_lo[t + s]);
-      buf_hi[t] = max(buf_hi[t], buf_hi[t + s]);
-    }
-    __syncthreads();
+// Maxima of N values over the 256 threads (a minimum is the maximum of ~v).
+template <int N>
+__device__ void block_max(int32_t (&v)[N], int (*buf)[4]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v[i] = max(v[i], __shfl_xor(v[i], s, kWave));
+    if ((threadIdx.x & 63) == 0) buf[i][threadIdx.x / kWave] = v[i];
   }
-  *mn = buf_lo[0];
-  *mx = buf_hi[0];
   __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = max(max(buf[i][0], buf[i][1]), max(buf[i][2], buf[i][3]));
+  __syncthreads();
+}
+
+// How often a thread's sample occurs among the k, and whether it is the first
+// of them. vals[j] is the same word for all lanes; from k on the array holds
+// zeros, which are taken off again. Two instructions per comparison, and two
+// more for the samples of the thread's own wave, where it matters which come
+// before it.
+__device__ __forceinline__ void sample_freq(const int32_t* vals, int k, int* count, bool* first) {
+  const int t = threadIdx.x, wave = t / kWave, lane = t % kWave;
+  const int32_t v = vals[t];
+  const int4* const v4 = reinterpret_cast<const int4*>(vals);
+  int c = 0, before = 0;
+  for (int w = 0; w < kMaxSample / kWave; ++w) {
+    if (w == wave) before += c;
+#pragma unroll
+    for (int j = 0; j < kWave / 4; ++j) {
+      const int4 x = v4[w * (kWave / 4) + j];
+      c += (x.x == v) + (x.y == v) + (x.z == v) + (x.w == v);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kWave / 4; ++j) {
+    const int4 x = v4[wave * (kWave / 4) + j];
+    before += (x.x == v && 4 * j < lane) + (x.y == v && 4 * j + 1 < lane) + (x.z == v && 4 * j + 2 < lane) + (x.w == v && 4 * j + 3 < lane);
+  }
+  *count = c - (v == 0 ? kMaxSample - k : 0);
+  *first = before == 0;
+}
+
+// A column's 64 registers, one per lane: estimate, zero registers, sum, largest.
+__device__ double hll_estimate(uint32_t reg, int* zeros, double* sum, uint32_t* most) {
+  double z = ldexp(1.0, -(int)reg), t = (double)reg;
+  uint32_t mx = reg;
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+    z += __shfl_xor(z, s, kWave);
+    t += __shfl_xor(t, s, kWave);
+    mx = max(mx, (uint32_t)__shfl_xor((int)mx, s, kWave));
+  }
+  const int zr = __popcll(__ballot(reg == 0));
+  double e = 0.709 * 64.0 * 64.0 / z;
+  if (e <= 2.5 * 64.0 && zr > 0) e = 64.0 * log(64.0 / (double)zr);
+  *zeros = zr;
+  *sum = t;
+  *most = mx;
+  return e;
 }
 
 // The 40 features (one workgroup of 256 threads, k <= 256 samples):
@@ -163,96 +261,103 @@ __device__ void block_minmax(const int32_t* vals, int k, int32_t* mn, int32_t* m
 //  37..38 HLL(grp): log2(1 + estimate), zero registers / 64
 //  39 Pearson correlation of sampled (day, fk), 0 when degenerate
 __global__ __launch_bounds__(256) void k_sketch_features(SketchArgs a) {
-  __shared__ int32_t s_fk[kMaxSample], s_day[kMaxSample], s_pk[kMaxSample], s_grp[kMaxSample];
-  __shared__ double dbuf[256];
-  __shared__ int32_t ibuf_lo[256], ibuf_hi[256];
+  static_assert(kMaxSample == 256, "a sample per thread");
+  __shared__ alignas(16) int32_t s_fk[kMaxSample], s_grp[kMaxSample];
+  __shared__ double dbuf[3][256];
+  __shared__ int ibuf[8][4];
+  __shared__ int hist[16];
   __shared__ double f[kFeat];
   const int t = threadIdx.x, k = a.k;
   const double kk = (double)k;
+  const bool in = t < k, hn = a.n > 0, hm = a.m > 0, hg = hm && a.grp != nullptr;
+  uint32_t reg = 0;
+#pragma unroll
+  for (int c = 0; c < kHllCopies; ++c) reg = max(reg, a.regs[c * 128 + (t & 127)]);
+  const int64_t fs = in && hn ? a.fsample[t] : 0, ds = in && hm ? a.dsample[t] : 0;
+  const int32_t fk = in && hn ? a.fk[fs] : 0, day = in && hn ? a.day[fs] : 0;
+  const int32_t pk = in && hm ? a.pk[ds] : 0, grp = in && hg ? a.grp[ds] : 0;
+  s_fk[t] = fk;
+  s_grp[t] = grp;
   if (t < kFeat) f[t] = 0.0;
-  if (t < k) {
-    const bool hn = a.n > 0, hm = a.m > 0;
-    const int64_t fs = hn ? a.fsample[t] : 0, ds = hm ? a.dsample[t] : 0;
-    s_fk[t] = hn ? a.fk[fs] : 0;
-    s_day[t] = hn ? a.day[fs] : 0;
-    s_pk[t] = hm ? a.pk[ds] : 0;
-    s_grp[t] = (hm && a.grp) ? a.grp[ds] : 0;
-  }
+  if (t < 16) hist[t] = 0;
+  if (t < 128) a.hll_out[t] = (uint8_t)reg;
   __syncthreads();
-  if (t == 0) {
-    f[0] = log2(1.0 + (double)a.n);
-    f[1] = log2(1.0 + (double)a.m);
-    f[2] = log2((1.0 + (double)a.n) / (1.0 + (double)a.m));
+  // every thread takes part in all of these, also where a side has no rows
+  int32_t ext[6] = {in ? fk : INT32_MIN, in ? ~fk : INT32_MIN, in ? pk : INT32_MIN, in ? ~pk : INT32_MIN,
+                    in ? grp : INT32_MIN, in ? ~grp : INT32_MIN};
+  int fc, gc;
+  bool ffirst, gfirst;
+  sample_freq(s_fk, k, &fc, &ffirst);
+  sample_freq(s_grp, k, &gc, &gfirst);
+  block_max(ext, ibuf);
+  const int32_t fmax = ext[0], fmin = ~ext[1], pmax = ext[2], pmin = ~ext[3], gmax = ext[4], gmin = ~ext[5];
+  int32_t freq[1] = {in ? fc : 0};
+  block_max(freq, ibuf);
+  int cnt[7];  // rows passed, keys inside; distinct, single and double keys; distinct and single groups
+  const bool cond[7] = {in && day < a.day_lt, in && fk >= pmin && fk <= pmax, in && ffirst, in && fc == 1,
+                        in && ffirst && fc == 2, in && gfirst, in && gc == 1};
+  block_counts(cond, cnt, ibuf);
+  double mean[2] = {in ? (double)day : 0.0, in ? (double)fk : 0.0};
+  block_sum_d(mean, dbuf);
+  const double da = in ? (double)day - mean[0] / kk : 0.0, db = in ? (double)fk - mean[1] / kk : 0.0;
+  double mom[3] = {da * da, db * db, da * db};
+  block_sum_d(mom, dbuf);
+  if (t < kWave) {  // the fk registers
+    int zeros;
+    double sum;
+    uint32_t mx;
+    const double e = hll_estimate(reg, &zeros, &sum, &mx);
+    atomicAdd(&hist[min(reg, 15u)], 1);
+    if (t == 0) {
+      f[17] = log2(1.0 + e);
+      f[18] = zeros / 64.0;
+      f[19] = sum / 64.0 / 16.0;
+      f[20] = mx / 64.0;
+    }
+  } else if (t < 2 * kWave) {  // the grp registers
+    int zeros;
+    double sum;
+    uint32_t mx;
+    const double e = hll_estimate(reg, &zeros, &sum, &mx);
+    if (t == kWave && a.grp != nullptr) {
+      f[37] = log2(1.0 + e);
+      f[38] = zeros / 64.0;
+    }
+  } else if (t < 3 * kWave) {  // the logarithms, one per lane
+    const int l = t - 2 * kWave;
+    const double n1 = 1.0 + (double)a.n, m1 = 1.0 + (double)a.m;
+    const double x = l == 0   ? n1
+                     : l == 1 ? m1
+                     : l == 2 ? n1 / m1
+                     : l == 3 ? (hn ? 1.0 + ((double)fmax - (double)fmin) : 1.0)
+                     : l == 4 ? (hn && hm ? 1.0 + ((double)pmax - (double)pmin) : 1.0)
+                     : l == 5 ? (hg ? 1.0 + ((double)gmax - (double)gmin) : 1.0)
+                              : 1.0;
+    const double y = log2(x);
+    const int at = l < 3 ? l : l == 3 ? 12 : l == 4 ? 13 : 16;
+    if (l < 6) f[at] = y;
+  } else if (t == 3 * kWave) {
     f[4] = a.group_by == REL_GROUP_FK;
     f[5] = a.group_by == REL_GROUP_DIM_GRP;
     f[6] = a.group_by == REL_GROUP_PRIO_FLAG;
-  }
-  __syncthreads();
-  if (a.n > 0) {  // uniform branch
-    const double pass = block_sum_d(t < k && s_day[t] < a.day_lt ? 1.0 : 0.0, dbuf);
-    const FreqStats fs = freq_stats(s_fk, k, dbuf);
-    int32_t fmin, fmax;
-    block_minmax(s_fk, k, &fmin, &fmax, ibuf_lo, ibuf_hi);
-    double inside = 0.0, prange = 0.0;
-    if (a.m > 0) {
-      int32_t pmin, pmax;
-      block_minmax(s_pk, k, &pmin, &pmax, ibuf_lo, ibuf_hi);
-      inside = block_sum_d(t < k && s_fk[t] >= pmin && s_fk[t] <= pmax ? 1.0 : 0.0, dbuf);
-      prange = (double)pmax - (double)pmin;
+    if (hn) {
+      f[3] = cnt[0] / kk;
+      f[7] = cnt[2] / kk;
+      f[8] = cnt[3] / kk;
+      f[9] = cnt[4] / kk;
+      f[10] = freq[0] / kk;
+      if (hm) f[11] = cnt[1] / kk;
+      f[39] = (mom[0] > 0 && mom[1] > 0) ? mom[2] / sqrt(mom[0] * mom[1]) : 0.0;
     }
-    const double md = block_sum_d(t < k ? (double)s_day[t] : 0.0, dbuf) / kk;
-    const double mf = block_sum_d(t < k ? (double)s_fk[t] : 0.0, dbuf) / kk;
-    const double a_ = t < k ? (double)s_day[t] - md : 0.0, b_ = t < k ? (double)s_fk[t] - mf : 0.0;
-    const double sdd = block_sum_d(a_ * a_, dbuf), sff = block_sum_d(b_ * b_, dbuf), sdf = block_sum_d(a_ * b_, dbuf);
-    if (t == 0) {
-      f[3] = pass / kk;
-      f[7] = fs.distinct / kk;
-      f[8] = fs.singles / kk;
-      f[9] = fs.doubles / kk;
-      f[10] = fs.maxfreq / kk;
-      f[12] = log2(1.0 + ((double)fmax - (double)fmin));
-      if (a.m > 0) {
-        f[11] = inside / kk;
-        f[13] = log2(1.0 + prange);
-      }
-      f[39] = (sdd > 0 && sff > 0) ? sdf / sqrt(sdd * sff) : 0.0;
-    }
-  }
-  if (a.grp != nullptr && a.m > 0) {
-    const FreqStats gs = freq_stats(s_grp, k, dbuf);
-    int32_t gmin, gmax;
-    block_minmax(s_grp, k, &gmin, &gmax, ibuf_lo, ibuf_hi);
-    if (t == 0) {
-      f[14] = gs.distinct / kk;
-      f[15] = gs.singles / kk;
-      f[16] = log2(1.0 + ((double)gmax - (double)gmin));
+    if (hg) {
+      f[14] = cnt[5] / kk;
+      f[15] = cnt[6] / kk;
     }
   }
   __syncthreads();
-  if (t == 0) {
-    int zeros;
-    const double e = hll_estimate(a.regs, &zeros);
-    uint32_t mx = 0;
-    double sum = 0;
-    for (int r = 0; r < 64; ++r) {
-      mx = max(mx, a.regs[r]);
-      sum += a.regs[r];
-      f[21 + min(a.regs[r], 15u)] += 1.0 / 64.0;
-    }
-    f[17] = log2(1.0 + e);
-    f[18] = zeros / 64.0;
-    f[19] = sum / 64.0 / 16.0;
-    f[20] = mx / 64.0;
-    if (a.grp != nullptr) {
-      int gz;
-      const double ge = hll_estimate(a.regs + 64, &gz);
-      f[37] = log2(1.0 + ge);
-      f[38] = gz / 64.0;
-    }
-  }
+  if (t < 16) f[21 + t] = hist[t] / 64.0;
   __syncthreads();
   if (t < kFeat) a.features[t] = (float)f[t];
-  if (t < 128) a.hll_out[t] = (uint8_t)a.regs[t];
 }
 
 // ---- MLP ----------------------------------------------------------------------------------------------------------------
@@ -596,16 +701,15 @@ rel_status rel_sketch(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim, co
   if ((fact->fk && !relh::aligned16(fact->fk)) || (dim->grp && !relh::aligned16(dim->grp)))
     return relh::fail(ctx, REL_INVALID_ARG, "rel_sketch: column not 16-byte aligned");
   void* regs;
-  TRY(relh::scratch(ctx, SCR_SKETCH, 128 * sizeof(uint32_t), &regs));
-  TRY(relh::fill_u32(ctx, regs, 128, 0));
+  TRY(relh::scratch(ctx, SCR_SKETCH, kHllCopies * 128 * sizeof(uint32_t), &regs));
+  TRY(relh::fill_u32(ctx, regs, kHllCopies * 128, 0));
   {
     relh::KernelTimer kt(ctx, "sketch_hll");
-    if (fact->n > 0)
-      hipLaunchKernelGGL(k_hll, dim3(relh::grid_for(ctx, fact->n / 4 + 1, 256 * 8, 4)), dim3(256), 0, ctx->stream,
-                         fact->fk, fact->n, (uint32_t*)regs);
-    if (dim->grp && dim->m > 0)
-      hipLaunchKernelGGL(k_hll, dim3(relh::grid_for(ctx, dim->m / 4 + 1, 256 * 8, 4)), dim3(256), 0, ctx->stream,
-                         dim->grp, dim->m, (uint32_t*)regs + 64);
+    const int64_t gm = dim->grp ? dim->m : 0;
+    auto grid = [&](int64_t rows) { return rows > 0 ? (unsigned)relh::grid_for(ctx, rows / 4 + 1, kHllBlock * kHllLoads, 2) : 0u; };
+    const unsigned g0 = grid(fact->n), g1 = grid(gm);
+    if (g0 + g1 > 0)
+      hipLaunchKernelGGL(k_hll, dim3(g0 + g1), dim3(kHllBlock), 0, ctx->stream, fact->fk, fact->n, g0, dim->grp, gm, (uint32_t*)regs);
   }
   SketchArgs a{};
   a.fk = fact->fk;
