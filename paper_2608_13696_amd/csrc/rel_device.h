@@ -540,6 +540,13 @@ __device__ __forceinline__ void group_add_wave(const GroupView& t, bool active, 
   if (active) group_add(t, key, sp, sq, 1ull);
 }
 
+// The bins of a group-by that partitions its rows: the key folded to 32 bits;
+// the bin and the LDS slot are taken from different products of it.
+__device__ __forceinline__ uint32_t group_fold(int64_t key) {
+  return (uint32_t)key ^ ((uint32_t)((uint64_t)key >> 32) * 0x85EBCA6Bu);
+}
+__device__ __forceinline__ uint32_t group_bin(int64_t key, uint32_t shift) { return (group_fold(key) * 2654435769u) >> shift; }
+
 // group_add_wave for partial aggregates: each active lane adds (sp, sq, cnt).
 __device__ __forceinline__ void group_add_wave_n(const GroupView& t, bool active, int64_t key, uint64_t sp, uint64_t sq,
                                                  uint64_t cnt) {

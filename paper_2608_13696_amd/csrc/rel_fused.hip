@@ -935,6 +935,9 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   uint32_t gl = 0;
   void* gt = nullptr;
   size_t clean_after = 0;
+  bool eager = false, by_partials = false;
+  relh::Partials partials{};
+  int64_t partials_expected = 0;
   if (gb == REL_GROUP_FK) {
     gp = G_ROWAGG;  // group key == join key: per-dim-row accumulators
     group_cap = m;
@@ -964,12 +967,31 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     if (gl > 31) return relh::fail(ctx, REL_UNSUPPORTED, "rel_filter_join_agg: group table above 2^31 slots");
     group_cap = 1ll << gl;
     const size_t gbytes = (size_t)(group_cap + 1) * sizeof(GroupSlot);
-    if (part) {
+    eager = part && gb == REL_GROUP_DIM_GRP && (gp != G_LDS || a.lds_probe != kLdsProbe);
+    // The partial sums of a planned call are partitioned by group and summed in
+    // LDS; the device table takes three atomics for each. Measured, device table
+    // against partitioned partials, uniform keys, half of the rows selected: 250K
+    // rows 142 and 123 us, 4M 261 and 188, 16M 738 and 403, 60M with 1000 groups
+    // 5080 and 1357, with 15M groups 3462 and 2134 (1% of the rows selected: 138
+    // and 144, 262 and 255, 718 and 644, 1296 and 666). A call without a plan
+    // would gain as much (60M rows, 1M groups: 1.86 ms to 1.19), but keeps the
+    // table: a planned run pays 0.15 ms for its sketch and its read by the host
+    // (1.34 ms), and is held to be no slower than the plain one. Without memory
+    // for the partials the table serves, too.
+    if (eager && planned) {
+      int64_t rows;
+      unsigned wgs;
+      size_t bytes;
+      relh::partials_bounds(ctx, n, m, &rows, &wgs, &bytes);
+      by_partials = relh::partials_take(ctx, rows, wgs, expected, bytes, (uint32_t*)(cnt + CNT_AUX2), &partials) == REL_OK;
+      partials_expected = expected;
+    }
+    if (part && !by_partials) {
       TRY(relh::scratch(ctx, SCR_GROUP_TABLE, gbytes, &gt));
       TRY(init_groups(ctx, (GroupSlot*)gt, group_cap + 1));
     } else {
-      // the plain path's table is emptied again by the kernel that reads it,
-      // so only its first use (or a larger one) clears it
+      // this table is emptied again by the kernel that reads it, so only its
+      // first use (or a larger one) clears it
       TRY(relh::scratch(ctx, SCR_GROUP_CLEAN, gbytes, &gt));
       ScratchBuf& sb = ctx->scratch[SCR_GROUP_CLEAN];
       clean_after = sb.clean > gbytes ? sb.clean : gbytes;
@@ -985,10 +1007,19 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     // none); grouping by dim.grp with more groups than LDS holds aggregates per
     // dim key first
     TRY(relh::fill_u64(ctx, cnt, CNT_AUX2 + 1, 0));
-    const bool eager = gb == REL_GROUP_DIM_GRP && (gp != G_LDS || a.lds_probe != kLdsProbe);
     TRY(relh::partitioned_join_agg(ctx, fact, dim, q->day_lt, gb, gt, gl, a.groups.max_probe,
-                                   gp == G_LDS ? a.lds_probe : 0, eager, cnt));
-    TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, false}, group_cap + 1, out_args(ctx, out)));
+                                   gp == G_LDS ? a.lds_probe : 0, eager, by_partials ? &partials : nullptr, cnt));
+    OutArgs oa = out_args(ctx, out);
+    if (by_partials) {
+      uint32_t* flags = (uint32_t*)(cnt + CNT_AUX1);  // [0] touched, [1] stays 0
+      const relh::DirectOut direct{out->key, out->sum_price, out->sum_qty, out->count, out->cap, (uint64_t*)(cnt + CNT_GROUPS), flags};
+      TRY(relh::partials_reduce(ctx, partials, partials_expected, flags + 1, a.groups, direct));
+      oa.base = direct.n_direct;
+      oa.touched = flags;
+      oa.limit = planned ? group_cap + 1 : INT64_MAX;
+    }
+    TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, by_partials}, group_cap + 1, oa));
+    if (by_partials) ctx->scratch[SCR_GROUP_CLEAN].clean = clean_after;
     return sync_stats(ctx, fact, dim, q, plan, out, stats, cnt, m, group_cap, REL_PLACE_PARTITIONED,
                       gp == G_LDS ? REL_PLACE_LDS : REL_PLACE_GLOBAL);
   }

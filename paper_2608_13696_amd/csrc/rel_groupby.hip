@@ -13,9 +13,15 @@
 //   k_gb_scatter  a tile's rows sorted by bin in LDS and written as runs
 //   k_gb_agg      per unit an LDS table; its groups go straight to the output
 //
+// The partitioned join's partial sums by group (rel_ops.h, Partials) take the
+// same way: their kernel counts them per (chunk, bin) itself, a chunk is a tile.
+//
 // A key that finds no room in a unit's LDS table, and every group of a bin that
 // was cut into pieces (hot keys), goes to the group table in device memory,
 // which the caller's finalize kernel appends to the output.
+#include <algorithm>
+#include <type_traits>
+
 #include "rel_device.h"
 #include "rel_host.h"
 #include "rel_ops.h"
@@ -33,18 +39,14 @@ constexpr int kGbChunks = 32;
 constexpr int kGbSubRows = 32768;  // a bin with more rows is cut into pieces of this many
 constexpr int kGbProbe = 64;       // LDS probe walk before a row goes to device memory
 
-// The key folded to 32 bits; the bin and the LDS slot are taken from different products of it.
-__device__ __forceinline__ uint32_t fold(int64_t key) {
-  return (uint32_t)key ^ ((uint32_t)((uint64_t)key >> 32) * 0x85EBCA6Bu);
-}
-__device__ __forceinline__ uint32_t bin_of(int64_t key, uint32_t shift) { return (fold(key) * 2654435769u) >> shift; }
-
 // Every kernel returns at once when the sample found few groups (`few`, see k_gb_begin).
 struct GbArgs {
   GroupRows in;
   const uint32_t* few;
   uint32_t nb, shift;  // bins, 32 - log2(bins)
   int64_t ntiles;
+  const uint32_t* more_tiles;  // with partials: beside ntiles (null: none)
+  relh::Partials part;
   uint32_t* hist;      // [ntiles][nb], then offsets
   uint32_t* chunk;     // [kGbChunks][nb]
   uint32_t* start;     // [nb]
@@ -53,6 +55,8 @@ struct GbArgs {
   int64_t* key;        // the rows by bin
   int64_t* price;
   int32_t* qty;
+  relh::PartialCols bin;  // the partials by bin
+  __device__ __forceinline__ int64_t tiles() const { return more_tiles ? ntiles + *more_tiles : ntiles; }
 };
 
 __device__ __forceinline__ int64_t row_of(const GroupRows& in, int64_t i) { return in.sel ? (int64_t)ld_once(in.sel + i) : i; }
@@ -86,7 +90,7 @@ __global__ __launch_bounds__(kGbBlock) void k_gb_hist(GbArgs a) {
   for (int k = 0; k < kGbRows; ++k) key[k] = row[k] >= 0 ? ld_once((const long long*)a.in.key + row[k]) : 0;
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kGbRows; ++k) (void)bin_rank(cnt, bin_of(key[k], a.shift), row[k] >= 0);
+  for (int k = 0; k < kGbRows; ++k) (void)bin_rank(cnt, group_bin(key[k], a.shift), row[k] >= 0);
   __syncthreads();
   for (uint32_t b = t; b < a.nb; b += kGbBlock) a.hist[tile * a.nb + b] = cnt[b];
 }
@@ -95,9 +99,9 @@ __global__ __launch_bounds__(kGbBlock) void k_gb_hist(GbArgs a) {
 constexpr int kColBins = 64, kColWaves = 4;
 
 __device__ __forceinline__ void chunk_tiles(const GbArgs& a, int64_t* lo, int64_t* hi) {
-  const int64_t per = (a.ntiles + kGbChunks - 1) / kGbChunks;
-  *lo = min(a.ntiles, (int64_t)blockIdx.y * per);
-  *hi = min(a.ntiles, *lo + per);
+  const int64_t ntiles = a.tiles(), per = (ntiles + kGbChunks - 1) / kGbChunks;
+  *lo = min(ntiles, (int64_t)blockIdx.y * per);
+  *hi = min(ntiles, *lo + per);
 }
 
 __global__ __launch_bounds__(kColBins * kColWaves) void k_gb_colsum(GbArgs a) {
@@ -175,29 +179,58 @@ __global__ __launch_bounds__(kGbBlock) void k_gb_units(GbArgs a) {
   if (threadIdx.x == 0) *a.n_units = n_units;
 }
 
+// One row of the sorted tile: a fact row, or (P) a partial.
+template <bool P>
+struct GbRow {
+  using Key = std::conditional_t<P, int32_t, int64_t>;
+  using Qty = std::conditional_t<P, uint64_t, int32_t>;
+  static constexpr int kRows = P ? relh::kPartialTile / kGbBlock : kGbRows;
+  Key key[kRows * kGbBlock];
+  int64_t price[kRows * kGbBlock];
+  Qty qty[kRows * kGbBlock];
+  uint32_t count[P ? kRows * kGbBlock : 1];
+};
+
+template <bool P>
 __global__ __launch_bounds__(kGbBlock) void k_gb_scatter(GbArgs a) {
   __shared__ uint32_t cnt[kGbMaxBins];    // rows per bin, then the bin's first LDS row
   __shared__ uint32_t delta[kGbMaxBins];  // output position minus LDS row (mod 2^32)
-  __shared__ int64_t s_key[kGbTile];
-  __shared__ int64_t s_price[kGbTile];
-  __shared__ int32_t s_qty[kGbTile];
+  __shared__ GbRow<P> lds;
   __shared__ uint32_t scr[kGbBlock / kWave];
+  constexpr int kRows = GbRow<P>::kRows;
   if (*a.few) return;
+  const int64_t ntiles = P ? a.tiles() : (int64_t)gridDim.x;
+  if (blockIdx.x >= ntiles) return;
   const uint32_t t = threadIdx.x;
   constexpr int kPer = kGbMaxBins / kGbBlock;
 #pragma unroll
   for (int k = 0; k < kPer; ++k) cnt[t + k * kGbBlock] = 0;
-  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x), i0 = tile * kGbTile + t;
-  int64_t row[kGbRows], key[kGbRows], price[kGbRows];
-  int32_t qty[kGbRows];
+  const int64_t tile = xcd_tile(blockIdx.x, (uint32_t)ntiles), i0 = tile * (kRows * kGbBlock) + t;
+  int64_t row[kRows], price[kRows];
+  typename GbRow<P>::Key key[kRows];
+  typename GbRow<P>::Qty qty[kRows];
+  uint32_t count[P ? kRows : 1];
+  if constexpr (P) {
+    const int64_t end = tile * (kRows * kGbBlock) + a.part.fill[tile];
 #pragma unroll
-  for (int k = 0; k < kGbRows; ++k) row[k] = i0 + k * kGbBlock < a.in.n ? row_of(a.in, i0 + k * kGbBlock) : -1;
+    for (int k = 0; k < kRows; ++k) {
+      row[k] = i0 + k * kGbBlock < end ? i0 + k * kGbBlock : -1;
+      const int64_t r = row[k] >= 0 ? row[k] : tile * (kRows * kGbBlock);
+      key[k] = ld_once(a.part.cols.key + r);
+      price[k] = ld_once((const long long*)a.part.cols.price + r);
+      qty[k] = (uint64_t)ld_once((const long long*)a.part.cols.qty + r);
+      count[k] = (uint32_t)ld_once((const int32_t*)a.part.cols.count + r);
+    }
+  } else {
 #pragma unroll
-  for (int k = 0; k < kGbRows; ++k) {
-    const int64_t r = row[k] >= 0 ? row[k] : 0;
-    key[k] = ld_once((const long long*)a.in.key + r);
-    price[k] = ld_once((const long long*)a.in.price + r);
-    qty[k] = ld_once(a.in.qty + r);
+    for (int k = 0; k < kRows; ++k) row[k] = i0 + k * kGbBlock < a.in.n ? row_of(a.in, i0 + k * kGbBlock) : -1;
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+      const int64_t r = row[k] >= 0 ? row[k] : 0;
+      key[k] = ld_once((const long long*)a.in.key + r);
+      price[k] = ld_once((const long long*)a.in.price + r);
+      qty[k] = ld_once(a.in.qty + r);
+    }
   }
   uint32_t at[kPer];  // where this tile's run of the thread's bins starts
 #pragma unroll
@@ -206,9 +239,9 @@ __global__ __launch_bounds__(kGbBlock) void k_gb_scatter(GbArgs a) {
     at[k] = b < a.nb ? a.start[b] + a.hist[tile * a.nb + b] : 0u;
   }
   __syncthreads();
-  uint32_t rank[kGbRows];
+  uint32_t rank[kRows];
 #pragma unroll
-  for (int k = 0; k < kGbRows; ++k) rank[k] = bin_rank(cnt, bin_of(key[k], a.shift), row[k] >= 0);
+  for (int k = 0; k < kRows; ++k) rank[k] = bin_rank(cnt, group_bin(key[k], a.shift), row[k] >= 0);
   __syncthreads();
   uint32_t c[kPer], sum = 0, total;
 #pragma unroll
@@ -225,20 +258,28 @@ __global__ __launch_bounds__(kGbBlock) void k_gb_scatter(GbArgs a) {
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kGbRows; ++k)
+  for (int k = 0; k < kRows; ++k)
     if (row[k] >= 0) {
-      const uint32_t slot = cnt[bin_of(key[k], a.shift)] + rank[k];
-      s_key[slot] = key[k];
-      s_price[slot] = price[k];
-      s_qty[slot] = qty[k];
+      const uint32_t slot = cnt[group_bin(key[k], a.shift)] + rank[k];
+      lds.key[slot] = key[k];
+      lds.price[slot] = price[k];
+      lds.qty[slot] = qty[k];
+      if constexpr (P) lds.count[slot] = count[k];
     }
   __syncthreads();
   for (uint32_t j = t; j < total; j += kGbBlock) {
-    const int64_t kv = s_key[j];
-    const uint32_t pos = delta[bin_of(kv, a.shift)] + j;
-    a.key[pos] = kv;
-    a.price[pos] = s_price[j];
-    a.qty[pos] = s_qty[j];
+    const typename GbRow<P>::Key kv = lds.key[j];
+    const uint32_t pos = delta[group_bin(kv, a.shift)] + j;
+    if constexpr (P) {
+      a.bin.key[pos] = kv;
+      a.bin.price[pos] = (uint64_t)lds.price[j];
+      a.bin.qty[pos] = lds.qty[j];
+      a.bin.count[pos] = lds.count[j];
+    } else {
+      a.key[pos] = kv;
+      a.price[pos] = lds.price[j];
+      a.qty[pos] = lds.qty[j];
+    }
   }
 }
 
@@ -256,7 +297,7 @@ struct GbTable {
   }
   __device__ __forceinline__ int find(int64_t k) {
     // (the finalizer of MurmurHash3: one multiplication fewer left consecutive keys of a bin in runs of over 64 slots)
-    uint32_t f = fold(k);
+    uint32_t f = group_fold(k);
     f = (f ^ (f >> 16)) * 0x85EBCA6Bu;
     f = (f ^ (f >> 13)) * 0xC2B2AE35u;
     uint32_t h = f >> (32 - __builtin_ctz(SLOTS));
@@ -281,7 +322,7 @@ struct GbTable {
 // Workgroup b takes units b, b + G, ... A table key is found by its first row,
 // so a key is either in the unit's LDS table for all its rows or (64 occupied
 // slots after its home one, which stay occupied) in device memory for all.
-template <int SLOTS, int NT>
+template <bool P, int SLOTS, int NT>
 __global__ __launch_bounds__(NT) void k_gb_agg(GbArgs a, GroupView g, relh::DirectOut o) {
   __shared__ GbTable<SLOTS> tab;
   __shared__ uint32_t scr[NT / kWave];
@@ -300,17 +341,26 @@ __global__ __launch_bounds__(NT) void k_gb_agg(GbArgs a, GroupView g, relh::Dire
     for (uint32_t r0 = d.x + t; r0 - t < d.y; r0 += NT * kAhead) {
       int64_t key[kAhead];
       uint64_t sp[kAhead], sq[kAhead];
+      uint32_t ct[kAhead];
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) {
         const uint32_t r = min(r0 + k * NT, d.y - 1);
-        key[k] = a.key[r];
-        sp[k] = (uint64_t)a.price[r];
-        sq[k] = (uint64_t)(int64_t)a.qty[r];
+        if constexpr (P) {
+          key[k] = a.bin.key[r];
+          sp[k] = a.bin.price[r];
+          sq[k] = a.bin.qty[r];
+          ct[k] = a.bin.count[r];
+        } else {
+          key[k] = a.key[r];
+          sp[k] = (uint64_t)a.price[r];
+          sq[k] = (uint64_t)(int64_t)a.qty[r];
+          ct[k] = 1;
+        }
       }
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) {
         bool mine = r0 + k * NT < d.y;
-        uint32_t c = 1;
+        uint32_t c = ct[k];
         if (cut) {
           // a hot key's rows sit side by side: the lanes that share the first lane's key are summed first
           const uint64_t act = wave_ballot(mine);
@@ -321,10 +371,11 @@ __global__ __launch_bounds__(NT) void k_gb_agg(GbArgs a, GroupView g, relh::Dire
           const uint64_t ball = wave_ballot(same);
           if (__popcll(ball) >= kWaveCombineMin) {
             const uint64_t p = wave_sum_u64(same ? sp[k] : 0), q = wave_sum_u64(same ? sq[k] : 0);
+            const uint32_t all = P ? (uint32_t)wave_sum_u64(same ? c : 0u) : (uint32_t)__popcll(ball);
             if ((int)lane_id() == first) {
               sp[k] = p;
               sq[k] = q;
-              c = (uint32_t)__popcll(ball);
+              c = all;
             } else {
               mine = mine && !same;
             }
@@ -470,12 +521,83 @@ rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expect
   hipLaunchKernelGGL(k_gb_colsum, cols, dim3(kColBins * kColWaves), 0, ctx->stream, a);
   hipLaunchKernelGGL(k_gb_offsets, cols, dim3(kColBins * kColWaves), 0, ctx->stream, a);
   hipLaunchKernelGGL(k_gb_units, dim3(1), dim3(kGbBlock), 0, ctx->stream, a);
-  hipLaunchKernelGGL(k_gb_scatter, tiles, dim3(kGbBlock), 0, ctx->stream, a);
+  hipLaunchKernelGGL(k_gb_scatter<false>, tiles, dim3(kGbBlock), 0, ctx->stream, a);
   if (small)
-    hipLaunchKernelGGL((k_gb_agg<2048, 512>), dim3(2 * ctx->num_cus), dim3(512), 0, ctx->stream, a, g, o);
+    hipLaunchKernelGGL((k_gb_agg<false, 2048, 512>), dim3(2 * ctx->num_cus), dim3(512), 0, ctx->stream, a, g, o);
   else
-    hipLaunchKernelGGL((k_gb_agg<4096, 1024>), dim3(ctx->num_cus), dim3(1024), 0, ctx->stream, a, g, o);
+    hipLaunchKernelGGL((k_gb_agg<false, 4096, 1024>), dim3(ctx->num_cus), dim3(1024), 0, ctx->stream, a, g, o);
   REL_LAUNCH_CHECK(ctx, "groupby");
+  return REL_OK;
+}
+
+rel_status partials_take(rel_ctx* ctx, int64_t max_rows, unsigned workgroups, int64_t expected, size_t at_least,
+                         uint32_t* n_chunks, Partials* p) {
+  // Bins: as above by the groups, and so many that a bin's partials make about
+  // one unit.
+  uint32_t bits = 6;
+  while (bits < 11 && ((expected >> bits) > 2048 || (max_rows >> bits) > kGbSubRows / 2)) ++bits;
+  p->nb = 1u << bits;
+  p->shift = 32 - bits;
+  p->max_rows = max_rows;
+  p->first_chunks = workgroups;
+  p->max_chunks = max_rows / (kPartialTile - kPartialMost) + workgroups;  // (a chunk ends when the next unit's might not fit)
+  p->n_chunks = n_chunks;
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  auto cols = [&](int id, size_t n, PartialCols* c) {
+    void* mem;
+    rel_status s = scratch(ctx, id, std::max(at_least, 2 * up(n * 8) + 2 * up(n * 4)), &mem);
+    if (s != REL_OK) return s;
+    char* q = (char*)mem;
+    c->price = (uint64_t*)q;
+    c->qty = (uint64_t*)(q + up(n * 8));
+    c->key = (int32_t*)(q + 2 * up(n * 8));
+    c->count = (uint32_t*)(q + 2 * up(n * 8) + up(n * 4));
+    return s;
+  };
+  rel_status s = cols(SCR_PART_A, (size_t)p->max_chunks * kPartialTile, &p->cols);
+  if (s == REL_OK) s = cols(SCR_PART_B, (size_t)max_rows, &p->binned);
+  const size_t fill = up((size_t)p->max_chunks * 4), hist = up((size_t)p->max_chunks * p->nb * 4);
+  const size_t chunk = up((size_t)kGbChunks * p->nb * 4), max_units = p->nb + (size_t)max_rows / kGbSubRows + 1;
+  void* mem = nullptr;
+  if (s == REL_OK) s = scratch(ctx, SCR_GROUPBY, fill + hist + chunk + up(p->nb * 4) + up(max_units * 16) + 256, &mem);
+  char* q = (char*)mem;
+  p->fill = (uint32_t*)q;
+  p->hist = (uint32_t*)(q + fill);
+  p->work = q + fill + hist;
+  return s;
+}
+
+rel_status partials_reduce(rel_ctx* ctx, const Partials& p, int64_t expected, const uint32_t* zero, const rel::GroupView& g,
+                           const DirectOut& o) {
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  GbArgs a{};
+  a.few = zero;
+  a.nb = p.nb;
+  a.shift = p.shift;
+  a.ntiles = p.first_chunks;
+  a.more_tiles = p.n_chunks;
+  a.part = p;
+  a.hist = p.hist;
+  char* q = p.work;
+  a.chunk = (uint32_t*)q;
+  q += up((size_t)kGbChunks * p.nb * 4);
+  a.start = (uint32_t*)q;
+  q += up(p.nb * 4);
+  a.units = (uint4*)q;
+  q += up((p.nb + (size_t)p.max_rows / kGbSubRows + 1) * 16);
+  a.n_units = (uint32_t*)q;
+  a.bin = p.binned;
+  KernelTimer kt(ctx, "partials");
+  const dim3 cols(a.nb / kColBins, kGbChunks);
+  hipLaunchKernelGGL(k_gb_colsum, cols, dim3(kColBins * kColWaves), 0, ctx->stream, a);
+  hipLaunchKernelGGL(k_gb_offsets, cols, dim3(kColBins * kColWaves), 0, ctx->stream, a);
+  hipLaunchKernelGGL(k_gb_units, dim3(1), dim3(kGbBlock), 0, ctx->stream, a);
+  hipLaunchKernelGGL(k_gb_scatter<true>, dim3((unsigned)p.max_chunks), dim3(kGbBlock), 0, ctx->stream, a);
+  if ((expected >> (32 - p.shift)) <= 1024)
+    hipLaunchKernelGGL((k_gb_agg<true, 2048, 512>), dim3(2 * ctx->num_cus), dim3(512), 0, ctx->stream, a, g, o);
+  else
+    hipLaunchKernelGGL((k_gb_agg<true, 4096, 1024>), dim3(ctx->num_cus), dim3(1024), 0, ctx->stream, a, g, o);
+  REL_LAUNCH_CHECK(ctx, "partials");
   return REL_OK;
 }
 

@@ -50,11 +50,14 @@ rel_status partitioned_groupjoin(rel_ctx* ctx, const rel_fact* fact, const rel_d
 // aggregates into the device-memory group table group_slots (2^group_log2cap
 // slots plus the side slot, initialised by the caller; probe walks bounded by
 // max_probe) through per-workgroup LDS tables (probe budget lds_probe), or,
-// with eager (dim.grp only), through per-unit partials per dim key. Adds to
-// the same two counters.
+// with eager (dim.grp only), through per-unit partials per dim key, which go to
+// `partials` instead when that is given. Adds to the same two counters.
 rel_status partitioned_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim, int32_t day_lt, int group_by,
                                 void* group_slots, uint32_t group_log2cap, uint32_t max_probe, int32_t lds_probe,
-                                bool eager, int64_t* counters);
+                                bool eager, const struct Partials* partials, int64_t* counters);
+// The most partials that the eager form yields, its workgroups, and the bytes of
+// the buffers SCR_PART_A and SCR_PART_B that the partitioning itself needs.
+void partials_bounds(rel_ctx* ctx, int64_t n, int64_t m, int64_t* max_rows, unsigned* workgroups, size_t* fact_bytes);
 
 // Rows of a stand-alone group-by: row = sel ? sel[k] : k for k in [0, n).
 struct GroupRows {
@@ -86,5 +89,34 @@ rel_status groupby_begin(rel_ctx* ctx, const GroupRows& in, int mode, uint32_t* 
 // (set *o.touched), about `expected` of them.
 rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expected, const uint32_t* few,
                                const rel::GroupView& g, const DirectOut& o);
+
+// Partial sums by group that a kernel's workgroups leave in chunks of memory, and
+// how many of a chunk's lie in each bin. Workgroup w of the first_chunks fills
+// chunk w first and takes more from *n_chunks (on from first_chunks).
+constexpr int kPartialTile = 5120;  // of a chunk: a tile that is sorted in LDS
+constexpr int kPartialMost = 2048;  // that a workgroup adds at a time
+struct PartialCols {
+  int32_t* key;
+  uint64_t* price;
+  uint64_t* qty;
+  uint32_t* count;
+};
+struct Partials {
+  PartialCols cols;    // [max_chunks * kPartialTile]
+  PartialCols binned;  // [max_rows]
+  uint32_t* fill;      // [max_chunks]
+  uint32_t* hist;      // [max_chunks][nb]
+  char* work;
+  uint32_t* n_chunks;
+  uint32_t nb, shift;
+  int64_t first_chunks, max_chunks, max_rows;
+};
+// Memory for partials, in SCR_PART_A and _B (at least `at_least` bytes each, for
+// what lies there before) and SCR_GROUPBY. *n_chunks is zero at the start.
+rel_status partials_take(rel_ctx* ctx, int64_t max_rows, unsigned workgroups, int64_t expected, size_t at_least,
+                         uint32_t* n_chunks, Partials* p);
+// The partials' groups to `o`, or to the device table g (set *o.touched); *zero is 0.
+rel_status partials_reduce(rel_ctx* ctx, const Partials& p, int64_t expected, const uint32_t* zero, const rel::GroupView& g,
+                           const DirectOut& o);
 
 }  // namespace relh
