@@ -71,7 +71,7 @@ struct KeyMap {
   uint32_t range;      // dense: kmax - kmin + 1 (fact keys outside it match nothing)
   uint32_t merge;      // dense: log2 of the partitions per groupjoin unit
   uint32_t lbits;      // dense: L, the key positions are [0, 2^L)
-  uint32_t inv;        // dense: mul^-1 mod 2^32 (key - kmin = position * inv mod 2^L)
+  uint32_t inv;        // mul^-1 mod 2^32 (dense: key - kmin = position * inv mod 2^L; hash: key = hash * inv)
 };
 
 __device__ __forceinline__ uint32_t key_hash(uint32_t sub, uint32_t mul, uint32_t sh, int32_t key) {
@@ -94,11 +94,16 @@ __device__ __forceinline__ uint32_t key_hash(uint32_t sub, uint32_t mul, uint32_
 // first-level scatter's per-wave values, combined by the second-level scan;
 // signed values are kept order-encoded (sign bit flipped) so that unsigned
 // atomics order them.
+// In the hash order (grouping by dim.grp) the low bits hold what of the key's
+// hash the partition does not fix, 32 - P bits for 2^P partitions: the hash is
+// a bijection, so a unit's kernel gets the key back from them and the hash of
+// any dim key of the unit. 8 bytes per row instead of 16 took the second-level
+// scatter of 28M rows from 180 us to 130; the join kernel, bound by its steps and
+// not by its reads, gained where the keys are uniform (whole call 1.55 to 1.45 ms).
 constexpr uint32_t kSignFlip = 0x80000000u;
 constexpr int kRngWaves = 8;  // waves of a first-level scatter workgroup
 static_assert(kRngWaves == kSBlk / kWave, "one range entry per wave of a first-level scatter workgroup");
 constexpr uint32_t kNarrowSlotBits = 11;  // >= kJSlotBits
-constexpr uint32_t kNarrowFieldBits = 64 - kNarrowSlotBits - 1;
 __device__ __forceinline__ uint32_t order_enc(int32_t v) { return (uint32_t)v ^ kSignFlip; }
 __device__ __forceinline__ int32_t order_dec(uint32_t u) { return (int32_t)(u ^ kSignFlip); }
 __device__ __forceinline__ uint32_t bits_of(uint64_t x) { return x ? 64u - (uint32_t)__clzll((long long)x) : 0u; }
@@ -106,20 +111,23 @@ __device__ __forceinline__ uint32_t bits_of(uint64_t x) { return x ? 64u - (uint
 struct Narrow {
   uint32_t on;      // rows are 64-bit words
   uint32_t qb;      // quantity field bits
+  uint32_t kb;      // key bits, below the fields
   int64_t pmin, qmin;
 };
+enum NarrowMode : uint32_t { kNarrowOff = 0, kNarrowDense, kNarrowHash };  // rows may be narrow in that key order
 // rng: {min, max} of the order-encoded price high words, then of the
 // quantities. Prices lie in [hmin * 2^32, (hmax + 1) * 2^32), a span below
 // 2^(32 + bits(hmax - hmin)).
-__device__ __forceinline__ Narrow narrow_of(const KeyMap* km, const uint32_t* rng, uint32_t enabled) {
-  Narrow n{0u, 0u, 0, 0};
-  if (!enabled || !km->dense || rng[0] > rng[1]) return n;
+__device__ __forceinline__ Narrow narrow_of(const KeyMap* km, const uint32_t* rng, uint32_t mode, uint32_t pbits) {
+  Narrow n{0u, 0u, 0u, 0, 0};
+  if (mode != (km->dense ? kNarrowDense : kNarrowHash) || rng[0] > rng[1]) return n;
   const int32_t hmin = order_dec(rng[0]), hmax = order_dec(rng[1]);
   n.pmin = (int64_t)hmin * 4294967296ll;
   n.qmin = order_dec(rng[2]);
   const uint32_t pb = 32u + bits_of((uint64_t)((int64_t)hmax - hmin));
   n.qb = bits_of((uint64_t)((int64_t)order_dec(rng[3]) - n.qmin));
-  n.on = pb + n.qb <= kNarrowFieldBits;
+  n.kb = km->dense ? kNarrowSlotBits + 1 : 32 - pbits;
+  n.on = pb + n.qb + n.kb <= 64;
   return n;
 }
 
@@ -128,13 +136,13 @@ struct NarrowPack {
   Narrow n;
   uint32_t sub, mul, range, smask;
 };
-__device__ __forceinline__ NarrowPack narrow_pack(const KeyMap* km, const uint32_t* rng, uint32_t enabled) {
-  NarrowPack np{narrow_of(km, rng, enabled), 0u, 0u, 0u, 0u};
+__device__ __forceinline__ NarrowPack narrow_pack(const KeyMap* km, const uint32_t* rng, uint32_t mode, uint32_t pbits) {
+  NarrowPack np{narrow_of(km, rng, mode, pbits), 0u, 0u, 0u, 0u};
   if (np.n.on) {
     np.sub = km->sub;
     np.mul = km->mul;
-    np.range = km->range;
-    np.smask = (1u << (km->slot_bits + km->merge)) - 1u;
+    np.range = km->range;  // (hash order: 0)
+    np.smask = (1u << (km->dense ? km->slot_bits + km->merge : np.n.kb)) - 1u;
   }
   return np;
 }
@@ -205,11 +213,11 @@ __global__ __launch_bounds__(kWave) void k_keymap(const uint32_t* __restrict__ p
       k.range = (uint32_t)range;
       k.merge = min((uint32_t)kJSlotBits - k.slot_bits, pbits);
       k.lbits = L;
-      uint32_t x = k.mul;  // Newton's iteration for the inverse of an odd number mod 2^32: 3, 6, 12, 24, 48 bits
-      for (int i = 0; i < 4; ++i) x *= 2u - k.mul * x;
-      k.inv = x;
     }
   }
+  uint32_t x = k.mul;  // Newton's iteration for the inverse of an odd number mod 2^32: 3, 6, 12, 24, 48 bits
+  for (int i = 0; i < 4; ++i) x *= 2u - k.mul * x;
+  k.inv = x;
   *km = k;
 }
 
@@ -242,7 +250,7 @@ struct PartSide {
   uint32_t* pass1;   // fact only: bit r of word r / 32 set when row r passes the filter (the histogram writes it)
   uint32_t* rng_part;  // fact only, nullable: per wave of a first-level tile, the passing rows' encoded ranges (narrow_of)
   uint32_t* rng;       // fact only: those ranges over all tiles
-  uint32_t narrow;     // fact only: the second level may write narrow rows (GROUP BY fk)
+  uint32_t narrow;     // fact only: the second level may write narrow rows (NarrowMode)
   uint32_t* hist2;   // [max tiles2][nb2]
   uint32_t* pstart;  // [nb1 * nb2]
   uint32_t* pcount;  // [nb1 * nb2]
@@ -555,8 +563,8 @@ __device__ __forceinline__ void stage_and_write(Stage<FACT, TILE>& st, TileRows<
     if (FACT && np.n.on) {  // one 64-bit word per row, in the price column's place
       const uint32_t off = (uint32_t)kv.x - np.sub;
       const uint64_t w = (uint64_t)((off * np.mul) & np.smask) | ((uint64_t)(off < np.range) << kNarrowSlotBits) |
-                         ((uint64_t)((int64_t)kv.y - np.n.qmin) << (kNarrowSlotBits + 1)) |
-                         (((uint64_t)(st.price[j] - np.n.pmin) << (kNarrowSlotBits + 1)) << np.n.qb);
+                         ((uint64_t)((int64_t)kv.y - np.n.qmin) << np.n.kb) |
+                         (((uint64_t)(st.price[j] - np.n.pmin) << np.n.kb) << np.n.qb);
       reinterpret_cast<uint64_t*>(dprice)[pos] = w;
       continue;
     }
@@ -899,7 +907,7 @@ __global__ __launch_bounds__(kSBlk) void k_p2_scatter(PartSide s) {
   if (threadIdx.x < kMaxBins) st.lcnt[threadIdx.x] = 0;
   if (threadIdx.x < nb2) st.gbase[threadIdx.x] = s.pstart[x.p * nb2 + threadIdx.x] + s.hist2[(size_t)t * nb2 + threadIdx.x];
   __syncthreads();
-  const NarrowPack np = FACT ? narrow_pack(s.km, s.rng, s.narrow) : NarrowPack{};
+  const NarrowPack np = FACT ? narrow_pack(s.km, s.rng, s.narrow, s.b1 + s.b2) : NarrowPack{};
   stage_and_write<FACT, false, kSBlk, (int)kTile>(st, r, bin_of, nb2, pay, s.key2, s.price2, FACT ? s.qty2 : s.pay2,
                                                   FACT ? s.flag2 : nullptr, np);
 }
@@ -1680,8 +1688,8 @@ __device__ __forceinline__ void groupjoin_dense(const JoinArgs& a, GroupjoinLds&
   const uint32_t lmask = L >= 32 ? ~0u : (1u << L) - 1u;
   const uint32_t nslots = 1u << ubits, smask = nslots - 1u;
   const uint32_t nw = ubits >= 5 ? nslots >> 5 : 1u;  // bitmap words of a unit
-  const Narrow nar = narrow_of(a.km, a.rng, a.narrow);
-  const uint64_t qmask = (1ull << nar.qb) - 1ull;  // qb <= kNarrowFieldBits < 64
+  const Narrow nar = narrow_of(a.km, a.rng, a.narrow, 0u);
+  const uint64_t qmask = (1ull << nar.qb) - 1ull;  // qb < 64 (narrow rows)
   uint32_t* const cnt = sh.t.d.cnt;
   uint32_t* const own = sh.t.d.own;
   uint64_t* const tsp = sh.tsp;
@@ -1951,6 +1959,9 @@ struct AggArgs {
   GroupView groups;
   int32_t lds_probe;
   uint32_t zero;  // 0 at run time; see take_ticket
+  const KeyMap* km;
+  const uint32_t* rng;    // the fact rows' price and quantity ranges (narrow_of)
+  uint32_t narrow, pbits;
   relh::Partials part;  // eager form: where the partials go (part.nb 0: the device table)
 };
 
@@ -1969,12 +1980,41 @@ struct AggRows {
   uint32_t fl;  // the rows' flag bytes (FL only)
 };
 
+// Narrow rows of the hash order (in the price column's place; NarrowMode).
+struct AggNarrow {
+  Narrow n;
+  uint32_t mul, inv, kmask;
+  AggNarrow() = default;
+  __device__ __forceinline__ explicit AggNarrow(const AggArgs& a)
+      : n(narrow_of(a.km, a.rng, a.narrow, a.pbits)), mul(a.km->mul), inv(a.km->inv), kmask((1u << n.kb) - 1u) {}
+  // the part of the hash that all keys of dim key `key`'s partition share
+  __device__ __forceinline__ uint32_t high(int32_t key) const { return ((uint32_t)key * mul) & ~kmask; }
+  template <class Rows>
+  __device__ __forceinline__ void unpack(uint32_t high, Rows& r) const {
+#pragma unroll
+    for (int k = 0; k < kJR; ++k) {
+      const uint64_t w = r.sp[k], f = w >> n.kb;
+      r.key[k] = (int32_t)((high | ((uint32_t)w & kmask)) * inv);
+      r.sp[k] = (uint64_t)n.pmin + (f >> n.qb);
+      r.qty[k] = (int32_t)(n.qmin + (int64_t)(f & ((1ull << n.qb) - 1ull)));
+    }
+  }
+};
+
 // Fact rows i0 + k * kABlock of a unit, indices clamped into its (never
 // empty) range so that the number of loads is fixed; the probe skips the
 // copies past the range.
 template <bool FL>
-__device__ __forceinline__ void load_agg_rows(const AggArgs& a, uint32_t i0, uint32_t fhi, AggRows<FL>& r) {
+__device__ __forceinline__ void load_agg_rows(const AggArgs& a, const AggNarrow& nar, uint32_t i0, uint32_t fhi, AggRows<FL>& r) {
   r.fl = 0;
+  if (!FL && nar.n.on) {
+#pragma unroll
+    for (int k = 0; k < kJR; ++k) {
+      const uint32_t i = i0 + k * kABlock;
+      r.sp[k] = (uint64_t)a.fprice[i < fhi ? i : fhi - 1];
+    }
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < kJR; ++k) {
     uint32_t i = i0 + k * kABlock;
@@ -2012,6 +2052,8 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_agg(AggArgs a) {
   __shared__ uint4 s_desc;
   __shared__ uint2 s_split;
   __shared__ int64_t s_u;
+  __shared__ uint32_t s_high;
+  const AggNarrow nar = FL ? AggNarrow{} : AggNarrow(a);
   const int64_t n_units = *a.n_units;
   const uint32_t tid = threadIdx.x, lane = lane_id();
   uint64_t matched = 0;
@@ -2037,7 +2079,7 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_agg(AggArgs a) {
   AggRows<FL> cur, nxt;
   if (u < n_units) {
     load_agg_dim(a, d, dk, dp);
-    load_agg_rows<FL>(a, d.z + tid, d.w, cur);
+    load_agg_rows<FL>(a, nar, d.z + tid, d.w, cur);
   }
   while (u < n_units) {
     const uint32_t dlo = d.x, dhi = d.y, flo = d.z, fhi = d.w;
@@ -2077,9 +2119,11 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_agg(AggArgs a) {
       s_u = t_ahead;
       s_desc = nd;
       s_split = ns;
+      if (!FL) s_high = nar.high(dk[0]);
     }
     __syncthreads();
     const int64_t un = s_u;
+    const uint32_t high = FL ? 0u : s_high;
     const uint4 dn = s_desc;
     const uint2 sn = s_split;
     if (usplit.x == 0 && usplit.y > dhi) check_later_chunks<kABlock>(tkey, a.dkey, dhi, usplit.y, a.status);
@@ -2090,12 +2134,13 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_agg(AggArgs a) {
     const bool early = iters <= 1;
     if (early) {
       load_agg_dim(a, pd, ndk, ndp);
-      load_agg_rows<FL>(a, pd.z + tid, pd.w, nxt);
+      load_agg_rows<FL>(a, nar, pd.z + tid, pd.w, nxt);
     }
     for (uint32_t it = 0; it < iters; ++it) {
       const uint32_t i0 = flo + it * (kJR * kABlock) + tid;
       if (it > 0) cur = nxt;
-      if (it + 1 < iters) load_agg_rows<FL>(a, i0 + kJR * kABlock, fhi, nxt);
+      if (!FL && nar.n.on) nar.unpack(high, cur);
+      if (it + 1 < iters) load_agg_rows<FL>(a, nar, i0 + kJR * kABlock, fhi, nxt);
       bool fnd[kJR];
       int32_t pay[kJR];
 #pragma unroll
@@ -2145,7 +2190,7 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_agg(AggArgs a) {
     }
     if (!early) {
       load_agg_dim(a, pd, ndk, ndp);
-      load_agg_rows<FL>(a, pd.z + tid, pd.w, nxt);
+      load_agg_rows<FL>(a, nar, pd.z + tid, pd.w, nxt);
     }
     __syncthreads();  // the join table and s_u / s_desc are reused by the next unit
     t_ahead = t_req;
@@ -2203,6 +2248,8 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
   __shared__ uint4 s_desc;
   __shared__ uint2 s_split;
   __shared__ int64_t s_u;
+  __shared__ uint32_t s_high;
+  const AggNarrow nar(a);
   const int64_t n_units = *a.n_units;
   const uint32_t tid = threadIdx.x, lane = lane_id();
   uint64_t matched = 0;
@@ -2242,7 +2289,7 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
   AggRows<false> cur, nxt;
   if (u < n_units) {
     load_agg_dim(a, d, dk, dp);
-    load_agg_rows<false>(a, d.z + tid, d.w, cur);
+    load_agg_rows<false>(a, nar, d.z + tid, d.w, cur);
   }
   while (u < n_units) {
     const uint32_t dlo = d.x, dhi = d.y, flo = d.z, fhi = d.w;
@@ -2284,9 +2331,11 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
       s_u = t_ahead;
       s_desc = nd;
       s_split = ns;
+      s_high = nar.high(dk[0]);
     }
     __syncthreads();
     const int64_t un = s_u;
+    const uint32_t high = s_high;
     const uint4 dn = s_desc;
     const uint2 sn = s_split;
     if (usplit.x == 0 && usplit.y > dhi) check_later_chunks<kABlock>(tkc, a.dkey, dhi, usplit.y, a.status);
@@ -2297,12 +2346,13 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
     const bool early = iters <= 1;
     if (early) {
       load_agg_dim(a, pd, ndk, ndp);
-      load_agg_rows<false>(a, pd.z + tid, pd.w, nxt);
+      load_agg_rows<false>(a, nar, pd.z + tid, pd.w, nxt);
     }
     for (uint32_t it = 0; it < iters; ++it) {
       const uint32_t i0 = flo + it * (kJR * kABlock) + tid;
       if (it > 0) cur = nxt;
-      if (it + 1 < iters) load_agg_rows<false>(a, i0 + kJR * kABlock, fhi, nxt);
+      if (nar.n.on) nar.unpack(high, cur);
+      if (it + 1 < iters) load_agg_rows<false>(a, nar, i0 + kJR * kABlock, fhi, nxt);
       bool fnd[kJR];
       int slt[kJR];
 #pragma unroll
@@ -2354,7 +2404,7 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
     }
     if (!early) {
       load_agg_dim(a, pd, ndk, ndp);
-      load_agg_rows<false>(a, pd.z + tid, pd.w, nxt);
+      load_agg_rows<false>(a, nar, pd.z + tid, pd.w, nxt);
     }
     __syncthreads();
     // one partial per matched dim key under its grp: to the chunk, or into the
@@ -2594,10 +2644,11 @@ rel_status partition_both(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim
   F.flag2 = with_flag ? cb.take<int8_t>(n) : nullptr;
   F.hist1 = cd.take<uint32_t>((size_t)fnt1 * nb1);
   F.pass1 = cd.take<uint32_t>(((size_t)n / 64 + 1) * 2);
-  // GROUP BY fk: the passing rows' price and quantity ranges, for narrow second-level rows
-  F.rng_part = dense_ok ? cd.take<uint32_t>((size_t)fnt1 * kRngWaves * 4) : nullptr;
-  F.rng = dense_ok ? cd.take<uint32_t>(4) : nullptr;
-  F.narrow = dense_ok ? 1u : 0u;
+  // the passing rows' price and quantity ranges, for narrow second-level rows (a row's flag has no place in them)
+  const uint32_t narrow = dense_ok ? kNarrowDense : with_flag ? kNarrowOff : kNarrowHash;
+  F.rng_part = narrow ? cd.take<uint32_t>((size_t)fnt1 * kRngWaves * 4) : nullptr;
+  F.rng = narrow ? cd.take<uint32_t>(4) : nullptr;
+  F.narrow = narrow;
   F.tot1 = cd.take<uint32_t>(nb1);
   F.hist2 = cd.take<uint32_t>((size_t)fnt2 * nb2);
   F.pstart = cd.take<uint32_t>(nparts);
@@ -2784,6 +2835,10 @@ rel_status partitioned_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_di
                        ctx->d_status, max_probe};
   a.lds_probe = lds_probe;
   a.zero = 0;
+  a.km = P.F.km;
+  a.rng = P.F.rng;
+  a.narrow = P.F.narrow;
+  a.pbits = P.b1 + P.b2;
   if (partials) a.part = *partials;
   const unsigned grid = join_agg_grid(ctx);
   if (prio_flag) hipLaunchKernelGGL(k_part_join_agg<REL_GROUP_PRIO_FLAG>, dim3(grid), dim3(kABlock), 0, ctx->stream, a);

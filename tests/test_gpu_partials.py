@@ -35,9 +35,9 @@ def _tables(n, m, seed, grp, hot=0.0, negative=False):
     return T
 
 
-def _check(ctx, T, capacity, **kw):
+def _check(ctx, T, capacity, groups="global", **kw):
     fact, dim = to_dev(T)
-    plan = rel.Plan(capacity, rel.PLACE["global"], rel.PLACE["partitioned"], 0, 0)
+    plan = rel.Plan(capacity, rel.PLACE[groups], rel.PLACE["partitioned"], 0, 0)
     out, st = ctx.filter_join_agg(fact, dim, T.day_lt, T.group_by, plan=plan, **kw)
     ora, ost = oracle.run_tables(T)
     assert_groups_equal(gpu_groups(out), ora, f"n={T.n} m={T.m} capacity={capacity}")
@@ -97,6 +97,23 @@ def test_other_calls_between_and_small_output(ctx):
         ctx.filter_join_agg(fact, dim, T.day_lt, T.group_by, plan=plan, out_cap=1000)
     assert e.value.status == rel.CAPACITY
     _check(ctx, T, 40_000)
+
+
+@pytest.mark.parametrize("m,groups", [(40_000, 30), (100_000, 30_000), (20_000, 9000)])  # 64 partitions and more; fewer
+@pytest.mark.parametrize("price,qty", [((90_000, 10_500_000), (1, 51)), ((-5, 5), (-3, 1)), ((2**32 - 3, 2**32 + 3), (0, 1)),
+                                       ((-(2**40), 2**40), (-(2**31), 2**31)), ((-(2**63), 2**63), (7, 8)),
+                                       ((2**62, 2**62 + 1000), (-(2**31), -(2**31) + 5))])
+def test_value_ranges(ctx, m, groups, price, qty):
+    """Rows of one word where the values' ranges allow, of 16 bytes where they don't; few groups and many."""
+    T = _tables(150_000, m, 12, groups, negative=True)
+    r = np.random.default_rng(m)
+    T.pk = (T.pk.astype(np.int64) * 7 - 3000).astype(np.int32)  # keys of both signs
+    T.fk = T.pk[r.integers(0, m, T.n)]
+    T.fk[::10] = r.integers(-(2**31), 2**31, len(T.fk[::10])).astype(np.int32)
+    T.price_cents = r.integers(price[0], price[1] - 1, T.n, dtype=np.int64, endpoint=True)
+    T.qty = r.integers(qty[0], qty[1], T.n, dtype=np.int64).astype(np.int32)
+    for placement in ("global", "lds"):
+        _check(ctx, T, groups, placement)
 
 
 def test_repeated_key_is_reported(ctx):
