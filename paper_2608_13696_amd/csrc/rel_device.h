@@ -77,6 +77,40 @@ __device__ __forceinline__ uint32_t mask_rank(uint64_t m) {
 
 __device__ __forceinline__ uint64_t wave_ballot(bool p) { return __ballot(p); }
 
+// A lane's value, the same for all lanes (lane is).
+__device__ __forceinline__ int32_t wave_at(int32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ int64_t wave_at(int64_t v, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+// The value that a data-parallel-primitive move brings from another lane, 0
+// where none is brought.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, true);
+  return (uint64_t)hi << 32 | lo;
+}
+
+// Sum of a 64-bit value over the 64 lanes of a wave, all of them active, by
+// moves inside the register file: shifts by 1, 2, 4 and 8 lanes sum each row of
+// 16 in its last lane, which then goes to the next row (rows 1 and 3) and to the
+// upper half. Six rounds of two permutes through LDS took the partitioned join by
+// dim attribute from 239 to 296 us (28M rows, Zipf(1.2) foreign keys), which
+// pre-sums hot keys with it.
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
+  constexpr int kRowShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
+  v += dpp_u64<kRowShr + 1, 0xf>(v);
+  v += dpp_u64<kRowShr + 2, 0xf>(v);
+  v += dpp_u64<kRowShr + 4, 0xf>(v);
+  v += dpp_u64<kRowShr + 8, 0xf>(v);
+  v += dpp_u64<kBcast15, 0xa>(v);
+  v += dpp_u64<kBcast31, 0xc>(v);
+  return (uint64_t)wave_at((int64_t)v, kWave - 1);
+}
+
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
@@ -104,6 +138,14 @@ __device__ __forceinline__ T dev_cas(T* p, T expected, T desired) {
                                        __HIP_MEMORY_SCOPE_AGENT);
   return expected;  // the value found
 }
+
+// Waits until this wave's device atomics (dev_add) are done where every XCD sees
+// them, so that a counter raised afterwards tells others that they can be read,
+// by agent-scope atomic loads. A fence of that scope would also write back the
+// XCD's whole L2 first, for plain stores that nobody waits for: with one per
+// sub-unit of a split partition the groupjoin took 574 us instead of 247 (28M rows,
+// Zipf(1.2) foreign keys), 208 instead of 160 with Zipf(0.8).
+__device__ __forceinline__ void wait_device_atomics() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---- workgroup scan and decoupled look-back ----------------------------------------------------------------------------
 
@@ -456,12 +498,6 @@ __device__ __forceinline__ void group_add(const GroupView& t, int64_t key, uint6
   dev_add<uint64_t>(&g->count, cnt);
 }
 
-// Sum of a 64-bit value over the 64 lanes of a wave.
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, o, kWave);
-  return v;
-}
 
 // Sum of a 64-bit value over a workgroup of NT threads, valid in thread 0.
 // Every thread must call it; s is NT / 64 words of LDS that no thread touches
@@ -528,7 +564,7 @@ __device__ __forceinline__ void group_add_wave(const GroupView& t, bool active, 
   const uint64_t act = wave_ballot(active);
   if (act == 0) return;
   const int first = __ffsll((long long)act) - 1;
-  const int64_t k0 = __shfl(key, first, kWave);
+  const int64_t k0 = wave_at(key, first);
   const bool mine = active && key == k0;
   const uint64_t same = wave_ballot(mine);
   if (__popcll(same) >= kWaveCombineMin) {
@@ -553,7 +589,7 @@ __device__ __forceinline__ void group_add_wave_n(const GroupView& t, bool active
   const uint64_t act = wave_ballot(active);
   if (act == 0) return;
   const int first = __ffsll((long long)act) - 1;
-  const int64_t k0 = __shfl(key, first, kWave);
+  const int64_t k0 = wave_at(key, first);
   const bool mine = active && key == k0;
   const uint64_t same = wave_ballot(mine);
   if (__popcll(same) >= kWaveCombineMin) {

@@ -366,7 +366,7 @@ __global__ __launch_bounds__(NT) void k_gb_agg(GbArgs a, GroupView g, relh::Dire
           const uint64_t act = wave_ballot(mine);
           if (act == 0) continue;
           const int first = __ffsll((long long)act) - 1;
-          const int64_t k0 = __shfl(key[k], first, kWave);
+          const int64_t k0 = wave_at(key[k], first);
           const bool same = mine && key[k] == k0;
           const uint64_t ball = wave_ballot(same);
           if (__popcll(ball) >= kWaveCombineMin) {

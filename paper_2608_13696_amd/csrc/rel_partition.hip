@@ -1483,7 +1483,6 @@ __device__ __forceinline__ void groupjoin_units(const JoinArgs& a, GroupjoinLds&
     // The next unit's descriptor is published at the end of the probe (so no
     // thread waits at the build barrier for thread 0's read of it); its loads
     // go out then and travel during the emission.
-    const bool combine = sp.x != 0;
     for (uint32_t it = 0; it < iters; ++it) {
       const uint32_t i0 = flo + it * (kGR * kJBlock) + tid;
       ck = nk;
@@ -1531,13 +1530,13 @@ __device__ __forceinline__ void groupjoin_units(const JoinArgs& a, GroupjoinLds&
         matched += found;
         // Hot keys: when many lanes of the wave hit one slot, pre-sum them so the
         // LDS sees one update instead of a serialised run of same-address atomics.
-        // Only sub-units of split chunks check: the hottest keys are what makes
-        // a chunk split, and elsewhere the check costs more than it saves.
-        if (combine) {
+        // In all units: the check costs nothing beside the loads (uniform keys 154
+        // us with and without), and unsplit units hold warm keys, too (Zipf(1.2)
+        // 247 to 199 us, Zipf(0.8) 160 to 148).
         const uint64_t act = wave_ballot(found);
         if (act == 0) continue;
         const int first = __ffsll((long long)act) - 1;
-        const int s0 = __shfl(slot, first, kWave);
+        const int s0 = wave_at(slot, first);
         const uint64_t same = wave_ballot(found && slot == s0);
         if (__popcll(same) >= kCombineMin) {
           const bool mine = found && slot == s0;
@@ -1549,7 +1548,6 @@ __device__ __forceinline__ void groupjoin_units(const JoinArgs& a, GroupjoinLds&
             atomicAdd((unsigned long long*)&tkc[s0], (unsigned long long)__popcll(same) << 32);
           }
           found = found && !mine;
-        }
         }
         if (found) {
           atomicAdd((unsigned long long*)&tsp[slot], (unsigned long long)pay.sp[k]);
@@ -1629,12 +1627,11 @@ __device__ __forceinline__ void groupjoin_units(const JoinArgs& a, GroupjoinLds&
         dev_add<uint64_t>(&e->sq, tsq[s]);
         dev_add<uint64_t>(&e->cnt, (uint64_t)c);
       }
-      __threadfence();
+      wait_device_atomics();
       __syncthreads();
       if (tid == 0) s_last = dev_add_ret<uint32_t>(&a.split_done[sp.x - 1], 1u) + 1 == sp.y;
       __syncthreads();
       if (s_last) {
-        __threadfence();
         // a count fits 32 bits (fewer than 2^31 fact rows); the sums are read again when written
         uint32_t vc[kJDK];
         uint32_t mine = 0;
@@ -1759,7 +1756,6 @@ __device__ __forceinline__ void groupjoin_dense(const JoinArgs& a, GroupjoinLds&
     __syncthreads();
     const uint32_t nrows = fhi - flo;
     const uint32_t iters = (nrows + kGR * kJBlock - 1) / (kGR * kJBlock);
-    const bool combine = sp.x != 0;
     for (uint32_t it = 0; it < iters; ++it) {
       const uint32_t i0 = flo + it * (kGR * kJBlock) + tid;
       ck = nk;
@@ -1783,24 +1779,22 @@ __device__ __forceinline__ void groupjoin_dense(const JoinArgs& a, GroupjoinLds&
           pv = pay.sp[k];
           qv = (uint64_t)(int64_t)pay.qty[k];
         }
-        // hot keys (split sub-units): lanes of the wave on one slot are summed first
-        if (combine) {
-          const uint64_t act = wave_ballot(found);
-          if (act == 0) continue;
-          const int first = __ffsll((long long)act) - 1;
-          const int s0 = __shfl(slot, first, kWave);
-          const uint64_t same = wave_ballot(found && slot == s0);
-          if (__popcll(same) >= kCombineMin) {
-            const bool mine = found && slot == s0;
-            const uint64_t tsum_p = wave_sum_u64(mine ? pv : 0);
-            const uint64_t tsum_q = wave_sum_u64(mine ? qv : 0);
-            if ((int)lane == first) {
-              atomicAdd((unsigned long long*)&tsp[s0], (unsigned long long)tsum_p);
-              atomicAdd((unsigned long long*)&tsq[s0], (unsigned long long)tsum_q);
-              atomicAdd(&cnt[s0], (uint32_t)__popcll(same));
-            }
-            found = found && !mine;
+        // hot keys: lanes of the wave on one slot are summed first
+        const uint64_t act = wave_ballot(found);
+        if (act == 0) continue;
+        const int first = __ffsll((long long)act) - 1;
+        const int s0 = wave_at(slot, first);
+        const uint64_t same = wave_ballot(found && slot == s0);
+        if (__popcll(same) >= kCombineMin) {
+          const bool mine = found && slot == s0;
+          const uint64_t tsum_p = wave_sum_u64(mine ? pv : 0);
+          const uint64_t tsum_q = wave_sum_u64(mine ? qv : 0);
+          if ((int)lane == first) {
+            atomicAdd((unsigned long long*)&tsp[s0], (unsigned long long)tsum_p);
+            atomicAdd((unsigned long long*)&tsq[s0], (unsigned long long)tsum_q);
+            atomicAdd(&cnt[s0], (uint32_t)__popcll(same));
           }
+          found = found && !mine;
         }
         if (found) {
           atomicAdd((unsigned long long*)&tsp[slot], (unsigned long long)pv);
@@ -1883,12 +1877,11 @@ __device__ __forceinline__ void groupjoin_dense(const JoinArgs& a, GroupjoinLds&
         tsp[s] = 0;
         tsq[s] = 0;
       }
-      __threadfence();
+      wait_device_atomics();
       __syncthreads();
       if (tid == 0) s_last = dev_add_ret<uint32_t>(&a.split_done[sp.x - 1], 1u) + 1 == sp.y;
       __syncthreads();
       if (s_last) {
-        __threadfence();
         uint32_t vc[kJPer];
         uint32_t mine = 0;
 #pragma unroll
@@ -2174,7 +2167,7 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_agg(AggArgs a) {
         const uint64_t act = wave_ballot(add);
         if (act != 0) {
           const int first = __ffsll((long long)act) - 1;
-          const int s0 = __shfl(s, first, kWave);
+          const int s0 = wave_at(s, first);
           const bool mine = add && s == s0;
           const uint64_t same = wave_ballot(mine);
           if (__popcll(same) >= kCombineMin) {
@@ -2382,7 +2375,7 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
         const uint64_t act = wave_ballot(found);
         if (act == 0) continue;
         const int first = __ffsll((long long)act) - 1;
-        const int s0 = __shfl(slot, first, kWave);
+        const int s0 = wave_at(slot, first);
         const uint64_t same = wave_ballot(found && slot == s0);
         if (__popcll(same) >= kCombineMin) {
           const bool mine = found && slot == s0;
