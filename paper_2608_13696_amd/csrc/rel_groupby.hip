@@ -4,7 +4,7 @@
 // Updating a table in device memory costs three or four atomics per row, and
 // those run at about 27 G/s for the whole chip: 20M rows into 2M groups took
 // 2.7 ms. Partitioning reads and writes every row once more, but in runs, and
-// then all updates are LDS operations: 0.43 ms (6M rows of 15 groups: 147 -> 41 us).
+// then all updates are LDS operations: 0.41 ms (6M rows of 15 groups: 147 -> 41 us).
 //
 //   k_gb_hist     rows per (tile, bin), one tile per workgroup
 //   k_gb_colsum   those summed over chunks of tiles, per bin
@@ -329,14 +329,46 @@ __global__ __launch_bounds__(NT) void k_gb_agg(GbArgs a, GroupView g, relh::Dire
   __shared__ int64_t s_pos;
   if (*a.few) return;
   const uint32_t t = threadIdx.x;
-  constexpr int kPer = SLOTS / NT, kAhead = 4;
+  constexpr int kPer = SLOTS / NT, kAhead = 2;
 #pragma unroll
   for (int k = 0; k < kPer; ++k) tab.clear(t + k * NT);
   const uint32_t n_units = *a.n_units;
   bool device = false;  // this thread sent a row or a group to device memory
+  // One step's rows of a thread. The next step's, or the next unit's first, are
+  // on their way while a step's go into the table: there is no second workgroup
+  // on the CU to fill the wait (20M rows of 2M groups: 172 us without, 159 with 2
+  // rows ahead, 163 with 4, 195 with 6). What is left is the table: walks side by
+  // side instead of one after the other took 178, so it is its LDS operations.
+  typename GbRow<P>::Key nkey[kAhead];
+  uint64_t nsp[kAhead];
+  typename GbRow<P>::Qty nqty[kAhead];
+  uint32_t nct[kAhead];
+  auto load = [&](uint32_t r0, uint32_t end) {
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const uint32_t r = min(r0 + k * NT, end - 1);
+      if constexpr (P) {
+        nkey[k] = a.bin.key[r];
+        nsp[k] = a.bin.price[r];
+        nqty[k] = a.bin.qty[r];
+        nct[k] = a.bin.count[r];
+      } else {
+        nkey[k] = a.key[r];
+        nsp[k] = (uint64_t)a.price[r];
+        nqty[k] = a.qty[r];
+        nct[k] = 1;
+      }
+    }
+  };
+  uint4 next = make_uint4(0, 0, 0, 0);
+  if (blockIdx.x < n_units) {
+    next = a.units[blockIdx.x];
+    load(next.x + t, next.y);
+  }
   for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
-    const uint4 d = a.units[u];
+    const uint4 d = next;
     const bool cut = d.z != 0;
+    if (u + gridDim.x < n_units) next = a.units[u + gridDim.x];
     __syncthreads();  // the table is clear
     for (uint32_t r0 = d.x + t; r0 - t < d.y; r0 += NT * kAhead) {
       int64_t key[kAhead];
@@ -344,19 +376,13 @@ __global__ __launch_bounds__(NT) void k_gb_agg(GbArgs a, GroupView g, relh::Dire
       uint32_t ct[kAhead];
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) {
-        const uint32_t r = min(r0 + k * NT, d.y - 1);
-        if constexpr (P) {
-          key[k] = a.bin.key[r];
-          sp[k] = a.bin.price[r];
-          sq[k] = a.bin.qty[r];
-          ct[k] = a.bin.count[r];
-        } else {
-          key[k] = a.key[r];
-          sp[k] = (uint64_t)a.price[r];
-          sq[k] = (uint64_t)(int64_t)a.qty[r];
-          ct[k] = 1;
-        }
+        key[k] = (int64_t)nkey[k];
+        sp[k] = nsp[k];
+        sq[k] = (uint64_t)(int64_t)nqty[k];
+        ct[k] = nct[k];
       }
+      if (r0 - t + NT * kAhead < d.y) load(r0 + NT * kAhead, d.y);
+      else if (u + gridDim.x < n_units) load(next.x + t, next.y);
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) {
         bool mine = r0 + k * NT < d.y;
