@@ -29,13 +29,13 @@ __device__ __forceinline__ uint32_t hash64(int64_t key, uint32_t shift) {
   return (x * 2654435769u) >> shift;
 }
 
-// Non-temporal loads, for the partitioning kernels' reads of data that one
-// kernel reads exactly once (input columns, first-level runs). Measured on
-// the 60M-row workload: the level-1 histogram 126 -> 102 us, the level-1
-// scatter 378 -> 368 us. Not a general rule on this chip: the same loads in
-// the filter (0.10 -> 0.16 ms), the compiled predicate, the fused streaming
-// kernel and the groupjoin made each of them slower, so they keep ordinary
-// loads. Stores stay ordinary everywhere: non-temporal stores are not merged
+// Non-temporal loads, for reads of data that one kernel reads exactly once
+// (input columns, first-level runs), where a wave's lanes read consecutive
+// elements and many such loads are in flight. Measured on 60M rows: the level-1
+// histogram 126 -> 102 us, the level-1 scatter 378 -> 368 us. Not a general rule
+// on this chip: a thread that reads a run of its own with them fetches each line
+// several times (a filter of 32 rows per thread: 0.10 -> 0.16 ms), and lookups in
+// a table lose its lines (the join index, the groupjoin). Stores stay ordinary everywhere: non-temporal stores are not merged
 // in L2 with their neighbours, and the scatters, whose runs share cache lines
 // at their ends, ran twice as long with them.
 typedef int v4i_t __attribute__((ext_vector_type(4)));

@@ -24,7 +24,8 @@
 // units a presence bitmap over the key positions instead of its keys. The same partitions and units
 // serve grouping by a dim attribute: k_part_join_agg (few groups, an LDS
 // group table per workgroup) and k_part_join_eager (many groups, partials per
-// dim key added to a device-memory table at the end of each unit).
+// dim key, which a planned call partitions by group and sums in LDS, and another
+// adds to a device-memory table at the end of each unit).
 #include "rel_device.h"
 #include "rel_host.h"
 #include "rel_ops.h"

@@ -671,10 +671,12 @@ constexpr float kSkewMaxFreq = 4.0f / 256.0f;
 // Under such a heavy hitter, with at most this many groups from a dim
 // attribute, the plain join (device-memory table) beats the partitioned one:
 // the hot keys' probes stay in cache and the groups in LDS, while
-// partitioning still pays its passes (measured on 60M fact rows, Zipf(1.2):
-// 1.05 vs 1.26 ms at 100 groups; the partitioned path wins from 10^4 groups,
-// and for every group count when no key is hot).
-constexpr int64_t kSkewPlainJoinGroups = 2048;
+// partitioning still pays its passes (measured on 60M fact rows, Zipf(1.2),
+// plain against partitioned: 0.61 and 0.97 ms at 100 groups, 0.84 and 1.05 at
+// 900, 1.04 and 1.05 at 1200, 1.22 and 1.06 at 1350, 1.89 and 1.05 at 2000, 2.47
+// and 1.06 at 10^4; the partitioned path also wins for every group count when no
+// key is hot).
+constexpr int64_t kSkewPlainJoinGroups = 1280;
 
 #define TRY(e)                   \
   do {                           \

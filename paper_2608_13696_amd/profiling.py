@@ -69,7 +69,8 @@ def timer_name(kernel: str) -> str:
              "k_pred_compiled": "pred_compiled", "k_pred_interpreted": "pred_interpreted", "k_bw_copy": "bw_copy",
              "k_bw_read": "bw_read", "k_bw_write": "bw_write", "k_key_minmax": "key_minmax", "k_keymap": "keymap",
              "k_index_clear": "join_table_init", "k_index_build": "join_build", "k_group_merge": "group_merge",
-             "k_init_groups": "group_table_init", "k_index_verify": "join_index_verify"}
+             "k_init_groups": "group_table_init", "k_index_verify": "join_index_verify",
+             "k_join_probe_index": "join_probe"}
     return names.get(base, base)
 
 
