@@ -566,6 +566,9 @@ struct SlotSource {
     *sp = g.sum_price;
     *sq = g.sum_qty;
     *cnt = g.count;
+    drop(i);
+  }
+  __device__ void drop(int64_t i) const {  // (a group past the output's end, too)
     if (clean) slots[i] = GroupSlot{kGroupEmpty, 0, 0, 0};
   }
 };
@@ -580,13 +583,15 @@ struct RowAggSource {  // groupjoin accumulators, zeroed as they are read; the k
     *sp = r.sum_price;
     *sq = r.sum_qty;
     *cnt = r.count;
-    agg[i] = RowAgg{0, 0, 0};
+    drop(i);
   }
+  __device__ void drop(int64_t i) const { agg[i] = RowAgg{0, 0, 0}; }
 };
 
+// (four waves per SIMD: with 156 registers instead of 128 it took 114 us instead of 101 over 2M slots)
 template <class Src>
-__global__ __launch_bounds__(kBlock) void k_finalize(Src src, int64_t nitems, OutArgs o, uint64_t* __restrict__ state,
-                                                     int64_t* __restrict__ ticket, int64_t ngroups, JoinIndex wipe) {
+__global__ __launch_bounds__(kBlock, 4) void k_finalize(Src src, int64_t nitems, OutArgs o, uint64_t* __restrict__ state,
+                                                     int64_t* __restrict__ ticket, int64_t ngroups) {
   static_assert(kFinTile < (1 << 16) && kFinTilesPerTicket * 16 <= 64, "packed per-tile counts");
   __shared__ int64_t s_group;
   __shared__ uint64_t s_excl;
@@ -603,10 +608,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Src src, int64_t nitems, Ou
   if (threadIdx.x == 0) s_group = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)ticket, 1ull);
   __syncthreads();
   const int64_t group = s_group;
-  if (group >= ngroups) {  // the launch's other workgroups empty the join index
-    join_index_wipe(wipe, (group - ngroups) * kBlock + threadIdx.x, ((int64_t)gridDim.x - ngroups) * kBlock);
-    return;
-  }
   const int64_t t0 = group * kFinTilesPerTicket;
   uint32_t bits[kFinTilesPerTicket];
   uint64_t c = 0;
@@ -659,15 +660,16 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Src src, int64_t nitems, Ou
     int64_t pos = (int64_t)s_excl + before + (int64_t)((my_off >> (16 * g)) & 0xFFFFu);
     for (int k = 0; k < kFinIPT; ++k) {
       if (!(bits[g] & (1u << k))) continue;
-      int64_t key;
-      uint64_t sp, sq, cnt;
-      src.get(i0 + (int64_t)k * kBlock, &key, &sp, &sq, &cnt);  // (also empties the slot of a group past cap)
       if (pos < o.cap) {
+        int64_t key;
+        uint64_t sp, sq, cnt;
+        src.get(i0 + (int64_t)k * kBlock, &key, &sp, &sq, &cnt);
         o.key[pos] = key;
         o.sum_price[pos] = (int64_t)sp;
         o.sum_qty[pos] = (int64_t)sq;
         o.count[pos] = (int64_t)cnt;
       } else {
+        src.drop(i0 + (int64_t)k * kBlock);
         set_status(o.status, kDevOverflow);
       }
       ++pos;
@@ -689,20 +691,23 @@ rel_status finalize_state(rel_ctx* ctx, int64_t nitems, uint64_t** st) {
   return s;
 }
 
-// Workgroups of nt threads that empty a join index beside another kernel's work.
-unsigned wipe_grid(rel_ctx* ctx, const JoinIndex& x, int nt) {
+__global__ __launch_bounds__(kBlock) void k_index_wipe(JoinIndex x) {
+  join_index_wipe(x, blockIdx.x * (int64_t)kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+}
+
+// Workgroups of nt threads that empty a join index (beside another kernel's work: one per CU).
+unsigned wipe_grid(rel_ctx* ctx, const JoinIndex& x, int nt, int per_cu = 1) {
   const int64_t words = std::max<int64_t>((int64_t)x.hash.mask + 2, x.dense_cap / 4);
-  return relh::grid_for(ctx, words, (int64_t)nt * 8, 1);
+  return relh::grid_for(ctx, words, (int64_t)nt * 8, per_cu);
 }
 
 // zeroed: the look-back state (finalize_state) and the ticket counter are
 // already zero (an earlier kernel of the call cleared them), else they are
-// cleared here. wipe: a join index that this kernel empties (null: none).
+// cleared here.
 template <class Src>
-rel_status finalize(rel_ctx* ctx, const Src& src, int64_t nitems, const OutArgs& o, bool zeroed = false,
-                    const JoinIndex* wipe = nullptr) {
+rel_status finalize(rel_ctx* ctx, const Src& src, int64_t nitems, const OutArgs& o, bool zeroed = false) {
   // (when the kernel runs, its last group of tiles writes the group count)
-  if (nitems == 0 && o.n_wg == 0 && !wipe) return relh::fill_u64(ctx, o.d_n, 1, 0);
+  if (nitems == 0 && o.n_wg == 0) return relh::fill_u64(ctx, o.d_n, 1, 0);
   rel_status s;
   const int64_t ntiles = finalize_tiles(nitems);
   uint64_t* st;
@@ -714,8 +719,8 @@ rel_status finalize(rel_ctx* ctx, const Src& src, int64_t nitems, const OutArgs&
   }
   relh::KernelTimer kt(ctx, "finalize");
   const int64_t ngroups = (ntiles + kFinTilesPerTicket - 1) / kFinTilesPerTicket;
-  hipLaunchKernelGGL(k_finalize<Src>, dim3((unsigned)ngroups + (wipe ? wipe_grid(ctx, *wipe, kBlock) : 0u)), dim3(kBlock), 0,
-                     ctx->stream, src, nitems, o, (uint64_t*)st, ticket, ngroups, wipe ? *wipe : JoinIndex{});
+  hipLaunchKernelGGL(k_finalize<Src>, dim3((unsigned)ngroups), dim3(kBlock), 0, ctx->stream, src, nitems, o, (uint64_t*)st,
+                     ticket, ngroups);
   REL_LAUNCH_CHECK(ctx, "finalize");
   return REL_OK;
 }
@@ -1070,14 +1075,21 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     TRY(relh::join_index_verify(ctx, jx));  // (no probing kernel runs)
   }
 
+  // Without a merge kernel, whose other workgroups do it, a kernel of its own
+  // empties the index: beside the finalize kernel's workgroups the stores hold up
+  // its look-back (375K rows, 277K sparse dim keys, 221K groups: 109 us, 99 so).
+  const bool wipe = gp != G_LDS || n == 0;
   if (gp == G_ROWAGG) {
-    TRY(finalize(ctx, RowAggSource{(RowAgg*)gt, dim->pk}, m, oa, true, &jx));
+    TRY(finalize(ctx, RowAggSource{(RowAgg*)gt, dim->pk}, m, oa, true));
     ctx->scratch[SCR_ROW_AGG].dirty = false;
   } else {
-    // (the merge kernel has emptied the index)
     if (!merge_ends)
-      TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, true}, group_cap + 1, oa, true, gp == G_LDS && n > 0 ? nullptr : &jx));
+      TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, true}, group_cap + 1, oa, true));
     ctx->scratch[SCR_GROUP_CLEAN].clean = clean_after;
+  }
+  if (wipe) {
+    hipLaunchKernelGGL(k_index_wipe, dim3(wipe_grid(ctx, jx, kBlock, 8)), dim3(kBlock), 0, ctx->stream, jx);
+    REL_LAUNCH_CHECK(ctx, "index_wipe");
   }
   relh::join_index_wiped(ctx);
   return sync_stats(ctx, fact, dim, q, plan, out, stats, cnt, (int64_t)1 << jl, group_cap, REL_PLACE_GLOBAL,
