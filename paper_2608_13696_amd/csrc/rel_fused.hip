@@ -74,10 +74,13 @@ __device__ __forceinline__ int64_t group_key(int32_t payload, int32_t fk, int8_t
   return (int64_t)fk;
 }
 
-// One thread's rows of a tile: kIPT consecutive rows, loaded with 16-byte
-// non-temporal loads (6M rows from HBM beside a join index in L2: the whole
-// query 77.6 us against 83.0 with ordinary ones; the same when the columns are
-// in the last-level cache).
+// One thread's rows of a tile: kIPT consecutive rows, loaded with 16-byte loads.
+// `once`: non-temporal ones, which leave L2 to a dense join index and an LDS group
+// table's few device rows (6M rows: the whole query 75.3 us against 80.7 with
+// ordinary ones; the same when the columns are in the last-level cache). Beside a
+// hash index, which L2 does not hold, or a group table in device memory ordinary
+// ones are better (4.7M rows, 853K sparse keys: 95.2 against 98.1 us; 571K rows
+// into 294 groups of a device table: 339.6 against 344.3).
 struct FusedRows {
   int32_t d[kIPT], f[kIPT], q[kIPT];
   int64_t p[kIPT];
@@ -86,14 +89,24 @@ struct FusedRows {
 };
 
 template <int MODE>
-__device__ __forceinline__ void load_fused(const FusedArgs& a, int64_t r0, FusedRows& r) {
+__device__ __forceinline__ void load_fused(const FusedArgs& a, int64_t r0, bool once, FusedRows& r) {
   if (r0 + kIPT <= a.n) {
     r.nv = kIPT;
-    const int4 dv = ld_once(reinterpret_cast<const int4*>(a.day + r0));
-    const int4 fv = ld_once(reinterpret_cast<const int4*>(a.fk + r0));
-    const int4 qv = ld_once(reinterpret_cast<const int4*>(a.qty + r0));
-    const longlong2 p01 = ld_once(reinterpret_cast<const longlong2*>(a.price + r0));
-    const longlong2 p23 = ld_once(reinterpret_cast<const longlong2*>(a.price + r0 + 2));
+    int4 dv, fv, qv;
+    longlong2 p01, p23;
+    if (once) {
+      dv = ld_once(reinterpret_cast<const int4*>(a.day + r0));
+      fv = ld_once(reinterpret_cast<const int4*>(a.fk + r0));
+      qv = ld_once(reinterpret_cast<const int4*>(a.qty + r0));
+      p01 = ld_once(reinterpret_cast<const longlong2*>(a.price + r0));
+      p23 = ld_once(reinterpret_cast<const longlong2*>(a.price + r0 + 2));
+    } else {
+      dv = *reinterpret_cast<const int4*>(a.day + r0);
+      fv = *reinterpret_cast<const int4*>(a.fk + r0);
+      qv = *reinterpret_cast<const int4*>(a.qty + r0);
+      p01 = *reinterpret_cast<const longlong2*>(a.price + r0);
+      p23 = *reinterpret_cast<const longlong2*>(a.price + r0 + 2);
+    }
     r.d[0] = dv.x; r.d[1] = dv.y; r.d[2] = dv.z; r.d[3] = dv.w;
     r.f[0] = fv.x; r.f[1] = fv.y; r.f[2] = fv.z; r.f[3] = fv.w;
     r.q[0] = qv.x; r.q[1] = qv.y; r.q[2] = qv.z; r.q[3] = qv.w;
@@ -160,11 +173,12 @@ __global__ __launch_bounds__(NT) void k_fused(FusedArgs a) {
   }
   uint64_t passed = 0, matched = 0, dev_rows = 0;
   const DenseRange dr = dense_range(a.join);
+  const bool once = GP == G_LDS && dr.dense;
   constexpr int64_t tile_rows = (int64_t)NT * kIPT;
   const int64_t ntiles = (a.n + tile_rows - 1) / tile_rows;
   int64_t tile = blockIdx.x;
   FusedRows cur, nxt;
-  if (tile < ntiles) load_fused<MODE>(a, tile * tile_rows + (int64_t)threadIdx.x * kIPT, cur);
+  if (tile < ntiles) load_fused<MODE>(a, tile * tile_rows + (int64_t)threadIdx.x * kIPT, once, cur);
   // this workgroup's share of the dense index's duplicate check (a count of
   // its entries), while its first tile loads
   uint64_t entries = 0;
@@ -176,7 +190,7 @@ __global__ __launch_bounds__(NT) void k_fused(FusedArgs a) {
   }
   for (; tile < ntiles; tile += gridDim.x) {
     const int64_t tn = tile + gridDim.x;
-    if (tn < ntiles) load_fused<MODE>(a, tn * tile_rows + (int64_t)threadIdx.x * kIPT, nxt);
+    if (tn < ntiles) load_fused<MODE>(a, tn * tile_rows + (int64_t)threadIdx.x * kIPT, once, nxt);
     // every row's first join read (its dense entry, or its first hash slot)
     // is issued before any is examined, so the tile's random reads overlap
     // instead of following one another
