@@ -591,8 +591,10 @@ __device__ __forceinline__ bool w_plan(const BWhole& a, const BInst& I, WShared&
   return fits;
 }
 
-// Step 2: the join table, a slice of the range at a time.
-__device__ __forceinline__ void w_build(const BWhole& a, const BInst& I, WShared& s) {
+// Step 2: the join table, a slice of the range at a time. False: a dim key
+// occurs twice, and its entry is the bitwise or of two rows' values, which may
+// name a group that does not exist.
+__device__ __forceinline__ bool w_build(const BWhole& a, const BInst& I, WShared& s) {
   const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
   const int32_t m = (int32_t)I.m;
   const uint32_t range = w_uni(s.p.range), kmin = (uint32_t)w_uni(s.p.kmin);
@@ -640,11 +642,12 @@ __device__ __forceinline__ void w_build(const BWhole& a, const BInst& I, WShared
   if (w_uni(s.p.chunks) <= 1) s.sums(groups).clear(groups);
   for (uint32_t c = t; c <= (uint32_t)kWMaxChunks; c += kWBlock) s.cnt[c] = 0;
   __syncthreads();
-  if (t == 0) {
-    uint64_t e = 0;
-    for (int w = 0; w < kWBlock / kWave; ++w) e += s.red[2][w];
-    if (e != (uint64_t)m) set_status(a.status, kDevDupKey);
-  }
+  uint32_t e = 0;
+#pragma unroll
+  for (int w = 0; w < kWBlock / kWave; ++w) e += (uint32_t)s.red[2][w];
+  if (w_uni(e) == (uint32_t)m) return true;
+  if (t == 0) set_status(a.status, kDevDupKey);
+  return false;
 }
 
 // One thread's rows of a tile, all loads in flight together.
@@ -833,7 +836,11 @@ __global__ __launch_bounds__(kWBlock) void k_batch_whole(BWhole a) {
       __syncthreads();
       continue;
     }
-    w_build(a, I, s);
+    if (!w_build(a, I, s)) {  // (the call reports the key; the instance keeps the zeros it started with)
+      if (t == 0) a.done[inst] = 1u;
+      __syncthreads();
+      continue;
+    }
     if (w_uni(s.p.chunks) <= 1) w_rows<false>(a, I, s);
     else w_rows<true>(a, I, s);
     const int64_t out = w_groups(a, I, s);
