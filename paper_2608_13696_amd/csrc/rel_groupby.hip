@@ -46,6 +46,8 @@ struct GbArgs {
   uint32_t nb, shift;  // bins, 32 - log2(bins)
   int64_t ntiles;
   const uint32_t* more_tiles;  // with partials: beside ntiles (null: none)
+  uint32_t max_rows;           // that the memory is laid out for
+  uint32_t* status;
   relh::Partials part;
   uint32_t* hist;      // [ntiles][nb], then offsets
   uint32_t* chunk;     // [kGbChunks][nb]
@@ -56,7 +58,9 @@ struct GbArgs {
   int64_t* price;
   int32_t* qty;
   relh::PartialCols bin;  // the partials by bin
-  __device__ __forceinline__ int64_t tiles() const { return more_tiles ? ntiles + *more_tiles : ntiles; }
+  __device__ __forceinline__ int64_t tiles() const {
+    return more_tiles ? min(ntiles + (int64_t)*more_tiles, part.max_chunks) : ntiles;
+  }
 };
 
 __device__ __forceinline__ int64_t row_of(const GroupRows& in, int64_t i) { return in.sel ? (int64_t)ld_once(in.sel + i) : i; }
@@ -168,6 +172,13 @@ __global__ __launch_bounds__(kGbBlock) void k_gb_units(GbArgs a) {
   uint32_t total, n_units;
   uint32_t lo = block_excl_scan<kGbBlock>(rows, scr, &total);
   uint32_t u = block_excl_scan<kGbBlock>(pieces, scr, &n_units);
+  if (total > a.max_rows) {  // (partials, and only of a repeated dim key: see k_part_join_eager)
+    if (threadIdx.x == 0) {
+      *a.n_units = 0;
+      set_status(a.status, kDevDupKey);
+    }
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const uint32_t b = threadIdx.x * kPer + k;
@@ -200,7 +211,7 @@ __global__ __launch_bounds__(kGbBlock) void k_gb_scatter(GbArgs a) {
   constexpr int kRows = GbRow<P>::kRows;
   if (*a.few) return;
   const int64_t ntiles = P ? a.tiles() : (int64_t)gridDim.x;
-  if (blockIdx.x >= ntiles) return;
+  if (blockIdx.x >= ntiles || (P && *a.n_units == 0)) return;
   const uint32_t t = threadIdx.x;
   constexpr int kPer = kGbMaxBins / kGbBlock;
 #pragma unroll
@@ -518,6 +529,8 @@ rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expect
   GbArgs a{};
   a.in = in;
   a.few = few;
+  a.max_rows = (uint32_t)in.n;
+  a.status = g.status;
   a.nb = 1u << bits;
   a.shift = 32 - bits;
   a.ntiles = (in.n + kGbTile - 1) / kGbTile;
@@ -598,6 +611,8 @@ rel_status partials_reduce(rel_ctx* ctx, const Partials& p, int64_t expected, co
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   GbArgs a{};
   a.few = zero;
+  a.max_rows = (uint32_t)p.max_rows;
+  a.status = g.status;
   a.nb = p.nb;
   a.shift = p.shift;
   a.ntiles = p.first_chunks;

@@ -2248,6 +2248,7 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
   const uint32_t tid = threadIdx.x, lane = lane_id();
   uint64_t matched = 0;
   [[maybe_unused]] uint32_t chunk = blockIdx.x, fill = 0;
+  [[maybe_unused]] bool full = false;  // no chunk was left
   if constexpr (P) {
     for (uint32_t b = tid; b < a.part.nb; b += kABlock) out.bins[b] = 0;
   } else {
@@ -2257,10 +2258,10 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
   [[maybe_unused]] auto close_chunk = [&] {
     if constexpr (P) {
       for (uint32_t b = tid; b < a.part.nb; b += kABlock) {
-        a.part.hist[(size_t)chunk * a.part.nb + b] = out.bins[b];
+        if (!full) a.part.hist[(size_t)chunk * a.part.nb + b] = out.bins[b];
         out.bins[b] = 0;
       }
-      if (tid == 0) a.part.fill[chunk] = fill;
+      if (tid == 0 && !full) a.part.fill[chunk] = fill;
     }
   };
   // units in static round robin from the largest-first list, thread 0 a unit ahead
@@ -2432,12 +2433,20 @@ __global__ __launch_bounds__(kABlock, 4) void k_part_join_eager(AggArgs a) {
         __syncthreads();
         chunk = out.chunk;
         fill = 0;
+        full = chunk >= (uint32_t)a.part.max_chunks;
+      }
+      if (full) {
+        // More partials than fact rows, or than dim keys and sub-units allow:
+        // a key occurs in several chunks of a partition's dim keys, each of which
+        // all its fact rows probe. The call reports the key; no partial is kept.
+        if (tid == 0) set_status(a.status, kDevDupKey);
+        total = 0;
       }
       const size_t at = (size_t)chunk * relh::kPartialTile + fill;
 #pragma unroll
       for (int k = 0; k < kPer; ++k) {
         const int s = k * kABlock + tid;
-        if (c[k] == 0) continue;
+        if (c[k] == 0 || full) continue;
         const size_t o = at + base[k] + mask_rank(bal[k]);
         a.part.cols.key[o] = tpay[s];
         a.part.cols.price[o] = tsp[s];
@@ -2797,7 +2806,8 @@ rel_status partitioned_groupjoin(rel_ctx* ctx, const rel_fact* fact, const rel_d
 // with the rows when the key needs it), and k_part_join_agg aggregates into
 // the device-memory group table g with an LDS table in front of it.
 void partials_bounds(rel_ctx* ctx, int64_t n, int64_t m, int64_t* max_rows, unsigned* workgroups, size_t* fact_bytes) {
-  // one per dim key of a whole unit, at most kJChunk per sub-unit of a split one; each has a row
+  // one per dim key of a whole unit, at most kJChunk per sub-unit of a split one;
+  // each has a row of its own (a repeated key's may not: the kernels watch the bound)
   *max_rows = std::min<int64_t>(n, m + (n / kSubRows + kMaxSplit) * kJChunk);
   *workgroups = join_agg_grid(ctx);
   *fact_bytes = part_fact_bytes(n);

@@ -67,3 +67,31 @@ def test_hot_repeated_key_in_a_batch(ctx, by, m, span, attrs):
         assert_groups_equal(rel.sorted_groups(batch.outs[1].host()), oracle.run_tables(good)[0], "beside a repeated key")
     batch.close()
     assert ctx.sync() == 0
+
+
+def _one_partition(keys):
+    """int32 keys whose hashes in the partitioned join are 0, 1, ..: all in one partition."""
+    inv = pow(2654435769, -1, 2**32)
+    return (np.arange(keys, dtype=np.uint64) * np.uint64(inv) & np.uint64(2**32 - 1)).astype(np.uint32).view(np.int32)
+
+
+# A key in several chunks of a partition's dim keys gives each of them a partial sum of the same rows: more partial
+# sums than fact rows, and (8M rows) than there are chunks of memory for.
+@pytest.mark.parametrize("n,m,keys", [(1, 6000, 1), (100, 200_000, 1), (100, 40_000, 3), (3000, 300_000, 700), (5000, 8_000_000, 1000)])
+def test_key_in_many_chunks_of_a_planned_join(n, m, keys):
+    pk = _one_partition(keys)
+    T = datagen.make_tables(n, m, 7 + m, day_lt=2556, group_by="dim_grp", grp_card=9)
+    T.pk, T.fk = np.resize(pk, m), np.resize(pk, n)
+    T.grp = (np.arange(m) % 5000).astype(np.int32)
+    fact, dim = to_dev(T)
+    good = _tables(9000, 2500, "dim_grp", 8, 2000)
+    good.day_lt = T.day_lt
+    plan = lambda: rel.Plan(6000, rel.PLACE["global"], rel.PLACE["partitioned"], 0, 0)  # noqa: E731
+    c = rel.Context(0)  # (with no memory of an earlier, larger call)
+    with pytest.raises(rel.RelError) as e:
+        c.filter_join_agg(fact, dim, T.day_lt, "dim_grp", plan=plan())
+    assert e.value.status == rel.DUPLICATE_KEY
+    gf, gd = to_dev(good)
+    out, _ = c.filter_join_agg(gf, gd, good.day_lt, "dim_grp", plan=plan())
+    assert_groups_equal(rel.sorted_groups(out.host()), oracle.run_tables(good)[0], "the next call")
+    c.close()
