@@ -64,6 +64,15 @@ rel_status scratch(rel_ctx* ctx, int id, size_t bytes, void** out) {
   return REL_OK;
 }
 
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 rel_status ensure_counters(rel_ctx* ctx) {
   void* p;
   return scratch(ctx, SCR_COUNTERS, CNT_WORDS * sizeof(int64_t), &p);

@@ -757,6 +757,12 @@ rel_status init_groups(rel_ctx* ctx, GroupSlot* slots, int64_t nslots) {
   return REL_OK;
 }
 
+// An empty group table in SCR_GROUP_CLEAN.
+rel_status clean_groups(rel_ctx* ctx, int64_t nslots, void** out) {
+  return relh::scratch_empty(ctx, SCR_GROUP_CLEAN, (size_t)nslots * sizeof(GroupSlot), out,
+                             [&](void* p) { return init_groups(ctx, (GroupSlot*)p, nslots); });
+}
+
 bool out_ok(const rel_groups_out* out) {
   return out && out->key && out->sum_price && out->sum_qty && out->count && out->d_n_groups && out->cap >= 0;
 }
@@ -845,15 +851,9 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
   const bool lds = placement == REL_PLACE_LDS || (placement == REL_PLACE_AUTO && (few_expected || !hinted));
   const bool many = placement == REL_PLACE_GLOBAL || (placement == REL_PLACE_AUTO && !few_expected);
   const bool partition = placement == REL_PLACE_AUTO && many && n >= (hinted ? kGroupbyPartitionRows : 2 * kGroupbyPartitionRows);
-  // the table is left empty by the finalize kernel, so only its first use (or a larger one) clears it
   const int64_t nslots = (1ll << l) + 1;
-  const size_t gbytes = (size_t)nslots * sizeof(GroupSlot);
-  void* tbl;
-  TRY(relh::scratch(ctx, SCR_GROUP_CLEAN, gbytes, &tbl));
-  ScratchBuf& sb = ctx->scratch[SCR_GROUP_CLEAN];
-  const size_t clean_after = sb.clean > gbytes ? sb.clean : gbytes;
-  if (sb.clean < gbytes) TRY(init_groups(ctx, (GroupSlot*)tbl, nslots));
-  sb.clean = 0;  // until this call's finalize kernel is enqueued
+  void* tbl;  // (left empty by the finalize kernel)
+  TRY(clean_groups(ctx, nslots, &tbl));
   const uint32_t probe = hinted ? kPlannedProbe : (uint32_t)(1ull << l);
   const GroupView g{(GroupSlot*)tbl, (uint32_t)((1ull << l) - 1), 32u - l, ctx->d_status, probe};
   const relh::GroupRows in{key, price, qty, sel, n};
@@ -863,13 +863,13 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
   uint32_t* few = (uint32_t*)(cnt + CNT_AUX2);
   uint64_t* state;
   TRY(finalize_state(ctx, nslots, &state));
+  const unsigned grid = relh::grid_for(ctx, n, partition || !many ? kLdsBlock * kGbAhead : kLdsBlock, 1);
+  Stage stage{};
+  if (lds) TRY(take_stage(ctx, grid, flags, &stage));
   const int mode = !many ? relh::GB_FEW : !lds ? relh::GB_MANY : relh::GB_SAMPLE;
   TRY(relh::groupby_begin(ctx, in, mode, few, (uint64_t*)cnt, CNT_AUX2, state, finalize_tiles(nslots)));
   OutArgs oa = out_args(ctx, out);
   if (lds) {
-    const unsigned grid = relh::grid_for(ctx, n, partition || !many ? kLdsBlock * kGbAhead : kLdsBlock, 1);
-    Stage stage;
-    TRY(take_stage(ctx, grid, flags, &stage));
     relh::KernelTimer kt(ctx, "groupby");
     hipLaunchKernelGGL(k_groupby_lds, dim3(grid), dim3(kLdsBlock), 0, ctx->stream, in, (const uint32_t*)few, g,
                        few_expected || placement == REL_PLACE_LDS ? kLdsProbe : kLdsCacheProbe, !partition, stage);
@@ -890,7 +890,7 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
     oa.limit = hinted ? nslots : INT64_MAX;
   }
   TRY(finalize(ctx, SlotSource{(GroupSlot*)tbl, nslots - 1, true}, nslots, oa, true));
-  ctx->scratch[SCR_GROUP_CLEAN].clean = clean_after;
+  relh::scratch_emptied(ctx, SCR_GROUP_CLEAN);
   return REL_OK;
 }
 
@@ -953,7 +953,6 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   int64_t group_cap = 0;
   uint32_t gl = 0;
   void* gt = nullptr;
-  size_t clean_after = 0;
   bool eager = false, by_partials = false;
   relh::Partials partials{};
   int64_t partials_expected = 0;
@@ -961,14 +960,10 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     gp = G_ROWAGG;  // group key == join key: per-dim-row accumulators
     group_cap = m;
     const size_t bytes = (size_t)(m > 0 ? m : 1) * sizeof(RowAgg);
-    TRY(relh::scratch(ctx, SCR_ROW_AGG, bytes, &gt));
-    ScratchBuf& sb = ctx->scratch[SCR_ROW_AGG];
-    if (sb.clean < bytes) {
+    TRY(relh::scratch_empty(ctx, SCR_ROW_AGG, bytes, &gt, [&](void* p) {
       relh::KernelTimer kt(ctx, "group_table_init");
-      TRY(relh::fill_u64(ctx, gt, bytes / 8, 0));
-      sb.clean = bytes;
-    }
-    sb.dirty = true;  // until this call's finalize kernel is enqueued
+      return relh::fill_u64(ctx, p, bytes / 8, 0);
+    }));
     a.row_agg = (RowAgg*)gt;
   } else {
     const int64_t ub = gb == REL_GROUP_PRIO_FLAG ? (n < 65536 ? n : 65536) : (n < m ? n : m);
@@ -985,7 +980,6 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     gl = group_log2cap(expected, 0.5);
     if (gl > 31) return relh::fail(ctx, REL_UNSUPPORTED, "rel_filter_join_agg: group table above 2^31 slots");
     group_cap = 1ll << gl;
-    const size_t gbytes = (size_t)(group_cap + 1) * sizeof(GroupSlot);
     eager = part && gb == REL_GROUP_DIM_GRP && (gp != G_LDS || a.lds_probe != kLdsProbe);
     // The partial sums of a planned call are partitioned by group and summed in
     // LDS; the device table takes three atomics for each. Measured, device table
@@ -1006,16 +1000,10 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
       partials_expected = expected;
     }
     if (part && !by_partials) {
-      TRY(relh::scratch(ctx, SCR_GROUP_TABLE, gbytes, &gt));
+      TRY(relh::scratch(ctx, SCR_GROUP_TABLE, (size_t)(group_cap + 1) * sizeof(GroupSlot), &gt));
       TRY(init_groups(ctx, (GroupSlot*)gt, group_cap + 1));
     } else {
-      // this table is emptied again by the kernel that reads it, so only its
-      // first use (or a larger one) clears it
-      TRY(relh::scratch(ctx, SCR_GROUP_CLEAN, gbytes, &gt));
-      ScratchBuf& sb = ctx->scratch[SCR_GROUP_CLEAN];
-      clean_after = sb.clean > gbytes ? sb.clean : gbytes;
-      if (sb.clean < gbytes) TRY(init_groups(ctx, (GroupSlot*)gt, group_cap + 1));
-      sb.clean = 0;  // until this call's finalize kernel is enqueued
+      TRY(clean_groups(ctx, group_cap + 1, &gt));  // emptied again by the kernel that reads it
     }
     a.groups = GroupView{(GroupSlot*)gt, (uint32_t)(group_cap - 1), 32u - gl, ctx->d_status,
                          planned ? kPlannedProbe : (uint32_t)group_cap};
@@ -1038,7 +1026,7 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
       oa.limit = planned ? group_cap + 1 : INT64_MAX;
     }
     TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, by_partials}, group_cap + 1, oa));
-    if (by_partials) ctx->scratch[SCR_GROUP_CLEAN].clean = clean_after;
+    if (by_partials) relh::scratch_emptied(ctx, SCR_GROUP_CLEAN);
     return sync_stats(ctx, fact, dim, q, plan, out, stats, cnt, m, group_cap, REL_PLACE_PARTITIONED,
                       gp == G_LDS ? REL_PLACE_LDS : REL_PLACE_GLOBAL);
   }
@@ -1055,25 +1043,26 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   const uint32_t jl = relh::join_log2cap(m, nullptr);
   const void* payload = gb == REL_GROUP_PRIO_FLAG ? (const void*)dim->prio : gb == REL_GROUP_DIM_GRP ? (const void*)dim->grp : nullptr;
   const int pkind = gb == REL_GROUP_PRIO_FLAG ? relh::PAY_I8 : gb == REL_GROUP_DIM_GRP ? relh::PAY_I32 : relh::PAY_ROW_ID;
+  const bool merge_ends = gp == G_LDS && n > 0 && n <= kMergeEndsRows;
+  const unsigned grid = gp != G_LDS  ? relh::grid_for(ctx, n, kBlock * kIPT, 8)
+                        : merge_ends ? relh::grid_for(ctx, n, kBlock * kIPT, 1)
+                                     : relh::grid_for(ctx, n, kLdsBlock * kIPT, 1);
+  uint32_t* flags = (uint32_t*)(cnt + CNT_AUX1);  // [0] touched, [1] done
+  // (all memory of the call is taken before the first kernel that fills a table)
+  void* wc;
+  TRY(relh::scratch(ctx, SCR_WG_COUNTS, (size_t)grid * 24, &wc));
+  if (gp == G_LDS) TRY(take_stage(ctx, grid, flags, &a.stage));
   JoinIndex jx{};
   TRY(relh::join_index_build(ctx, dim->pk, payload, pkind, m, (uint32_t*)(cnt + CNT_AUX2), zero, &jx));
   a.join = jx;
-  const bool merge_ends = gp == G_LDS && n > 0 && n <= kMergeEndsRows;
 
   OutArgs oa = out_args(ctx, out);
   if (n > 0) {
-    const unsigned grid = gp != G_LDS  ? relh::grid_for(ctx, n, kBlock * kIPT, 8)
-                          : merge_ends ? relh::grid_for(ctx, n, kBlock * kIPT, 1)
-                                       : relh::grid_for(ctx, n, kLdsBlock * kIPT, 1);
-    void* wc;
-    TRY(relh::scratch(ctx, SCR_WG_COUNTS, (size_t)grid * 24, &wc));
     a.wg_counts = (uint64_t*)wc;
     oa.wg_counts = a.wg_counts;
     oa.n_wg = grid;
     oa.counters = cnt;
     oa.join = jx;
-    uint32_t* flags = (uint32_t*)(cnt + CNT_AUX1);  // [0] touched, [1] done
-    if (gp == G_LDS) TRY(take_stage(ctx, grid, flags, &a.stage));
     if (gb == REL_GROUP_PRIO_FLAG) TRY(launch_fused<M_PRIO_FLAG>(ctx, gp, a, grid));
     else if (gb == REL_GROUP_FK) TRY(launch_fused<M_FK>(ctx, gp, a, grid));
     else TRY(launch_fused<M_DIM_GRP>(ctx, gp, a, grid));
@@ -1095,17 +1084,17 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   const bool wipe = gp != G_LDS || n == 0;
   if (gp == G_ROWAGG) {
     TRY(finalize(ctx, RowAggSource{(RowAgg*)gt, dim->pk}, m, oa, true));
-    ctx->scratch[SCR_ROW_AGG].dirty = false;
+    relh::scratch_emptied(ctx, SCR_ROW_AGG);
   } else {
     if (!merge_ends)
       TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, true}, group_cap + 1, oa, true));
-    ctx->scratch[SCR_GROUP_CLEAN].clean = clean_after;
+    relh::scratch_emptied(ctx, SCR_GROUP_CLEAN);
   }
   if (wipe) {
     hipLaunchKernelGGL(k_index_wipe, dim3(wipe_grid(ctx, jx, kBlock, 8)), dim3(kBlock), 0, ctx->stream, jx);
     REL_LAUNCH_CHECK(ctx, "index_wipe");
   }
-  relh::join_index_wiped(ctx);
+  relh::join_index_wiped(ctx, jx);
   return sync_stats(ctx, fact, dim, q, plan, out, stats, cnt, (int64_t)1 << jl, group_cap, REL_PLACE_GLOBAL,
                     gp == G_LDS ? REL_PLACE_LDS : REL_PLACE_GLOBAL);
 }

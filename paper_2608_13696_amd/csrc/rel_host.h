@@ -124,6 +124,26 @@ rel_status fail(rel_ctx* ctx, rel_status s, const char* fmt, ...);
 rel_status hip_fail(rel_ctx* ctx, hipError_t e, const char* what);
 // Device buffer of at least `bytes` in scratch slot `id` (contents undefined).
 rel_status scratch(rel_ctx* ctx, int id, size_t bytes, void** out);
+// The stream's work is being recorded, not run (or the runtime cannot say).
+bool capturing(hipStream_t stream);
+// Scratch that is empty between calls: every call finds it so and its last
+// kernels leave it so, which it tells by scratch_emptied once they are enqueued.
+// Memory that is not known to be empty (a first use, a larger one, one after a
+// call that failed on the way) is emptied by fill(p). A recorded fill counts for
+// the recorded call only: it has not run when the next call is made.
+template <class Fill>
+rel_status scratch_empty(rel_ctx* ctx, int id, size_t bytes, void** out, Fill&& fill) {
+  rel_status s = scratch(ctx, id, bytes, out);
+  if (s != REL_OK) return s;
+  ScratchBuf& b = ctx->scratch[id];
+  if (b.clean < bytes) {
+    s = fill(*out);
+    if (s == REL_OK && !capturing(ctx->stream)) b.clean = bytes;
+  }
+  b.dirty = true;
+  return s;
+}
+inline void scratch_emptied(rel_ctx* ctx, int id) { ctx->scratch[id].dirty = false; }
 int64_t* counters(rel_ctx* ctx);  // valid after ensure_counters
 rel_status ensure_counters(rel_ctx* ctx);
 

@@ -428,16 +428,9 @@ rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload
   const uint32_t jl = join_log2cap(m, nullptr);
   const size_t hash_bytes = ((size_t)8 << jl) + 8;
   rel_status s;
-  // both structures are empty between calls (join_index_wipe), so only their
-  // first use, or a larger one, fills them
+  // both structures are empty between calls (join_index_wipe)
   auto empty = [&](int id, size_t bytes, uint64_t word, void** p) {
-    rel_status r = scratch(ctx, id, bytes, p);
-    ScratchBuf& sb = ctx->scratch[id];
-    if (r == REL_OK && sb.clean < bytes) {
-      r = fill_u64(ctx, *p, (bytes + 7) / 8, word);
-      if (r == REL_OK) sb.clean = bytes;
-    }
-    return r;
+    return scratch_empty(ctx, id, bytes, p, [&](void* q) { return fill_u64(ctx, q, (bytes + 7) / 8, word); });
   };
   void *jt, *dt = nullptr, *part = nullptr;
   if ((s = empty(SCR_JOIN_TABLE, hash_bytes, rel::kJoinEmpty, &jt)) != REL_OK) return s;
@@ -458,16 +451,13 @@ rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload
     const int32_t parts = key_minmax(ctx, pk, m, (uint32_t*)part, zero);
     s = index_entries(ctx, pk, payload_kind, x, (const uint32_t*)part, parts);
   }
-  // until join_index_wiped: whatever happens to the call, the next one does not trust the memory
-  ctx->scratch[SCR_JOIN_TABLE].dirty = true;
-  ctx->scratch[SCR_DENSE].dirty = true;
   *out = x;
   return s;
 }
 
-void join_index_wiped(rel_ctx* ctx) {
-  ctx->scratch[SCR_JOIN_TABLE].dirty = false;
-  ctx->scratch[SCR_DENSE].dirty = false;
+void join_index_wiped(rel_ctx* ctx, const rel::JoinIndex& x) {
+  scratch_emptied(ctx, SCR_JOIN_TABLE);
+  if (x.dense) scratch_emptied(ctx, SCR_DENSE);
 }
 
 rel_status join_index_verify(rel_ctx* ctx, const rel::JoinIndex& x) {
@@ -524,17 +514,8 @@ rel::JoinIndex table_index(const rel_join_table* t, const int32_t* payload) {
 // stream, whose kernels follow the old ones'; any other goes back through
 // hipFree, which waits for the device. Under capture nothing is kept or
 // reused, so that no graph holds memory that another table gets.
-bool capturing(hipStream_t stream) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;
-  }
-  return st != hipStreamCaptureStatusNone;
-}
-
 rel_status take_table(rel_ctx* ctx, size_t bytes, uint64_t** out) {
-  if (!capturing(ctx->stream)) {
+  if (!relh::capturing(ctx->stream)) {
     std::lock_guard<std::mutex> lock(ctx->table_mu);
     ScratchBuf& b = ctx->spare;
     if (b.ptr && b.bytes == bytes && ctx->spare_stream == ctx->stream) {
@@ -644,7 +625,7 @@ rel_status rel_join_table_destroy(rel_join_table* t) {
   bool last = false;
   {
     std::lock_guard<std::mutex> lock(ctx->table_mu);
-    if (!ctx->closed && !t->many_streams && !capturing(t->stream)) {
+    if (!ctx->closed && !t->many_streams && !relh::capturing(t->stream)) {
       std::swap(give, ctx->spare.ptr);
       ctx->spare.bytes = t->bytes;
       ctx->spare_stream = t->stream;

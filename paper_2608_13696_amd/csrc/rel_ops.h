@@ -31,7 +31,7 @@ struct ZeroSpans {
 };
 rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
                             uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out);
-void join_index_wiped(rel_ctx* ctx);
+void join_index_wiped(rel_ctx* ctx, const rel::JoinIndex& x);
 rel_status join_index_verify(rel_ctx* ctx, const rel::JoinIndex& x);
 // Order-encoded minimum and maximum of pk[0..m) per workgroup: pair i is
 // {max of ~(key ^ 2^31), max of (key ^ 2^31)} over workgroup i's keys, so the

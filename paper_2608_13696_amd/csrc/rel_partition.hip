@@ -2620,9 +2620,7 @@ rel_status partition_both(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim
   // left zero by every call (the last sub-unit of a chunk clears what it emits)
   void* pe;
   const size_t split_bytes = (size_t)kMaxSplit * kJSlots * sizeof(SplitAcc) + (kMaxSplit + 1) * sizeof(uint32_t);
-  const bool fresh = ctx->scratch[SCR_PART_E].bytes < split_bytes;
-  TRY(scratch(ctx, SCR_PART_E, split_bytes, &pe));
-  if (fresh) TRY(fill_u32(ctx, pe, split_bytes / 4, 0));
+  TRY(scratch_empty(ctx, SCR_PART_E, split_bytes, &pe, [&](void* q) { return fill_u32(ctx, q, split_bytes / 4, 0); }));
   uint32_t* split_done = (uint32_t*)((char*)pe + (size_t)kMaxSplit * kJSlots * sizeof(SplitAcc));
   uint32_t* split_ctr = split_done + kMaxSplit;
 
@@ -2798,6 +2796,7 @@ rel_status partitioned_groupjoin(rel_ctx* ctx, const rel_fact* fact, const rel_d
   const unsigned grid = (unsigned)ctx->num_cus * 3;  // 48 KB of LDS each: three per CU
   hipLaunchKernelGGL(k_part_groupjoin, dim3(grid), dim3(kJBlock), 0, ctx->stream, a);
   REL_LAUNCH_CHECK(ctx, "part_groupjoin");
+  scratch_emptied(ctx, SCR_PART_E);
   return REL_OK;
 }
 
@@ -2850,6 +2849,7 @@ rel_status partitioned_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_di
   else if (eager) hipLaunchKernelGGL(k_part_join_eager<false>, dim3(grid), dim3(kABlock), 0, ctx->stream, a);
   else hipLaunchKernelGGL(k_part_join_agg<REL_GROUP_DIM_GRP>, dim3(grid), dim3(kABlock), 0, ctx->stream, a);
   REL_LAUNCH_CHECK(ctx, "part_join_agg");
+  scratch_emptied(ctx, SCR_PART_E);
   return REL_OK;
 }
 
