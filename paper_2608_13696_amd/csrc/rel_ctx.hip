@@ -280,6 +280,7 @@ rel_status rel_ctx_destroy(rel_ctx* ctx) {
 rel_status rel_ctx_set_stream(rel_ctx* ctx, void* hip_stream) {
   if (!ctx) return REL_INVALID_ARG;
   ctx->stream = (hipStream_t)hip_stream;
+  ++ctx->stream_turn;
   return REL_OK;
 }
 

@@ -70,6 +70,7 @@ struct KernelTiming {
 struct rel_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
+  uint64_t stream_turn = 0;  // how often the stream was set: a stream's address may come back as another stream's
   int num_cus = 256;
   size_t lds_per_block = 65536;
   // Device status words (64 x u32, one allocation). Word 0 is the sticky word
@@ -94,12 +95,12 @@ struct rel_ctx {
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // Under table_mu (a table may be destroyed by another thread than the one
   // that uses the context): memory of the last destroyed join table, for the
-  // next one of its size, with the one stream it was used on; and the number
-  // of join tables alive. A context destroyed before its tables keeps this
+  // next one of its size, with the stream_turn that it was used in; and the
+  // number of join tables alive. A context destroyed before its tables keeps this
   // struct (all else freed) until the last of them is gone.
   std::mutex table_mu;
   ScratchBuf spare;
-  hipStream_t spare_stream = nullptr;
+  uint64_t spare_turn = 0;
   int tables = 0;
   bool closed = false;
 };
@@ -112,8 +113,8 @@ struct rel_join_table {
   int64_t m = 0;
   bool may_be_dense = false;  // dense or hash by the keys' range, known on the device only
   bool wide = false;          // built with a payload column
-  hipStream_t stream = nullptr;       // the stream it was built on
-  mutable bool many_streams = false;  // and probed on another one
+  uint64_t turn = 0;           // the context's stream_turn when it was built
+  mutable bool keep = true;    // all its work went to that stream, and none was recorded
 };
 
 namespace relh {

@@ -510,15 +510,17 @@ rel::JoinIndex table_index(const rel_join_table* t, const int32_t* payload) {
 // (one buffer, freed with the context, when another one takes its place or
 // when an allocation fails), because allocating and freeing the 256 MB of a
 // 15M-key table for each query took 0.3 ms, as long as building and probing
-// it. A table that only ever saw one stream is kept, for a table on the same
-// stream, whose kernels follow the old ones'; any other goes back through
-// hipFree, which waits for the device. Under capture nothing is kept or
-// reused, so that no graph holds memory that another table gets.
+// it. The memory of a table whose work all went to one stream is kept, for a
+// table on the same stream, whose kernels follow the old ones'; any other goes
+// back through hipFree, which waits for the device. The stream is the caller's
+// and may be gone by now, so it is told by the context's turns, not by its
+// address, and not asked. Of recorded work nothing is kept or reused, so that no
+// graph holds memory that another table gets.
 rel_status take_table(rel_ctx* ctx, size_t bytes, uint64_t** out) {
   if (!relh::capturing(ctx->stream)) {
     std::lock_guard<std::mutex> lock(ctx->table_mu);
     ScratchBuf& b = ctx->spare;
-    if (b.ptr && b.bytes == bytes && ctx->spare_stream == ctx->stream) {
+    if (b.ptr && b.bytes == bytes && ctx->spare_turn == ctx->stream_turn) {
       *out = (uint64_t*)b.ptr;
       b = ScratchBuf{};
       return REL_OK;
@@ -543,9 +545,9 @@ rel_status take_table(rel_ctx* ctx, size_t bytes, uint64_t** out) {
   return REL_OK;
 }
 
-// A kernel of the context's stream is about to use the table.
-void note_stream(const rel_join_table* t) {
-  if (t->stream != t->ctx->stream) t->many_streams = true;
+// Kernels of the context's stream are about to use the table.
+void note_use(const rel_join_table* t) {
+  if (t->turn != t->ctx->stream_turn || relh::capturing(t->ctx->stream)) t->keep = false;
 }
 
 rel_status build_table(rel_ctx* ctx, const int32_t* pk, const int32_t* payload, const rel_join_table* t) {
@@ -597,12 +599,13 @@ rel_status rel_join_build(rel_ctx* ctx, const int32_t* pk, const int32_t* payloa
   t->log2cap = l;
   t->m = m;
   t->may_be_dense = m >= kDenseMinKeys && relh::aligned16(pk);  // (the range is found by 16-byte loads)
-  t->stream = ctx->stream;
+  t->turn = ctx->stream_turn;
   t->wide = payload != nullptr;
   const size_t bytes = ((size_t)8 << l) + 8;
   t->bytes = (bytes + 15) / 16 * 16 + kTailBytes;
   rel_status s = take_table(ctx, t->bytes, &t->slots);
   if (s == REL_OK) {
+    note_use(t);
     s = build_table(ctx, pk, payload, t);
     if (s != REL_OK) (void)hipFree(t->slots);
   }
@@ -625,10 +628,10 @@ rel_status rel_join_table_destroy(rel_join_table* t) {
   bool last = false;
   {
     std::lock_guard<std::mutex> lock(ctx->table_mu);
-    if (!ctx->closed && !t->many_streams && !relh::capturing(t->stream)) {
+    if (!ctx->closed && t->keep) {
       std::swap(give, ctx->spare.ptr);
       ctx->spare.bytes = t->bytes;
-      ctx->spare_stream = t->stream;
+      ctx->spare_turn = t->turn;
     }
     last = --ctx->tables == 0 && ctx->closed;
   }
@@ -648,7 +651,7 @@ rel_status rel_join_probe(rel_ctx* ctx, const rel_join_table* t, const int32_t* 
   rel_status s = relh::fill_u64(ctx, d_out_count, 1, 0);
   if (s != REL_OK || n == 0) return s;
   const rel::JoinIndex x = table_index(t, nullptr);
-  note_stream(t);
+  note_use(t);
   const unsigned grid = relh::grid_for(ctx, n, kProbeBlock * kProbeRows, 8);
   relh::KernelTimer kt(ctx, "join_probe");
   auto* kernel = !t->may_be_dense ? &k_join_probe : t->wide ? &k_join_probe_index<true> : &k_join_probe_index<false>;

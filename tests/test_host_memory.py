@@ -28,3 +28,46 @@ def test_recorded_fill_counts_for_the_recorded_call_only(host, by):
     assert query(c, *large, {by!r}) == 0 and launched(kernels(), fill)  # nothing has run yet
     assert query(c, *large, {by!r}) == 0 and not launched(kernels(), fill)
     """)
+
+
+def test_table_memory_is_kept_for_a_stream_while_the_context_is_on_it(host):
+    host("""
+    c = new_ctx(0x1000)
+    st, t = table(c, 100_000); assert st == 0
+    slots = stub.stub_used()
+    L.rel_join_table_destroy(t)
+    assert stub.stub_used() == slots and stub.stub_frees() == 0
+    st, t = table(c, 100_000)  # takes it again
+    assert stub.stub_used() == slots
+    L.rel_ctx_set_stream(c, ctypes.c_void_p(0x2000))
+    stub.stub_kill(0x1000)  # the borrowed stream's owner destroys it
+    L.rel_join_table_destroy(t)
+    assert stub.stub_dead_uses() == 0
+    stub.stub_revive(0x1000)  # a new stream at the old one's address: nothing orders it after the old one's work
+    L.rel_ctx_set_stream(c, ctypes.c_void_p(0x1000))
+    st, t2 = table(c, 100_000)
+    assert stub.stub_used() > slots or stub.stub_frees() == 1
+    L.rel_join_table_destroy(t2)
+    L.rel_ctx_destroy(c)
+    assert stub.stub_used() == 0
+    """)
+
+
+def test_table_memory_of_recorded_work_is_not_kept(host):
+    host("""
+    c = new_ctx()
+    st, t = table(c, 100_000)
+    stub.stub_capture(1)
+    assert L.rel_join_probe(c, t, column(), None, 1000, column(), column(), 1000, column()) == 0
+    stub.stub_capture(0)
+    L.rel_join_table_destroy(t)
+    assert stub.stub_frees() == 1
+    st, t = table(c, 100_000)
+    L.rel_join_table_destroy(t)
+    assert stub.stub_frees() == 1
+    stub.stub_capture(1)  # kept memory is not for a recorded build either, and a recorded build's is not kept
+    st, t = table(c, 100_000)
+    L.rel_join_table_destroy(t)
+    stub.stub_capture(0)
+    assert stub.stub_frees() == 2
+    """)
