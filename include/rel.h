@@ -14,7 +14,11 @@
  * - All column and output buffers are owned by the caller; librel never frees
  *   them. librel owns contexts, join tables, batches and planners and frees
  *   them in the matching *_destroy call. A context keeps its scratch device
- *   memory (hash tables, counters) between calls and frees it on destroy.
+ *   memory (hash tables, counters) between calls and frees it on destroy. It
+ *   also keeps the memory of the join table destroyed last (8 bytes per slot)
+ *   for the next one of its size on the same stream; that goes when the next
+ *   table is destroyed, when an allocation of the library's for this context
+ *   fails (which is then tried again), or with the context.
  * - Every call is stream-ordered on the context's HIP stream (borrowed, e.g.
  *   torch.cuda.current_stream().cuda_stream) and returns once the work is
  *   enqueued, unless it says it synchronises. Counts are written to device

@@ -1169,9 +1169,7 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
   const size_t o_join = al(o_zero + 8 * b->zero_words);
   const size_t o_groups = al(o_join + 8 * jw);
   const size_t total = al(o_groups + sizeof(GroupSlot) * gs);
-  hipError_t e = hipMalloc(&b->mem, total);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
+  if (relh::device_alloc(ctx, total, &b->mem) != REL_OK) {
     free_batch(b);
     return relh::fail(ctx, REL_OOM, "rel_batch_create: %zu bytes of device memory", total);
   }

@@ -36,6 +36,23 @@ rel_status hip_fail(rel_ctx* ctx, hipError_t e, const char* what) {
   return fail(ctx, e == hipErrorOutOfMemory ? REL_OOM : REL_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+rel_status device_alloc(rel_ctx* ctx, size_t bytes, void** out) {
+  hipError_t e = hipMalloc(out, bytes);
+  if (e == hipErrorOutOfMemory) {
+    std::lock_guard<std::mutex> lock(ctx->table_mu);
+    if (ctx->spare.ptr) {
+      (void)hipGetLastError();
+      (void)hipFree(ctx->spare.ptr);
+      ctx->spare = ScratchBuf{};
+      e = hipMalloc(out, bytes);
+    }
+  }
+  if (e == hipSuccess) return REL_OK;
+  (void)hipGetLastError();
+  *out = nullptr;
+  return REL_OOM;
+}
+
 rel_status scratch(rel_ctx* ctx, int id, size_t bytes, void** out) {
   ScratchBuf& b = ctx->scratch[id];
   if (b.bytes < bytes) {
@@ -47,12 +64,7 @@ rel_status scratch(rel_ctx* ctx, int id, size_t bytes, void** out) {
       b.bytes = 0;
     }
     size_t want = bytes < 4096 ? 4096 : bytes;
-    hipError_t e = hipMalloc(&b.ptr, want);
-    if (e != hipSuccess) {
-      b.ptr = nullptr;
-      (void)hipGetLastError();
-      return fail(ctx, REL_OOM, "scratch allocation of %zu bytes failed: %s", want, hipGetErrorString(e));
-    }
+    if (device_alloc(ctx, want, &b.ptr) != REL_OK) return fail(ctx, REL_OOM, "scratch allocation of %zu bytes failed", want);
     b.bytes = want;
     b.clean = 0;
   }

@@ -125,6 +125,9 @@ rel_status fail(rel_ctx* ctx, rel_status s, const char* fmt, ...);
 rel_status hip_fail(rel_ctx* ctx, hipError_t e, const char* what);
 // Device buffer of at least `bytes` in scratch slot `id` (contents undefined).
 rel_status scratch(rel_ctx* ctx, int id, size_t bytes, void** out);
+// Device memory; what the context keeps for a next join table is given back when
+// there is none left. REL_OOM otherwise (not noted as the context's error).
+rel_status device_alloc(rel_ctx* ctx, size_t bytes, void** out);
 // The stream's work is being recorded, not run (or the runtime cannot say).
 bool capturing(hipStream_t stream);
 // Scratch that is empty between calls: every call finds it so and its last

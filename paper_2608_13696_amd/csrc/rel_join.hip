@@ -508,14 +508,14 @@ rel::JoinIndex table_index(const rel_join_table* t, const int32_t* payload) {
 
 // Table memory: a context keeps the last table's memory that was given back
 // (one buffer, freed with the context, when another one takes its place or
-// when an allocation fails), because allocating and freeing the 256 MB of a
-// 15M-key table for each query took 0.3 ms, as long as building and probing
-// it. The memory of a table whose work all went to one stream is kept, for a
-// table on the same stream, whose kernels follow the old ones'; any other goes
-// back through hipFree, which waits for the device. The stream is the caller's
-// and may be gone by now, so it is told by the context's turns, not by its
-// address, and not asked. Of recorded work nothing is kept or reused, so that no
-// graph holds memory that another table gets.
+// when any of the library's allocations for the context fails), because
+// allocating and freeing the 256 MB of a 15M-key table for each query took 0.3
+// ms, as long as building and probing it. The memory of a table whose work all
+// went to one stream is kept, for a table on the same stream, whose kernels
+// follow the old ones'; any other goes back through hipFree, which waits for the
+// device. The stream is the caller's and may be gone by now, so it is told by the
+// context's turns, not by its address, and not asked. Of recorded work nothing is
+// kept or reused, so that no graph holds memory that another table gets.
 rel_status take_table(rel_ctx* ctx, size_t bytes, uint64_t** out) {
   if (!relh::capturing(ctx->stream)) {
     std::lock_guard<std::mutex> lock(ctx->table_mu);
@@ -527,20 +527,8 @@ rel_status take_table(rel_ctx* ctx, size_t bytes, uint64_t** out) {
     }
   }
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, bytes);
-  if (e == hipErrorOutOfMemory) {
-    std::lock_guard<std::mutex> lock(ctx->table_mu);
-    if (ctx->spare.ptr) {
-      (void)hipGetLastError();
-      (void)hipFree(ctx->spare.ptr);
-      ctx->spare = ScratchBuf{};
-      e = hipMalloc(&p, bytes);
-    }
-  }
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return relh::fail(ctx, REL_OOM, "rel_join_build: table allocation failed");
-  }
+  const rel_status s = relh::device_alloc(ctx, bytes, &p);
+  if (s != REL_OK) return relh::fail(ctx, REL_OOM, "rel_join_build: table allocation failed");
   *out = (uint64_t*)p;
   return REL_OK;
 }

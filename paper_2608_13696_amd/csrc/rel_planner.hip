@@ -781,9 +781,10 @@ rel_status rel_planner_create(rel_ctx* ctx, const float* params, const float* me
   p->ctx = ctx;
   p->margin = margin_log2;
   const size_t floats = kParams + 3 * kFeat + 8 + 64;  // params, mean, scale, features, prediction + aux, HLL bytes
-  hipError_t e = hipMalloc(&p->mem, floats * sizeof(float));
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
+  void* mem;
+  const rel_status s = relh::device_alloc(ctx, floats * sizeof(float), &mem);
+  p->mem = (float*)mem;
+  if (s != REL_OK) {
     delete p;
     return relh::fail(ctx, REL_OOM, "rel_planner_create: allocation failed");
   }

@@ -71,3 +71,21 @@ def test_table_memory_of_recorded_work_is_not_kept(host):
     stub.stub_capture(0)
     assert stub.stub_frees() == 2
     """)
+
+
+@pytest.mark.parametrize("call", ["query(c, 1_000_000, 500_000, 'fk')", "table(c, 300_000)[0]", "batch(c, [(1000, 100_000, 'fk')])"])
+def test_kept_table_memory_is_given_back_when_there_is_none_left(host, call):
+    host(f"""
+    def batch(c, sizes):
+        items = (rel.BatchItem * len(sizes))()
+        for it, (n, m, by) in zip(items, sizes):
+            it.fact, it.dim, it.q, it.out = fact(n), dim(m), rel.Query(1000, rel.GROUP_BY[by]), groups(n)
+        return L.rel_batch_create(c, items, len(sizes), None, 0, P(ctypes.c_void_p()))
+    c = new_ctx()
+    st, t = table(c, 4_000_000)
+    assert st == 0
+    L.rel_join_table_destroy(t)
+    stub.stub_limit(stub.stub_used() + 1_000_000)
+    assert {call} == 0
+    assert stub.stub_frees() >= 1
+    """)
