@@ -341,7 +341,9 @@ typedef struct rel_batch rel_batch;
 
 /* Plan, allocate and capture a batch of k instances (descriptors are copied;
  * the column and output buffers they point to must stay valid until
- * rel_batch_destroy). tuning nullable (library defaults), n_tuning entries. */
+ * rel_batch_destroy). tuning nullable (library defaults), n_tuning entries.
+ * Beside its tables a batch takes up to 8 GB of working memory for instances
+ * of many groups, if there is as much, and keeps it until it is destroyed. */
 rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k, const rel_batch_tuning* tuning,
                             int32_t n_tuning, rel_batch** out);
 /* Enqueue one run of every instance on the context's stream (one graph launch). */

@@ -1067,11 +1067,6 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
   }
   const size_t spill_tiles = (size_t)((spill_rows + kWTile - 1) / kWTile);
   const size_t spill_bytes = (size_t)b->whole_grid * ((size_t)spill_rows * 16 + spill_tiles * (kWMaxChunks + 1) * 4);
-  if (spill_rows > 0 && (spill_bytes > kWMaxSpill || hipMalloc(&b->spill, spill_bytes) != hipSuccess)) {
-    (void)hipGetLastError();
-    b->spill = nullptr;
-    spill_rows = 0;  // instances with more groups than one chunk go the other way
-  }
 
   // table sizes and offsets
   std::vector<BInst> hinst(k);
@@ -1172,6 +1167,12 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
   if (relh::device_alloc(ctx, total, &b->mem) != REL_OK) {
     free_batch(b);
     return relh::fail(ctx, REL_OOM, "rel_batch_create: %zu bytes of device memory", total);
+  }
+  // (after the memory that the batch cannot do without)
+  if (spill_rows > 0 && (spill_bytes > kWMaxSpill || hipMalloc(&b->spill, spill_bytes) != hipSuccess)) {
+    (void)hipGetLastError();
+    b->spill = nullptr;
+    spill_rows = 0;  // instances with more groups than one chunk go the other way
   }
   char* base = (char*)b->mem;
   b->d_inst = (BInst*)(base + o_inst);

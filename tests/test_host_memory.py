@@ -89,3 +89,30 @@ def test_kept_table_memory_is_given_back_when_there_is_none_left(host, call):
     assert {call} == 0
     assert stub.stub_frees() >= 1
     """)
+
+
+def test_batch_without_memory_for_the_groups_of_large_instances(host):
+    """The working memory beside the tables is one that a batch can do without."""
+    host("""
+    k, n, m = 256, 100_000, 20_000
+    def batch(c):
+        items = (rel.BatchItem * k)()
+        for it in items:
+            it.fact, it.dim, it.q, it.out = fact(n), dim(m), rel.Query(1000, rel.GROUP_BY["dim_grp"]), groups(n)
+        h = ctypes.c_void_p()
+        before = stub.stub_used()
+        st = L.rel_batch_create(c, items, k, None, 0, P(h))
+        used = stub.stub_used() - before
+        if st == 0:
+            L.rel_batch_destroy(h)
+        return st, used
+    c = new_ctx()
+    st, all_of_it = batch(c)
+    extra = k * n * 16
+    assert st == 0 and all_of_it > extra
+    stub.stub_limit(stub.stub_used() + all_of_it - extra)
+    st, tables = batch(c)
+    assert st == 0 and tables < all_of_it - extra
+    stub.stub_limit(stub.stub_used() + tables - 1)
+    assert batch(c)[0] == rel.OOM
+    """)
