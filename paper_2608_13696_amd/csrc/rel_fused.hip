@@ -850,7 +850,7 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
   const bool few_expected = expected <= kLdsSlots / 2;
   const bool lds = placement == REL_PLACE_LDS || (placement == REL_PLACE_AUTO && (few_expected || !hinted));
   const bool many = placement == REL_PLACE_GLOBAL || (placement == REL_PLACE_AUTO && !few_expected);
-  const bool partition = placement == REL_PLACE_AUTO && many && n >= (hinted ? kGroupbyPartitionRows : 2 * kGroupbyPartitionRows);
+  bool partition = placement == REL_PLACE_AUTO && many && n >= (hinted ? kGroupbyPartitionRows : 2 * kGroupbyPartitionRows);
   const int64_t nslots = (1ll << l) + 1;
   void* tbl;  // (left empty by the finalize kernel)
   TRY(clean_groups(ctx, nslots, &tbl));
@@ -863,6 +863,8 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
   uint32_t* few = (uint32_t*)(cnt + CNT_AUX2);
   uint64_t* state;
   TRY(finalize_state(ctx, nslots, &state));
+  // (20 B per row: without them the device table, which is slower, serves)
+  if (partition) TRY(relh::if_memory(ctx, [&] { return relh::groupby_memory(ctx, n, expected); }, &partition));
   const unsigned grid = relh::grid_for(ctx, n, partition || !many ? kLdsBlock * kGbAhead : kLdsBlock, 1);
   Stage stage{};
   if (lds) TRY(take_stage(ctx, grid, flags, &stage));

@@ -518,23 +518,19 @@ rel_status groupby_begin(rel_ctx* ctx, const GroupRows& in, int mode, uint32_t* 
   return REL_OK;
 }
 
-rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expected, const uint32_t* few,
-                               const rel::GroupView& g, const DirectOut& o) {
-  // Bins: a unit's groups should take at most half of the larger LDS table
-  // (4096 slots, one workgroup per CU), or of the smaller one (2048 slots, two)
-  // while 64 bins and more allow it. More bins cost the scatter its runs.
+// Memory of a partitioned group-by of n rows and about `expected` groups.
+//
+// Bins: a unit's groups should take at most half of the larger LDS table
+// (4096 slots, one workgroup per CU), or of the smaller one (2048 slots, two)
+// while 64 bins and more allow it. More bins cost the scatter its runs.
+static rel_status take_rows(rel_ctx* ctx, int64_t rows, int64_t expected, GbArgs* out) {
   uint32_t bits = 6;
   while (bits < 11 && (expected >> bits) > 2048) ++bits;
-  const bool small = (expected >> bits) <= 1024;
   GbArgs a{};
-  a.in = in;
-  a.few = few;
-  a.max_rows = (uint32_t)in.n;
-  a.status = g.status;
   a.nb = 1u << bits;
   a.shift = 32 - bits;
-  a.ntiles = (in.n + kGbTile - 1) / kGbTile;
-  const size_t n = (size_t)in.n, max_units = a.nb + n / kGbSubRows + 1;
+  a.ntiles = (rows + kGbTile - 1) / kGbTile;
+  const size_t n = (size_t)rows, max_units = a.nb + n / kGbSubRows + 1;
   const size_t hist = (size_t)a.ntiles * a.nb * 4, chunk = (size_t)kGbChunks * a.nb * 4;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   void* mem;
@@ -554,6 +550,25 @@ rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expect
   a.start = (uint32_t*)take(a.nb * 4);
   a.units = (uint4*)take(max_units * 16);
   a.n_units = (uint32_t*)take(4);
+  *out = a;
+  return REL_OK;
+}
+
+rel_status groupby_memory(rel_ctx* ctx, int64_t rows, int64_t expected) {
+  GbArgs a;
+  return take_rows(ctx, rows, expected, &a);
+}
+
+rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expected, const uint32_t* few,
+                               const rel::GroupView& g, const DirectOut& o) {
+  GbArgs a;
+  rel_status s = take_rows(ctx, in.n, expected, &a);
+  if (s != REL_OK) return s;
+  a.in = in;
+  a.few = few;
+  a.max_rows = (uint32_t)in.n;
+  a.status = g.status;
+  const bool small = (expected >> (32 - a.shift)) <= 1024;
   KernelTimer kt(ctx, "groupby");
   const dim3 tiles((unsigned)a.ntiles), cols(a.nb / kColBins, kGbChunks);
   hipLaunchKernelGGL(k_gb_hist, tiles, dim3(kGbBlock), 0, ctx->stream, a);

@@ -130,6 +130,16 @@ rel_status scratch(rel_ctx* ctx, int id, size_t bytes, void** out);
 rel_status device_alloc(rel_ctx* ctx, size_t bytes, void** out);
 // The stream's work is being recorded, not run (or the runtime cannot say).
 bool capturing(hipStream_t stream);
+// Takes memory that a call can do without: *taken says whether there was any.
+template <class Take>
+rel_status if_memory(rel_ctx* ctx, Take&& take, bool* taken) {
+  const std::string err = ctx->err;
+  const rel_status s = take();
+  *taken = s == REL_OK;
+  if (s != REL_OOM) return s;
+  ctx->err = err;  // (no failure of the call's)
+  return REL_OK;
+}
 // Scratch that is empty between calls: every call finds it so and its last
 // kernels leave it so, which it tells by scratch_emptied once they are enqueued.
 // Memory that is not known to be empty (a first use, a larger one, one after a

@@ -85,6 +85,8 @@ enum GroupbyMode : int { GB_FEW = 0, GB_MANY, GB_SAMPLE };
 // Writes the decision (1: few groups) to *few and clears words[0, n_words) and state[0, n_state).
 rel_status groupby_begin(rel_ctx* ctx, const GroupRows& in, int mode, uint32_t* few, uint64_t* words, int32_t n_words,
                          uint64_t* state, int64_t n_state);
+// Takes the memory that groupby_partitioned needs.
+rel_status groupby_memory(rel_ctx* ctx, int64_t rows, int64_t expected);
 // Groups of the rows, unless *few: straight to `o`, or to the device table g
 // (set *o.touched), about `expected` of them.
 rel_status groupby_partitioned(rel_ctx* ctx, const GroupRows& in, int64_t expected, const uint32_t* few,

@@ -116,3 +116,19 @@ def test_batch_without_memory_for_the_groups_of_large_instances(host):
     stub.stub_limit(stub.stub_used() + tables - 1)
     assert batch(c)[0] == rel.OOM
     """)
+
+
+@pytest.mark.parametrize("hint", [0, 1_000_000])
+def test_groupby_without_memory_to_partition_its_rows(host, hint):
+    host(f"""
+    n = 20_000_000
+    c = new_ctx()
+    assert groupby(c, n, {hint}) == 0 and launched(kernels(), "k_gb_scatter")
+    L.rel_ctx_destroy(c)
+    c = new_ctx()
+    stub.stub_limit(stub.stub_used() + 32 * (2 << 25 if not {hint} else 2 << 20) + n * 15)  # the group table, and too little more
+    assert groupby(c, n, {hint}) == 0
+    names = kernels()
+    assert not launched(names, "k_gb_scatter") and launched(names, "k_groupby_global" if {hint} else "k_groupby_lds")
+    assert L.rel_last_error(c) == b""
+    """)
