@@ -955,7 +955,7 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   int64_t group_cap = 0;
   uint32_t gl = 0;
   void* gt = nullptr;
-  bool eager = false, by_partials = false;
+  bool eager = false, by_partials = false, clean_table = false;
   relh::Partials partials{};
   int64_t partials_expected = 0;
   if (gb == REL_GROUP_FK) {
@@ -993,19 +993,26 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     // table: a planned run pays 0.15 ms for its sketch and its read by the host
     // (1.34 ms), and is held to be no slower than the plain one. Without memory
     // for the partials the table serves, too.
+    clean_table = !part || (eager && planned);
+    if (clean_table) {
+      TRY(clean_groups(ctx, group_cap + 1, &gt));  // emptied again by the kernel that reads it
+    } else {
+      TRY(relh::scratch(ctx, SCR_GROUP_TABLE, (size_t)(group_cap + 1) * sizeof(GroupSlot), &gt));
+      TRY(init_groups(ctx, (GroupSlot*)gt, group_cap + 1));
+    }
     if (eager && planned) {
+      // (last, after the memory that the call cannot do without)
+      uint64_t* state;
+      TRY(finalize_state(ctx, group_cap + 1, &state));
+      TRY(relh::partitioned_memory(ctx, n, m));
       int64_t rows;
       unsigned wgs;
       size_t bytes;
       relh::partials_bounds(ctx, n, m, &rows, &wgs, &bytes);
-      by_partials = relh::partials_take(ctx, rows, wgs, expected, bytes, (uint32_t*)(cnt + CNT_AUX2), &partials) == REL_OK;
+      TRY(relh::if_memory(ctx, [&] {
+        return relh::partials_take(ctx, rows, wgs, expected, bytes, (uint32_t*)(cnt + CNT_AUX2), &partials);
+      }, &by_partials));
       partials_expected = expected;
-    }
-    if (part && !by_partials) {
-      TRY(relh::scratch(ctx, SCR_GROUP_TABLE, (size_t)(group_cap + 1) * sizeof(GroupSlot), &gt));
-      TRY(init_groups(ctx, (GroupSlot*)gt, group_cap + 1));
-    } else {
-      TRY(clean_groups(ctx, group_cap + 1, &gt));  // emptied again by the kernel that reads it
     }
     a.groups = GroupView{(GroupSlot*)gt, (uint32_t)(group_cap - 1), 32u - gl, ctx->d_status,
                          planned ? kPlannedProbe : (uint32_t)group_cap};
@@ -1027,8 +1034,8 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
       oa.touched = flags;
       oa.limit = planned ? group_cap + 1 : INT64_MAX;
     }
-    TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, by_partials}, group_cap + 1, oa));
-    if (by_partials) relh::scratch_emptied(ctx, SCR_GROUP_CLEAN);
+    TRY(finalize(ctx, SlotSource{(GroupSlot*)gt, group_cap, clean_table}, group_cap + 1, oa));
+    if (clean_table) relh::scratch_emptied(ctx, SCR_GROUP_CLEAN);
     return sync_stats(ctx, fact, dim, q, plan, out, stats, cnt, m, group_cap, REL_PLACE_PARTITIONED,
                       gp == G_LDS ? REL_PLACE_LDS : REL_PLACE_GLOBAL);
   }

@@ -55,6 +55,8 @@ rel_status partitioned_groupjoin(rel_ctx* ctx, const rel_fact* fact, const rel_d
 rel_status partitioned_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim, int32_t day_lt, int group_by,
                                 void* group_slots, uint32_t group_log2cap, uint32_t max_probe, int32_t lds_probe,
                                 bool eager, const struct Partials* partials, int64_t* counters);
+// Takes the memory that partitioned_join_agg needs (without partials).
+rel_status partitioned_memory(rel_ctx* ctx, int64_t n, int64_t m);
 // The most partials that the eager form yields, its workgroups, and the bytes of
 // the buffers SCR_PART_A and SCR_PART_B that the partitioning itself needs.
 void partials_bounds(rel_ctx* ctx, int64_t n, int64_t m, int64_t* max_rows, unsigned* workgroups, size_t* fact_bytes);

@@ -2586,6 +2586,44 @@ struct Partitioned {
   uint32_t* bitmap;  // dense order (GROUP BY fk): the dim keys' presence bits
 };
 
+// Scratch of a partitioned call: the fact columns' first (a) and second level
+// (b), the dim columns of both and, with dense_ok, the presence bitmap of the
+// dense order (c: at most 2^(P + 11) key positions, one bit each), bookkeeping (d).
+struct PartMemory {
+  void *a, *b, *c, *d;
+  size_t bitmap_bytes;
+  int64_t max_units;
+};
+constexpr size_t kSplitBytes = (size_t)kMaxSplit * kJSlots * sizeof(SplitAcc) + (kMaxSplit + 1) * sizeof(uint32_t);
+
+rel_status take_partition(rel_ctx* ctx, int64_t n, int64_t m, bool dense_ok, PartMemory* p) {
+  uint32_t b1, b2;
+  split_bits(m, &b1, &b2);
+  const uint32_t nb1 = 1u << b1, nb2 = 1u << b2, nparts = nb1 * nb2;
+  const int64_t fnt1 = (n + kTile1 - 1) / kTile1, dnt1 = (m + kTile1 - 1) / kTile1;
+  const int64_t fnt2 = n / kTile + nb1, dnt2 = m / kTile + nb1;
+  // whole chunks, plus the sub-units of split chunks (each split chunk adds at most one partial sub-unit)
+  p->max_units = (int64_t)nparts + m / kJChunk + 1 + n / kSubRows + kMaxSplit;
+  const size_t fact_bytes = part_fact_bytes(n);
+  TRY(scratch(ctx, SCR_PART_A, fact_bytes, &p->a));
+  TRY(scratch(ctx, SCR_PART_B, fact_bytes, &p->b));
+  p->bitmap_bytes = dense_ok ? ((size_t)1 << (b1 + b2 + kJSlotBits)) / 8 + 256 : 0;
+  TRY(scratch(ctx, SCR_PART_C, (size_t)(m > 0 ? m : 1) * 16 + 4 * 256 + p->bitmap_bytes, &p->c));
+  const size_t book = ((size_t)fnt1 * nb1 + (size_t)dnt1 * nb1 + (size_t)fnt2 * nb2 + (size_t)dnt2 * nb2 + 2 * nb1 +
+                       5 * (size_t)nparts + ((size_t)nparts / kUBlk + 1) * kClasses) * 4 +
+                      (size_t)p->max_units * (sizeof(uint4) + sizeof(uint2)) + (size_t)(fnt2 + dnt2) * sizeof(uint4) +
+                      sizeof(KeyMap) + 8 * (size_t)kKeyMinMaxParts + ((size_t)n / 64 + 1) * 8 + ((size_t)fnt1 * kRngWaves + 1) * 16 +
+                      64 * 256;
+  return scratch(ctx, SCR_PART_D, book, &p->d);
+}
+
+rel_status partitioned_memory(rel_ctx* ctx, int64_t n, int64_t m) {
+  PartMemory p;
+  TRY(take_partition(ctx, n, m, false, &p));
+  void* pe;
+  return scratch(ctx, SCR_PART_E, kSplitBytes, &pe);
+}
+
 // dense_ok: the key order may be the dense one (GROUP BY fk), decided on the
 // device from the dim keys' range; otherwise the hash order.
 rel_status partition_both(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim, int32_t day_lt, int pkind,
@@ -2598,29 +2636,13 @@ rel_status partition_both(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim
   const int64_t fnt1 = (n + kTile1 - 1) / kTile1, dnt1 = (m + kTile1 - 1) / kTile1;
   // second-level tiles: sum over partitions of ceil(c_p / kTile) <= rows / kTile + partitions
   const int64_t fnt2 = n / kTile + nb1, dnt2 = m / kTile + nb1;
-  // whole chunks, plus the sub-units of split chunks (each split chunk adds at most one partial sub-unit)
-  const int64_t max_units = (int64_t)nparts + m / kJChunk + 1 + n / kSubRows + kMaxSplit;
-
-  // scratch: partitioned columns (A: fact level 1, B: fact level 2, C: dim both levels), bookkeeping (D)
-  void *pa, *pb, *pc, *pd;
-  const size_t fact_bytes = part_fact_bytes(n);
-  TRY(scratch(ctx, SCR_PART_A, fact_bytes, &pa));
-  TRY(scratch(ctx, SCR_PART_B, fact_bytes, &pb));
-  // dim copies, and (GROUP BY fk) the presence bitmap of the dense order: at
-  // most 2^(P + 11) key positions, one bit each
-  const size_t bitmap_bytes = dense_ok ? ((size_t)1 << (b1 + b2 + kJSlotBits)) / 8 + 256 : 0;
-  TRY(scratch(ctx, SCR_PART_C, (size_t)(m > 0 ? m : 1) * 16 + 4 * 256 + bitmap_bytes, &pc));
-  const size_t book = ((size_t)fnt1 * nb1 + (size_t)dnt1 * nb1 + (size_t)fnt2 * nb2 + (size_t)dnt2 * nb2 + 2 * nb1 +
-                       5 * (size_t)nparts + ((size_t)nparts / kUBlk + 1) * kClasses) * 4 +
-                      (size_t)max_units * (sizeof(uint4) + sizeof(uint2)) + (size_t)(fnt2 + dnt2) * sizeof(uint4) +
-                      sizeof(KeyMap) + 8 * (size_t)kKeyMinMaxParts + ((size_t)n / 64 + 1) * 8 + ((size_t)fnt1 * kRngWaves + 1) * 16 +
-                      64 * 256;
-  TRY(scratch(ctx, SCR_PART_D, book, &pd));
+  PartMemory mem;
+  TRY(take_partition(ctx, n, m, dense_ok, &mem));
+  const int64_t max_units = mem.max_units;
   // split-chunk accumulators and their done counters: zero when allocated, and
   // left zero by every call (the last sub-unit of a chunk clears what it emits)
   void* pe;
-  const size_t split_bytes = (size_t)kMaxSplit * kJSlots * sizeof(SplitAcc) + (kMaxSplit + 1) * sizeof(uint32_t);
-  TRY(scratch_empty(ctx, SCR_PART_E, split_bytes, &pe, [&](void* q) { return fill_u32(ctx, q, split_bytes / 4, 0); }));
+  TRY(scratch_empty(ctx, SCR_PART_E, kSplitBytes, &pe, [&](void* q) { return fill_u32(ctx, q, kSplitBytes / 4, 0); }));
   uint32_t* split_done = (uint32_t*)((char*)pe + (size_t)kMaxSplit * kJSlots * sizeof(SplitAcc));
   uint32_t* split_ctr = split_done + kMaxSplit;
 
@@ -2634,7 +2656,7 @@ rel_status partition_both(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim
   F.n = n;
   F.b1 = b1;
   F.b2 = b2;
-  Carver ca{(char*)pa}, cb{(char*)pb}, cc{(char*)pc}, cd{(char*)pd};
+  Carver ca{(char*)mem.a}, cb{(char*)mem.b}, cc{(char*)mem.c}, cd{(char*)mem.d};
   F.key1 = ca.take<int32_t>(n);
   F.qty1 = ca.take<int32_t>(n);
   F.price1 = ca.take<int64_t>(n);
@@ -2669,7 +2691,7 @@ rel_status partition_both(rel_ctx* ctx, const rel_fact* fact, const rel_dim* dim
   D.pay1 = cc.take<int32_t>(m);
   D.key2 = cc.take<int32_t>(m);
   D.pay2 = cc.take<int32_t>(m);
-  uint32_t* bitmap = dense_ok ? cc.take<uint32_t>(bitmap_bytes / 4) : nullptr;
+  uint32_t* bitmap = dense_ok ? cc.take<uint32_t>(mem.bitmap_bytes / 4) : nullptr;
   D.dense_stop = dense_ok ? 1u : 0u;
   D.hist1 = cd.take<uint32_t>((size_t)dnt1 * nb1);
   D.tot1 = cd.take<uint32_t>(nb1);

@@ -132,3 +132,29 @@ def test_groupby_without_memory_to_partition_its_rows(host, hint):
     assert not launched(names, "k_gb_scatter") and launched(names, "k_groupby_global" if {hint} else "k_groupby_lds")
     assert L.rel_last_error(c) == b""
     """)
+
+
+def test_planned_join_without_memory_for_its_partials(host):
+    """The partials' memory is taken last, so that every limit from what the call needs at the least upwards will do."""
+    host("""
+    n, m, expected = 8_000_000, 6_000_000, 3_000_000
+    def call(limit):
+        c = new_ctx()
+        stub.stub_limit(limit if limit else BIG)
+        plan = rel.Plan(expected, rel.PLACE["global"], rel.PLACE["partitioned"], 0, 0)
+        st, names, used = query(c, n, m, "dim_grp", plan), kernels(), stub.stub_used()
+        assert st != 0 or L.rel_last_error(c) == b""
+        stub.stub_limit(BIG)
+        L.rel_ctx_destroy(c)
+        return st, launched(names, "k_part_join_eagerILb1E"), used
+    st, partials, most = call(0)
+    assert st == 0 and partials
+    least = 2 * (n * 17 + 1024) + m * 16 + 32 * (2 << 22)  # columns and the group table
+    seen = set()
+    for limit in [*range(least, most, (most - least) // 40), most]:
+        st, partials, used = call(limit)
+        assert st == 0 or not seen, limit  # refused for want of bookkeeping memory at the lowest limits only
+        if st == 0:
+            seen.add(partials)
+    assert seen == {False, True}
+    """)
