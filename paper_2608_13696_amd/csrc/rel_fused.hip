@@ -37,7 +37,10 @@ constexpr int kLdsCacheProbe = 4;
 constexpr uint32_t kPlannedProbe = 256;
 // Groups a workgroup of the LDS variant may stage for the merge kernel (more
 // and it adds them to the device table itself): 32 with a full grid, and as
-// many more with fewer workgroups as keep the merge's work the same.
+// many more with fewer workgroups as keep the merge's work the same, up to half
+// of what the merge's LDS table holds (a workgroup that has more would only have
+// the one that merges add to the device table for it: 5000 rows, 3600 groups: 74
+// us without that limit, 39 with it).
 constexpr int kStageMax = 32;
 constexpr int kStageTotal = 256 * kStageMax;
 
@@ -260,8 +263,9 @@ __global__ __launch_bounds__(NT) void k_fused(FusedArgs a) {
 // When nothing went to the device table and every merged group found an LDS
 // slot, it writes the output itself (groups, their number, the two counters)
 // and sets `done`, and the finalize kernel returns at once; otherwise it adds
-// its groups to the device table and the finalize kernel scans that. Other
-// workgroups of the launch empty the join index meanwhile.
+// its groups to the device table and the finalize kernel (or, where none
+// follows, this launch) scans that. Other workgroups of the launch empty the
+// join index meanwhile.
 constexpr int kMergeUnroll = 4;
 constexpr int kMaxStages = 1024;  // streaming workgroups at most
 
@@ -274,11 +278,13 @@ struct MergeArgs {
   uint32_t* done;
   JoinIndex join;  // for the dense index's entry count
   const uint32_t* few;  // clear: the stages were not written (null: they were)
-  // > 0: no finalize kernel follows, and when groups went to the device table,
-  // workgroup 0 writes the output from its nslots slots itself
+  // > 0: no finalize kernel follows; when groups went to the device table, all
+  // workgroups write the output from its nslots slots, on the merging one's word
   int64_t nslots;
-  bool wipe;            // workgroups 1, 2, ... empty the join index
+  uint32_t* ticket;
+  uint32_t* word;
 };
+enum MergeWord : uint32_t { kMergePending = 0, kMergeWritten, kMergeDrain };
 
 // The per-workgroup counts summed by NT threads (valid in thread 0): rows
 // passed and join matches into counters[0] and [1]; a dense index with fewer
@@ -418,27 +424,33 @@ struct OutArgs {
   int64_t limit;            // with base: more groups than this overflow the table that the caller sized
 };
 
-// The device table's groups to the output, by one workgroup, leaving the table
-// empty. The slots are read past L1, which may hold what they were before other
-// workgroups' atomics and this one's.
-__device__ void drain_groups(const GroupView& g, int64_t nslots, const OutArgs& o) {
-  __shared__ uint32_t s_n;
-  __threadfence();
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
+// Part `part` of `parts` of the device table's groups to the output, by one
+// workgroup, leaving them empty; *o.d_n counts the groups. The slots are read
+// past L1, which may hold what they were before other workgroups' atomics.
+__device__ void drain_groups(const GroupView& g, int64_t nslots, uint32_t part, uint32_t parts, const OutArgs& o) {
+  __shared__ uint32_t s_scan[kLdsBlock / kWave];
+  __shared__ int64_t s_pos;
   constexpr int kAhead = 8;
-  for (int64_t i0 = threadIdx.x; i0 < nslots; i0 += kAhead * kLdsBlock) {
+  const int64_t step = kAhead * kLdsBlock;
+  for (int64_t i0 = part * step; i0 < nslots; i0 += parts * step) {
     uint64_t c[kAhead];
+    uint32_t mine = 0, total;
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
-      const int64_t i = i0 + k * kLdsBlock;
+      const int64_t i = i0 + k * kLdsBlock + threadIdx.x;
       c[k] = i < nslots ? __hip_atomic_load(&g.slots[i].count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
     }
 #pragma unroll
+    for (int k = 0; k < kAhead; ++k) mine += c[k] != 0;
+    const uint32_t before = block_excl_scan<kLdsBlock>(mine, s_scan, &total);
+    if (total == 0) continue;
+    if (threadIdx.x == 0) s_pos = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)o.d_n, total);
+    __syncthreads();
+    int64_t pos = s_pos + before;
+#pragma unroll
     for (int k = 0; k < kAhead; ++k) {
       if (c[k] == 0) continue;
-      const int64_t i = i0 + k * kLdsBlock;
-      const int64_t pos = atomicAdd(&s_n, 1u);
+      const int64_t i = i0 + k * kLdsBlock + threadIdx.x;
       if (pos < o.cap) {
         o.key[pos] = i == nslots - 1 ? kGroupEmpty : __hip_atomic_load(&g.slots[i].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         o.sum_price[pos] = (int64_t)__hip_atomic_load(&g.slots[i].sum_price, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -448,10 +460,9 @@ __device__ void drain_groups(const GroupView& g, int64_t nslots, const OutArgs& 
         set_status(o.status, kDevOverflow);
       }
       g.slots[i] = GroupSlot{kGroupEmpty, 0, 0, 0};
+      ++pos;
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) *o.d_n = (int64_t)s_n;
 }
 
 __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs o) {
@@ -459,12 +470,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   __shared__ uint32_t s_lost;  // a group went to the device table here
   __shared__ uint32_t s_wcnt[kLdsBlock / kWave];
   const int t = threadIdx.x;
-  if (blockIdx.x > 0) {
-    join_index_wipe(m.join, (int64_t)(blockIdx.x - 1) * kLdsBlock + t, (int64_t)(gridDim.x - 1) * kLdsBlock);
-    return;
-  }
-  if (m.few != nullptr && *m.few == 0) return;
-  // the loads that nothing before them decides, in flight while the table is set up
+  // the loads that nothing before them decides, in flight while the rest is set up
   const uint32_t touched = *m.stage.touched;
   const uint32_t c0 = t < m.n_wg ? m.stage.n[t] : 0u;
   uint64_t wp = 0, wq = 0, we = 0;  // this thread's share of the streaming workgroups' totals (at most one each)
@@ -473,6 +479,28 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
     wq = m.wg_counts[3 * t + 1];
     we = m.wg_counts[3 * t + 2];
   }
+  uint32_t role = blockIdx.x;  // 0: the workgroup that merges
+  if (m.nslots > 0) {
+    // (the others wait for its word, so it is one that runs: the first to start)
+    __shared__ uint32_t s_role;
+    if (t == 0) s_role = dev_add_ret<uint32_t>(m.ticket, 1u);
+    __syncthreads();
+    role = s_role;
+  }
+  if (role > 0) {
+    join_index_wipe(m.join, (int64_t)(role - 1) * kLdsBlock + t, (int64_t)(gridDim.x - 1) * kLdsBlock);
+    if (m.nslots == 0) return;
+    __shared__ uint32_t s_word;
+    if (t == 0) {
+      uint32_t w;
+      while ((w = __hip_atomic_load(m.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kMergePending) __builtin_amdgcn_s_sleep(8);
+      s_word = w;
+    }
+    __syncthreads();
+    if (s_word == kMergeDrain) drain_groups(m.groups, m.nslots, role, gridDim.x, o);
+    return;
+  }
+  if (m.few != nullptr && *m.few == 0) return;
   lds.init(t, kLdsBlock);
   if (t == 0) s_lost = 0;
   // The stages' groups laid end to end, each stage padded to the largest one's
@@ -520,7 +548,12 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   if (touched != 0 || s_lost != 0) {
     if (t == 0) *m.stage.touched = 1u;
     if (occ) group_add(m.groups, lds.key[t], lds.sum_price[t], lds.sum_qty[t], lds.count[t]);
-    if (m.nslots > 0) drain_groups(m.groups, m.nslots, o);
+    if (m.nslots == 0) return;
+    if (t == 0) __hip_atomic_store((unsigned long long*)o.d_n, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wait_device_atomics();  // (every wave's, before the word goes out)
+    __syncthreads();
+    if (t == 0) __hip_atomic_store(m.word, (uint32_t)kMergeDrain, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    drain_groups(m.groups, m.nslots, 0, gridDim.x, o);
     return;
   }
   const uint64_t ball = wave_ballot(occ);
@@ -548,6 +581,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   if (t == 0) {
     *o.d_n = (int64_t)total;
     *m.done = 1u;
+    if (m.nslots > 0) __hip_atomic_store(m.word, (uint32_t)kMergeWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -741,7 +775,7 @@ rel_status finalize(rel_ctx* ctx, const Src& src, int64_t nitems, const OutArgs&
 
 // Stages for `grid` workgroups.
 rel_status take_stage(rel_ctx* ctx, unsigned grid, uint32_t* touched, Stage* out) {
-  const int cap = grid >= 256 ? kStageMax : std::min(kLdsSlots, kStageTotal / (int)grid);
+  const int cap = grid >= 256 ? kStageMax : std::min(kLdsSlots / 2, kStageTotal / (int)grid);
   const size_t slots = (size_t)grid * cap * sizeof(GroupSlot);
   void* p;
   rel_status s = relh::scratch(ctx, SCR_STAGE, slots + (size_t)grid * 4, &p);
@@ -779,17 +813,24 @@ uint32_t group_log2cap(int64_t expected, double load) {
   return l < 4 ? 4 : l;
 }
 
-// Fact rows up to which a plain LDS call runs in 256-thread workgroups (at most
-// one per CU; 60K rows: 8.2 us against 12.8 in fewer of 1024 threads) and its
-// merge kernel ends it: the stages hold at least 32 groups each, and the device
-// table, which is then rarely used, has at most 131073 slots for one workgroup
-// to go through.
-constexpr int64_t kMergeEndsRows = 256 * kBlock * kIPT;
+// Fact rows up to which a plain LDS call runs in 256-thread workgroups (60K rows,
+// 15 groups: the kernel takes 8.2 us, 12.8 in 15 of 1024 threads). More of them
+// would also mean more tables to add to the device table where a workgroup has
+// more groups than it may stage (120K rows, 400 groups: the call takes 57 us in
+// 118 workgroups of 256 threads, 36 in 30 of 1024; 250K rows: 89 and 42).
+constexpr int64_t kSmallRows = 1 << 16;
+// The merge kernel ends a plain LDS call of at most so many fact rows and slots
+// of the device table: its workgroups write the output from the table when groups
+// went there, 8192 slots at a time (60K rows, 131073 slots: 3600 groups 42 us
+// with one launch fewer, 49 us with a finalize kernel after it; one workgroup
+// going through all of them took 197; 15 groups 18.5 and 21.5 us). Beyond these
+// sizes the launch no longer counts.
+constexpr int64_t kMergeEndsRows = 1 << 18, kMergeEndsSlots = 1 << 20;
 
 template <int MODE>
 rel_status launch_fused(rel_ctx* ctx, int gp, const FusedArgs& a, unsigned grid) {
   relh::KernelTimer kt(ctx, "probe_agg");
-  if (gp == G_LDS && a.n <= kMergeEndsRows)
+  if (gp == G_LDS && a.n <= kSmallRows)
     hipLaunchKernelGGL((k_fused<MODE, G_LDS, kBlock>), dim3(grid), dim3(kBlock), 0, ctx->stream, a);
   else if (gp == G_LDS)
     hipLaunchKernelGGL((k_fused<MODE, G_LDS, kLdsBlock>), dim3(grid), dim3(kLdsBlock), 0, ctx->stream, a);
@@ -875,7 +916,7 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
     relh::KernelTimer kt(ctx, "groupby");
     hipLaunchKernelGGL(k_groupby_lds, dim3(grid), dim3(kLdsBlock), 0, ctx->stream, in, (const uint32_t*)few, g,
                        few_expected || placement == REL_PLACE_LDS ? kLdsProbe : kLdsCacheProbe, !partition, stage);
-    MergeArgs mg{stage, (int64_t)grid, nullptr, cnt, g, flags + 1, JoinIndex{}, few, 0, false};
+    MergeArgs mg{stage, (int64_t)grid, nullptr, cnt, g, flags + 1, JoinIndex{}, few, 0, nullptr, nullptr};
     hipLaunchKernelGGL(k_group_merge, dim3(1), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
     oa.done = flags + 1;
     REL_LAUNCH_CHECK(ctx, "groupby");
@@ -1052,10 +1093,10 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   const uint32_t jl = relh::join_log2cap(m, nullptr);
   const void* payload = gb == REL_GROUP_PRIO_FLAG ? (const void*)dim->prio : gb == REL_GROUP_DIM_GRP ? (const void*)dim->grp : nullptr;
   const int pkind = gb == REL_GROUP_PRIO_FLAG ? relh::PAY_I8 : gb == REL_GROUP_DIM_GRP ? relh::PAY_I32 : relh::PAY_ROW_ID;
-  const bool merge_ends = gp == G_LDS && n > 0 && n <= kMergeEndsRows;
+  const bool merge_ends = gp == G_LDS && n > 0 && n <= kMergeEndsRows && group_cap <= kMergeEndsSlots;
   const unsigned grid = gp != G_LDS  ? relh::grid_for(ctx, n, kBlock * kIPT, 8)
-                        : merge_ends ? relh::grid_for(ctx, n, kBlock * kIPT, 1)
-                                     : relh::grid_for(ctx, n, kLdsBlock * kIPT, 1);
+                        : n <= kSmallRows ? relh::grid_for(ctx, n, kBlock * kIPT, 1)
+                                          : relh::grid_for(ctx, n, kLdsBlock * kIPT, 1);
   uint32_t* flags = (uint32_t*)(cnt + CNT_AUX1);  // [0] touched, [1] done
   // (all memory of the call is taken before the first kernel that fills a table)
   void* wc;
@@ -1076,11 +1117,14 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
     else if (gb == REL_GROUP_FK) TRY(launch_fused<M_FK>(ctx, gp, a, grid));
     else TRY(launch_fused<M_DIM_GRP>(ctx, gp, a, grid));
     if (gp == G_LDS) {
-      MergeArgs mg{a.stage, (int64_t)grid, a.wg_counts, cnt, a.groups, flags + 1, jx, nullptr, merge_ends ? group_cap + 1 : 0, true};
+      const int64_t nslots = merge_ends ? group_cap + 1 : 0;
+      MergeArgs mg{a.stage, (int64_t)grid, a.wg_counts, cnt, a.groups, flags + 1, jx, nullptr, nslots,
+                   (uint32_t*)(cnt + CNT_TICKET), (uint32_t*)(cnt + CNT_AUX0)};
+      const unsigned others = std::max(wipe_grid(ctx, jx, kLdsBlock), relh::grid_for(ctx, nslots, kLdsBlock * 8, 1));
       oa.n_wg = 0;  // the merge kernel sums the counts
       oa.done = flags + 1;
       relh::KernelTimer kt(ctx, "group_merge");
-      hipLaunchKernelGGL(k_group_merge, dim3(1 + wipe_grid(ctx, jx, kLdsBlock)), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
+      hipLaunchKernelGGL(k_group_merge, dim3(1 + others), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
       REL_LAUNCH_CHECK(ctx, "group_merge");
     }
   } else {

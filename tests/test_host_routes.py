@@ -1,0 +1,35 @@
+"""Which kernels a call launches, and how wide, at the sizes where the choice changes (without a GPU)."""
+import os
+
+import pytest
+
+from tests import hoststub
+
+pytestmark = pytest.mark.skipif(not os.path.exists(os.path.join(hoststub.ROOT, "paper_2608_13696_amd", "librel.so")),
+                                reason="librel.so not built")
+
+
+@pytest.fixture
+def host(tmp_path_factory):
+    return lambda body: hoststub.run(tmp_path_factory, body)
+
+
+def test_whoever_reads_the_group_table_is_as_wide_as_the_table(host):
+    """Groups that did not fit LDS are in the device table: no single workgroup may have to go through a large one."""
+    host("""
+    c = new_ctx()
+    lds = lambda cap: rel.Plan(cap, rel.PLACE["lds"], rel.PLACE["global"], 0, 0)
+    for n, m, by, plan in ((1000, 500, "prio_flag", None), (60_000, 15_000, "prio_flag", None), (262_144, 15_000, "prio_flag", None),
+                           (262_145, 15_000, "prio_flag", None), (5000, 100_000, "dim_grp", lds(250_000)),
+                           (250_000, 100_000, "dim_grp", lds(500_000)), (250_000, 100_000, "dim_grp", lds(600_000)),
+                           (10_000, 100, "dim_grp", lds(100_000_000))):
+        kernels()
+        assert query(c, n, m, by, plan) == 0
+        slots = 16
+        while slots < 2 * (plan.group_capacity if plan else min(n, 65536)):
+            slots *= 2
+        grid = {part: g for name, g in kernels() for part in ("k_group_merge", "k_finalize") if part in name}
+        assert "k_group_merge" in grid
+        reader = 4 * grid["k_finalize"] if "k_finalize" in grid else grid["k_group_merge"]  # (8192 slots of a finalize workgroup's ticket)
+        assert reader * 8192 >= slots, (n, plan and plan.group_capacity, grid)
+    """)
