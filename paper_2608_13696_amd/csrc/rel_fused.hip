@@ -1103,7 +1103,7 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   TRY(relh::scratch(ctx, SCR_WG_COUNTS, (size_t)grid * 24, &wc));
   if (gp == G_LDS) TRY(take_stage(ctx, grid, flags, &a.stage));
   JoinIndex jx{};
-  TRY(relh::join_index_build(ctx, dim->pk, payload, pkind, m, (uint32_t*)(cnt + CNT_AUX2), zero, &jx));
+  TRY(relh::join_index_build(ctx, dim->pk, payload, pkind, m, n, (uint32_t*)(cnt + CNT_AUX2), zero, &jx));
   a.join = jx;
 
   OutArgs oa = out_args(ctx, out);

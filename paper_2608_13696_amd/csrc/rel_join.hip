@@ -417,14 +417,19 @@ static rel_status hash_entries(rel_ctx* ctx, const int32_t* pk, const void* payl
   return REL_OK;
 }
 
-// Up to this many keys the fused path's index is a hash table whatever their
-// range: its 2 MB stay in L2, and one launch builds it, where a dense array
-// takes two (the keys' range first). 15K keys: one launch of 3.5 us where the
-// range, the clearing and the dense entries took three of 9.8 us together.
-constexpr int64_t kHashMaxKeys = 1 << 16;
+// Up to this many keys, and for at most so many probe rows, the fused path's
+// index is a hash table whatever the keys' range: its 2 MB stay in L2, and one
+// launch builds it, where a dense array takes two (the keys' range first) of about
+// 3 us each. A probe of it costs more: it reads 8 bytes of a table of up to 2 MB
+// and walks on where keys collide or match nothing, against 2 or 4 bytes of at
+// most 128 or 256 KB. Measured, (prio, flag) of 16K keys, hash table and dense
+// array in us: 60K rows 17.4 and 21.5, 1M 20.7 and 26.3, 6M 45.5 and 51.4, 30M 208
+// and 171; a quarter of the rows with a match: 1M 23.2 and 25.9, 6M 56.4 and 48.4,
+// 30M 234 and 154.
+constexpr int64_t kHashMaxKeys = 1 << 16, kHashMaxRows = 1 << 21;
 
 rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
-                            uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out) {
+                            int64_t probes, uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out) {
   const uint32_t jl = join_log2cap(m, nullptr);
   const size_t hash_bytes = ((size_t)8 << jl) + 8;
   rel_status s;
@@ -440,7 +445,7 @@ rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload
   x.pkind = payload_kind;
   x.narrow = payload_kind == PAY_I8;
   x.m = m;
-  if (m <= kHashMaxKeys) {
+  if (m == 0 || (m <= kHashMaxKeys && probes <= kHashMaxRows)) {
     s = hash_entries(ctx, pk, payload, payload_kind, m, x.hash, zero);
   } else {
     x.dense_cap = 2 * m;

@@ -15,8 +15,8 @@ constexpr int64_t kLdsGroupCap = 512;
 
 // log2 of the join-table capacity for m keys under opts (plain: 2m rounded up).
 uint32_t join_log2cap(int64_t m, const rel_table_opts* opts);
-// The join index over pk[0..m) in the context's scratch: for few keys a hash
-// table, else a dense array when the keys' range is at most 2m wide, or the
+// The join index over pk[0..m) in the context's scratch: for few keys and not too
+// many rows that probe it a hash table, else a dense array when the keys' range is at most 2m wide, or the
 // plain-sized hash table (decided on the device). mm: two device words that
 // receive the keys' order-encoded minimum and maximum. The first kernel also
 // zeroes `zero`'s spans (words later kernels of the call start from). A dense
@@ -30,7 +30,7 @@ struct ZeroSpans {
   int64_t n[2];
 };
 rel_status join_index_build(rel_ctx* ctx, const int32_t* pk, const void* payload, int payload_kind, int64_t m,
-                            uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out);
+                            int64_t probes, uint32_t* mm, const ZeroSpans& zero, rel::JoinIndex* out);
 void join_index_wiped(rel_ctx* ctx, const rel::JoinIndex& x);
 rel_status join_index_verify(rel_ctx* ctx, const rel::JoinIndex& x);
 // Order-encoded minimum and maximum of pk[0..m) per workgroup: pair i is

@@ -33,3 +33,17 @@ def test_whoever_reads_the_group_table_is_as_wide_as_the_table(host):
         reader = 4 * grid["k_finalize"] if "k_finalize" in grid else grid["k_group_merge"]  # (8192 slots of a finalize workgroup's ticket)
         assert reader * 8192 >= slots, (n, plan and plan.group_capacity, grid)
     """)
+
+
+@pytest.mark.parametrize("by", ["prio_flag", "dim_grp"])
+def test_small_dim_side_of_a_large_fact_side_is_a_dense_array(host, by):
+    """Its range is looked for (k_key_minmax) where the rows that probe it are many; a hash table is built at once."""
+    host(f"""
+    c = new_ctx()
+    for n, m, dense in ((60_000, 65_536, False), (1 << 21, 65_536, False), ((1 << 21) + 1, 1, True), (30_000_000, 16_000, True),
+                        (60_000, 65_537, True), (30_000_000, 0, False)):
+        kernels()
+        assert query(c, n, m, {by!r}) == 0
+        names = kernels()
+        assert launched(names, "k_key_minmax") == dense and launched(names, "k_join_build") == (not dense), (n, m)
+    """)
