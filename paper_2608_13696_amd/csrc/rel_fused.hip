@@ -278,7 +278,7 @@ struct MergeArgs {
   uint32_t* done;
   JoinIndex join;  // for the dense index's entry count
   const uint32_t* few;  // clear: the stages were not written (null: they were)
-  // > 0: no finalize kernel follows; when groups went to the device table, all
+  // where no finalize kernel follows: when groups went to the device table, all
   // workgroups write the output from its nslots slots, on the merging one's word
   int64_t nslots;
   uint32_t* ticket;
@@ -328,7 +328,6 @@ __device__ void sum_wg_counts(const uint64_t* wg, int64_t n_wg, const JoinIndex&
 }
 
 struct OutArgs;
-__global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs o);
 
 // Stand-alone group-by over key[row], row = sel ? sel[k] : k, straight into the
 // device table.
@@ -465,12 +464,24 @@ __device__ void drain_groups(const GroupView& g, int64_t nslots, uint32_t part, 
   }
 }
 
+// ENDS: no finalize kernel follows (MergeArgs::nslots).
+template <bool ENDS>
 __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs o) {
   __shared__ LdsGroups<kLdsSlots> lds;
   __shared__ uint32_t s_lost;  // a group went to the device table here
   __shared__ uint32_t s_wcnt[kLdsBlock / kWave];
   const int t = threadIdx.x;
-  // the loads that nothing before them decides, in flight while the rest is set up
+  if (!ENDS && blockIdx.x > 0) {
+    join_index_wipe(m.join, (int64_t)(blockIdx.x - 1) * kLdsBlock + t, (int64_t)(gridDim.x - 1) * kLdsBlock);
+    return;
+  }
+  if (!ENDS && m.few != nullptr && *m.few == 0) return;
+  // the loads that nothing before them decides, in flight while the table is set
+  // up; among them this workgroup's turn: the others wait for the word of the one
+  // that merges, so that is one that runs, the first to start
+  __shared__ uint32_t s_role;
+  uint32_t turn = 0;
+  if (ENDS && t == 0) turn = dev_add_ret<uint32_t>(m.ticket, 1u);
   const uint32_t touched = *m.stage.touched;
   const uint32_t c0 = t < m.n_wg ? m.stage.n[t] : 0u;
   uint64_t wp = 0, wq = 0, we = 0;  // this thread's share of the streaming workgroups' totals (at most one each)
@@ -479,28 +490,6 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
     wq = m.wg_counts[3 * t + 1];
     we = m.wg_counts[3 * t + 2];
   }
-  uint32_t role = blockIdx.x;  // 0: the workgroup that merges
-  if (m.nslots > 0) {
-    // (the others wait for its word, so it is one that runs: the first to start)
-    __shared__ uint32_t s_role;
-    if (t == 0) s_role = dev_add_ret<uint32_t>(m.ticket, 1u);
-    __syncthreads();
-    role = s_role;
-  }
-  if (role > 0) {
-    join_index_wipe(m.join, (int64_t)(role - 1) * kLdsBlock + t, (int64_t)(gridDim.x - 1) * kLdsBlock);
-    if (m.nslots == 0) return;
-    __shared__ uint32_t s_word;
-    if (t == 0) {
-      uint32_t w;
-      while ((w = __hip_atomic_load(m.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kMergePending) __builtin_amdgcn_s_sleep(8);
-      s_word = w;
-    }
-    __syncthreads();
-    if (s_word == kMergeDrain) drain_groups(m.groups, m.nslots, role, gridDim.x, o);
-    return;
-  }
-  if (m.few != nullptr && *m.few == 0) return;
   lds.init(t, kLdsBlock);
   if (t == 0) s_lost = 0;
   // The stages' groups laid end to end, each stage padded to the largest one's
@@ -515,7 +504,23 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
     for (int d = 32; d > 0; d >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, kWave));
     if (lane_id() == 0) s_most[t / kWave] = most;
   }
+  if (ENDS && t == 0) s_role = turn;
   __syncthreads();
+  if constexpr (ENDS) {
+    const uint32_t role = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_role);
+    if (role > 0) {
+      join_index_wipe(m.join, (int64_t)(role - 1) * kLdsBlock + t, (int64_t)(gridDim.x - 1) * kLdsBlock);
+      __shared__ uint32_t s_word;
+      if (t == 0) {
+        uint32_t w;
+        while ((w = __hip_atomic_load(m.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kMergePending) __builtin_amdgcn_s_sleep(4);
+        s_word = w;
+      }
+      __syncthreads();
+      if (s_word == kMergeDrain) drain_groups(m.groups, m.nslots, role, gridDim.x, o);
+      return;
+    }
+  }
   uint32_t most = 0;
 #pragma unroll
   for (int w = 0; w < kLdsBlock / kWave; ++w) most = max(most, s_most[w]);
@@ -548,7 +553,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   if (touched != 0 || s_lost != 0) {
     if (t == 0) *m.stage.touched = 1u;
     if (occ) group_add(m.groups, lds.key[t], lds.sum_price[t], lds.sum_qty[t], lds.count[t]);
-    if (m.nslots == 0) return;
+    if (!ENDS) return;
     if (t == 0) __hip_atomic_store((unsigned long long*)o.d_n, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wait_device_atomics();  // (every wave's, before the word goes out)
     __syncthreads();
@@ -581,7 +586,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   if (t == 0) {
     *o.d_n = (int64_t)total;
     *m.done = 1u;
-    if (m.nslots > 0) __hip_atomic_store(m.word, (uint32_t)kMergeWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ENDS) __hip_atomic_store(m.word, (uint32_t)kMergeWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -917,7 +922,7 @@ rel_status rel_groupby_agg(rel_ctx* ctx, const int64_t* key, const int64_t* pric
     hipLaunchKernelGGL(k_groupby_lds, dim3(grid), dim3(kLdsBlock), 0, ctx->stream, in, (const uint32_t*)few, g,
                        few_expected || placement == REL_PLACE_LDS ? kLdsProbe : kLdsCacheProbe, !partition, stage);
     MergeArgs mg{stage, (int64_t)grid, nullptr, cnt, g, flags + 1, JoinIndex{}, few, 0, nullptr, nullptr};
-    hipLaunchKernelGGL(k_group_merge, dim3(1), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
+    hipLaunchKernelGGL(k_group_merge<false>, dim3(1), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
     oa.done = flags + 1;
     REL_LAUNCH_CHECK(ctx, "groupby");
   } else if (!partition) {
@@ -1124,7 +1129,8 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
       oa.n_wg = 0;  // the merge kernel sums the counts
       oa.done = flags + 1;
       relh::KernelTimer kt(ctx, "group_merge");
-      hipLaunchKernelGGL(k_group_merge, dim3(1 + others), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
+      if (merge_ends) hipLaunchKernelGGL(k_group_merge<true>, dim3(1 + others), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
+      else hipLaunchKernelGGL(k_group_merge<false>, dim3(1 + others), dim3(kLdsBlock), 0, ctx->stream, mg, oa);
       REL_LAUNCH_CHECK(ctx, "group_merge");
     }
   } else {
