@@ -105,7 +105,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_build(const BInst* __restrict__
     __syncthreads();
     if (it >= n_items) break;
     const BItem w = items[it];
-    if (list.done[w.inst] != 0) continue;
+    if (it >= list.n && list.done[w.inst] != 0) continue;
     const BInst& I = inst[w.inst];
     for (int64_t j = w.lo + threadIdx.x; j < w.hi; j += BLOCK) {
       join_insert(I.jslots, I.jmask, I.jshift, I.pk[j], batch_payload(I, j), status);
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_probe(const BInst* __restrict__
     const int64_t it = s_item;
     if (it >= n_items) break;
     const BItem w = items[it];
-    if (list.done[w.inst] != 0) {
+    if (it >= list.n && list.done[w.inst] != 0) {
       __syncthreads();  // (every thread has read s_item)
       continue;
     }
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void k_batch_finalize(const BInst* __restrict_
     __syncthreads();
     if (it >= n_items) break;
     const BItem w = items[it];
-    if (list.done[w.inst] != 0) continue;
+    if (it >= list.n && list.done[w.inst] != 0) continue;
     const BInst& I = inst[w.inst];
     const int64_t side = (int64_t)I.gmask + 1;
     // wave-uniform trip count, so ballots see every lane
@@ -955,10 +955,15 @@ unsigned persistent_grid(const rel_ctx* ctx, int64_t items, int block) {
   return (unsigned)(g < 1 ? 1 : g);
 }
 
-// Items that there should be for each CU: with the tuning's rows per item (up to
-// 65536, found on batches of thousands) a batch of 8 instances of up to 1M rows
-// kept 20 workgroups busy and took 606 us; with items of an even share 230 us.
-constexpr int64_t kItemsPerCu = 4;
+// Rows and keys per item where the tuning's (up to 65536, found on batches of
+// thousands) would leave CUs idle: an even share, but for a row item no less than
+// what pays for its LDS table's setting up and its flush to the device table. 8
+// instances of up to 1M rows by the tuning's items kept 20 workgroups busy and
+// took 606 us; one instance of 300K rows 112 us, 61 so. Shares of a quarter of a
+// CU's cost more than they gave (4 instances of 1M rows: 229 us, 86 so, 125 by the
+// tuning's).
+constexpr int64_t kItemMinRows = 2048, kItemMinKeys = 1024;
+constexpr int64_t kKeyItemsPerCu = 4;
 
 // How many of a batch's instances, largest first (`rows`: their fact rows), go
 // the shared-table way, so that the estimated times of both ways, which follow
@@ -1052,11 +1057,12 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
   for (int32_t i = 0; i < k; ++i) sorted_rows[i] = items[order[i]].fact.n;
   const int32_t n_shared = whole_from(sorted_rows, ctx->num_cus), n_whole = k - n_shared;
   b->whole_grid = (unsigned)std::min<int32_t>(n_whole, ctx->num_cus);
-  int64_t shared_rows = 0, spill_rows = 0;
+  int64_t shared_rows = 0, shared_keys = 0, spill_rows = 0;
   for (int32_t p = 0; p < k; ++p) {
     const rel_batch_item& it = items[order[p]];
     if (p < n_shared) {
       shared_rows += it.fact.n;
+      shared_keys += it.dim.m;
       continue;
     }
     const int64_t groups = it.q.group_by == REL_GROUP_FK         ? 2 * it.dim.m
@@ -1140,11 +1146,14 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
   for (size_t t = 0; t < tun.size(); ++t) {
     BucketPlan& bp = b->buckets[t];
     bp.t = tun[t];
-    const int64_t unit = (int64_t)tun[t].block * tun[t].items_per_thread, even = shared_rows / (ctx->num_cus * kItemsPerCu);
-    const int64_t few = std::min<int64_t>(std::max<int64_t>(even / unit, 1) * unit, tun[t].rows_per_item);
+    const int64_t unit = (int64_t)tun[t].block * tun[t].items_per_thread;
+    const int64_t share = std::max<int64_t>(shared_rows / ctx->num_cus, kItemMinRows);
+    const int64_t few = std::min<int64_t>((share + unit - 1) / unit * unit, tun[t].rows_per_item);
+    const int64_t key_share = std::max<int64_t>(shared_keys / (ctx->num_cus * kKeyItemsPerCu), kItemMinKeys);
     auto rows = [&](int32_t p) { return p < n_shared ? few : (int64_t)tun[t].rows_per_item; };
+    auto keys = [&](int32_t p) { return p < n_shared ? key_share : std::max<int64_t>(tun[t].rows_per_item / 4, 256); };
     bp.build_lo = (int64_t)hitems.size();
-    bp.build = add_items((int)t, [&](int32_t i) { return items[i].dim.m; }, [&](int32_t p) { return std::max<int64_t>(rows(p) / 4, 256); });
+    bp.build = add_items((int)t, [&](int32_t i) { return items[i].dim.m; }, keys);
     bp.probe_lo = (int64_t)hitems.size();
     bp.probe = add_items((int)t, [&](int32_t i) { return items[i].fact.n; }, rows);
   }

@@ -47,3 +47,24 @@ def test_small_dim_side_of_a_large_fact_side_is_a_dense_array(host, by):
         names = kernels()
         assert launched(names, "k_key_minmax") == dense and launched(names, "k_join_build") == (not dense), (n, m)
     """)
+
+
+def test_batch_work_items_are_no_smaller_than_pays(host):
+    """Instances that go by shared tables: about one item of rows per CU, unless the tuning asks for fewer rows."""
+    host("""
+    def grid(k, n, m):
+        c = new_ctx()
+        items = (rel.BatchItem * k)()
+        for it in items:
+            it.fact, it.dim, it.q, it.out, it.group_capacity = fact(n), dim(m), rel.Query(1000, rel.GROUP_BY["dim_grp"]), groups(n), 300
+        tune = (rel.BatchTuning * 1)(rel.BatchTuning(31, 4, 256, 512, 65536, 0))
+        kernels()
+        assert L.rel_batch_create(c, items, k, tune, 1, P(ctypes.c_void_p())) == 0
+        names = kernels()
+        probe = [g for name, g in names if "k_batch_probe" in name]
+        build = [g for name, g in names if "k_batch_build" in name]
+        return launched(names, "k_batch_whole"), probe and probe[0], build and build[0]
+    assert grid(1, 300_000, 75_000) == (False, 147, 74)      # 2048 rows, 1024 keys
+    assert grid(4, 1_000_000, 1000) == (False, 248, 4)       # 15625 rows, rounded up to whole steps
+    assert grid(1, 60_000_000, 1000)[1] == 916               # the tuning's 65536
+    """)
