@@ -14,6 +14,7 @@
 // device-memory group table, LDS or device-memory join table, rows per work
 // item) comes from a tuning table that the autotuner measures.
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 
 #include "rel_device.h"
@@ -965,36 +966,71 @@ unsigned persistent_grid(const rel_ctx* ctx, int64_t items, int block) {
 constexpr int64_t kItemMinRows = 2048, kItemMinKeys = 1024;
 constexpr int64_t kKeyItemsPerCu = 4;
 
-// How many of a batch's instances, largest first (`rows`: their fact rows), go
-// the shared-table way, so that the estimated times of both ways, which follow
-// one another, add up to the least. A workgroup takes 1.7 ns per row of an
-// instance of its own and 10 us besides, while all CUs have one; the shared
-// tables take 35 ps per row over the whole chip and 60 us besides. Measured,
-// all instances by the shared tables / all whole / as chosen, in us:
-//   8 of up to 32K rows         88 /   81 /   81
-//   8 of up to 1M              230 /  890 /  232
-//   128 of up to 32K           175 /  113 /  113
-//   128 of up to 250K          461 /  483 /  460
-//   128 of up to 1M           1346 / 1877 / 1349
-//   512 of up to 250K         1179 /  612 /  611
-//   512 of up to 1M           3480 / 2515 / 2521
-//   2048 of up to 1M         10251 / 3004 / 3003
-constexpr double kWholeNs = 10000, kWholeRowNs = 1.7, kSharedNs = 60000, kSharedRowNs = 0.035;
-int32_t whole_from(const std::vector<int64_t>& rows, int cus) {
-  const int32_t k = (int32_t)rows.size();
-  double after = 0, before = 0, best = 0;
-  for (int64_t n : rows) after += kWholeNs + kWholeRowNs * (double)n;
+// The most groups that an instance can have, or its hint where that is less.
+int64_t group_bound(const rel_batch_item& it, bool* hinted) {
+  const int64_t ub = it.q.group_by == REL_GROUP_PRIO_FLAG ? std::min<int64_t>(it.fact.n, 65536) : std::min(it.fact.n, it.dim.m);
+  *hinted = it.group_capacity > 0 && it.group_capacity < ub;
+  return *hinted ? it.group_capacity : ub;
+}
+
+// What an instance costs either way, in ns: a workgroup that takes it whole while
+// most CUs are idle and while all are busy, and its share of what the shared tables
+// cost the chip. Fitted to 261 batches of 1 to 256 equal instances of 1K to 1M
+// rows, 100 to 8M dim keys and all three group keys, timed both ways: the way
+// chosen is within 0.3% of the better one on average (14% at worst). Some of them,
+// all by the shared tables / all whole, in us:
+//   1 of 1K rows, 100 keys        28 /   30     1 of 1K rows, 1M keys         95 / 2639
+//   1 of 300K, 75K, 300 groups    75 /  368     64 of 30K, 7.5K, 300 groups   94 /   49
+//   16 of 30K, 3K, fk            116 /   47     16 of 300K, 75K, fk          662 /  517
+//   64 of 1M, 250K, 300 groups  1343 / 1483     256 of 300K, 75K, fk        8756 /  803
+// Keys count as rows do: the join table of many keys is filled in LDS slice by
+// slice, with all keys read again for each, so that whole instances of 8M keys
+// took 136 ms.
+struct BatchCost {
+  double alone, loaded, shared, shared_wait;
+};
+BatchCost batch_cost(const rel_batch_item& it) {
+  bool hinted;
+  const int64_t bound = group_bound(it, &hinted);
+  const double n = (double)it.fact.n, m = (double)it.dim.m;
+  const bool fk = it.q.group_by == REL_GROUP_FK, flag = it.q.group_by == REL_GROUP_PRIO_FLAG;
+  const int64_t groups = fk ? it.dim.m : flag ? 0 : std::min<int64_t>(it.group_capacity > 0 ? std::min(it.group_capacity, it.dim.m) : it.dim.m, 65536);
+  const int64_t chunks = std::max<int64_t>((groups + kWCap - 1) / kWCap, 1);
+  const double table = m * (fk ? 1 : flag ? 8 : 16) / 8;  // bytes, of the entries' likely width
+  const double front = (double)std::min<int64_t>(groups, kWCap) * kWGroupBytes;
+  const bool in_lds = front + table <= kWPool, spills = chunks > 1;
+  const double slices = in_lds ? 1 : std::ceil(table / kWPool);
+  const double keys = 8000 + m * (0.25 + 0.25 * slices) + (spills ? 7000.0 * (double)chunks : 0);
+  BatchCost c;
+  c.alone = keys + n * ((in_lds ? 0.5 : 1.0) + (spills ? 1.0 : 0));
+  c.loaded = keys + n * ((in_lds ? 0.8 : 1.6) + (spills ? 1.3 : 0));
+  if (groups > kWMaxRange) c.alone = c.loaded = 1e15;  // (more keys than group numbers: w_plan would only find it out)
+  const bool many = bound > 512 && !flag;
+  double slots = 16;
+  while (slots < 2 * (double)bound + 1) slots *= 2;
+  c.shared = 50 + n * (many ? 0.09 : 0.005) + m * 0.06 + slots * 0.010;
+  c.shared_wait = 7000 + (many ? 25000 : 0) + (it.dim.m > kBLdsJoinSlots / 2 ? 12000 : m * 5) + (flag && it.fact.n >= 2048 ? 8000 : 0);
+  return c;
+}
+
+// How many of the instances, costliest first, go by the shared tables, so that the
+// times of both ways, which follow one another, add up to the least.
+int32_t whole_from(const std::vector<BatchCost>& cost, int cus) {
+  const int32_t k = (int32_t)cost.size();
+  double after = 0, shared = 0, wait = 0, best = 0;
+  for (const BatchCost& c : cost) after += c.loaded;
   int32_t at = 0;
   for (int32_t c = 0; c <= k; ++c) {
-    const double whole = c < k ? std::max(kWholeNs + kWholeRowNs * (double)rows[c], after / cus) : 0;
-    const double t = whole + (c > 0 ? kSharedNs + kSharedRowNs * before : 0);
+    const double whole = c < k ? std::max(cost[c].alone, after / cus) : 0;
+    const double t = whole + shared + wait;
     if (c == 0 || t < best) {
       best = t;
       at = c;
     }
     if (c == k) break;
-    after -= kWholeNs + kWholeRowNs * (double)rows[c];
-    before += (double)rows[c];
+    after -= cost[c].loaded;
+    shared += cost[c].shared;
+    wait = std::max(wait, cost[c].shared_wait);
   }
   return at;
 }
@@ -1049,13 +1085,14 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
     return (int)tun.size() - 1;
   };
 
-  // largest instance first; from `order[n_shared]` on they are taken whole
+  // costliest instance first; from `order[n_shared]` on they are taken whole
+  std::vector<BatchCost> costs(k), sorted_costs(k);
+  for (int32_t i = 0; i < k; ++i) costs[i] = batch_cost(items[i]);
   std::vector<int32_t> order(k);
   std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return items[x].fact.n > items[y].fact.n; });
-  std::vector<int64_t> sorted_rows(k);
-  for (int32_t i = 0; i < k; ++i) sorted_rows[i] = items[order[i]].fact.n;
-  const int32_t n_shared = whole_from(sorted_rows, ctx->num_cus), n_whole = k - n_shared;
+  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return costs[x].alone > costs[y].alone; });
+  for (int32_t i = 0; i < k; ++i) sorted_costs[i] = costs[order[i]];
+  const int32_t n_shared = whole_from(sorted_costs, ctx->num_cus), n_whole = k - n_shared;
   b->whole_grid = (unsigned)std::min<int32_t>(n_whole, ctx->num_cus);
   int64_t shared_rows = 0, shared_keys = 0, spill_rows = 0;
   for (int32_t p = 0; p < k; ++p) {
@@ -1084,9 +1121,8 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
     const rel_batch_item& it = items[i];
     const int64_t n = it.fact.n, m = it.dim.m;
     const uint32_t jl = relh::join_log2cap(m, nullptr);
-    int64_t ub = it.q.group_by == REL_GROUP_PRIO_FLAG ? std::min<int64_t>(n, 65536) : std::min(n, m);
-    const bool hinted = it.group_capacity > 0 && it.group_capacity < ub;
-    if (hinted) ub = it.group_capacity;
+    bool hinted;
+    const int64_t ub = group_bound(it, &hinted);
     uint32_t gl = relh::log2_ceil((uint64_t)(std::max<int64_t>(ub, 1) * 2) + 1);
     if (gl < 4) gl = 4;
     const rel_batch_tuning& t = tun[bucket_of(n)];

@@ -68,3 +68,21 @@ def test_batch_work_items_are_no_smaller_than_pays(host):
     assert grid(4, 1_000_000, 1000) == (False, 248, 4)       # 15625 rows, rounded up to whole steps
     assert grid(1, 60_000_000, 1000)[1] == 916               # the tuning's 65536
     """)
+
+
+def test_batch_instances_of_many_dim_keys_go_by_shared_tables(host):
+    """A workgroup that takes an instance whole reads all its dim keys again for each slice of its join table."""
+    host("""
+    def whole(k, n, m, by, hint=300):
+        c = new_ctx()
+        items = (rel.BatchItem * k)()
+        for it in items:
+            it.fact, it.dim, it.q, it.out, it.group_capacity = fact(n), dim(m), rel.Query(1000, rel.GROUP_BY[by]), groups(n), hint
+        kernels()
+        assert L.rel_batch_create(c, items, k, None, 0, P(ctypes.c_void_p())) == 0
+        return sum(g for name, g in kernels() if "k_batch_whole" in name)
+    for by in ("dim_grp", "prio_flag", "fk"):
+        assert whole(1, 1000, 8_000_000, by) == 0 and whole(1, 1000, 1_000_000, by) == 0 and whole(4, 30_000, 1_000_000, by) == 0
+        assert whole(256, 30_000, 3000, by) == 256 and whole(256, 300_000, 75_000, by) == 256 and whole(1, 1_000_000, 1000, by) == 0
+    assert whole(300, 1000, 1 << 20, "fk") == 0  # more keys than group numbers
+    """)
