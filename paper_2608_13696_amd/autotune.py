@@ -113,13 +113,14 @@ def load(path: str = DEFAULT_TABLE) -> list[dict] | None:
 
 def gpu_measure(ctx, instances, reps: int = 3):
     """measure(candidate) for a list of device instances: median time of
-    `reps` graph launches of a batch built with that candidate for all of them."""
+    `reps` graph launches of a batch built with that candidate for all of them,
+    by the tables in device memory (what a workgroup takes whole has nothing to tune)."""
     import torch
 
     from . import rel
 
     def measure(c: Candidate) -> float:
-        b = rel.Batch(ctx, instances, tuning=[c.entry(31)])
+        b = rel.Batch(ctx, instances, tuning=[c.entry(31)], shared=True)
         b.run()  # warm-up
         torch.cuda.synchronize()
         times = []

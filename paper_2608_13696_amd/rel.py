@@ -23,6 +23,7 @@ PLACE = {"auto": 0, "lds": 1, "global": 2, "partitioned": 3}
 PLACE_NAME = {v: k for k, v in PLACE.items()}
 GROUP_BY = {"prio_flag": 0, "fk": 1, "dim_grp": 2}
 BW_MODE = {"read": 0, "copy": 1, "write": 2}
+BATCH_WAY = {"auto": 0, "shared": 1}
 
 _vp = ctypes.c_void_p
 _i64 = ctypes.c_int64
@@ -135,6 +136,7 @@ def lib():
         L.rel_ctx_enable_timing.argtypes = [_vp, ctypes.c_int]
         L.rel_ctx_kernel_times.argtypes = [_vp, _vp, _vp, _vp, ctypes.c_int, P(ctypes.c_int)]
         L.rel_batch_create.argtypes = [_vp, P(BatchItem), _i32, P(BatchTuning), _i32, P(_vp)]
+        L.rel_batch_create_as.argtypes = [_vp, P(BatchItem), _i32, P(BatchTuning), _i32, _i32, P(_vp)]
         L.rel_batch_run.argtypes = [_vp]
         L.rel_batch_sync.argtypes = [_vp, P(Stats)]
         L.rel_batch_destroy.argtypes = [_vp]
@@ -149,7 +151,7 @@ def lib():
         for name in ("rel_ctx_create", "rel_ctx_destroy", "rel_ctx_set_stream", "rel_ctx_sync", "rel_filter_compact",
                      "rel_join_build", "rel_join_table_destroy", "rel_join_probe", "rel_join_gather", "rel_pred_create", "rel_pred_filter", "rel_pred_destroy", "rel_groupby_agg",
                      "rel_filter_join_agg", "rel_ctx_enable_timing", "rel_ctx_kernel_times", "rel_batch_create",
-                     "rel_batch_run", "rel_batch_sync", "rel_batch_destroy", "rel_sketch", "rel_mlp_forward",
+                     "rel_batch_create_as", "rel_batch_run", "rel_batch_sync", "rel_batch_destroy", "rel_sketch", "rel_mlp_forward",
                      "rel_mlp_backward", "rel_mlp_adam_step", "rel_planner_create", "rel_planner_plan",
                      "rel_planner_destroy"):
             getattr(L, name).restype = ctypes.c_int
@@ -394,9 +396,10 @@ class Batch:
     """Many independent fused queries captured into one graph launch.
 
     instances: list of (fact dict, dim dict, day_lt, group_by[, group_capacity]).
-    Outputs are allocated here, one Groups per instance."""
+    Outputs are allocated here, one Groups per instance. shared: all instances
+    go by the tables in device memory that the tuning is for."""
 
-    def __init__(self, ctx: Context, instances, tuning: list[dict] | None = None):
+    def __init__(self, ctx: Context, instances, tuning: list[dict] | None = None, shared: bool = False):
         self.ctx = ctx
         self.k = len(instances)
         self._keep = []
@@ -423,7 +426,7 @@ class Batch:
             tarr = (BatchTuning * len(tuning))(*[BatchTuning(**t) for t in tuning])
             nt = len(tuning)
         h = ctypes.c_void_p()
-        ctx.check(lib().rel_batch_create(ctx.h, arr, self.k, tarr, nt, ctypes.byref(h)))
+        ctx.check(lib().rel_batch_create_as(ctx.h, arr, self.k, tarr, nt, BATCH_WAY["shared" if shared else "auto"], ctypes.byref(h)))
         self.h = h
 
     def run(self):

@@ -86,3 +86,33 @@ def test_batch_instances_of_many_dim_keys_go_by_shared_tables(host):
         assert whole(256, 30_000, 3000, by) == 256 and whole(256, 300_000, 75_000, by) == 256 and whole(1, 1_000_000, 1000, by) == 0
     assert whole(300, 1000, 1 << 20, "fk") == 0  # more keys than group numbers
     """)
+
+
+def test_tunings_are_measured_where_they_apply(host):
+    """autotune.gpu_measure's batches launch the kernels that read the tuning, with the candidate's workgroup size."""
+    host("""
+    import types
+    from paper_2608_13696_amd import autotune
+    c = new_ctx()
+    ctx = types.SimpleNamespace(h=c, check=lambda st: (_ for _ in ()).throw(AssertionError(st)) if st else None)
+    class Tensor:
+        is_cuda, device = True, None
+        def __init__(self, n): self.n = n
+        def numel(self): return self.n
+        def data_ptr(self): return column()
+    rel._alloc_groups = lambda cap, device: types.SimpleNamespace(c=groups(cap))
+    class Events:
+        def __init__(self, **kw): pass
+        def record(self): pass
+        def elapsed_time(self, other): return 1.0
+    import torch
+    torch.cuda.synchronize, torch.cuda.Event = (lambda: None), Events
+    n, m = 3000, 700
+    inst = ({k: Tensor(n) for k in ("fk", "price_cents", "qty", "day", "flag")}, {k: Tensor(m) for k in ("pk", "prio", "grp")}, 1000, "dim_grp", 90)
+    for cand in (autotune.Candidate(4, 256, 512, 4096), autotune.Candidate(1, 128, 128, 4096, 1024)):
+        kernels()
+        autotune.gpu_measure(ctx, [inst] * 300)(cand)
+        names = kernels()
+        assert not launched(names, "k_batch_whole")
+        assert launched(names, f"k_batch_probeILi{cand.block}ELi{cand.items_per_thread}E")
+    """)
