@@ -347,15 +347,18 @@ typedef struct rel_batch rel_batch;
 rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k, const rel_batch_tuning* tuning,
                             int32_t n_tuning, rel_batch** out);
 /* rel_batch_create, with the way that the instances go: chosen for each from its
- * sizes (what rel_batch_create does), or all by tables in device memory, which
- * the tuning is for (to measure tunings). */
-typedef enum rel_batch_way { REL_BATCH_AUTO = 0, REL_BATCH_SHARED = 1 } rel_batch_way;
+ * sizes (what rel_batch_create does); all by tables in device memory, which the
+ * tuning is for (to measure tunings); or all taken whole by a workgroup each but
+ * those that this turns out not to serve. */
+typedef enum rel_batch_way { REL_BATCH_AUTO = 0, REL_BATCH_SHARED = 1, REL_BATCH_WHOLE = 2 } rel_batch_way;
 rel_status rel_batch_create_as(rel_ctx* ctx, const rel_batch_item* items, int32_t k, const rel_batch_tuning* tuning,
                                int32_t n_tuning, int32_t way, rel_batch** out);
 /* Enqueue one run of every instance on the context's stream (one graph launch). */
 rel_status rel_batch_run(rel_batch* b);
 /* Synchronise and report on the last run: stats (nullable, k entries) with
- * rows passed / join matches / groups per instance; REL_OVERFLOW if any
+ * rows passed / join matches / groups per instance (capacities and placements are
+ * those of the tables in device memory that the tuning gives the instance, also
+ * where a workgroup took it whole); REL_OVERFLOW if any
  * instance's table overflowed, REL_DUPLICATE_KEY on a repeated pk (the batch's
  * own status word, cleared at the start of every run; the context's sticky
  * bits are not touched). */

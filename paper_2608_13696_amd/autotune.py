@@ -120,7 +120,7 @@ def gpu_measure(ctx, instances, reps: int = 3):
     from . import rel
 
     def measure(c: Candidate) -> float:
-        b = rel.Batch(ctx, instances, tuning=[c.entry(31)], shared=True)
+        b = rel.Batch(ctx, instances, tuning=[c.entry(31)], way="shared")
         b.run()  # warm-up
         torch.cuda.synchronize()
         times = []

@@ -1056,7 +1056,7 @@ rel_status rel_batch_create(rel_ctx* ctx, const rel_batch_item* items, int32_t k
 
 rel_status rel_batch_create_as(rel_ctx* ctx, const rel_batch_item* items, int32_t k, const rel_batch_tuning* tuning,
                                int32_t n_tuning, int32_t way, rel_batch** out) {
-  if (way != REL_BATCH_AUTO && way != REL_BATCH_SHARED) return relh::fail(ctx, REL_INVALID_ARG, "rel_batch_create_as: bad way");
+  if (way < REL_BATCH_AUTO || way > REL_BATCH_WHOLE) return relh::fail(ctx, REL_INVALID_ARG, "rel_batch_create_as: bad way");
   if (!ctx || !out || k < 0 || (k > 0 && !items) || n_tuning < 0 || (n_tuning > 0 && !tuning))
     return relh::fail(ctx, REL_INVALID_ARG, "rel_batch_create: bad argument");
   std::vector<rel_batch_tuning> tun;
@@ -1098,7 +1098,8 @@ rel_status rel_batch_create_as(rel_ctx* ctx, const rel_batch_item* items, int32_
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return costs[x].alone > costs[y].alone; });
   for (int32_t i = 0; i < k; ++i) sorted_costs[i] = costs[order[i]];
-  const int32_t n_shared = way == REL_BATCH_SHARED ? k : whole_from(sorted_costs, ctx->num_cus), n_whole = k - n_shared;
+  const int32_t n_shared = way == REL_BATCH_SHARED ? k : way == REL_BATCH_WHOLE ? 0 : whole_from(sorted_costs, ctx->num_cus);
+  const int32_t n_whole = k - n_shared;
   b->whole_grid = (unsigned)std::min<int32_t>(n_whole, ctx->num_cus);
   int64_t shared_rows = 0, shared_keys = 0, spill_rows = 0;
   for (int32_t p = 0; p < k; ++p) {

@@ -23,7 +23,7 @@ PLACE = {"auto": 0, "lds": 1, "global": 2, "partitioned": 3}
 PLACE_NAME = {v: k for k, v in PLACE.items()}
 GROUP_BY = {"prio_flag": 0, "fk": 1, "dim_grp": 2}
 BW_MODE = {"read": 0, "copy": 1, "write": 2}
-BATCH_WAY = {"auto": 0, "shared": 1}
+BATCH_WAY = {"auto": 0, "shared": 1, "whole": 2}
 
 _vp = ctypes.c_void_p
 _i64 = ctypes.c_int64
@@ -396,10 +396,11 @@ class Batch:
     """Many independent fused queries captured into one graph launch.
 
     instances: list of (fact dict, dim dict, day_lt, group_by[, group_capacity]).
-    Outputs are allocated here, one Groups per instance. shared: all instances
-    go by the tables in device memory that the tuning is for."""
+    Outputs are allocated here, one Groups per instance. way: "auto" (chosen for
+    each instance), "shared" (the tables in device memory that the tuning is
+    for) or "whole" (a workgroup each)."""
 
-    def __init__(self, ctx: Context, instances, tuning: list[dict] | None = None, shared: bool = False):
+    def __init__(self, ctx: Context, instances, tuning: list[dict] | None = None, way: str = "auto"):
         self.ctx = ctx
         self.k = len(instances)
         self._keep = []
@@ -426,7 +427,7 @@ class Batch:
             tarr = (BatchTuning * len(tuning))(*[BatchTuning(**t) for t in tuning])
             nt = len(tuning)
         h = ctypes.c_void_p()
-        ctx.check(lib().rel_batch_create_as(ctx.h, arr, self.k, tarr, nt, BATCH_WAY["shared" if shared else "auto"], ctypes.byref(h)))
+        ctx.check(lib().rel_batch_create_as(ctx.h, arr, self.k, tarr, nt, BATCH_WAY[way], ctypes.byref(h)))
         self.h = h
 
     def run(self):

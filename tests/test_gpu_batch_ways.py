@@ -1,5 +1,5 @@
 """GPU parity of batches whose instances go either way, one workgroup each or by
-tables in device memory: chosen from their sizes, and all by the tables."""
+tables in device memory: chosen from their sizes, all by the tables, all whole."""
 import numpy as np
 import pytest
 import torch
@@ -31,13 +31,14 @@ def test_both_ways(ctx, sizes):
         tables.append(T)
         insts.append((*to_dev(T), T.day_lt, by, 0))
     want = [oracle.run_tables(T) for T in tables]
-    for shared in (False, True):
-        b = rel.Batch(ctx, insts, shared=shared)
+    for way in ("auto", "shared", "whole"):
+        b = rel.Batch(ctx, insts, way=way)
         for run in range(2):
             b.run()
             st = b.sync()
             for i, (ora, ost) in enumerate(want):
-                what = f"shared={shared} run {run} instance {i} {sizes[i]}"
+                what = f"{way} run {run} instance {i} {sizes[i]}"
                 assert_groups_equal(rel.sorted_groups(b.outs[i].host()), ora, what)
                 assert [st[i][x] for x in ("rows_passed", "join_matches", "groups")] == [ost[x] for x in ("rows_passed", "join_matches", "groups")], what
         b.close()
+

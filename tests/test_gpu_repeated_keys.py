@@ -52,7 +52,7 @@ def test_hot_repeated_key_in_a_batch(ctx, by, m, span, attrs):
     bad.fk[1::4] = bad.pk[m // 4]
     dev = [to_dev(T) for T in (bad, good)]
     dev[0][1]["pk"][b] = int(bad.pk[a])
-    batch = rel.Batch(ctx, [(f, d, T.day_lt, T.group_by, 0) for (f, d), T in zip(dev, (bad, good))])
+    batch = rel.Batch(ctx, [(f, d, T.day_lt, T.group_by, 0) for (f, d), T in zip(dev, (bad, good))], way="whole")
     for repeated in (True, True, False):
         if not repeated:
             dev[0][1]["pk"][b] = int(key)
