@@ -417,7 +417,8 @@ rel_status rel_planner_create(rel_ctx* ctx, const float* params, const float* me
  * plain bound; group placement LDS when that is at most 512 or a key is hot
  * (sampled max frequency >= 4/256), else device memory; join placement plain
  * (device memory) when a key is hot, the group key is a dim attribute and the
- * capacity is at most 2048, else left to the library. Synchronises once (a
+ * capacity is at most 1280 (2048 where the sampled max frequency is at least 0.05
+ * log2(N / 2^21)), else left to the library. Synchronises once (a
  * few floats come back). pred (host, nullable) receives the predictions
  * log2(1 + join rows), log2(1 + groups). */
 rel_status rel_planner_plan(rel_planner* p, const rel_fact* fact, const rel_dim* dim, const rel_query* q,

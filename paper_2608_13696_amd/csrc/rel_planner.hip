@@ -668,15 +668,23 @@ __global__ void k_prepare_input(float* __restrict__ x, const float* __restrict__
 // A key seen this often among the sampled rows marks a heavy hitter (about
 // 1.5% of the rows or more).
 constexpr float kSkewMaxFreq = 4.0f / 256.0f;
-// Under such a heavy hitter, with at most this many groups from a dim
-// attribute, the plain join (device-memory table) beats the partitioned one:
-// the hot keys' probes stay in cache and the groups in LDS, while
-// partitioning still pays its passes (measured on 60M fact rows, Zipf(1.2),
-// plain against partitioned: 0.61 and 0.97 ms at 100 groups, 0.84 and 1.05 at
-// 900, 1.04 and 1.05 at 1200, 1.22 and 1.06 at 1350, 1.89 and 1.05 at 2000, 2.47
-// and 1.06 at 10^4; the partitioned path also wins for every group count when no
-// key is hot).
-constexpr int64_t kSkewPlainJoinGroups = 1280;
+// Under such a heavy hitter, with at most so many groups from a dim attribute,
+// the plain join (device-memory table) beats the partitioned one: the hot keys'
+// probes stay in cache and the groups in LDS, while partitioning still pays its
+// passes. How many groups that is depends on how hot the hottest key is and on the
+// rows: what LDS cannot hold is updates of few slots in device memory. Measured,
+// partitioned time over plain at 1350 / 1700 / 2048 groups and 5M dim keys, f the
+// hottest key's share of the rows:
+//    2M rows, f 0.03   1.19 1.08 1.07
+//    4M rows, f 0.03   0.93 0.76 0.77    f 0.14   1.29 1.17 1.13
+//    8M                0.73 0.56 0.58             1.19 1.04 1.04
+//   16M                0.57 0.41 0.43             1.04 0.79 0.65    f 0.24   1.43 1.33 1.09
+//   60M                0.39 0.27 0.28             0.84 0.63 0.60             1.35 1.16 1.13
+// (15M keys alike; 1000 groups at f 0.14 and more 1.17 to 1.80.) The partitioned
+// path also wins for every group count when no key is hot.
+int64_t plain_join_groups(int64_t n, float max_freq) {
+  return (double)max_freq >= 0.05 * std::log2((double)n / (1 << 21)) ? 2048 : 1280;
+}
 
 #define TRY(e)                   \
   do {                           \
@@ -838,7 +846,7 @@ rel_status rel_planner_plan(rel_planner* p, const rel_fact* fact, const rel_dim*
   // as a cache in front of a larger device-memory table
   const bool skewed = hy[2] >= kSkewMaxFreq;
   plan->group_placement = (expected <= relh::kLdsGroupCap || skewed) ? REL_PLACE_LDS : REL_PLACE_GLOBAL;
-  plan->join_placement = (skewed && q->group_by != REL_GROUP_FK && expected <= kSkewPlainJoinGroups)
+  plan->join_placement = (skewed && q->group_by != REL_GROUP_FK && expected <= plain_join_groups(n, hy[2]))
                              ? REL_PLACE_GLOBAL
                              : REL_PLACE_AUTO;
   plan->allow_fallback = 1;
