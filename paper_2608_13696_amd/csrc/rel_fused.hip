@@ -824,6 +824,11 @@ uint32_t group_log2cap(int64_t expected, double load) {
 // more groups than it may stage (120K rows, 400 groups: the call takes 57 us in
 // 118 workgroups of 256 threads, 36 in 30 of 1024; 250K rows: 89 and 42).
 constexpr int64_t kSmallRows = 1 << 16;
+// Workgroups per CU that update a group table in device memory. Its atomics are the
+// bound, and more of them at once collide more: with as many as registers allow (6)
+// 30M rows into 65K groups took 2045 us, 2008 so; 6M sparse keys into 500K 555 and
+// 547; 700 groups 1250 and 1229.
+constexpr int kGlobalPerCu = 3;
 // The merge kernel ends a plain LDS call of at most so many fact rows and slots
 // of the device table: its workgroups write the output from the table when groups
 // went there, 8192 slots at a time (60K rows, 131073 slots: 3600 groups 42 us
@@ -1099,7 +1104,8 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
   const void* payload = gb == REL_GROUP_PRIO_FLAG ? (const void*)dim->prio : gb == REL_GROUP_DIM_GRP ? (const void*)dim->grp : nullptr;
   const int pkind = gb == REL_GROUP_PRIO_FLAG ? relh::PAY_I8 : gb == REL_GROUP_DIM_GRP ? relh::PAY_I32 : relh::PAY_ROW_ID;
   const bool merge_ends = gp == G_LDS && n > 0 && n <= kMergeEndsRows && group_cap <= kMergeEndsSlots;
-  const unsigned grid = gp != G_LDS  ? relh::grid_for(ctx, n, kBlock * kIPT, 8)
+  const unsigned grid = gp == G_ROWAGG   ? relh::grid_for(ctx, n, kBlock * kIPT, 8)
+                        : gp == G_GLOBAL ? relh::grid_for(ctx, n, kBlock * kIPT, kGlobalPerCu)
                         : n <= kSmallRows ? relh::grid_for(ctx, n, kBlock * kIPT, 1)
                                           : relh::grid_for(ctx, n, kLdsBlock * kIPT, 1);
   uint32_t* flags = (uint32_t*)(cnt + CNT_AUX1);  // [0] touched, [1] done

@@ -116,3 +116,15 @@ def test_tunings_are_measured_where_they_apply(host):
         assert not launched(names, "k_batch_whole")
         assert launched(names, f"k_batch_probeILi{cand.block}ELi{cand.items_per_thread}E")
     """)
+
+
+def test_workgroups_that_update_a_group_table_in_device_memory(host):
+    """No more at once than its atomics are worth."""
+    host("""
+    c = new_ctx()
+    for n in (1000, 30_000_000):
+        kernels()
+        assert query(c, n, 130_000, "dim_grp") == 0
+        grids = [g for name, g in kernels() if "k_fusedILi2ELi1E" in name]
+        assert grids == [1 if n == 1000 else 3 * 256]
+    """)
