@@ -88,8 +88,11 @@ __device__ __forceinline__ int32_t batch_payload(const BInst& I, int64_t j) {
   return I.group_by == REL_GROUP_PRIO_FLAG ? (int32_t)I.prio[j] : I.group_by == REL_GROUP_DIM_GRP ? I.grp[j] : (int32_t)j;
 }
 
-__global__ void k_batch_zero_outputs(const BInst* __restrict__ inst, int32_t k) {
-  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) *inst[i].d_n = 0;
+// First kernel of a run: the run's words and the instances' output counts.
+__global__ void k_batch_reset(uint64_t* __restrict__ words, int64_t n_words, const BInst* __restrict__ inst, int32_t k) {
+  const int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = id; i < n_words; i += stride) words[i] = 0;
+  for (int64_t i = id; i < k; i += stride) *inst[i].d_n = 0;
 }
 
 template <int BLOCK>
@@ -1262,9 +1265,8 @@ rel_status rel_batch_create_as(rel_ctx* ctx, const rel_batch_item* items, int32_
   if (st == REL_OK) {
     hipStream_t s = b->cap;
     const unsigned fg = (unsigned)ctx->num_cus * 4;
-    hipLaunchKernelGGL(k_batch_fill, dim3(fg), dim3(256), 0, s, (uint64_t*)b->d_tickets, 0ull,
-                       list((int64_t)b->zero_words, (int64_t)b->zero_words));
-    if (k) hipLaunchKernelGGL(k_batch_zero_outputs, dim3((k + 255) / 256), dim3(256), 0, s, (const BInst*)b->d_inst, k);
+    hipLaunchKernelGGL(k_batch_reset, dim3(relh::grid_for(ctx, (int64_t)b->zero_words, 256, 4)), dim3(256), 0, s,
+                       (uint64_t*)b->d_tickets, (int64_t)b->zero_words, (const BInst*)b->d_inst, k);
     if (b->whole_grid) hipLaunchKernelGGL(k_batch_whole, dim3(b->whole_grid), dim3(kWBlock), 0, s, b->whole);
     if (jw) hipLaunchKernelGGL(k_batch_fill, dim3(fg), dim3(256), 0, s, b->d_join, kJoinEmpty, list((int64_t)jw_shared, (int64_t)jw));
     if (gs) hipLaunchKernelGGL(k_batch_init_groups, dim3(fg), dim3(256), 0, s, b->d_groups, list((int64_t)gs_shared, (int64_t)gs));
