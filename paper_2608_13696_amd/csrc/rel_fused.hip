@@ -825,10 +825,12 @@ uint32_t group_log2cap(int64_t expected, double load) {
 // 118 workgroups of 256 threads, 36 in 30 of 1024; 250K rows: 89 and 42).
 constexpr int64_t kSmallRows = 1 << 16;
 // Workgroups per CU that update a group table in device memory. Its atomics are the
-// bound, and more of them at once collide more: with as many as registers allow (6)
-// 30M rows into 65K groups took 2045 us, 2008 so; 6M sparse keys into 500K 555 and
-// 547; 700 groups 1250 and 1229.
-constexpr int kGlobalPerCu = 3;
+// bound, and more of them at once collide more; with fewer, rows that match nothing
+// wait for their reads. With 3, 4 and as many as registers allow (6), in us: 30M
+// rows into 65K groups 2009, 2008, 2045; 6M rows into 700 groups 1229, 1241, 1250;
+// 6M rows of sparse keys into 500K groups 548, 548, 555; 6M rows, a quarter of them
+// matching, into 100 groups 1014, 998, 1000.
+constexpr int kGlobalPerCu = 4;
 // The merge kernel ends a plain LDS call of at most so many fact rows and slots
 // of the device table: its workgroups write the output from the table when groups
 // went there, 8192 slots at a time (60K rows, 131073 slots: 3600 groups 42 us

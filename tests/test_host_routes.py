@@ -126,5 +126,5 @@ def test_workgroups_that_update_a_group_table_in_device_memory(host):
         kernels()
         assert query(c, n, 130_000, "dim_grp") == 0
         grids = [g for name, g in kernels() if "k_fusedILi2ELi1E" in name]
-        assert grids == [1 if n == 1000 else 3 * 256]
+        assert grids == [1 if n == 1000 else 4 * 256]
     """)
