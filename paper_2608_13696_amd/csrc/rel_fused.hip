@@ -40,7 +40,7 @@ constexpr uint32_t kPlannedProbe = 256;
 // many more with fewer workgroups as keep the merge's work the same, up to half
 // of what the merge's LDS table holds (a workgroup that has more would only have
 // the one that merges add to the device table for it: 5000 rows, 3600 groups: 74
-// us without that limit, 39 with it).
+// us without that limit, 37 with it).
 constexpr int kStageMax = 32;
 constexpr int kStageTotal = 256 * kStageMax;
 
@@ -278,8 +278,8 @@ struct MergeArgs {
   uint32_t* done;
   JoinIndex join;  // for the dense index's entry count
   const uint32_t* few;  // clear: the stages were not written (null: they were)
-  // where no finalize kernel follows: when groups went to the device table, all
-  // workgroups write the output from its nslots slots, on the merging one's word
+  // where no finalize kernel follows: when groups went to the device table, the
+  // others write the output from its nslots slots, on the merging workgroup's word
   int64_t nslots;
   uint32_t* ticket;
   uint32_t* word;
@@ -426,40 +426,39 @@ struct OutArgs {
 // Part `part` of `parts` of the device table's groups to the output, by one
 // workgroup, leaving them empty; *o.d_n counts the groups. The slots are read
 // past L1, which may hold what they were before other workgroups' atomics.
-__device__ void drain_groups(const GroupView& g, int64_t nslots, uint32_t part, uint32_t parts, const OutArgs& o) {
+__device__ __forceinline__ void drain_groups(const GroupView& g, int64_t nslots, uint32_t part, uint32_t parts, const OutArgs& o) {
   __shared__ uint32_t s_scan[kLdsBlock / kWave];
   __shared__ int64_t s_pos;
   constexpr int kAhead = 8;
   const int64_t step = kAhead * kLdsBlock;
   for (int64_t i0 = part * step; i0 < nslots; i0 += parts * step) {
     uint64_t c[kAhead];
-    uint32_t mine = 0, total;
+    uint32_t bits = 0, total;
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
       const int64_t i = i0 + k * kLdsBlock + threadIdx.x;
       c[k] = i < nslots ? __hip_atomic_load(&g.slots[i].count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
     }
 #pragma unroll
-    for (int k = 0; k < kAhead; ++k) mine += c[k] != 0;
-    const uint32_t before = block_excl_scan<kLdsBlock>(mine, s_scan, &total);
+    for (int k = 0; k < kAhead; ++k) bits |= (uint32_t)(c[k] != 0) << k;
+    const uint32_t before = block_excl_scan<kLdsBlock>((uint32_t)__popc(bits), s_scan, &total);
     if (total == 0) continue;
     if (threadIdx.x == 0) s_pos = (int64_t)dev_add_ret<unsigned long long>((unsigned long long*)o.d_n, total);
     __syncthreads();
     int64_t pos = s_pos + before;
-#pragma unroll
-    for (int k = 0; k < kAhead; ++k) {
-      if (c[k] == 0) continue;
-      const int64_t i = i0 + k * kLdsBlock + threadIdx.x;
+#pragma unroll 1
+    for (; bits != 0; bits &= bits - 1, ++pos) {
+      const int64_t i = i0 + (__ffs((int)bits) - 1) * kLdsBlock + threadIdx.x;
+      GroupSlot* s = &g.slots[i];
       if (pos < o.cap) {
-        o.key[pos] = i == nslots - 1 ? kGroupEmpty : __hip_atomic_load(&g.slots[i].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        o.sum_price[pos] = (int64_t)__hip_atomic_load(&g.slots[i].sum_price, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        o.sum_qty[pos] = (int64_t)__hip_atomic_load(&g.slots[i].sum_qty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        o.count[pos] = (int64_t)c[k];
+        o.key[pos] = i == nslots - 1 ? kGroupEmpty : __hip_atomic_load(&s->key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        o.sum_price[pos] = (int64_t)__hip_atomic_load(&s->sum_price, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        o.sum_qty[pos] = (int64_t)__hip_atomic_load(&s->sum_qty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        o.count[pos] = (int64_t)__hip_atomic_load(&s->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else {
         set_status(o.status, kDevOverflow);
       }
-      g.slots[i] = GroupSlot{kGroupEmpty, 0, 0, 0};
-      ++pos;
+      *s = GroupSlot{kGroupEmpty, 0, 0, 0};
     }
   }
 }
@@ -517,7 +516,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
         s_word = w;
       }
       __syncthreads();
-      if (s_word == kMergeDrain) drain_groups(m.groups, m.nslots, role, gridDim.x, o);
+      if (s_word == kMergeDrain) drain_groups(m.groups, m.nslots, role - 1, gridDim.x - 1, o);
       return;
     }
   }
@@ -558,9 +557,10 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
     wait_device_atomics();  // (every wave's, before the word goes out)
     __syncthreads();
     if (t == 0) __hip_atomic_store(m.word, (uint32_t)kMergeDrain, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    drain_groups(m.groups, m.nslots, 0, gridDim.x, o);
     return;
   }
+  // (at once: the others' way out is as long as what is left here)
+  if (ENDS && t == 0) __hip_atomic_store(m.word, (uint32_t)kMergeWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t ball = wave_ballot(occ);
   const uint32_t wave = t / kWave;
   if (lane_id() == 0) s_wcnt[wave] = (uint32_t)__popcll(ball);
@@ -586,7 +586,6 @@ __global__ __launch_bounds__(kLdsBlock) void k_group_merge(MergeArgs m, OutArgs 
   if (t == 0) {
     *o.d_n = (int64_t)total;
     *m.done = 1u;
-    if (ENDS) __hip_atomic_store(m.word, (uint32_t)kMergeWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -833,7 +832,7 @@ constexpr int64_t kSmallRows = 1 << 16;
 constexpr int kGlobalPerCu = 4;
 // The merge kernel ends a plain LDS call of at most so many fact rows and slots
 // of the device table: its workgroups write the output from the table when groups
-// went there, 8192 slots at a time (60K rows, 131073 slots: 3600 groups 42 us
+// went there, 8192 slots at a time (60K rows, 131073 slots: 3600 groups 35 us
 // with one launch fewer, 49 us with a finalize kernel after it; one workgroup
 // going through all of them took 197; 15 groups 18.5 and 21.5 us). Beyond these
 // sizes the launch no longer counts.
@@ -1095,7 +1094,7 @@ rel_status rel_filter_join_agg(rel_ctx* ctx, const rel_fact* fact, const rel_dim
 
   // Join index: a dense array when the dim keys span at most 2m values, else
   // a hash table of plain sizing (2m rounded up to a power of two); both in
-  // device memory, the choice made on the device. Its clearing kernel also
+  // device memory, the choice made on the device. Its first kernel also
   // zeroes the counter words (rows passed, join matches, the finalize ticket,
   // the merge kernel's two flags) and the finalize kernel's look-back state.
   const int64_t fin_items = gp == G_ROWAGG ? m : group_cap + 1;
