@@ -6,8 +6,8 @@
 // a workgroup each (k_batch_whole), and the instances that are too large for one
 // workgroup, or too sparse for its arrays, become work items of three more
 // kernels that share tables in device memory: build, probe/aggregate, finalize
-// (one per phase and size bucket). Workgroups pull instances and items
-// largest-first from ticket counters, and the whole sequence is captured once
+// (one per phase and size bucket). Workgroups pull instances, costliest first, and
+// items, largest first, from ticket counters, and the whole sequence is captured once
 // into a HIP graph so that a run is one graph launch.
 //
 // Per-bucket configuration of the shared tables (rows per thread, workgroup size, LDS or
@@ -376,7 +376,7 @@ static_assert(kWRankRows <= kWCap && kWRankRows * (kWGroupBytes + 4) + 64 + kWRa
 
 struct BWhole {
   const BInst* inst;
-  const int32_t* order;   // instances to take, largest first
+  const int32_t* order;   // instances to take, costliest first
   int32_t n;              // their number
   int64_t* ticket;
   uint32_t* status;
@@ -473,8 +473,8 @@ struct WRanks {
 // What the steps of an instance share, in LDS (each step reads what it needs:
 // kept in registers over all of them, these values spill).
 struct WPlan {
-  int32_t inst, kmin, amin;
-  uint32_t range, arange;  // of the keys and of the attributes
+  int32_t kmin, amin;
+  uint32_t range;          // of the keys
   uint32_t groups;         // group numbers
   uint32_t chunks;
   uint32_t ranked, in_lds;
@@ -582,7 +582,6 @@ __device__ __forceinline__ bool w_plan(const BWhole& a, const BInst& I, WShared&
     s.p.kmin = kmin;
     s.p.amin = amin;
     s.p.range = (uint32_t)range;
-    s.p.arange = (uint32_t)arange;
     s.p.groups = (uint32_t)groups;
     s.p.chunks = (uint32_t)chunks;
     s.p.ranked = ranked;

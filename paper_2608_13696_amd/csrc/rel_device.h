@@ -349,7 +349,7 @@ __device__ __forceinline__ DenseRange dense_range(const JoinIndex& x) {
 }
 
 // 16-byte words that hold the range's entries (the last one padded with
-// entries that the clearing kernel zeroes too).
+// entries that are zeroed and wiped with the others).
 __device__ __forceinline__ int64_t dense_words(const JoinIndex& x, const DenseRange& r) {
   if (r.range <= 0) return 0;
   return (r.range * (x.narrow ? 2 : x.wide ? 8 : 4) + 15) / 16;

@@ -48,8 +48,9 @@ __global__ __launch_bounds__(256) void k_join_build(const int32_t* __restrict__ 
 // Minimum and maximum of the build keys, order-encoded so that both are
 // maxima over unsigned words that start at 0 (see JoinIndex::mm). Few, large
 // workgroups with two 16-byte loads in flight per thread; each writes its pair
-// to part[2b], part[2b + 1], and the clearing kernel that follows combines
-// them (no atomics, and no word to zero first).
+// to part[2b], part[2b + 1], and a kernel that follows combines them (the
+// clearing kernel of a stand-alone table, the build where the table was left
+// empty): no atomics, and no word to zero first.
 constexpr int kIdxBlock = 256;
 constexpr int kMinMaxBlock = 512;
 constexpr int kMinMaxGrid = relh::kKeyMinMaxParts;
