@@ -959,12 +959,14 @@ unsigned persistent_grid(const rel_ctx* ctx, int64_t items, int block) {
 }
 
 // Rows and keys per item where the tuning's (up to 65536, found on batches of
-// thousands) would leave CUs idle: an even share, but for a row item no less than
-// what pays for its LDS table's setting up and its flush to the device table. 8
-// instances of up to 1M rows by the tuning's items kept 20 workgroups busy and
-// took 606 us; one instance of 300K rows 112 us, 61 so. Shares of a quarter of a
-// CU's cost more than they gave (4 instances of 1M rows: 229 us, 86 so, 125 by the
-// tuning's).
+// thousands) would leave CUs idle: a CU's share, of the rows that one kernel takes
+// (a bucket's) and of one kind, as rows of instances of many groups cost some
+// twenty times the others' (an update of the device table each). Where the groups
+// are few, no less than what pays for an item's LDS table, which is set up and
+// flushed once per item. In us: 8 instances of up to 1M rows 606 by the tuning's
+// items, which kept 20 workgroups busy, 187 so; 4 of 1M rows and 100 groups 125, 86
+// so, 229 with a quarter of the share; 64 of 1K to 1M rows, 1 to 65536 groups, 994
+// with a CU's share of the whole batch, 670 so.
 constexpr int64_t kItemMinRows = 2048, kItemMinKeys = 1024;
 constexpr int64_t kKeyItemsPerCu = 4;
 
@@ -973,6 +975,13 @@ int64_t group_bound(const rel_batch_item& it, bool* hinted) {
   const int64_t ub = it.q.group_by == REL_GROUP_PRIO_FLAG ? std::min<int64_t>(it.fact.n, 65536) : std::min(it.fact.n, it.dim.m);
   *hinted = it.group_capacity > 0 && it.group_capacity < ub;
   return *hinted ? it.group_capacity : ub;
+}
+
+// More groups than an LDS table holds. (The bound of (prio, flag) is of the values
+// there could be, not of those that occur.)
+bool many_groups(const rel_batch_item& it) {
+  bool hinted;
+  return it.q.group_by != REL_GROUP_PRIO_FLAG && group_bound(it, &hinted) > kBLdsSlots / 2;
 }
 
 // What an instance costs either way, in ns: a workgroup that takes it whole while
@@ -1007,7 +1016,7 @@ BatchCost batch_cost(const rel_batch_item& it) {
   c.alone = keys + n * ((in_lds ? 0.5 : 1.0) + (spills ? 1.0 : 0));
   c.loaded = keys + n * ((in_lds ? 0.8 : 1.6) + (spills ? 1.3 : 0));
   if (groups > kWMaxRange) c.alone = c.loaded = 1e15;  // (more keys than group numbers: w_plan would only find it out)
-  const bool many = bound > 512 && !flag;
+  const bool many = many_groups(it);
   double slots = 16;
   while (slots < 2 * (double)bound + 1) slots *= 2;
   c.shared = 50 + n * (many ? 0.09 : 0.005) + m * 0.06 + slots * 0.010;
@@ -1103,11 +1112,10 @@ rel_status rel_batch_create_as(rel_ctx* ctx, const rel_batch_item* items, int32_
   const int32_t n_shared = way == REL_BATCH_SHARED ? k : way == REL_BATCH_WHOLE ? 0 : whole_from(sorted_costs, ctx->num_cus);
   const int32_t n_whole = k - n_shared;
   b->whole_grid = (unsigned)std::min<int32_t>(n_whole, ctx->num_cus);
-  int64_t shared_rows = 0, shared_keys = 0, spill_rows = 0;
+  int64_t shared_keys = 0, spill_rows = 0;
   for (int32_t p = 0; p < k; ++p) {
     const rel_batch_item& it = items[order[p]];
     if (p < n_shared) {
-      shared_rows += it.fact.n;
       shared_keys += it.dim.m;
       continue;
     }
@@ -1192,10 +1200,18 @@ rel_status rel_batch_create_as(rel_ctx* ctx, const rel_batch_item* items, int32_
     BucketPlan& bp = b->buckets[t];
     bp.t = tun[t];
     const int64_t unit = (int64_t)tun[t].block * tun[t].items_per_thread;
-    const int64_t share = std::max<int64_t>(shared_rows / ctx->num_cus, kItemMinRows);
-    const int64_t few = std::min<int64_t>((share + unit - 1) / unit * unit, tun[t].rows_per_item);
+    int64_t bucket_rows[2] = {0, 0};  // of instances of few groups, and of many
+    for (int32_t p = 0; p < n_shared; ++p) {
+      const rel_batch_item& it = items[order[p]];
+      if (bucket_of(it.fact.n) == (int)t) bucket_rows[many_groups(it)] += it.fact.n;
+    }
+    auto share = [&](bool many) {
+      const int64_t even = std::max<int64_t>(bucket_rows[many] / ctx->num_cus, many ? 1 : kItemMinRows);
+      return std::min<int64_t>((even + unit - 1) / unit * unit, tun[t].rows_per_item);
+    };
+    const int64_t few_rows = share(false), many_rows = share(true);
     const int64_t key_share = std::max<int64_t>(shared_keys / (ctx->num_cus * kKeyItemsPerCu), kItemMinKeys);
-    auto rows = [&](int32_t p) { return p < n_shared ? few : (int64_t)tun[t].rows_per_item; };
+    auto rows = [&](int32_t p) { return p >= n_shared ? (int64_t)tun[t].rows_per_item : many_groups(items[order[p]]) ? many_rows : few_rows; };
     auto keys = [&](int32_t p) { return p < n_shared ? key_share : std::max<int64_t>(tun[t].rows_per_item / 4, 256); };
     bp.build_lo = (int64_t)hitems.size();
     bp.build = add_items((int)t, [&](int32_t i) { return items[i].dim.m; }, keys);

@@ -70,6 +70,25 @@ def test_batch_work_items_are_no_smaller_than_pays(host):
     """)
 
 
+def test_batch_work_items_are_a_share_of_what_their_kernel_takes(host):
+    """A bucket's instances are one kernel's, and rows of many groups cost more than others: instances of another size
+    or kind in the batch leave an instance's items as they are."""
+    host("""
+    def grids(*instances):
+        c = new_ctx()
+        items = (rel.BatchItem * len(instances))()
+        for it, (n, m, hint) in zip(items, instances):
+            it.fact, it.dim, it.q, it.out, it.group_capacity = fact(n), dim(m), rel.Query(1000, rel.GROUP_BY["dim_grp"]), groups(n), hint
+        tune = (rel.BatchTuning * 2)(rel.BatchTuning(18, 8, 512, 512, 16384, 0), rel.BatchTuning(31, 4, 512, 0, 65536, 0))
+        kernels()
+        assert L.rel_batch_create_as(c, items, len(instances), tune, 2, 1, P(ctypes.c_void_p())) == 0
+        return [g for name, g in kernels() if "k_batch_probe" in name]
+    many, few, large = (100_000, 25_000, 20_000), (200_000, 25_000, 300), (1_000_000, 1000, 300)
+    assert grids(*4 * [many]) == [4 * 25] and grids(*4 * [few]) == [4 * 49] and grids(*8 * [large]) == [8 * 31]
+    assert grids(*4 * [many], *4 * [few], *8 * [large]) == [4 * 25 + 4 * 49, 8 * 31]
+    """)
+
+
 def test_batch_instances_of_many_dim_keys_go_by_shared_tables(host):
     """A workgroup that takes an instance whole reads all its dim keys again for each slice of its join table."""
     host("""
