@@ -987,9 +987,11 @@ bool many_groups(const rel_batch_item& it) {
 // What an instance costs either way, in ns: a workgroup that takes it whole while
 // most CUs are idle and while all are busy, and its share of what the shared tables
 // cost the chip. Fitted to 261 batches of 1 to 256 equal instances of 1K to 1M
-// rows, 100 to 8M dim keys and all three group keys, timed both ways: the way
-// chosen is within 0.3% of the better one on average (14% at worst). Some of them,
-// all by the shared tables / all whole, in us:
+// rows, 100 to 8M dim keys and all three group keys, timed both ways, and to 61
+// batches of 8 to 2048 instances of different sizes, timed at up to 20 splits: the
+// way chosen is within 0.3% of the better one on average (20% at worst), and of 44
+// other batches of different sizes within 0.6% of the best measured split. Some of
+// the equal ones, all by the shared tables / all whole, in us:
 //   1 of 1K rows, 100 keys        28 /   30     1 of 1K rows, 1M keys         95 / 2639
 //   1 of 300K, 75K, 300 groups    75 /  368     64 of 30K, 7.5K, 300 groups   94 /   49
 //   16 of 30K, 3K, fk            116 /   47     16 of 300K, 75K, fk          662 /  517
@@ -999,8 +1001,9 @@ bool many_groups(const rel_batch_item& it) {
 // took 136 ms.
 struct BatchCost {
   double alone, loaded, shared, shared_wait;
+  int bucket;
 };
-BatchCost batch_cost(const rel_batch_item& it) {
+BatchCost batch_cost(const rel_batch_item& it, int bucket) {
   bool hinted;
   const int64_t bound = group_bound(it, &hinted);
   const double n = (double)it.fact.n, m = (double)it.dim.m;
@@ -1013,27 +1016,36 @@ BatchCost batch_cost(const rel_batch_item& it) {
   const double slices = in_lds ? 1 : std::ceil(table / kWPool);
   const double keys = 8000 + m * (0.25 + 0.25 * slices) + (spills ? 7000.0 * (double)chunks : 0);
   BatchCost c;
-  c.alone = keys + n * ((in_lds ? 0.5 : 1.0) + (spills ? 1.0 : 0));
+  c.alone = keys + n * ((in_lds ? 0.7 : 1.0) + (spills ? 0.8 : 0));
   c.loaded = keys + n * ((in_lds ? 0.8 : 1.6) + (spills ? 1.3 : 0));
   if (groups > kWMaxRange) c.alone = c.loaded = 1e15;  // (more keys than group numbers: w_plan would only find it out)
   const bool many = many_groups(it);
   double slots = 16;
   while (slots < 2 * (double)bound + 1) slots *= 2;
-  c.shared = 50 + n * (many ? 0.09 : 0.005) + m * 0.06 + slots * 0.010;
-  c.shared_wait = 7000 + (many ? 25000 : 0) + (it.dim.m > kBLdsJoinSlots / 2 ? 12000 : m * 5) + (flag && it.fact.n >= 2048 ? 8000 : 0);
+  c.shared = 50 + n * (many ? 0.1 : 0.005) + m * 0.06 + slots * 0.0115;
+  c.shared_wait = 7000 + (many ? 25000 : 0) + (it.dim.m > kBLdsJoinSlots / 2 ? 17000 : m * 5) + (flag && it.fact.n >= 2048 ? 6400 : 0);
+  c.bucket = bucket;
   return c;
 }
 
 // How many of the instances, costliest first, go by the shared tables, so that the
-// times of both ways, which follow one another, add up to the least.
+// times of both ways, which follow one another, add up to the least. Each bucket of
+// the tuning among them is two kernels more. A split costs more than its parts'
+// estimates (the whole instances that are left are not those that were expected to
+// be quick, and the shared tables' kernels have few items), so it has to promise a
+// tenth: 373 instances of 1K to 84K rows with the 15 costliest apart 363 us, all
+// whole 226; 42 of up to 108K rows by the shared tables 152, all whole 134.
+constexpr double kBucketNs = 5000, kSplitFactor = 1.1;
 int32_t whole_from(const std::vector<BatchCost>& cost, int cus) {
   const int32_t k = (int32_t)cost.size();
   double after = 0, shared = 0, wait = 0, best = 0;
   for (const BatchCost& c : cost) after += c.loaded;
+  uint64_t buckets = 0;  // a bit each (31 at most)
   int32_t at = 0;
   for (int32_t c = 0; c <= k; ++c) {
     const double whole = c < k ? std::max(cost[c].alone, after / cus) : 0;
-    const double t = whole + shared + wait;
+    const double more = kBucketNs * std::max(__builtin_popcountll(buckets) - 1, 0);
+    const double t = (whole + shared + wait + more) * (c > 0 && c < k ? kSplitFactor : 1);
     if (c == 0 || t < best) {
       best = t;
       at = c;
@@ -1042,6 +1054,7 @@ int32_t whole_from(const std::vector<BatchCost>& cost, int cus) {
     after -= cost[c].loaded;
     shared += cost[c].shared;
     wait = std::max(wait, cost[c].shared_wait);
+    buckets |= 1ull << cost[c].bucket;
   }
   return at;
 }
@@ -1104,7 +1117,7 @@ rel_status rel_batch_create_as(rel_ctx* ctx, const rel_batch_item* items, int32_
 
   // costliest instance first; from `order[n_shared]` on they are taken whole
   std::vector<BatchCost> costs(k), sorted_costs(k);
-  for (int32_t i = 0; i < k; ++i) costs[i] = batch_cost(items[i]);
+  for (int32_t i = 0; i < k; ++i) costs[i] = batch_cost(items[i], bucket_of(items[i].fact.n));
   std::vector<int32_t> order(k);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return costs[x].alone > costs[y].alone; });

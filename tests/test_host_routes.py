@@ -107,6 +107,25 @@ def test_batch_instances_of_many_dim_keys_go_by_shared_tables(host):
     """)
 
 
+def test_batch_is_split_between_the_ways_only_for_a_clear_gain(host):
+    """Instances of different sizes: a few of them apart cost the shared tables' kernels, one after another."""
+    host("""
+    def whole(k, hi):
+        c = new_ctx()
+        items = (rel.BatchItem * k)()
+        for i, it in enumerate(items):
+            n = int(1000 * (hi / 1000) ** (i / (k - 1)))
+            it.fact, it.dim, it.q, it.out, it.group_capacity = fact(n), dim(n // 4), rel.Query(1000, rel.GROUP_BY["dim_grp"]), groups(n), 2 ** (7 * i % 17)
+        tune = (rel.BatchTuning * 3)(rel.BatchTuning(12, 4, 512, 128, 4096, 1024), rel.BatchTuning(15, 1, 512, 512, 16384, 0),
+                                     rel.BatchTuning(31, 8, 512, 512, 16384, 0))
+        kernels()
+        assert L.rel_batch_create(c, items, k, tune, 3, P(ctypes.c_void_p())) == 0
+        return sum(g for name, g in kernels() if "k_batch_whole" in name)
+    assert [whole(k, hi) for k, hi in ((54, 36_000), (144, 66_000), (234, 62_000))] == [54, 144, 234]
+    assert 0 < whole(200, 400_000) < 200  # (the largest would keep the others waiting)
+    """)
+
+
 def test_tunings_are_measured_where_they_apply(host):
     """autotune.gpu_measure's batches launch the kernels that read the tuning, with the candidate's workgroup size."""
     host("""
